@@ -1057,6 +1057,237 @@ __global__ __launch_bounds__(512, 1) void gemm_bf16_lds8r3_kernel(const u32x4_t*
   }
 }
 
+// Large batches (more than 256 rows: prefill and scoring chunks, throughput decode).  A block of four waves owns NB
+// 32-row blocks of the weight matrix and 128 batch rows, 32 per wave, over the whole K range.  The weight tile goes
+// through LDS in three stages, one barrier per k block; the activation fragments come straight from L2.
+//
+// What bounds it: the matrix cores' power.  At 1024 rows gate/up keeps them busy 91 % of the cycles (1100 cycles per k
+// block for two resident blocks, 1024 of them matrix instructions), and the clock settles at 1.2 to 1.5 GHz; a loop of
+// nothing but these instructions on random operands does not get past 1.4 to 1.6 PFLOP/s.  What it takes to get there:
+//   - one memory instruction behind every matrix instruction.  A wave issues in order, so a run of LDS writes or loads
+//     leaves its matrix core idle (16 matrix instructions and 16 fragment reads take 577 cycles, with four LDS writes and
+//     four weight loads in a row 852, spread out 670);
+//   - the barrier does not wait for LDS reads in flight: a stage is rewritten one barrier after its last read;
+//   - two blocks per compute unit (256 registers per lane), which hides each other's barriers, quarter sums and ends.
+// The quarter sums keep a row's bits those of the K-split kernels: every K quarter in an accumulator of its own, added
+// in order; then, where the plan splits K, the splits in order, kept in LDS between them.  So a QKV, O or down product
+// leaves no split partials: QKV writes its sum once (100 MB less written and 75 MB less read at 1024 rows), O and down
+// add theirs to the residual stream themselves (kEpiResidual), in the order in which the norm kernel would.
+// Measured inside scoring, prefill and decode passes, against the kernels before: gate/up 120 -> 92 us at 301 rows, 139 -> 115 at 512, 208 -> 209
+// at 1024; QKV 44 -> 37, 55 -> 43, 88 -> 68; O 53 -> 48 and down 118 -> 124 at 1024, with the norm behind each 21 -> 11;
+// output projection with sampling 1403 -> 1321.
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t buffer_of(const void* base, uint32_t bytes) {
+  return __builtin_amdgcn_make_buffer_rsrc((void*)base, 0, bytes, 0x00020000);
+}
+__device__ __forceinline__ u32x4_t buffer_load16(__amdgpu_buffer_rsrc_t r, uint32_t voff, uint32_t soff) {
+  return __builtin_bit_cast(u32x4_t, __builtin_amdgcn_raw_buffer_load_b128(r, voff, soff, 0));
+}
+
+constexpr int tile_sums_in_registers(int nb) { return nb == 3 ? 1 : 0; }
+
+template <int NB, int EPI>
+__global__ __launch_bounds__(256, 2) void gemm_bf16_tile_kernel(const u32x4_t* __restrict__ X, const u32x4_t* __restrict__ W,
+                                                              void* __restrict__ out, int M, int N, int K, int seg, int splits,
+                                                              int n_tiles, int m_tiles, SampleEpilogue se) {
+  static_assert(NB == 4 || (NB == 3 && EPI != kEpiSample), "the sampling epilogue works on pairs of row blocks");
+  extern __shared__ u32x4_t smem[];  // three weight stages of NB x 4 KiB; then, with splits or a residual, the running sums
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int KB = K >> 6;
+  // Consecutive blocks go to the eight dies in turn: the batch tiles of one weight tile follow each other on one die.
+  const int j = blockIdx.x >> 3;
+  const int m_tile = j % m_tiles, n_tile = (j / m_tiles) * 8 + (blockIdx.x & 7);
+  if (n_tile >= n_tiles) return;  // block-uniform
+  const int n_rb = EPI == kEpiSwiGLU ? (N >> 4) : (N >> 5);
+  const int n_mb = (M + 31) >> 5;
+  const int rb0 = n_tile * NB;
+  const int mb = m_tile * 4 + wave;
+  const bool has_rows = mb < n_mb;  // idle waves shadow the last block (they still carry tiles and barriers)
+  const uint32_t row_bytes = (uint32_t)KB * 4096;
+  const auto wd = buffer_of((const char*)W + (size_t)rb0 * row_bytes, (uint32_t)min(NB, n_rb - rb0) * row_bytes);
+  const auto xd = buffer_of((const char*)X + (size_t)min(mb, n_mb - 1) * row_bytes, row_bytes);
+  const uint32_t wv = tid * 16, xv = lane * 16;
+  int w_left = KB, w_r = 0, w_q = 0;
+  uint32_t w_off = 0;  // offset of the next weight k block to load (weight_kb_slot order)
+  uint32_t w_row[NB];
+#pragma unroll
+  for (int b = 0; b < NB; ++b) w_row[b] = (uint32_t)min(b, n_rb - 1 - rb0) * row_bytes;
+  const int back = -((seg - 1) * 4 - 1) * 4096;
+  auto next_w = [&]() __attribute__((always_inline)) {  // without branches; the last one again once the range is exhausted
+    const bool wrap = ++w_r == seg;
+    w_r = wrap ? 0 : w_r;
+    w_q += wrap ? 1 : 0;
+    const bool next = w_q == 4;
+    w_q = next ? 0 : w_q;
+    const int by = wrap ? (next ? 4096 : back) : 4 * 4096;
+    w_off += --w_left > 0 ? by : 0;
+  };
+  constexpr int WS = 2;
+  u32x4_t wr[WS][NB], xr[2][4], fa[2][NB];  // weights on their way to LDS, activations, weight fragments of two phases
+  auto load_x = [&](u32x4_t (&x)[4], int kb, int t) __attribute__((always_inline)) {
+    x[t] = buffer_load16(xd, xv, (uint32_t)min(kb, KB - 1) * 4096 + t * 1024);
+  };
+  auto load_w = [&](u32x4_t (&w)[NB], int b) __attribute__((always_inline)) { w[b] = buffer_load16(wd, wv, w_row[b] + w_off); };
+  auto put_w = [&](int stage, const u32x4_t (&w)[NB], int b) __attribute__((always_inline)) { smem[(stage * NB + b) * 256 + tid] = w[b]; };
+  auto read = [&](u32x4_t (&f)[NB], int stage, int t, int b) __attribute__((always_inline)) { f[b] = smem[(stage * NB + b) * 256 + t * 64 + lane]; };
+  auto barrier = []() __attribute__((always_inline)) {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+    __builtin_amdgcn_s_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+  };
+  f32x16_t acc[NB], tot[NB];
+#pragma unroll
+  for (int s = 0; s < WS; ++s) {
+#pragma unroll
+    for (int b = 0; b < NB; ++b) load_w(wr[s], b);
+    next_w();
+  }
+#pragma unroll
+  for (int s = 0; s < 2; ++s)
+#pragma unroll
+    for (int t = 0; t < 4; ++t) load_x(xr[s], s, t);
+  // Running sums over the K splits, by lane: [row block][q][64 lanes] per wave in LDS; with three row blocks the first
+  // one's stay in registers, which keeps two blocks on a compute unit.
+  constexpr int UR = tile_sums_in_registers(NB);
+  f32x4_t* const usum = (f32x4_t*)(smem + 3 * NB * 256) + wave * (NB - UR) * 256 + lane;
+  f32x4_t ureg[4];
+#pragma unroll
+  for (int q = 0; q < 4; ++q) ureg[q] = (f32x4_t){0.f, 0.f, 0.f, 0.f};
+  auto get_sum = [&](int b, int q) __attribute__((always_inline)) { return b < UR ? ureg[q] : usum[((b - UR) * 4 + q) * 64]; };
+  auto set_sum = [&](int b, int q, f32x4_t v) __attribute__((always_inline)) {
+    if (b < UR) ureg[q] = v;
+    else usum[((b - UR) * 4 + q) * 64] = v;
+  };
+  const int col = lane & 31, hb = lane >> 5, m = mb * 32 + col;
+  if (EPI == kEpiResidual) {
+    const float* xo = (const float*)out + (size_t)min(m, M - 1) * N + 4 * hb;
+#pragma unroll
+    for (int b = 0; b < NB; ++b)
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        const f32x4_t v = *(const f32x4_t*)(xo + min(rb0 + b, n_rb - 1) * 32 + 8 * q);
+        tot[b][4 * q] = v[0]; tot[b][4 * q + 1] = v[1]; tot[b][4 * q + 2] = v[2]; tot[b][4 * q + 3] = v[3];
+      }
+#pragma unroll
+    for (int b = 0; b < NB; ++b)
+#pragma unroll
+      for (int q = 0; q < 4; ++q)
+        set_sum(b, q, (f32x4_t){tot[b][4 * q], tot[b][4 * q + 1], tot[b][4 * q + 2], tot[b][4 * q + 3]});
+  }
+  constexpr int LATE = NB - 1;  // this row block is staged in phase 0 of the next step, the others in phases 2 and 3
+#pragma unroll
+  for (int b = 0; b < NB; ++b) put_w(0, wr[0], b);
+#pragma unroll
+  for (int b = 0; b < NB; ++b) load_w(wr[0], b);
+  next_w();
+#pragma unroll
+  for (int b = 0; b < LATE; ++b) put_w(1, wr[1], b);
+#pragma unroll
+  for (int b = 0; b < LATE; ++b) load_w(wr[1], b);
+  barrier();
+#pragma unroll
+  for (int t = 0; t < 2; ++t)
+#pragma unroll
+    for (int b = 0; b < NB; ++b) read(fa[t], 0, t, b);
+  int cur = 0, rd = 1, wt = 2;  // LDS stages of k blocks i, i + 1 and i + 2
+  auto step = [&](int i, auto jc, auto fc) __attribute__((always_inline)) {
+    constexpr int J = decltype(jc)::value, jx = J & 1, j1 = (J + 1) % WS, j2 = (J + 2) % WS;
+    constexpr bool first = decltype(fc)::value;
+    auto phase = [&](auto pc) __attribute__((always_inline)) {
+      constexpr int P = decltype(pc)::value;
+      if (P == 3) next_w();
+#pragma unroll
+      for (int b = 0; b < NB; ++b) {
+        f32x16_t c;
+        if constexpr (first && P == 0) {
+#pragma unroll
+          for (int r = 0; r < 16; ++r) c[r] = 0.f;
+        } else {
+          c = acc[b];
+        }
+        acc[b] = mfma_f16(fa[P & 1][b], xr[jx][P], c);
+        read(fa[P & 1], P < 2 ? cur : rd, (P + 2) & 3, b);  // past the last k block: a stage nobody needs, never used
+        // one more memory instruction behind each matrix instruction
+        if (P == 0 && b == 0) put_w(rd, wr[j1], LATE);
+        if (P == 0 && b == 1) load_x(xr[jx ^ 1], i + 1, 3);
+        if (P == 0 && b == 2 && NB == 4) load_w(wr[j1], 2);
+        if (P == 1 && b == 0) load_w(wr[j1], LATE);
+        if (P == 1 && b == 1) load_x(xr[jx], i + 2, 0);
+        if (P == 2 && b == 0) put_w(wt, wr[j2], 0);
+        if (P == 2 && b == 1) load_x(xr[jx], i + 2, 1);
+        if (P == 2 && b == 2 && NB == 4) put_w(wt, wr[j2], 1);
+        if (P == 3 && b == 0) put_w(wt, wr[j2], LATE - 1);
+        if (P == 3 && b == 1) load_x(xr[jx], i + 2, 2);
+        if (P == 3 && b == NB - 1) {
+          load_w(wr[j2], 0);
+          load_w(wr[j2], 1);
+        }
+        __builtin_amdgcn_sched_barrier(0);
+      }
+    };
+    phase(std::integral_constant<int, 0>{});
+    phase(std::integral_constant<int, 1>{});
+    // LDS operations of a wave finish in order: with at most phase 1's reads outstanding, the stage of k block i + 1 is
+    // complete and all reads of k block i - 1, whose stage is written next, are done.
+    asm volatile("s_waitcnt lgkmcnt(%0)\n\ts_barrier" :: "n"(NB) : "memory");
+    phase(std::integral_constant<int, 2>{});
+    phase(std::integral_constant<int, 3>{});
+    const int c = cur;
+    cur = rd;
+    rd = wt;
+    wt = c;
+  };
+  auto steps4 = [&](int i, auto fc) __attribute__((always_inline)) {
+    step(i, std::integral_constant<int, 0>{}, fc);
+    step(i + 1, std::integral_constant<int, 1>{}, std::false_type{});
+    step(i + 2, std::integral_constant<int, 2>{}, std::false_type{});
+    step(i + 3, std::integral_constant<int, 3>{}, std::false_type{});
+  };
+  int i = 0;
+  for (int sp = 0; sp < splits; ++sp) {
+#pragma unroll
+    for (int b = 0; b < NB; ++b)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) tot[b][r] = -0.0f;  // -0 + x is x, bit for bit
+    for (int q = 0; q < 4; ++q) {
+      steps4(i, std::true_type{});
+      for (int e = i + seg, k = i + 4; k < e; k += 4) steps4(k, std::false_type{});
+      i += seg;
+#pragma unroll
+      for (int b = 0; b < NB; ++b) tot[b] += acc[b];
+    }
+    if (EPI == kEpiResidual || (EPI == kEpiPartial && splits > 1)) {
+#pragma unroll
+      for (int b = 0; b < NB; ++b)
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+          f32x4_t v = {tot[b][4 * q], tot[b][4 * q + 1], tot[b][4 * q + 2], tot[b][4 * q + 3]};
+          if (EPI == kEpiResidual || sp > 0) v = get_sum(b, q) + v;
+          if (sp + 1 < splits) set_sum(b, q, v);
+          else { tot[b][4 * q] = v[0]; tot[b][4 * q + 1] = v[1]; tot[b][4 * q + 2] = v[2]; tot[b][4 * q + 3] = v[3]; }
+        }
+    }
+  }
+  if (!has_rows || m >= M) return;
+  if constexpr (EPI == kEpiSample) {
+#pragma unroll
+    for (int b = 0; b < NB; b += 2) {
+      float sum[2][16];
+#pragma unroll
+      for (int r = 0; r < 16; ++r) { sum[0][r] = tot[b][r]; sum[1][r] = tot[b + 1][r]; }
+      if (rb0 + b < n_rb) store_block<EPI>(sum, m, hb, rb0 + b, rb0 + b + 1, 0, M, N, out, se, (rb0 + b) >> 1);
+    }
+  } else {
+#pragma unroll
+    for (int b = 0; b < NB; ++b) {
+      float sum[16];
+#pragma unroll
+      for (int r = 0; r < 16; ++r) sum[r] = tot[b][r];
+      if (rb0 + b < n_rb) store_rowblock<EPI == kEpiResidual ? kEpiPartial : EPI>(sum, m, hb, rb0 + b, 0, M, N, out);
+    }
+  }
+}
+
 struct Plan {
   int splits;       // K splits across blocks
   int kb_per_wave;  // 64-wide k blocks per wave
@@ -1135,8 +1366,48 @@ int wide_blocks(int N, int K, int epi, bool allow_split) {
   return ((tiles + 1) / 2) * (epi == kEpiPartial ? p.splits : 1);
 }
 
+// Row blocks per weight tile with which gemm_bf16_tile_kernel takes an M x N x K product, or 0 where another kernel does:
+//   - up to 256 rows the tiles above read the weights once and are faster (gate/up at 256 rows 59 us against 71);
+//   - the tile (4 or 3 row blocks) that gives the compute unit with most blocks the fewest row blocks, the larger one on
+//     a tie: it reads the activations less often (gate/up at 512 rows 116 us with 4, 123 with 3; at 301 rows 99 and 92);
+//   - where even smaller tiles would be needed to use the chip (O and down projections of the 8B shape at 512 rows), the
+//     kernels that spread the K splits over blocks stay: measured 35 against 29 us for O, 79 against 65 for down.
+int tile_row_blocks(int M, int N, int K, int epi, bool allow_split) {
+  if (M <= 256) return 0;
+  const Plan p = make_plan(N, K, epi == kEpiResidual ? kEpiPartial : epi, allow_split && epi != kEpiSample);
+  if (p.kb_per_wave % 4) return 0;
+  if (epi == kEpiSample) return 4;
+  const int n_rb = epi == kEpiSwiGLU ? (N >> 4) : (N >> 5), m_tiles = (M + 127) / 128;
+  int best = 0, best_cost = 0;
+  for (int nb = 4; nb >= 2; --nb) {
+    const int blocks = (n_rb + nb - 1) / nb * m_tiles;
+    const int cost = (blocks + kComputeUnits - 1) / kComputeUnits * nb;
+    if (!best || cost < best_cost) { best = nb; best_cost = cost; }
+  }
+  return best == 2 ? 0 : best;
+}
+
+template <int NB>
+void launch_tile(hipStream_t s, const void* X, const void* W, void* out, int M, int N, int K, int epi, bool allow_split,
+                 const SampleEpilogue& se) {
+  const Plan p = make_plan(N, K, epi == kEpiResidual ? kEpiPartial : epi, allow_split);  // same K split as the other variants: bit-identical results
+  const int n_rb = epi == kEpiSwiGLU ? (N >> 4) : (N >> 5);
+  const int n_tiles = (n_rb + NB - 1) / NB, m_tiles = (M + 127) / 128;
+  dim3 grid((n_tiles + 7) / 8 * 8 * m_tiles);
+  const bool sums = p.splits > 1 || epi == kEpiResidual;
+  const size_t lds = (size_t)NB * 3 * 4096 + (sums ? (size_t)(NB - tile_sums_in_registers(NB)) * 16384 : 0);
+#define RL_TILE(E) gemm_bf16_tile_kernel<NB, E><<<grid, 256, lds, s>>>((const u32x4_t*)X, (const u32x4_t*)W, out, M, N, K, p.kb_per_wave, p.splits, n_tiles, m_tiles, se)
+  if (epi == kEpiSwiGLU) RL_TILE(kEpiSwiGLU);
+  else if (epi == kEpiResidual) RL_TILE(kEpiResidual);
+  else if (epi == kEpiSample) { if constexpr (NB == 4) RL_TILE(kEpiSample); }
+  else RL_TILE(kEpiPartial);
+#undef RL_TILE
+}
+
 }  // namespace
 
+int gemm_bf16_partials(int M, int N, int K) { return tile_row_blocks(M, N, K, kEpiPartial, true) ? 1 : gemm_bf16_splits(N, K, kEpiPartial); }
+bool gemm_bf16_adds_residual(int M, int N, int K) { return tile_row_blocks(M, N, K, kEpiResidual, true) != 0; }
 int gemm_bf16_splits(int N, int K, int epi) { return make_plan(N, K, epi, true).splits; }
 int gemm_bf16_weight_segment(int N, int K, bool split_k) { return make_plan(N, K, kEpiPartial, split_k).kb_per_wave; }
 
@@ -1230,7 +1501,8 @@ void launch_cols(hipStream_t s, const void* X, const void* W, void* out, int M, 
     // 129..256 rows: one block of eight waves per weight tile where that still gives >= 192 blocks (gate/up 82 -> 65 us,
     // QKV 33 -> 29, output projection 538 -> 420 at 256 rows); the O and down projections would be left with 128 blocks
     // (measured 21 -> 26 and 42 -> 50 us) and run as two batch tiles of 128 whose blocks are paired on one die.
-    // (more than 256 rows: the batch tiles of 256 count as blocks too, which brings the O and down projections in)
+    // (more than 256 rows, where gemm_bf16_tile_kernel does not take over: the batch tiles of 256 count as blocks too,
+    // which brings the O and down projections in)
     if (M > 128 && wide_blocks * ((M + 255) / 256) >= 192) {
       // ... and 96-row tiles where those give every compute unit a block and 128-row tiles do not (M <= 256: one
       // batch tile per weight tile; gate/up and QKV of the 8B shape)
@@ -1273,6 +1545,10 @@ void launch_gemm_bf16(hipStream_t s, const void* X, const void* W, void* out, in
   static const SampleEpilogue none{};
   const SampleEpilogue& e = se ? *se : none;
   if (epi == kEpiSample) allow_split = false;
+  switch (tile_row_blocks(M, N, K, epi, allow_split)) {
+    case 4: launch_tile<4>(s, X, W, out, M, N, K, epi, allow_split, e); return;
+    case 3: launch_tile<3>(s, X, W, out, M, N, K, epi, allow_split, e); return;
+  }
   // 128-row tiles for the K-split projections whose halved grid still fills the chip (QKV at the 8B shape: 16 -> 15 us
   // at 32 rows, 20.5 -> 17.8 us at 64); measured a loss for gate/up and the output projection, which keep 64-row tiles.
   const bool wide = epi == kEpiPartial && make_plan(N, K, epi, allow_split).splits > 1 &&

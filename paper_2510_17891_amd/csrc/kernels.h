@@ -113,7 +113,7 @@ void launch_attn_f32(hipStream_t s, const Geometry& g, const float* q, const Row
                      float* o_out, int M);
 
 // ---- projections ---------------------------------------------------------------------------------
-enum Epilogue : int { kEpiPartial = 0, kEpiSwiGLU = 1, kEpiSample = 2 };
+enum Epilogue : int { kEpiPartial = 0, kEpiSwiGLU = 1, kEpiSample = 2, kEpiResidual = 3 };
 
 // Arguments of the sampling epilogue of the output projection (ignored by the other epilogues).
 struct SampleEpilogue {
@@ -130,9 +130,14 @@ struct SampleEpilogue {
 
 // Number of K splits the bf16 GEMM uses for (N, K); partial outputs are [S][M][N] fp32.
 int gemm_bf16_splits(int N, int K, int epi);
+// Partial outputs that a kEpiPartial launch of M rows leaves: the splits, or 1 where the kernel adds them up itself.
+int gemm_bf16_partials(int M, int N, int K);
+// Whether a product of M rows can be added to the residual stream by the projection itself (kEpiResidual).
+bool gemm_bf16_adds_residual(int M, int N, int K);
 // MFMA GEMM of the bf16 models: X f16 fragment-major [M x K], W bf16 fragment-major [N x K] (2N rows for SwiGLU: gate
 // and up rows interleaved in groups of 16).
-// kEpiPartial: out = fp32 [S][M][N];  kEpiSwiGLU: out = f16 fragment-major [M x N] = silu(gate)*up;
+// kEpiPartial: out = fp32 [gemm_bf16_partials(M, N, K)][M][N];  kEpiResidual (only where gemm_bf16_adds_residual): out =
+// fp32 [M][N], to which the product's split sums are added in split order;  kEpiSwiGLU: out = f16 fragment-major [M x N] = silu(gate)*up;
 // kEpiSample: out unused, results go through *se.  allow_split = false forces S = 1 (finished [M][N] product).
 void launch_gemm_bf16(hipStream_t s, const void* X, const void* W, void* out, int M, int N, int K, int epi,
                       bool allow_split = true, const SampleEpilogue* se = nullptr);

@@ -223,7 +223,8 @@ rl_status ring_acquire(rl_model* m, int* slot_out) {
 }
 
 // Run all decoder layers on the M rows whose residual stream sits in ws.x.  Leaves the last down-projection's
-// split partials pending; returns their count so that the caller's final residual_norm adds them.
+// split partials pending; returns their count (0 where the projection added them itself) so that the caller's final
+// residual_norm adds them.
 struct SharedAttn {  // device pointers into the metadata slot of the call (empty: every row on its own)
   const int32_t* skip = nullptr;
   const AttnShared* sets = nullptr;
@@ -253,7 +254,7 @@ int run_layers(rl_model* m, hipStream_t st, int M, const RowMeta* rows, int max_
       launch_residual_norm(st, g.dtype, x, pend ? part : nullptr, pend, m->attn_norm[l], h, cap, M, H, g.rms_eps); }
     int s_qkv = 1;
     { Timer t(m, st, K_QKV);
-      if (bf) { launch_gemm_bf16(st, h, m->wqkv[l], part, M, nqkv, H, kEpiPartial); s_qkv = gemm_bf16_splits(nqkv, H, kEpiPartial); }
+      if (bf) { launch_gemm_bf16(st, h, m->wqkv[l], part, M, nqkv, H, kEpiPartial); s_qkv = gemm_bf16_partials(M, nqkv, H); }
       else launch_gemm_f32(st, (const float*)h, (const float*)m->wqkv[l], part, M, nqkv, H, kEpiPartial); }
     const void* q_gain = g.qk_norm ? m->q_norm[l] : nullptr;
     const void* k_gain = g.qk_norm ? m->k_norm[l] : nullptr;
@@ -279,15 +280,17 @@ int run_layers(rl_model* m, hipStream_t st, int M, const RowMeta* rows, int max_
     }
     int s_o = 1;
     { Timer t(m, st, K_OPROJ);
-      if (bf) { launch_gemm_bf16(st, o, m->wo[l], part, M, H, nqd, kEpiPartial); s_o = gemm_bf16_splits(H, nqd, kEpiPartial); }
+      if (bf && gemm_bf16_adds_residual(M, H, nqd)) { launch_gemm_bf16(st, o, m->wo[l], x, M, H, nqd, kEpiResidual); s_o = 0; }
+      else if (bf) { launch_gemm_bf16(st, o, m->wo[l], part, M, H, nqd, kEpiPartial); s_o = gemm_bf16_partials(M, H, nqd); }
       else launch_gemm_f32(st, (const float*)o, (const float*)m->wo[l], part, M, H, nqd, kEpiPartial); }
     { Timer t(m, st, K_NORM);
-      launch_residual_norm(st, g.dtype, x, part, s_o, m->mlp_norm[l], h, nullptr, M, H, g.rms_eps); }
+      launch_residual_norm(st, g.dtype, x, s_o ? part : nullptr, s_o, m->mlp_norm[l], h, nullptr, M, H, g.rms_eps); }
     { Timer t(m, st, K_GATEUP);
       if (bf) launch_gemm_bf16(st, h, m->w_gate_up[l], a, M, F, H, kEpiSwiGLU);
       else launch_gemm_f32(st, (const float*)h, (const float*)m->w_gate_up[l], (float*)a, M, F, H, kEpiSwiGLU); }
     { Timer t(m, st, K_DOWN);
-      if (bf) { launch_gemm_bf16(st, a, m->w_down[l], part, M, H, F, kEpiPartial); pend = gemm_bf16_splits(H, F, kEpiPartial); }
+      if (bf && gemm_bf16_adds_residual(M, H, F)) { launch_gemm_bf16(st, a, m->w_down[l], x, M, H, F, kEpiResidual); pend = 0; }
+      else if (bf) { launch_gemm_bf16(st, a, m->w_down[l], part, M, H, F, kEpiPartial); pend = gemm_bf16_partials(M, H, F); }
       else { launch_gemm_f32(st, (const float*)a, (const float*)m->w_down[l], part, M, H, F, kEpiPartial); pend = 1; } }
   }
   return pend;
@@ -791,7 +794,8 @@ rl_status rl_decode_hidden(rl_model* m, void* stream, int32_t n, const int32_t* 
   HIP_TRY(hipMemcpyAsync(x, hidden_in, bytes, hipMemcpyDeviceToDevice, st));
   int pend = run_layers(m, st, n, rows, max_ctx_in_batch, sa, true);
   float* cap = m->capture ? m->capture + (size_t)m->geo.n_layers * m->cfg.max_rows * m->geo.hidden : nullptr;
-  { Timer t(m, st, K_NORM);
+  if (pend || cap) {
+    Timer t(m, st, K_NORM);
     launch_residual_norm(st, m->geo.dtype, x, m->wsp<float>(m->lay.part), pend, nullptr, nullptr, cap, n, m->geo.hidden, m->geo.rms_eps); }
   HIP_TRY(hipMemcpyAsync(hidden_out, x, bytes, hipMemcpyDeviceToDevice, st));
   HIP_TRY(hipGetLastError());
@@ -922,7 +926,8 @@ static rl_status prefill_impl(rl_model* m, hipStream_t st, int32_t n_prompts, in
     int pend = run_layers(m, st, M, rows, max_ctx, sa);
     // fold the pending partials into x, then keep the rows that end a prompt (one copy per group member)
     float* cap = m->capture ? m->capture + (size_t)m->geo.n_layers * m->cfg.max_rows * H : nullptr;
-    { Timer t(m, st, K_NORM);
+    if (pend || cap) {
+      Timer t(m, st, K_NORM);
       launch_residual_norm(st, m->geo.dtype, x, m->wsp<float>(m->lay.part), pend, nullptr, nullptr, cap, M, H, m->geo.rms_eps); }
     for (const Last& l : lasts)
       for (int j = 0; j < group; ++j)

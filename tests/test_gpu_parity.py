@@ -1455,3 +1455,21 @@ def test_bf16_layer_bits_do_not_depend_on_batch_size_class(amd):
         ro.close()
     for o in outs[1:]:
         assert torch.equal(o, outs[0])
+
+
+@pytest.mark.parametrize("over, sizes", [
+    (dict(), (257, 512, 897)),                                       # 8B shape: whole-K tiles of 4 and 3 row blocks, residual sums
+    (dict(hidden=2048, n_q=16, n_kv=4, ffn=6400), (300, 641)),       # gate/up in 400 row blocks: ragged tiles and batch tiles
+])
+def test_bf16_layer_bits_in_whole_k_tiles(amd, over, sizes):
+    """More than 256 rows run the projections that walk the whole K range of a tile and add split sums and the residual
+    themselves; the first five rows keep the bits they have in a batch of five."""
+    base = [40, 513, 100, 257, 31]
+    outs = []
+    for n in (5,) + sizes:
+        ctxs = base + [(11 * i) % 60 for i in range(n - 5)]
+        shape, wn, ro, ks, vs, x = _layer_case(amd, ctxs, seed=37, **over)
+        outs.append(ro.rl_decode_hidden(list(range(n)), x.to(DEV)).cpu()[:5])
+        ro.close()
+    for o in outs[1:]:
+        assert torch.equal(o, outs[0])
