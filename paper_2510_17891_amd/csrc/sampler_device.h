@@ -77,6 +77,13 @@ __device__ __forceinline__ unsigned long long fexp_weight(float x) {
   p = __fmaf_rn(p, f, 0x1.ebfbe0p-3f);
   p = __fmaf_rn(p, f, 0x1.62e430p-1f);
   p = __fmaf_rn(p, f, 1.0f);
+  // p lies in (0.7, 1.5): its 24-bit significand moved to where 2^(n+32) puts it, which is the conversion of
+  // ldexpf(p, n + 32) for n <= 0 (a third of its instructions; n > 0 only when s_max itself is rounded by more than 0.3)
+  if (n <= 0.0f) {
+    const uint32_t b = __float_as_uint(p);
+    const int e = (int)(b >> 23) - 127;
+    return ((unsigned long long)((b & 0x007fffffu) | 0x00800000u) << 10) >> (1 - e - (int)n);
+  }
   return (unsigned long long)ldexpf(p, (int)n + 32);
 }
 // A cut of the order: token i with key k is kept iff it does not come after (key, idx).

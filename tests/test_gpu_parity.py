@@ -1473,3 +1473,28 @@ def test_bf16_layer_bits_in_whole_k_tiles(amd, over, sizes):
         ro.close()
     for o in outs[1:]:
         assert torch.equal(o, outs[0])
+
+
+def test_truncated_sampler_rows_that_leave_the_list_path(amd):
+    """Rows whose cut does not fit the list of its bin (thousands of tokens within a thousandth of the range, long runs
+    of equal logits, a single infinite logit) are selected digit by digit: same cut and draw as the oracle."""
+    V, n = 20000, 5
+    ro = _sampler_model(amd, V, False)
+    z = ri.normal((n, V), 2.0, 8, 73)
+    z[0] = z[0] * 1e-4                       # a narrow crowd ...
+    z[0, 11] = 60.0                          # ... and one outlier that sets the range
+    z[1] = torch.round(z[1] * 2) / 2         # runs of thousands of equal logits
+    z[2] = torch.round(z[2] * 32) / 32       # runs of hundreds
+    z[3, 4000:] = float("-inf")              # mostly masked
+    z[4, 77] = float("inf")
+    zd = z.to(DEV)
+    seqs, poss = [3, 0, 7, 63, 1], [0, 1, 65535, 77, 2048]
+    for T, k, p in [(0.6, 0, 0.95), (1.0, 5000, 0.0), (1.3, 700, 0.9), (25.0, 0, 0.97), (25.0, 12000, 0.5)]:
+        tok, lp = ro.rl_sample_logits(zd, seqs, poss, T, 5, top_k=k, top_p=p)
+        torch.cuda.synchronize()
+        for r in range(n if p == 0.0 else 4):
+            t_ref, lp_ref, kept = orc.sample_truncated(z[r].numpy(), T, k, p, 5, seqs[r], poss[r])
+            assert int(tok[r]) == t_ref, (T, k, p, r, kept)
+            if r < 4:
+                assert abs(float(lp[r]) - lp_ref) < 1e-5 * max(1.0, abs(lp_ref)), (T, k, p, r, float(lp[r]), lp_ref)
+    ro.close()
