@@ -1,133 +1,227 @@
-// fp32 kernels for models stored in fp32 (any dimensions that are multiples of 8): projections on the vector
-// ALUs and single-pass paged attention.  These serve the small full-precision configuration, where every
-// tensor fits in cache and launches dominate; they are written for exactness and generality, not bandwidth.
+// fp32 kernels for models stored in fp32 (any dimensions that are multiples of 8): projections on the vector ALUs and
+// paged attention.  These serve the small full-precision configuration, where every tensor fits in cache and a step is a
+// chain of launches that each last about as long as a few dependent memory round trips.  They are therefore written for
+// few launches (norm and residual inside the projections, rotation and KV append inside the attention) and for having
+// all loads of a launch in flight at once.  A decode step of 4 rows through two layers of 256 hidden dimensions, sampling
+// included: 73 us in 15 launches, where separate norms, rotation and append, projections with one 4-byte load per lane
+// and 48 exchanges per 8 sums, and a single wave per attention head took 150 us in 23.
 #include "device_utils.h"
 #include "kernels.h"
+#include "rope_device.h"
 
 namespace rl {
 
 namespace {
 
-constexpr int kRowsPerPass = 8;
+// Sums of R values over the 64 lanes, the total of value i in lanes i, i + R, ...: every exchange step halves the values a
+// lane still carries (7 exchanges for 4 values instead of 24).  Each value is added up in the same tree whatever R is.
+template <int R>
+__device__ __forceinline__ float wave_sums(const float (&v)[R], int lane) {
+  float a[R];
+#pragma unroll
+  for (int i = 0; i < R; ++i) a[i] = v[i];
+  int n = R;
+#pragma unroll
+  for (int mask = 1; mask < 64; mask <<= 1) {
+    if (n > 1) {
+      const bool up = (lane & mask) != 0;
+#pragma unroll
+      for (int i = 0; i < R / 2; ++i)
+        if (i < n / 2) {
+          const float keep = up ? a[2 * i + 1] : a[2 * i], send = up ? a[2 * i] : a[2 * i + 1];
+          a[i] = keep + __shfl_xor(send, mask, kWave);
+        }
+      n >>= 1;
+    } else {
+      a[0] += __shfl_xor(a[0], mask, kWave);
+    }
+  }
+  return a[0];
+}
 
-// One wave per output column n (4 waves per block), all M rows in passes of 8.
-// kEpiSwiGLU: W has 2N rows (gate then up); out[m][n] = silu(gate)*up.
-template <int EPI>
+// One wave per output column n (4 waves per block) and R rows: lane l takes the elements 4l .. 4l + 3 of every 256.
+// kEpiSwiGLU: W has 2N rows (gate then up); out[m][n] = silu(gate)*up.  kEpiResidual: out[m][n] += product.
+// gain (may be null): the rows are RMS-normalised first, x * rsqrt(mean(x^2) + eps) * gain; every wave forms the row's
+// mean square from the elements it holds anyway.  A row's result depends neither on R nor on the rows beside it.
+template <int EPI, int R>
 __global__ __launch_bounds__(256) void gemm_f32_kernel(const float* __restrict__ X, const float* __restrict__ W,
-                                                       float* __restrict__ out, int M, int N, int K) {
+                                                       float* __restrict__ out, int M, int N, int K,
+                                                       const float* __restrict__ gain, float eps) {
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-  const int n = blockIdx.x * 4 + wave;
+  const int n = blockIdx.x * 4 + wave, m0 = blockIdx.y * R;
   if (n >= N) return;
   const float* w0 = W + (size_t)n * K;
   const float* w1 = W + (size_t)(n + N) * K;  // only read for SwiGLU
-  for (int m0 = 0; m0 < M; m0 += kRowsPerPass) {
-    float a0[kRowsPerPass], a1[kRowsPerPass];
+  float a0[R], a1[R], ss[R];
 #pragma unroll
-    for (int i = 0; i < kRowsPerPass; ++i) a0[i] = a1[i] = 0.f;
-    for (int k = lane; k < K; k += 64) {
-      const float wv0 = w0[k];
-      const float wv1 = (EPI == kEpiSwiGLU) ? w1[k] : 0.f;
+  for (int i = 0; i < R; ++i) a0[i] = a1[i] = ss[i] = 0.f;
+#pragma unroll 4
+  for (int k = 4 * lane; k < K; k += 256) {
+    const float4 u = *(const float4*)(w0 + k);
+    float4 v = make_float4(0.f, 0.f, 0.f, 0.f), g = make_float4(1.f, 1.f, 1.f, 1.f);
+    if (EPI == kEpiSwiGLU) v = *(const float4*)(w1 + k);
+    if (gain) g = *(const float4*)(gain + k);
 #pragma unroll
-      for (int i = 0; i < kRowsPerPass; ++i) {
-        const int m = min(m0 + i, M - 1);
-        const float xv = X[(size_t)m * K + k];
-        a0[i] = fmaf(wv0, xv, a0[i]);
-        if (EPI == kEpiSwiGLU) a1[i] = fmaf(wv1, xv, a1[i]);
+    for (int i = 0; i < R; ++i) {
+      float4 x = *(const float4*)(X + (size_t)min(m0 + i, M - 1) * K + k);
+      if (gain) {
+        ss[i] = fmaf(x.x, x.x, fmaf(x.y, x.y, fmaf(x.z, x.z, fmaf(x.w, x.w, ss[i]))));
+        x.x *= g.x; x.y *= g.y; x.z *= g.z; x.w *= g.w;
+      }
+      a0[i] = fmaf(u.x, x.x, fmaf(u.y, x.y, fmaf(u.z, x.z, fmaf(u.w, x.w, a0[i]))));
+      if (EPI == kEpiSwiGLU) a1[i] = fmaf(v.x, x.x, fmaf(v.y, x.y, fmaf(v.z, x.z, fmaf(v.w, x.w, a1[i]))));
+    }
+  }
+  float s0 = wave_sums<R>(a0, lane), s1 = 0.f;
+  if (EPI == kEpiSwiGLU) s1 = wave_sums<R>(a1, lane);
+  if (gain) {
+    const float inv = 1.0f / sqrtf(wave_sums<R>(ss, lane) / (float)K + eps);
+    s0 *= inv;
+    s1 *= inv;
+  }
+  const int m = m0 + lane;
+  if (lane >= R || m >= M) return;
+  float* o = out + (size_t)m * N + n;
+  if (EPI == kEpiSwiGLU) *o = s0 / (1.0f + expf(-s0)) * s1;
+  else if (EPI == kEpiResidual) *o += s0;
+  else *o = s0;
+}
+
+struct F32Append {
+  const float* qkv;  // [M][(n_q + 2 n_kv) * d]
+  const float* q_gain;
+  const float* k_gain;
+  const float2* rope;
+  float eps;
+};
+
+// One block of four waves per (row, q head), keys in tiles of 256: one key per thread for the scores; for the weighted
+// sum a thread owns VEC dims and every (256 / (d / VEC))-th key; online softmax across tiles.  d <= 128, d % VEC == 0.
+// APPEND (one row per sequence): the block forms its query and the row's new key and value from the QKV projection, uses
+// the latter two from LDS, and the first head of the group writes them to the row's page.
+template <bool APPEND, int VEC>
+__global__ __launch_bounds__(256) void attn_f32_kernel(const float* __restrict__ q, const RowMeta* __restrict__ rows,
+                                                       const int32_t* __restrict__ block_table, int max_blocks,
+                                                       float* k_pool, float* v_pool, float* __restrict__ o_out, int n_q,
+                                                       int n_kv, int d, float scale, F32Append ap) {
+  typedef float vec_t __attribute__((ext_vector_type(VEC)));
+  __shared__ __align__(16) float qs[128], kn[128], vn[128], ps[256], part[256 * VEC];
+  __shared__ float red[8];
+  const int h = blockIdx.x, r = blockIdx.y, tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
+  const RowMeta rm = rows[r];
+  const int ctx = rm.pos + 1, group = n_q / n_kv, hk = h / group;
+  const int32_t* bt = block_table + (size_t)rm.seq * max_blocks;
+  const size_t page_elems = (size_t)kPageTokens * d;
+  if (APPEND) {
+    if (wave < 3) {  // query, new key, new value: one wave each
+      const int half = d >> 1;
+      const int head = wave == 0 ? h : wave == 1 ? n_q + hk : n_q + n_kv + hk;
+      const bool norm = ap.q_gain != nullptr && wave < 2;
+      HeadPair hp = head_pair_load<false>(ap.qkv + ((size_t)r * (n_q + 2 * n_kv) + head) * d, 1, 0, d, lane, wave < 2,
+                                          ap.rope + (size_t)rm.pos * half, norm ? (wave == 0 ? ap.q_gain : ap.k_gain) : nullptr);
+      head_pair_finish(hp, d, wave < 2, norm, ap.eps);
+      if (lane < half) {
+        float* s = wave == 0 ? qs : wave == 1 ? kn : vn;
+        s[lane] = hp.v0;
+        s[lane + half] = hp.v1;
+        if (wave > 0 && h == hk * group) {
+          float* p = (wave == 1 ? k_pool : v_pool) + ((size_t)rm.page * n_kv + hk) * 2 * page_elems + (size_t)(rm.pos & 15) * d;
+          p[lane] = hp.v0;
+          p[lane + half] = hp.v1;
+        }
       }
     }
+  } else {
+    for (int i = tid; i < d; i += 256) qs[i] = q[((size_t)r * n_q + h) * d + i];
+  }
+  __syncthreads();
+  const int nd = d / VEC, groups = 256 / nd, dim = (tid % nd) * VEC, grp = tid / nd;
+  vec_t acc = 0.f;
+  float m_run = -INFINITY, l_run = 0.f;
+  for (int kb = 0; kb < ctx; kb += 256) {
+    const int key = kb + tid;
+    float sc = -INFINITY;
+    if (key < ctx) {
+      const float* kp = APPEND && key == rm.pos ? kn : k_pool + ((size_t)bt[key >> 4] * n_kv + hk) * 2 * page_elems + (size_t)(key & 15) * d;
+      vec_t dot = 0.f;
+#pragma unroll 8
+      for (int i = 0; i < d; i += VEC) dot += *(const vec_t*)(qs + i) * *(const vec_t*)(kp + i);
+      float s = dot[0];
 #pragma unroll
-    for (int i = 0; i < kRowsPerPass; ++i) {
-      const float s0 = wave_sum(a0[i]);
-      const float s1 = (EPI == kEpiSwiGLU) ? wave_sum(a1[i]) : 0.f;
-      if (lane == 0 && m0 + i < M) {
-        if (EPI == kEpiSwiGLU)
-          out[(size_t)(m0 + i) * N + n] = s0 / (1.0f + expf(-s0)) * s1;
-        else
-          out[(size_t)(m0 + i) * N + n] = s0;
+      for (int e = 1; e < VEC; ++e) s += dot[e];
+      sc = s * scale;
+    }
+    float mx = wave_max(sc);
+    if (lane == 0) red[wave] = mx;
+    __syncthreads();
+    const float m_new = fmaxf(m_run, fmaxf(fmaxf(red[0], red[1]), fmaxf(red[2], red[3])));
+    const float p = expf(sc - m_new);
+    ps[tid] = p;
+    const float sum = wave_sum(p);
+    if (lane == 0) red[4 + wave] = sum;
+    __syncthreads();
+    const float alpha = expf(m_run - m_new);
+    l_run = l_run * alpha + ((red[4] + red[5]) + (red[6] + red[7]));
+    m_run = m_new;
+    acc *= alpha;
+    if (grp < groups) {
+      const int nk = min(256, ctx - kb);
+#pragma unroll 4
+      for (int t = grp; t < nk; t += groups) {
+        const int kt = kb + t;
+        const float* vp = APPEND && kt == rm.pos ? vn : v_pool + ((size_t)bt[kt >> 4] * n_kv + hk) * 2 * page_elems + (size_t)(kt & 15) * d;
+        acc += ps[t] * *(const vec_t*)(vp + dim);
       }
     }
+    __syncthreads();
+  }
+  if (grp < groups) *(vec_t*)(part + grp * d + dim) = acc;  // groups * d <= 256 * VEC
+  __syncthreads();
+  const float inv = 1.0f / l_run;
+  for (int i = tid; i < d; i += 256) {
+    float s = 0.f;
+    for (int g = 0; g < groups; ++g) s += part[g * d + i];
+    o_out[((size_t)r * n_q + h) * d + i] = s * inv;
   }
 }
 
-// One wave per (row, q head); keys in blocks of 64 (one key per lane for the scores, one dim per lane for
-// the weighted sum), online softmax across blocks.  head_dim <= 256.
-__global__ __launch_bounds__(64) void attn_f32_kernel(const float* __restrict__ q, const RowMeta* __restrict__ rows,
-                                                      const int32_t* __restrict__ block_table, int max_blocks,
-                                                      const float* __restrict__ k_pool, const float* __restrict__ v_pool,
-                                                      float* __restrict__ o_out, int n_q, int n_kv, int d, float scale) {
-  __shared__ float qs[256];
-  __shared__ float ps[64];
-  __shared__ int32_t pg[4];
-  const int h = blockIdx.x, r = blockIdx.y, lane = threadIdx.x;
-  const RowMeta rm = rows[r];
-  const int ctx = rm.pos + 1;
-  const int hk = h / (n_q / n_kv);
-  for (int i = lane; i < d; i += 64) qs[i] = q[((size_t)r * n_q + h) * d + i];
-  __syncthreads();
-  const size_t page_elems = (size_t)kPageTokens * d;
-  float acc[4] = {0.f, 0.f, 0.f, 0.f};  // dims lane, lane+64, lane+128, lane+192
-  float m_run = -INFINITY, l_run = 0.f;
-  for (int kb = 0; kb < ctx; kb += 64) {
-    if (lane < 4) {
-      int blk = (kb >> 4) + lane;
-      const int last = (ctx - 1) >> 4;
-      pg[lane] = block_table[(size_t)rm.seq * max_blocks + (blk > last ? last : blk)];
-    }
-    __syncthreads();
-    const int key = kb + lane;
-    float sc = -INFINITY;
-    if (key < ctx) {
-      const float* kp = k_pool + ((size_t)pg[lane >> 4] * n_kv + hk) * 2 * page_elems + (size_t)(key & 15) * d;
-      float dot = 0.f;
-      for (int i = 0; i < d; ++i) dot = fmaf(qs[i], kp[i], dot);
-      sc = dot * scale;
-    }
-    const float m_new = fmaxf(m_run, wave_max(sc));
-    const float alpha = expf(m_run - m_new);
-    const float p = expf(sc - m_new);
-    l_run = l_run * alpha + wave_sum(p);
-    m_run = m_new;
-    ps[lane] = p;
-    __syncthreads();
-    const int nk = min(64, ctx - kb);
-#pragma unroll
-    for (int c = 0; c < 4; ++c) {
-      const int i = lane + 64 * c;
-      if (i < d) {
-        float a = acc[c] * alpha;
-        for (int t = 0; t < nk; ++t) {
-          const float* vp = v_pool + ((size_t)pg[t >> 4] * n_kv + hk) * 2 * page_elems + (size_t)(t & 15) * d;
-          a = fmaf(ps[t], vp[i], a);
-        }
-        acc[c] = a;
-      }
-    }
-    __syncthreads();
-  }
-  const float inv = 1.0f / l_run;
-#pragma unroll
-  for (int c = 0; c < 4; ++c) {
-    const int i = lane + 64 * c;
-    if (i < d) o_out[((size_t)r * n_q + h) * d + i] = acc[c] * inv;
-  }
+template <int R>
+void launch_gemm_rows(hipStream_t s, const float* X, const float* W, float* out, int M, int N, int K, int epi, const float* gain,
+                      float eps) {
+  const dim3 grid((N + 3) / 4, (M + R - 1) / R);
+  if (epi == kEpiSwiGLU)
+    gemm_f32_kernel<kEpiSwiGLU, R><<<grid, 256, 0, s>>>(X, W, out, M, N, K, gain, eps);
+  else if (epi == kEpiResidual)
+    gemm_f32_kernel<kEpiResidual, R><<<grid, 256, 0, s>>>(X, W, out, M, N, K, gain, eps);
+  else
+    gemm_f32_kernel<kEpiPartial, R><<<grid, 256, 0, s>>>(X, W, out, M, N, K, gain, eps);
 }
 
 }  // namespace
 
-void launch_gemm_f32(hipStream_t s, const float* X, const float* W, float* out, int M, int N, int K, int epi) {
-  dim3 grid((N + 3) / 4);
-  if (epi == kEpiSwiGLU)
-    gemm_f32_kernel<kEpiSwiGLU><<<grid, 256, 0, s>>>(X, W, out, M, N, K);
-  else
-    gemm_f32_kernel<kEpiPartial><<<grid, 256, 0, s>>>(X, W, out, M, N, K);
+void launch_gemm_f32(hipStream_t s, const float* X, const float* W, float* out, int M, int N, int K, int epi, const float* gain,
+                     float eps) {
+  // rows per wave: the smallest of 1, 4 and 8 that holds the batch (rows beyond it would be computed for nothing), 8 beyond
+  if (M == 1) launch_gemm_rows<1>(s, X, W, out, M, N, K, epi, gain, eps);
+  else if (M <= 4) launch_gemm_rows<4>(s, X, W, out, M, N, K, epi, gain, eps);
+  else launch_gemm_rows<8>(s, X, W, out, M, N, K, epi, gain, eps);
 }
 
 void launch_attn_f32(hipStream_t s, const Geometry& g, const float* q, const RowMeta* rows, const int32_t* block_table,
-                     const void* k_pool_layer, const void* v_pool_layer, float* o_out, int M) {
-  dim3 grid(g.n_q, M);
-  attn_f32_kernel<<<grid, 64, 0, s>>>(q, rows, block_table, g.max_blocks, (const float*)k_pool_layer,
-                                      (const float*)v_pool_layer, o_out, g.n_q, g.n_kv, g.head_dim,
-                                      1.0f / sqrtf((float)g.head_dim));
+                     void* k_pool_layer, void* v_pool_layer, float* o_out, int M, const AttnAppend* append) {
+  const dim3 grid(g.n_q, M);
+  F32Append ap = {};
+  if (append) ap = F32Append{append->qkv_part, (const float*)append->q_gain, (const float*)append->k_gain, append->rope_table, g.rms_eps};
+  const float scale = 1.0f / sqrtf((float)g.head_dim);
+#define RL_ATTN_F32(APP, VEC)                                                                                       \
+  attn_f32_kernel<APP, VEC><<<grid, 256, 0, s>>>(q, rows, block_table, g.max_blocks, (float*)k_pool_layer,          \
+                                                 (float*)v_pool_layer, o_out, g.n_q, g.n_kv, g.head_dim, scale, ap)
+  if (g.head_dim % 4 == 0) {
+    if (append) RL_ATTN_F32(true, 4); else RL_ATTN_F32(false, 4);
+  } else {  // an even head_dim: pairs keep the loads aligned
+    if (append) RL_ATTN_F32(true, 2); else RL_ATTN_F32(false, 2);
+  }
+#undef RL_ATTN_F32
 }
 
 }  // namespace rl

@@ -107,10 +107,11 @@ bool launch_attn_decode_bf16(hipStream_t s, const Geometry& g, const float* q, c
                              int max_shared_segs = 0, const AttnAppend* append = nullptr, int segs_per_block = 16);
 void launch_attn_merge_bf16(hipStream_t s, const Geometry& g, const RowMeta* rows, float* part, int max_segs_alloc,
                             void* o_out, int M, const int32_t* skip_segs, int n_shared);
-// fp32, any head_dim <= 256: one wave per (row, q head), whole context, output fp32 row-major [M][n_q*d].
+// fp32, even head_dim <= 128: one block per (row, q head), whole context, output fp32 row-major [M][n_q*d].  append (may
+// be null; S == 1): as for the bf16 attention, only for batches with one row per sequence.
 void launch_attn_f32(hipStream_t s, const Geometry& g, const float* q, const RowMeta* rows,
-                     const int32_t* block_table, const void* k_pool_layer, const void* v_pool_layer,
-                     float* o_out, int M);
+                     const int32_t* block_table, void* k_pool_layer, void* v_pool_layer,
+                     float* o_out, int M, const AttnAppend* append = nullptr);
 
 // ---- projections ---------------------------------------------------------------------------------
 enum Epilogue : int { kEpiPartial = 0, kEpiSwiGLU = 1, kEpiSample = 2, kEpiResidual = 3 };
@@ -141,8 +142,10 @@ bool gemm_bf16_adds_residual(int M, int N, int K);
 // kEpiSample: out unused, results go through *se.  allow_split = false forces S = 1 (finished [M][N] product).
 void launch_gemm_bf16(hipStream_t s, const void* X, const void* W, void* out, int M, int N, int K, int epi,
                       bool allow_split = true, const SampleEpilogue* se = nullptr);
-// fp32 GEMM on vector ALUs, row-major everything; kEpiPartial writes [M][N] (one split).
-void launch_gemm_f32(hipStream_t s, const float* X, const float* W, float* out, int M, int N, int K, int epi);
+// fp32 GEMM on vector ALUs, row-major everything, K % 4 == 0; kEpiPartial writes [M][N] (one split), kEpiResidual adds to
+// it.  gain (may be null): K gains; the rows of X are RMS-normalised with them first.
+void launch_gemm_f32(hipStream_t s, const float* X, const float* W, float* out, int M, int N, int K, int epi,
+                     const float* gain = nullptr, float eps = 0.f);
 
 // Row-major [N x K] bf16 -> fragment-major with the k blocks in weight_kb_slot order for segments of `seg` k blocks
 // (N % 32 == 0, K % 64 == 0, (K / 64) % (4 seg) == 0).

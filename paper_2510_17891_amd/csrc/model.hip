@@ -250,15 +250,18 @@ int run_layers(rl_model* m, hipStream_t st, int M, const RowMeta* rows, int max_
   int pend = 0;
   for (int l = 0; l < g.n_layers; ++l) {
     float* cap = m->capture ? m->capture + (size_t)l * m->cfg.max_rows * H : nullptr;
-    { Timer t(m, st, K_NORM);
-      launch_residual_norm(st, g.dtype, x, pend ? part : nullptr, pend, m->attn_norm[l], h, cap, M, H, g.rms_eps); }
+    if (bf || cap) {  // fp32: the projections normalise their rows themselves; this only copies x for a capture
+      Timer t(m, st, K_NORM);
+      launch_residual_norm(st, g.dtype, x, pend ? part : nullptr, pend, bf ? m->attn_norm[l] : nullptr, h, cap, M, H, g.rms_eps);
+    }
     int s_qkv = 1;
     { Timer t(m, st, K_QKV);
       if (bf) { launch_gemm_bf16(st, h, m->wqkv[l], part, M, nqkv, H, kEpiPartial); s_qkv = gemm_bf16_partials(M, nqkv, H); }
-      else launch_gemm_f32(st, (const float*)h, (const float*)m->wqkv[l], part, M, nqkv, H, kEpiPartial); }
+      else launch_gemm_f32(st, x, (const float*)m->wqkv[l], part, M, nqkv, H, kEpiPartial, (const float*)m->attn_norm[l], g.rms_eps); }
     const void* q_gain = g.qk_norm ? m->q_norm[l] : nullptr;
     const void* k_gain = g.qk_norm ? m->k_norm[l] : nullptr;
-    const bool fused = bf && one_row_per_seq && m->attention_appends && s_qkv <= kAttnAppendMaxSplits;
+    const bool fused = one_row_per_seq && m->attention_appends && s_qkv <= kAttnAppendMaxSplits;
+    const AttnAppend ap = {part, s_qkv, q_gain, k_gain, rope};
     if (!fused) {
       Timer t(m, st, K_ROPE_APPEND);
       launch_qk_rope_append(st, g, part, s_qkv, q_gain, k_gain, rope, rows, m->k_pool(l), m->v_pool(l), q, M);
@@ -266,7 +269,6 @@ int run_layers(rl_model* m, hipStream_t st, int M, const RowMeta* rows, int max_
     if (bf) {
       bool merge;
       { Timer t(m, st, K_ATTN);
-        const AttnAppend ap = {part, s_qkv, q_gain, k_gain, rope};
         merge = launch_attn_decode_bf16(st, g, q, rows, bt, m->k_pool(l), m->v_pool(l), apart, m->lay.max_segs, max_ctx_in_batch,
                                         o, M, sa.skip, sa.sets, sa.n_sets, sa.max_segs, fused ? &ap : nullptr,
                                         m->attn_segs_per_block); }
@@ -276,22 +278,24 @@ int run_layers(rl_model* m, hipStream_t st, int M, const RowMeta* rows, int max_
       }
     } else {
       Timer t(m, st, K_ATTN);
-      launch_attn_f32(st, g, q, rows, bt, m->k_pool(l), m->v_pool(l), (float*)o, M);
+      launch_attn_f32(st, g, q, rows, bt, m->k_pool(l), m->v_pool(l), (float*)o, M, fused ? &ap : nullptr);
     }
     int s_o = 1;
     { Timer t(m, st, K_OPROJ);
       if (bf && gemm_bf16_adds_residual(M, H, nqd)) { launch_gemm_bf16(st, o, m->wo[l], x, M, H, nqd, kEpiResidual); s_o = 0; }
       else if (bf) { launch_gemm_bf16(st, o, m->wo[l], part, M, H, nqd, kEpiPartial); s_o = gemm_bf16_partials(M, H, nqd); }
-      else launch_gemm_f32(st, (const float*)o, (const float*)m->wo[l], part, M, H, nqd, kEpiPartial); }
-    { Timer t(m, st, K_NORM);
-      launch_residual_norm(st, g.dtype, x, s_o ? part : nullptr, s_o, m->mlp_norm[l], h, nullptr, M, H, g.rms_eps); }
+      else { launch_gemm_f32(st, (const float*)o, (const float*)m->wo[l], x, M, H, nqd, kEpiResidual); s_o = 0; } }
+    if (bf) {
+      Timer t(m, st, K_NORM);
+      launch_residual_norm(st, g.dtype, x, s_o ? part : nullptr, s_o, m->mlp_norm[l], h, nullptr, M, H, g.rms_eps);
+    }
     { Timer t(m, st, K_GATEUP);
       if (bf) launch_gemm_bf16(st, h, m->w_gate_up[l], a, M, F, H, kEpiSwiGLU);
-      else launch_gemm_f32(st, (const float*)h, (const float*)m->w_gate_up[l], (float*)a, M, F, H, kEpiSwiGLU); }
+      else launch_gemm_f32(st, x, (const float*)m->w_gate_up[l], (float*)a, M, F, H, kEpiSwiGLU, (const float*)m->mlp_norm[l], g.rms_eps); }
     { Timer t(m, st, K_DOWN);
       if (bf && gemm_bf16_adds_residual(M, H, F)) { launch_gemm_bf16(st, a, m->w_down[l], x, M, H, F, kEpiResidual); pend = 0; }
       else if (bf) { launch_gemm_bf16(st, a, m->w_down[l], part, M, H, F, kEpiPartial); pend = gemm_bf16_partials(M, H, F); }
-      else { launch_gemm_f32(st, (const float*)a, (const float*)m->w_down[l], part, M, H, F, kEpiPartial); pend = 1; } }
+      else { launch_gemm_f32(st, (const float*)a, (const float*)m->w_down[l], x, M, H, F, kEpiResidual); pend = 0; } }
   }
   return pend;
 }
@@ -306,8 +310,11 @@ void run_head(rl_model* m, hipStream_t st, int M, float* xbuf, int pend, const R
   float* part = m->wsp<float>(m->lay.part);
   float* logits = m->wsp<float>(m->lay.logits);
   float* cap = m->capture ? m->capture + (size_t)g.n_layers * m->cfg.max_rows * g.hidden : nullptr;
-  { Timer t(m, st, K_NORM);
-    launch_residual_norm(st, g.dtype, xbuf, pend ? part : nullptr, pend, m->final_norm, h, cap, M, g.hidden, g.rms_eps); }
+  const bool bf = g.dtype == kBF16;
+  if (bf || cap) {
+    Timer t(m, st, K_NORM);
+    launch_residual_norm(st, g.dtype, xbuf, pend ? part : nullptr, pend, bf ? m->final_norm : nullptr, h, cap, M, g.hidden, g.rms_eps);
+  }
   float* spart = m->wsp<float>(m->lay.samp_part);
   float* fz = m->wsp<float>(m->lay.forced_z);
   const int top_k = sp->top_k > (uint32_t)g.vocab ? 0 : (int)sp->top_k;
@@ -328,7 +335,7 @@ void run_head(rl_model* m, hipStream_t st, int M, float* xbuf, int pend, const R
     // logits to memory (a truncated distribution needs the whole row first), then the stand-alone sampler
     { Timer t(m, st, K_LMHEAD);
       if (g.dtype == kBF16) launch_gemm_bf16(st, h, m->lm_head, logits, M, g.vocab, g.hidden, kEpiPartial, false);
-      else launch_gemm_f32(st, (const float*)h, (const float*)m->lm_head, logits, M, g.vocab, g.hidden, kEpiPartial); }
+      else launch_gemm_f32(st, xbuf, (const float*)m->lm_head, logits, M, g.vocab, g.hidden, kEpiPartial, (const float*)m->final_norm, g.rms_eps); }
     { Timer t(m, st, K_SAMPLE);
       launch_sample(st, logits, M, g.vocab, rows, pos_offset, forced, sp->temperature, sp->seed, spart, fz, out_tokens, out_lp,
                     truncated ? top_k : 0, truncated ? sp->top_p : 0.f, m->wsp<void>(m->lay.cuts), last_tok); }

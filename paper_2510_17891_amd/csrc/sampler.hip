@@ -29,16 +29,16 @@ __global__ __launch_bounds__(256) void sample_stage1_kernel(const float* __restr
   float m = -INFINITY, s = 0.f;
   const int i_end = min(V, (tile + 1) * kSampleTile);
   for (int i0 = tile * kSampleTile + threadIdx.x * 4; i0 < i_end; i0 += 256 * 4) {
+    const float zs[4] = {z[i0], z[i0 + 1], z[i0 + 2], z[i0 + 3]};  // V and the tile are multiples of four
     uint32_t rnd[4] = {0, 0, 0, 0};
     if (!greedy) philox4x32_10((uint32_t)i0 >> 2, pos, seq, 0u, seed_lo, seed_hi, rnd);
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
       const int i = i0 + e;
-      if (i >= i_end) break;
-      const float zi = z[i];
+      const float zi = zs[e];
       const float y = greedy ? zi : __fmaf_rn(zi, inv_t, gumbel(rnd[e]));
       best = better(best, Best{y, i, zi});
-      lse_merge(m, s, zi * inv_t, 1.0f);
+      lse_add(m, s, zi * inv_t);
       if (i == f) forced_z[r] = zi;
     }
   }
@@ -61,7 +61,8 @@ __global__ __launch_bounds__(256) void sample_stage1_kernel(const float* __restr
   }
 }
 
-// Stage 2: one block of 1024 threads per row merges the tile partials and emits token and log-probability.
+// Stage 2: one block per row merges the tile partials and emits token and log-probability: 1024 threads, or one wave
+// where there are at most 64 partials (the same merges: further waves would hold nothing).
 __global__ __launch_bounds__(1024) void sample_stage2_kernel(const float* __restrict__ part, int n_tiles, int V,
                                                              const int32_t* __restrict__ forced,
                                                              const float* __restrict__ forced_z, float inv_t,
@@ -72,7 +73,7 @@ __global__ __launch_bounds__(1024) void sample_stage2_kernel(const float* __rest
   const int r = blockIdx.x, lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   Best best{-INFINITY, -1, 0.f};
   float m = -INFINITY, s = 0.f;
-  for (int t = threadIdx.x; t < n_tiles; t += 1024) {
+  for (int t = threadIdx.x; t < n_tiles; t += blockDim.x) {
     const float* p = part + ((size_t)r * n_tiles + t) * kSamplePartFloats;
     const float4 a = *(const float4*)p;
     const float4 b = *(const float4*)(p + 4);
@@ -87,7 +88,7 @@ __global__ __launch_bounds__(1024) void sample_stage2_kernel(const float* __rest
   if (lane == 0) { sh_y[wave] = best.y; sh_i[wave] = best.idx; sh_z[wave] = best.z; sh_m[wave] = m; sh_s[wave] = s; }
   __syncthreads();
   if (threadIdx.x == 0) {
-    for (int w = 1; w < 16; ++w) {
+    for (int w = 1; w < (int)(blockDim.x >> 6); ++w) {
       best = better(best, Best{sh_y[w], sh_i[w], sh_z[w]});
       lse_merge(m, s, sh_m[w], sh_s[w]);
     }
@@ -309,7 +310,7 @@ struct Draw {
   float m, s;
   __device__ __forceinline__ void add(int i, float z, float inv_t, uint32_t rnd) {
     best = better(best, Best{__fmaf_rn(z, inv_t, gumbel(rnd)), i, z});
-    lse_merge(m, s, z * inv_t, 1.0f);
+    lse_add(m, s, z * inv_t);
   }
   __device__ __forceinline__ void merge(const Draw& o) {
     best = better(best, o.best);
@@ -732,14 +733,14 @@ void launch_sample(hipStream_t st, const float* logits, int M, int V, const RowM
   }
   sample_stage1_kernel<<<dim3(n_tiles, M), 256, 0, st>>>(logits, V, rows, pos_offset, inv_t, greedy, seed_lo, seed_hi, forced,
                                                          forced_z, part, n_tiles);
-  sample_stage2_kernel<<<M, 1024, 0, st>>>(part, n_tiles, V, forced, forced_z, inv_t, out_tokens, out_logprobs, rows, last_tok);
+  sample_stage2_kernel<<<M, n_tiles <= 64 ? 64 : 1024, 0, st>>>(part, n_tiles, V, forced, forced_z, inv_t, out_tokens, out_logprobs, rows, last_tok);
 }
 
 void launch_sample_merge(hipStream_t st, const float* part, int n_tiles, int M, int V, const int32_t* forced,
                          const float* forced_z, float temperature, int32_t* out_tokens, float* out_logprobs,
                          const RowMeta* rows, int32_t* last_tok) {
   const float inv_t = temperature > 0.f ? 1.0f / temperature : 1.0f;
-  sample_stage2_kernel<<<M, 1024, 0, st>>>(part, n_tiles, V, forced, forced_z, inv_t, out_tokens, out_logprobs, rows, last_tok);
+  sample_stage2_kernel<<<M, n_tiles <= 64 ? 64 : 1024, 0, st>>>(part, n_tiles, V, forced, forced_z, inv_t, out_tokens, out_logprobs, rows, last_tok);
 }
 
 }  // namespace rl

@@ -1498,3 +1498,45 @@ def test_truncated_sampler_rows_that_leave_the_list_path(amd):
             if r < 4:
                 assert abs(float(lp[r]) - lp_ref) < 1e-5 * max(1.0, abs(lp_ref)), (T, k, p, r, float(lp[r]), lp_ref)
     ro.close()
+
+
+@pytest.mark.parametrize("over", [dict(head_dim=126), dict(head_dim=20, n_q=6, n_kv=2, hidden=520, ffn=72, qk_norm=0), dict(head_dim=128)])
+def test_f32_steps_for_other_head_dims_and_batch_sizes(amd, over):
+    """The fp32 kernels at head dims whose rows are 8- or 16-byte aligned, widths that are no multiple of a wave's 256
+    elements, contexts beyond one tile of 256 keys, and 1, 4, 8 or more rows per launch: logits match the oracle and a
+    row keeps its bits in every batch size."""
+    shape = dict(ri.SHAPES["tiny"], **over)
+    w, wn = make_both(shape, 21)
+    wd = to_device(w)
+    lens = [270, 5, 256, 17, 1, 3, 255, 40, 9]
+    prompts = [ri.tokens((n,), shape["vocab"], 21, 700 + i).tolist() for i, n in enumerate(lens)]
+    res = []
+    for n in (9, 4, 1):
+        ro = amd.Rollout(shape, wd, max_seqs=9, max_ctx=288, max_rows=64, kv_pages=9 * 18)
+        ids = list(range(n))
+        z = torch.empty(n, shape["vocab"], device=DEV)
+        tok, _ = ro.rl_prefill(ids, prompts[:n], 0.0, 1)
+        outs = []
+        for _ in range(3):
+            cur = tok
+            tok, lp = ro.rl_decode_step(ids, cur, 0.0, 1, debug_logits=z)
+            outs.append((cur[:1].clone(), z[:1].clone(), lp[:1].clone()))
+        if n == 9:
+            last, zl = cur.cpu(), z.cpu()
+            ro.rl_debug_attention_appends(0)   # the separate rotation and append kernel
+            ro.rl_free_seqs(ids)
+            tok, _ = ro.rl_prefill(ids, prompts, 0.0, 1)
+            for _ in range(3):
+                tok, _ = ro.rl_decode_step(ids, tok, 0.0, 1, debug_logits=z)
+            assert torch.equal(z.cpu(), zl)
+        torch.cuda.synchronize()
+        res.append(outs)
+        ro.close()
+    for other in res[1:]:
+        for a, b in zip(res[0], other):
+            assert all(torch.equal(x, y) for x, y in zip(a, b))
+    om = orc.OracleModel(dims_of(shape), wn, max_ctx=288)
+    om.prefill(0, prompts[0])
+    for cur, z1, _ in res[0]:
+        zr = om.forward_token(0, int(cur[0]))
+        assert rel_inf(z1[0].cpu().numpy(), zr) < 1e-4
