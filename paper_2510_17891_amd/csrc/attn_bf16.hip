@@ -35,7 +35,8 @@
 // Rows that feed neighbouring positions of one sequence (prefill, scoring) form sets in the same way when they lie
 // in one aligned window of 32 positions: equal step counts and segments, each row's keys a prefix of the next row's.
 // Such a set computes all segments of its rows, every column masked at its own context length, and the window's
-// keys are read once per set instead of once per row.
+// keys are read once per set instead of once per row.  Up to four segments (1024 keys) are merged by the set's own block,
+// one wave per segment: at 1024 rows the merge launch (20 us) and 68 MB of partials written and read back are gone.
 //
 // Decode steps (one row per sequence) run the variant that also does what would otherwise be a kernel of its own
 // before this one: it sums the QKV projection's split partials, normalises and rotates the heads of its columns, and
@@ -275,7 +276,11 @@ __global__ __launch_bounds__(256, KV8 ? 3 : 2) void attn_decode_bf16_kernel(cons
   const int n_blk = (ctx + 15) >> 4;
   const int n_it = (ctx + 31) >> 5;  // 32-key steps
   auto seg_begin = [&](int sgm) { return attn_seg_begin(sgm, n_it, n_seg); };
+  // A set that covers every segment of its rows (neighbouring rows of one sequence) and has them all in this block, one
+  // per wave, is merged here: the partials stay in registers until the waves are done, then meet in LDS.
+  const bool set_merges = !APPEND && is_set && shared_segs == n_seg && n_seg <= 4;  // block-uniform
   int seg = lo + (wave * (hi - lo)) / 4;  // contiguous, balanced share of the block's segments
+  const int first_seg = seg;
   const int seg_end = lo + ((wave + 1) * (hi - lo)) / 4;
   const int it_begin = seg_begin(seg), it_end = seg_begin(seg_end);
   const u32x4_t* kb = k_pool + (size_t)hk * kPairU4(KV8);
@@ -488,7 +493,7 @@ __global__ __launch_bounds__(256, KV8 ? 3 : 2) void attn_decode_bf16_kernel(cons
   };
   reset(std::integral_constant<int, 2>{});
   while (seg < seg_end && seg_begin(seg + 1) == seg_begin(seg)) ++seg;  // skip leading empty segments
-  int boundary = seg < seg_end ? seg_begin(seg + 1) : it_end;
+  int boundary = set_merges ? -1 : seg < seg_end ? seg_begin(seg + 1) : it_end;
 
   // One step = 32 keys (two pages): scores, online softmax, P*V; at a segment end the partial is written.
   // NG = 2: the same for both column groups of a wide set, from the same key and value registers.
@@ -719,6 +724,35 @@ __global__ __launch_bounds__(256, KV8 ? 3 : 2) void attn_decode_bf16_kernel(cons
     run(std::integral_constant<int, 1>{});
   }
 
+  if (set_merges) {
+    __syncthreads();  // every wave has read its last q operand: the place is free for the partials
+    if (it_begin < it_end) {
+#pragma unroll
+      for (int c = 0; c < (KV8 ? 1 : 2); ++c) {
+        float l_tot = l_run[c] + __shfl_xor(l_run[c], 16, kWave);
+        l_tot += __shfl_xor(l_tot, 32, kWave);
+        if (col_valid[c]) {  // never in the second group of a set that is not wide
+          float* p = lds_part + ((size_t)(j + 16 * c) * n_seg + first_seg) * kPartStride;
+#pragma unroll
+          for (int b = 0; b < 8; ++b) {
+            p[16 * b + 4 * g] = o_acc[c][b][0]; p[16 * b + 4 * g + 1] = o_acc[c][b][1];
+            p[16 * b + 4 * g + 2] = o_acc[c][b][2]; p[16 * b + 4 * g + 3] = o_acc[c][b][3];
+          }
+          if (g == 0) { p[kD] = m_run[c]; p[kD + 1] = l_tot; }
+        }
+      }
+    }
+    __syncthreads();
+    const AttnShared* sh = shared + (blockIdx.y - n_rows);
+    for (int c = wave; c < n_cols; c += 4) {
+      const int head = hk * group + c % group;
+      const float* p = lds_part + (size_t)c * n_seg * kPartStride;
+      const uint32_t o2 = merge_short([&](int e) { return p + (size_t)e * kPartStride; },
+                                      [&](int e) { return p + (size_t)e * kPartStride + kD; }, n_seg, n_it, lane);
+      *(uint32_t*)(o_out + frag_offset(sh->rows[c / group], head * kD + 2 * lane, (n_q * kD) >> 6)) = o2;
+    }
+    return;
+  }
   if (!in_lds) {  // the merge kernel combines the partials in the workspace
     if (APPEND && appends) store_new();
     return;
@@ -750,6 +784,7 @@ __global__ __launch_bounds__(64) void attn_merge_bf16_kernel(const float* __rest
   const float* p = part + ((size_t)r * n_q + head) * max_segs * kPartStride;
   if (n_seg <= kLdsSegs) {
     if (!skip_segs || skip_segs[r] == 0) return;  // finished by its own block
+    if (n_seg <= 4 && skip_segs[r] == n_seg) return;  // ... or by that of a set that covers all its segments
     const uint32_t o2 = merge_short([&](int c) { return p + part_o(max_segs, c); }, [&](int c) { return p + part_ml(max_segs, c); },
                                     n_seg, (ctx + 31) >> 5, lane);
     *(uint32_t*)(o_out + frag_offset(r, head * kD + 2 * lane, (n_q * kD) >> 6)) = o2;
@@ -811,17 +846,22 @@ bool launch_attn_decode_bf16(hipStream_t s, const Geometry& g, const float* q, c
                              const int32_t* block_table, void* k_pool_layer, void* v_pool_layer, float* part,
                              int max_segs_alloc, int max_ctx_in_batch, void* o_out, int M, const int32_t* skip_segs,
                              const AttnShared* shared, int n_shared, int max_shared_segs, const AttnAppend* append,
-                             int segs_per_block) {
+                             int segs_per_block, bool window_sets) {
   const int n_seg_max = attn_num_segments(max_ctx_in_batch);
   const int spb = std::min(std::max(segs_per_block, 1), kLdsSegs);
   const int page_ints = ((max_ctx_in_batch + 15) / 16 + 1 + 3) & ~3;  // keeps the partials 16-byte aligned
   if (n_shared <= 0) { skip_segs = nullptr; n_shared = 0; max_shared_segs = 0; }
-  const int z = std::max(attn_num_splits(n_seg_max, spb), (max_shared_segs + 3) / 4);
-  dim3 grid(g.n_kv, M + n_shared, z);
+  // Window sets hold every row: no row blocks (at 1024 rows 8192 blocks that only find out that they have nothing to do,
+  // 70 -> 52 us for up to 1024 keys, the longest contexts first).
+  const int row_blocks = n_shared > 0 && window_sets ? 0 : M;
+  const int z = std::max(row_blocks > 0 ? attn_num_splits(n_seg_max, spb) : 1, (max_shared_segs + 3) / 4);
+  dim3 grid(g.n_kv, row_blocks + n_shared, z);
   const int segs = n_seg_max > kLdsSegs ? kLdsSegs : n_seg_max;
   int part_floats = (g.n_q / g.n_kv) * segs * kPartStride;  // a multiple of 4
   // a set of more than 16 columns keeps the queries of its columns 16.. and the two q operands there
   if (n_shared > 0 && !g.kv_fp8) part_floats = std::max(part_floats, 3 * 16 * kD);
+  // ... and one that covers all (up to four) segments of its rows their partials, afterwards
+  if (n_shared > 0 && window_sets) part_floats = std::max(part_floats, (g.kv_fp8 ? 16 : 32) * 4 * kPartStride);
   // the queries of up to 16 columns, the new key and value (bf16); fp8 pages: the q operand (in the queries' place)
   const int q_ints = append ? 16 * kD + kD : g.kv_fp8 ? 16 * kD : 0;
   const size_t lds = (size_t)(page_ints + part_floats + q_ints) * 4;
@@ -835,7 +875,7 @@ bool launch_attn_decode_bf16(hipStream_t s, const Geometry& g, const float* q, c
 #define RL_ATTN_LAUNCH(APP, K8)                                                                                          \
   attn_decode_bf16_kernel<APP, K8><<<grid, 256, lds, s>>>(q, rows, block_table, g.max_blocks, (const u32x4_t*)k_pool_layer, \
                                                           (const u32x4_t*)v_pool_layer, part, max_segs_alloc, g.n_q, g.n_kv, \
-                                                          scale, (uint16_t*)o_out, page_ints, page_ints + part_floats, M,  \
+                                                          scale, (uint16_t*)o_out, page_ints, page_ints + part_floats, row_blocks, \
                                                           skip_segs, shared, ap, spb)
   if (append) {
     if (g.kv_fp8) RL_ATTN_LAUNCH(true, true); else RL_ATTN_LAUNCH(true, false);
@@ -843,6 +883,8 @@ bool launch_attn_decode_bf16(hipStream_t s, const Geometry& g, const float* q, c
     if (g.kv_fp8) RL_ATTN_LAUNCH(false, true); else RL_ATTN_LAUNCH(false, false);
   }
 #undef RL_ATTN_LAUNCH
+  // every row of a set over at most four segments is merged by the set's block, every other short row by its own
+  if (n_shared > 0 && window_sets && n_seg_max <= 4) return false;
   return n_seg_max > kLdsSegs || n_shared > 0;
 }
 

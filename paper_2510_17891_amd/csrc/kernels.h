@@ -88,6 +88,7 @@ int attn_bf16_max_segments(int max_ctx);
 // launch_qk_rope_append is not called.  Only for batches with one row per sequence: the block of a row is then the
 // only one that needs the row's new key, and it takes it from registers, not from the page.  The arithmetic is the
 // one of launch_qk_rope_append, bit for bit.
+// window_sets: every row is in a set, and every set in `shared` covers all segments of its rows.
 // segs_per_block (1..16): segments one block takes of a context of more than 16 segments (> 4096 keys); results do
 // not depend on it.
 constexpr int kAttnAppendMaxSplits = 4;
@@ -104,7 +105,8 @@ bool launch_attn_decode_bf16(hipStream_t s, const Geometry& g, const float* q, c
                              const int32_t* block_table, void* k_pool_layer, void* v_pool_layer,
                              float* part, int max_segs_alloc, int max_ctx_in_batch, void* o_out, int M,
                              const int32_t* skip_segs = nullptr, const AttnShared* shared = nullptr, int n_shared = 0,
-                             int max_shared_segs = 0, const AttnAppend* append = nullptr, int segs_per_block = 16);
+                             int max_shared_segs = 0, const AttnAppend* append = nullptr, int segs_per_block = 16,
+                             bool window_sets = false);
 void launch_attn_merge_bf16(hipStream_t s, const Geometry& g, const RowMeta* rows, float* part, int max_segs_alloc,
                             void* o_out, int M, const int32_t* skip_segs, int n_shared);
 // fp32, even head_dim <= 128: one block per (row, q head), whole context, output fp32 row-major [M][n_q*d].  append (may

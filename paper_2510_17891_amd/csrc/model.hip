@@ -9,6 +9,7 @@
 #include <stdio.h>
 #include <string.h>
 
+#include <algorithm>
 #include <chrono>
 #include <cmath>
 #include <string>
@@ -100,7 +101,7 @@ void compute_layout(const rl_model_config& c, Layout* L) {
   L->slot_tok = L->slot_upd + align_up(R * 3 * sizeof(int32_t));
   L->slot_skip = L->slot_tok + align_up(R * sizeof(int32_t));
   L->slot_sets = L->slot_skip + align_up(R * sizeof(int32_t));
-  L->slot_bytes = L->slot_sets + align_up(R / 2 * sizeof(AttnShared) + sizeof(AttnShared));
+  L->slot_bytes = L->slot_sets + align_up(R * sizeof(AttnShared));  // window sets: up to one per row
   L->block_table = take((size_t)c.max_seqs * (c.max_ctx / 16) * 4);
   L->rope = take((size_t)c.max_ctx * (d / 2) * sizeof(float2));
   L->ring = take(kRing * L->slot_bytes);
@@ -229,6 +230,7 @@ struct SharedAttn {  // device pointers into the metadata slot of the call (empt
   const int32_t* skip = nullptr;
   const AttnShared* sets = nullptr;
   int n_sets = 0, max_segs = 0;
+  bool window = false;  // every row is in a set, and the sets cover all segments of their rows
 };
 
 // one_row_per_seq: the batch is a decode step, which lets the bf16 attention kernel take over the rotation and the
@@ -271,7 +273,7 @@ int run_layers(rl_model* m, hipStream_t st, int M, const RowMeta* rows, int max_
       { Timer t(m, st, K_ATTN);
         merge = launch_attn_decode_bf16(st, g, q, rows, bt, m->k_pool(l), m->v_pool(l), apart, m->lay.max_segs, max_ctx_in_batch,
                                         o, M, sa.skip, sa.sets, sa.n_sets, sa.max_segs, fused ? &ap : nullptr,
-                                        m->attn_segs_per_block); }
+                                        m->attn_segs_per_block, sa.window); }
       if (merge) {
         Timer t(m, st, K_ATTN_MERGE);
         launch_attn_merge_bf16(st, g, rows, apart, m->lay.max_segs, o, M, sa.skip, sa.n_sets);
@@ -394,7 +396,23 @@ rl_status upload_window_plan(rl_model* m, hipStream_t st, char* hs, char* ds, in
   for (int i = 0; i < n; ++i) { seq[i] = hr[i].seq; pos[i] = hr[i].pos; }
   AttnPlan plan;
   plan_window_sets(n, seq.data(), pos.data(), rows_per_set(m, n), &plan);
-  return upload_attn_plan(m, st, hs, ds, n, plan, sa);
+  if (plan.sets.empty()) return RL_OK;  // every row on its own
+  // The rows left over become sets of one, so that the launch needs no row blocks; the longest contexts come first, so
+  // that the blocks still running at its end are short ones.
+  for (int i = 0; i < n; ++i) {
+    if (plan.skip[i]) continue;
+    AttnShared s;
+    s.n_rows = 1;
+    s.n_segs = attn_num_segments(pos[i] + 1);
+    for (int k = 0; k < kAttnSetRows; ++k) s.rows[k] = i;
+    plan.skip[i] = s.n_segs;
+    plan.sets.push_back(s);
+    plan.max_shared_segs = std::max(plan.max_shared_segs, s.n_segs);
+  }
+  std::stable_sort(plan.sets.begin(), plan.sets.end(), [&](const AttnShared& a, const AttnShared& b) { return pos[a.rows[0]] > pos[b.rows[0]]; });
+  const rl_status rs = upload_attn_plan(m, st, hs, ds, n, plan, sa);
+  sa->window = sa->n_sets > 0;
+  return rs;
 }
 
 // Write the rows, page grants and shared-attention plan of one decode call into the host slot hs and describe them

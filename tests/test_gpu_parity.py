@@ -1540,3 +1540,29 @@ def test_f32_steps_for_other_head_dims_and_batch_sizes(amd, over):
     for cur, z1, _ in res[0]:
         zr = om.forward_token(0, int(cur[0]))
         assert rel_inf(z1[0].cpu().numpy(), zr) < 1e-4
+
+
+@pytest.mark.parametrize("kv_fp8", [False, True])
+def test_prefill_and_score_bits_with_and_without_window_sets(amd, kv_fp8):
+    """Neighbouring rows of a sequence attend in sets (of four rows or of eight, left-over rows in sets of one, up to
+    1024 keys merged by the set's own block): the same bits as every row on its own."""
+    shape = dict(ri.SHAPES["layer8b"], n_layers=2, hidden=512, n_q=8, n_kv=2, ffn=768, vocab=8192)
+    w, _ = make_both(shape, 67, std=0.05)
+    wd = to_device(w)
+    prompts = [ri.tokens((n,), shape["vocab"], 67, 940 + i).tolist() for i, n in enumerate([1300, 33, 1, 65, 1024, 2])]
+    ids = list(range(6))
+    res = []
+    for mode in (0, 1, 2, 3):
+        ro = amd.Rollout(shape, wd, max_seqs=8, max_ctx=1312, max_rows=720, kv_pages=200, kv_fp8=kv_fp8)
+        ro.rl_debug_share_attention(mode)
+        t, lp = ro.rl_prefill(ids, prompts, 1.0, 3)
+        z = torch.empty(6, shape["vocab"], device=DEV)
+        ro.rl_decode_step(ids, t, 1.0, 3, debug_logits=z)
+        ro.rl_free_seqs(ids)
+        sc = ro.rl_score([6, 7], [prompts[0], prompts[4]], 1.0)
+        torch.cuda.synchronize()
+        res.append([x.cpu() for x in (t, lp, z, sc)])
+        ro.close()
+    for other in res[1:]:
+        for a, b in zip(res[0], other):
+            assert torch.equal(a, b)
