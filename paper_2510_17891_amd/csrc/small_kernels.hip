@@ -160,11 +160,75 @@ __global__ __launch_bounds__(256) void qk_rope_append_kernel(const float* __rest
   }
 }
 
+// The same for bf16 models, many rows and a finished projection (one partial): one block per row, its heads in groups of
+// four per wave, so that a wave has the loads of four heads in flight and fetches the row's rotation and the gains once.
+// Same arithmetic, same bits.  It moves 46 MB at 1024 rows: 19.7 -> 13.1 us.
+template <int KVT>
+__global__ __launch_bounds__(256) void qk_rope_append_rows_kernel(const float* __restrict__ part, const void* __restrict__ q_gain,
+                                                                 const void* __restrict__ k_gain, const float2* __restrict__ rope, const RowMeta* __restrict__ rows,
+                                                                 void* __restrict__ k_pool, void* __restrict__ v_pool,
+                                                                 float* __restrict__ q_out, int n_q, int n_kv, int qk_norm, float eps) {
+  constexpr int d = 128, half = 64;
+  const int r = blockIdx.x, wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+  const int n_rot = n_q + n_kv, n_heads = n_rot + n_kv;
+  const RowMeta rm = rows[r];
+  const float* row_part = part + (size_t)r * n_heads * d;
+  const float2 cs = rope[(size_t)rm.pos * half + lane];
+  float gq[2] = {1.f, 1.f}, gk[2] = {1.f, 1.f};
+  if (qk_norm) {
+    gq[0] = bf2f(((const uint16_t*)q_gain)[lane]); gq[1] = bf2f(((const uint16_t*)q_gain)[lane + half]);
+    gk[0] = bf2f(((const uint16_t*)k_gain)[lane]); gk[1] = bf2f(((const uint16_t*)k_gain)[lane + half]);
+  }
+  for (int h0 = 4 * wave; h0 < n_heads; h0 += 16) {
+    float ld[4][2];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      const float* p = row_part + (size_t)min(h0 + u, n_heads - 1) * d;
+      ld[u][0] = p[lane];
+      ld[u][1] = p[lane + half];
+    }
+    HeadPair hp[4], raw[4];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      hp[u].v0 = 0.f + ld[u][0];  // the sum over one split
+      hp[u].v1 = 0.f + ld[u][1];
+      const bool is_q = h0 + u < n_q;
+      hp[u].cs = cs;
+      hp[u].g0 = is_q ? gq[0] : gk[0];
+      hp[u].g1 = is_q ? gq[1] : gk[1];
+      raw[u] = hp[u];
+    }
+    if (h0 < n_rot) head_pairs_finish<4>(hp, d, qk_norm != 0, eps);  // wave-uniform
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      const int hh = h0 + u;
+      if (hh >= n_heads) continue;
+      if (hh < n_q) {
+        float* q = q_out + ((size_t)r * n_q + hh) * d;
+        q[lane] = hp[u].v0;
+        q[lane + half] = hp[u].v1;
+      } else {
+        const bool is_k = hh < n_rot;
+        const int hk = is_k ? hh - n_q : hh - n_rot, t = rm.pos & 15;
+        kv_store<KVT>(is_k ? k_pool : v_pool, rm.page, hk, n_kv, d, t, lane, is_k ? hp[u].v0 : raw[u].v0, !is_k);
+        kv_store<KVT>(is_k ? k_pool : v_pool, rm.page, hk, n_kv, d, t, lane + half, is_k ? hp[u].v1 : raw[u].v1, !is_k);
+      }
+    }
+  }
+}
+
 void launch_qk_rope_append(hipStream_t s, const Geometry& g, const float* qkv_part, int S, const void* q_gain,
                            const void* k_gain, const float2* rope_table, const RowMeta* rows, void* k_pool_layer,
                            void* v_pool_layer, float* q_out, int M) {
   dim3 grid((g.n_q + 2 * g.n_kv + 3) / 4, M);
   size_t stride = (size_t)M * (g.n_q + 2 * g.n_kv) * g.head_dim;
+  if (g.dtype == kBF16 && M >= 512 && S == 1) {  // fewer rows: one wave per head gives more waves (301 rows 8.2 us, by row 10.4)
+    if (g.kv_fp8)
+      qk_rope_append_rows_kernel<2><<<M, 256, 0, s>>>(qkv_part, q_gain, k_gain, rope_table, rows, k_pool_layer, v_pool_layer, q_out, g.n_q, g.n_kv, g.qk_norm, g.rms_eps);
+    else
+      qk_rope_append_rows_kernel<1><<<M, 256, 0, s>>>(qkv_part, q_gain, k_gain, rope_table, rows, k_pool_layer, v_pool_layer, q_out, g.n_q, g.n_kv, g.qk_norm, g.rms_eps);
+    return;
+  }
   if (g.dtype == kBF16 && g.kv_fp8)
     qk_rope_append_kernel<true, 2><<<grid, 256, 0, s>>>(qkv_part, S, stride, q_gain, k_gain, rope_table, rows,
                                                        k_pool_layer, v_pool_layer, q_out, g.n_q, g.n_kv,

@@ -1566,3 +1566,26 @@ def test_prefill_and_score_bits_with_and_without_window_sets(amd, kv_fp8):
     for other in res[1:]:
         for a, b in zip(res[0], other):
             assert torch.equal(a, b)
+
+
+@pytest.mark.parametrize("kv_fp8", [False, True])
+def test_prefill_bits_do_not_depend_on_the_row_chunk_at_8b_width(amd, kv_fp8):
+    """One layer at 8B width, prompts in chunks of 600, 320 or 48 rows: finished projections with rotation and append by
+    row, the same by head, and split sums give the same scores, tokens and logits, bit for bit."""
+    shape = dict(ri.SHAPES["layer8b"], vocab=4096)
+    w, _ = make_both(shape, 68)
+    wd = to_device(w)
+    prompts = [ri.tokens((n,), shape["vocab"], 68, 950 + i).tolist() for i, n in enumerate([610, 37])]
+    res = []
+    for rows in (600, 320, 48):
+        ro = amd.Rollout(shape, wd, max_seqs=4, max_ctx=640, max_rows=rows, kv_pages=100, kv_fp8=kv_fp8)
+        t, lp = ro.rl_prefill([0, 1], prompts, 1.0, 3)
+        z = torch.empty(2, shape["vocab"], device=DEV)
+        ro.rl_decode_step([0, 1], t, 1.0, 3, debug_logits=z)
+        sc = ro.rl_score([2], [prompts[0]], 1.0)
+        torch.cuda.synchronize()
+        res.append([x.cpu() for x in (t, lp, z, sc)])
+        ro.close()
+    for other in res[1:]:
+        for a, b in zip(res[0], other):
+            assert torch.equal(a, b)
