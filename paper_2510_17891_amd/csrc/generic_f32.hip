@@ -1,5 +1,5 @@
-// fp32 kernels for models stored in fp32 (any dimensions that are multiples of 8): projections on the vector ALUs and
-// paged attention.  These serve the small full-precision configuration, where every tensor fits in cache and a step is a
+// fp32 kernels for models stored in fp32 (hidden and ffn multiples of 8, any even head_dim up to 128 with any number of
+// heads): projections on the vector ALUs and paged attention.  These serve the small full-precision configuration, where every tensor fits in cache and a step is a
 // chain of launches that each last about as long as a few dependent memory round trips.  They are therefore written for
 // few launches (norm and residual inside the projections, rotation and KV append inside the attention) and for having
 // all loads of a launch in flight at once.  A decode step of 4 rows through two layers of 256 hidden dimensions, sampling
@@ -39,14 +39,17 @@ __device__ __forceinline__ float wave_sums(const float (&v)[R], int lane) {
   return a[0];
 }
 
-// One wave per output column n (4 waves per block) and R rows: lane l takes the elements 4l .. 4l + 3 of every 256.
+// One wave per output column n (4 waves per block) and R rows: lane l takes VEC elements from VEC l on of every 64 VEC.
+// K % VEC == 0.  VEC is 4 except for the O projection of an odd number of heads whose head_dim is no multiple of four:
+// there K is only even, rows begin on 8-byte boundaries, and a group of four would reach into the next row.
 // kEpiSwiGLU: W has 2N rows (gate then up); out[m][n] = silu(gate)*up.  kEpiResidual: out[m][n] += product.
 // gain (may be null): the rows are RMS-normalised first, x * rsqrt(mean(x^2) + eps) * gain; every wave forms the row's
 // mean square from the elements it holds anyway.  A row's result depends neither on R nor on the rows beside it.
-template <int EPI, int R>
+template <int EPI, int R, int VEC>
 __global__ __launch_bounds__(256) void gemm_f32_kernel(const float* __restrict__ X, const float* __restrict__ W,
                                                        float* __restrict__ out, int M, int N, int K,
                                                        const float* __restrict__ gain, float eps) {
+  typedef float vec_t __attribute__((ext_vector_type(VEC)));
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
   const int n = blockIdx.x * 4 + wave, m0 = blockIdx.y * R;
   if (n >= N) return;
@@ -56,20 +59,24 @@ __global__ __launch_bounds__(256) void gemm_f32_kernel(const float* __restrict__
 #pragma unroll
   for (int i = 0; i < R; ++i) a0[i] = a1[i] = ss[i] = 0.f;
 #pragma unroll 4
-  for (int k = 4 * lane; k < K; k += 256) {
-    const float4 u = *(const float4*)(w0 + k);
-    float4 v = make_float4(0.f, 0.f, 0.f, 0.f), g = make_float4(1.f, 1.f, 1.f, 1.f);
-    if (EPI == kEpiSwiGLU) v = *(const float4*)(w1 + k);
-    if (gain) g = *(const float4*)(gain + k);
+  for (int k = VEC * lane; k < K; k += 64 * VEC) {
+    const vec_t u = *(const vec_t*)(w0 + k);
+    vec_t v = 0.f, g = 1.f;
+    if (EPI == kEpiSwiGLU) v = *(const vec_t*)(w1 + k);
+    if (gain) g = *(const vec_t*)(gain + k);
 #pragma unroll
     for (int i = 0; i < R; ++i) {
-      float4 x = *(const float4*)(X + (size_t)min(m0 + i, M - 1) * K + k);
+      vec_t x = *(const vec_t*)(X + (size_t)min(m0 + i, M - 1) * K + k);
       if (gain) {
-        ss[i] = fmaf(x.x, x.x, fmaf(x.y, x.y, fmaf(x.z, x.z, fmaf(x.w, x.w, ss[i]))));
-        x.x *= g.x; x.y *= g.y; x.z *= g.z; x.w *= g.w;
+#pragma unroll
+        for (int e = VEC - 1; e >= 0; --e) ss[i] = fmaf(x[e], x[e], ss[i]);
+        x *= g;
       }
-      a0[i] = fmaf(u.x, x.x, fmaf(u.y, x.y, fmaf(u.z, x.z, fmaf(u.w, x.w, a0[i]))));
-      if (EPI == kEpiSwiGLU) a1[i] = fmaf(v.x, x.x, fmaf(v.y, x.y, fmaf(v.z, x.z, fmaf(v.w, x.w, a1[i]))));
+#pragma unroll
+      for (int e = VEC - 1; e >= 0; --e) {
+        a0[i] = fmaf(u[e], x[e], a0[i]);
+        if (EPI == kEpiSwiGLU) a1[i] = fmaf(v[e], x[e], a1[i]);
+      }
     }
   }
   float s0 = wave_sums<R>(a0, lane), s1 = 0.f;
@@ -185,26 +192,33 @@ __global__ __launch_bounds__(256) void attn_f32_kernel(const float* __restrict__
   }
 }
 
-template <int R>
+template <int R, int VEC>
 void launch_gemm_rows(hipStream_t s, const float* X, const float* W, float* out, int M, int N, int K, int epi, const float* gain,
                       float eps) {
   const dim3 grid((N + 3) / 4, (M + R - 1) / R);
   if (epi == kEpiSwiGLU)
-    gemm_f32_kernel<kEpiSwiGLU, R><<<grid, 256, 0, s>>>(X, W, out, M, N, K, gain, eps);
+    gemm_f32_kernel<kEpiSwiGLU, R, VEC><<<grid, 256, 0, s>>>(X, W, out, M, N, K, gain, eps);
   else if (epi == kEpiResidual)
-    gemm_f32_kernel<kEpiResidual, R><<<grid, 256, 0, s>>>(X, W, out, M, N, K, gain, eps);
+    gemm_f32_kernel<kEpiResidual, R, VEC><<<grid, 256, 0, s>>>(X, W, out, M, N, K, gain, eps);
   else
-    gemm_f32_kernel<kEpiPartial, R><<<grid, 256, 0, s>>>(X, W, out, M, N, K, gain, eps);
+    gemm_f32_kernel<kEpiPartial, R, VEC><<<grid, 256, 0, s>>>(X, W, out, M, N, K, gain, eps);
+}
+
+template <int VEC>
+void launch_gemm_vec(hipStream_t s, const float* X, const float* W, float* out, int M, int N, int K, int epi, const float* gain,
+                     float eps) {
+  // rows per wave: the smallest of 1, 4 and 8 that holds the batch (rows beyond it would be computed for nothing), 8 beyond
+  if (M == 1) launch_gemm_rows<1, VEC>(s, X, W, out, M, N, K, epi, gain, eps);
+  else if (M <= 4) launch_gemm_rows<4, VEC>(s, X, W, out, M, N, K, epi, gain, eps);
+  else launch_gemm_rows<8, VEC>(s, X, W, out, M, N, K, epi, gain, eps);
 }
 
 }  // namespace
 
 void launch_gemm_f32(hipStream_t s, const float* X, const float* W, float* out, int M, int N, int K, int epi, const float* gain,
                      float eps) {
-  // rows per wave: the smallest of 1, 4 and 8 that holds the batch (rows beyond it would be computed for nothing), 8 beyond
-  if (M == 1) launch_gemm_rows<1>(s, X, W, out, M, N, K, epi, gain, eps);
-  else if (M <= 4) launch_gemm_rows<4>(s, X, W, out, M, N, K, epi, gain, eps);
-  else launch_gemm_rows<8>(s, X, W, out, M, N, K, epi, gain, eps);
+  if (K % 4 == 0) launch_gemm_vec<4>(s, X, W, out, M, N, K, epi, gain, eps);
+  else launch_gemm_vec<2>(s, X, W, out, M, N, K, epi, gain, eps);
 }
 
 void launch_attn_f32(hipStream_t s, const Geometry& g, const float* q, const RowMeta* rows, const int32_t* block_table,

@@ -1500,11 +1500,14 @@ def test_truncated_sampler_rows_that_leave_the_list_path(amd):
     ro.close()
 
 
-@pytest.mark.parametrize("over", [dict(head_dim=126), dict(head_dim=20, n_q=6, n_kv=2, hidden=520, ffn=72, qk_norm=0), dict(head_dim=128)])
+@pytest.mark.parametrize("over", [
+    dict(head_dim=126), dict(head_dim=20, n_q=6, n_kv=2, hidden=520, ffn=72, qk_norm=0), dict(head_dim=128),
+    # an odd number of heads and head_dim % 4 == 2: the O projection's rows are no multiple of four elements
+    dict(head_dim=126, n_q=3, n_kv=1), dict(head_dim=6, n_q=1, n_kv=1), dict(head_dim=18, n_q=5, n_kv=5, qk_norm=0)])
 def test_f32_steps_for_other_head_dims_and_batch_sizes(amd, over):
     """The fp32 kernels at head dims whose rows are 8- or 16-byte aligned, widths that are no multiple of a wave's 256
-    elements, contexts beyond one tile of 256 keys, and 1, 4, 8 or more rows per launch: logits match the oracle and a
-    row keeps its bits in every batch size."""
+    elements or of four, contexts beyond one tile of 256 keys, and 1, 4, 8 or more rows per launch: logits match the
+    oracle and a row keeps its bits in every batch size."""
     shape = dict(ri.SHAPES["tiny"], **over)
     w, wn = make_both(shape, 21)
     wd = to_device(w)
