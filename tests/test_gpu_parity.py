@@ -1500,6 +1500,33 @@ def test_truncated_sampler_rows_that_leave_the_list_path(amd):
     ro.close()
 
 
+def test_truncated_logprobs_have_the_same_bits_in_every_call_and_batch(amd):
+    """Tokens and log-probabilities of truncated sampling depend on the row alone: repeated calls, and batches of 128,
+    20 and 1 rows (which cut a row into slices of other sizes), give the same bits."""
+    V, n = 151936, 128
+    shape = dict(ri.SHAPES["layer8b"], n_layers=1, hidden=256, n_q=2, n_kv=1, ffn=256, vocab=V)
+    w, _ = make_both(shape, 11)
+    ro = amd.Rollout(shape, to_device(w), max_seqs=n, max_ctx=64, max_rows=n, kv_pages=8)
+    g = torch.Generator(device=DEV)
+    g.manual_seed(74)
+    z = torch.randn(n, V, generator=g, device=DEV) * 3.0
+    z[1] *= 0.1                              # flat: most tokens kept
+    z[2] = torch.round(z[2] * 4) / 4         # long runs of equal logits
+    z[3] = z[3] * 1e-4
+    z[3, 11] = 9.0                           # a narrow crowd below one outlier
+    seqs, poss = list(range(n)), [17 + 5 * i for i in range(n)]
+    for T, k, p in [(0.6, 0, 0.95), (0.7, 1000, 0.9), (1.0, 50, 0.0), (1.0, 60000, 0.0)]:
+        ref = ro.rl_sample_logits(z, seqs, poss, T, 5, top_k=k, top_p=p)
+        for _ in range(3):
+            for b in (128, 20, 1):
+                tok, lp = ro.rl_sample_logits(z[:b], seqs[:b], poss[:b], T, 5, top_k=k, top_p=p)
+                assert torch.equal(tok, ref[0][:b]) and torch.equal(lp, ref[1][:b]), (T, k, p, b)
+        for r in range(5, 9):
+            tok, lp = ro.rl_sample_logits(z[r:r + 1], [r], [17 + 5 * r], T, 5, top_k=k, top_p=p)
+            assert torch.equal(tok, ref[0][r:r + 1]) and torch.equal(lp, ref[1][r:r + 1]), (T, k, p, r)
+    ro.close()
+
+
 @pytest.mark.parametrize("over", [
     dict(head_dim=126), dict(head_dim=20, n_q=6, n_kv=2, hidden=520, ffn=72, qk_norm=0), dict(head_dim=128),
     # an odd number of heads and head_dim % 4 == 2: the O projection's rows are no multiple of four elements
