@@ -105,26 +105,31 @@ __global__ __launch_bounds__(1024) void sample_stage2_kernel(const float* __rest
 // ------------------------------------------------------------------------------------------------
 // Truncated sampling: the top-k / top-p cut of every row (the last kept token of the order) and the draw from what is
 // left, in three passes over the logits.
-//   1. cut_range: largest and smallest (finite) logit of the row.
-//   2. cut_hist: count or integer mass per bin, the bins being kCutBins equal steps of the logit below the largest one --
-//      over the 22 / inv_t in which weights are not zero for a mass, over the whole range for a count.  The bin is a
-//      monotone function of the logit, so the bins are runs of the order, and integer masses make every sum exact.
+//   1. cut_range: largest and smallest logit of the row, and how far below the largest its bulk lies.
+//   2. cut_hist: count or integer mass per bin, the bins being steps of the logit below the largest one.  A mass has
+//      kCutBins equal steps over the 22 / inv_t in which weights are not zero.  A count has the finest steps over four
+//      times the distance to the largest minimum of four neighbouring logits (or 64 times that of two, where that is less:
+//      most tokens are masked), coarser ones beyond -- one banned token at -1e9 or at the lowest float would otherwise put
+//      the whole row into one bin -- and a bin for the smallest logit alone.  The bin is a monotone function of the
+//      logit, so the bins are runs of the order, and integer masses make every sum exact.
 //   3. cut_gather: every block redoes the scan of the histogram, which names the bin that holds the cut and what is still
 //      to be covered inside it.  Tokens of earlier bins are certainly kept and take part in the draw at once; those of
 //      the cut's bin (a few hundred at most over a row of logits) are collected in a list.
-// sample_finish then finds the cut inside the list -- bins of the key between the list's smallest and largest, then a
-// direct comparison of the tokens of one bin --, lets the list's kept tokens take part, and emits token and
+// sample_finish then finds the cut inside the list, lets the list's kept tokens take part, and emits token and
 // log-probability.  With both cuts, the count is selected first (passes 2, 3 and cut_finish) and the mass among what it
-// keeps.  Rows whose list overflows (thousands of tokens within a thousandth of the range) or whose largest score is not
-// a number of ordinary size are selected by one block digit by digit instead (radix_cut).
-// A radix selection over the row's key digits took five passes, each with its own scan: 217 us for 128 rows of 151936
-// entries at 0.6 / 0.95, of which 151 us were these passes and 37 us a draw over every entry; now 76 us.
+// keeps.  Where a bin overflows the list (a crowd of thousands of tokens in a thousandth of the range, thousands of equal
+// logits, or masked ones that the cut reaches) the finishing block goes over the row itself (row_cut).
+// What bounds it: the passes' arithmetic per token (order keys, weights, LDS additions), then the finishing blocks, one per
+// row.  A radix selection over the digits of the key took five passes, each with its own scan, and a draw over every
+// entry.  Rows of 151936 entries, that selection -> these passes: 0.6 / 0.95 at 128 rows 217 -> 74 us, at one row 65 -> 33;
+// top-k 50 198 -> 69 and 56 -> 31, also with masked tokens or logits rounded to 16 bits; a top-k cut among masked tokens
+// 323 -> 97 and 58 -> 41.  Slower at few rows are a crowd 30000 times narrower than the distance of an outlier above it
+// (top-k: 197 -> 140 at 128 rows, 56 -> 76 at one) and the mass of equal logits (360 -> 270, 63 -> 160).
 // ------------------------------------------------------------------------------------------------
 constexpr int kCutBins = 1024;
 constexpr int kCutList = 4096;
 constexpr int kCutThreads = 512;
 constexpr int kCutSlices = 32;  // at most, per row
-constexpr int kRadixBins = 2048;
 
 struct CutSel {            // after the scan of a histogram
   int32_t bin;             // the bin that holds the cut
@@ -134,34 +139,33 @@ struct CutSel {            // after the scan of a histogram
 struct CutRow {  // per row
   unsigned long long hist[2][kCutBins];  // selection 0: count (top-k), 1: mass (top-p)
   CutSel sel[2];
-  uint32_t n_list[2];                    // tokens that asked for a place in the list
+  uint32_t n_list[2];                    // tokens of the cut's bin, also where they are more than the list holds
+  uint32_t lo[2], hi[2];                 // their smallest and largest key
   OrderCut cut_k;
-  uint32_t kmax[kCutSlices], kmin[kCutSlices];  // per slice: largest key; smallest key of a finite logit (or 0xffffffff)
+  // per slice: largest and smallest key; the same of the finite logits (or 0, 0xffffffff); the largest minimum of two and
+  // of four neighbouring logits, as keys
+  uint32_t kmax[kCutSlices], kmin[kCutSlices], fmax[kCutSlices], fmin[kCutSlices], two[kCutSlices], four[kCutSlices];
   uint2 list[2][kCutList];               // (key, index)
 };
 static_assert(sizeof(CutRow) % 16 == 0, "rows lie one behind the other, histograms are read in pairs");
 
-// Calls fn(i, z[i]) for the tokens of float4 groups [g_begin, g_end) of the row (V % 4 == 0, rows 16-byte aligned),
-// four 16-byte loads in flight per thread.
-template <typename F>
+// Calls fn(i, z[i .. i + 3]) for the float4 groups [g_begin, g_end) of the row (V % 4 == 0, rows 16-byte aligned), kLoads
+// 16-byte loads in flight per thread.
+template <int kLoads, typename F>
 __device__ __forceinline__ void for_each_group(const float* __restrict__ z, int g_begin, int g_end, int tid, int nthr, F fn) {
-  for (int g0 = g_begin + tid; g0 < g_end; g0 += 4 * nthr) {
-    float4 v[4];
+  for (int g0 = g_begin + tid; g0 < g_end; g0 += kLoads * nthr) {
+    float4 v[kLoads];
 #pragma unroll
-    for (int e = 0; e < 4; ++e) {
+    for (int e = 0; e < kLoads; ++e) {
       const int g = g0 + e * nthr;
       v[e] = g < g_end ? ((const float4*)z)[g] : make_float4(0.f, 0.f, 0.f, 0.f);
     }
 #pragma unroll
-    for (int e = 0; e < 4; ++e) {
+    for (int e = 0; e < kLoads; ++e) {
       const int g = g0 + e * nthr;
       if (g < g_end) fn(4 * g, v[e]);
     }
   }
-}
-template <typename F>
-__device__ __forceinline__ void for_each_token(const float* __restrict__ z, int g_begin, int g_end, int tid, int nthr, F fn) {
-  for_each_group(z, g_begin, g_end, tid, nthr, [&](int i, float4 v) { fn(i, v.x); fn(i + 1, v.y); fn(i + 2, v.z); fn(i + 3, v.w); });
 }
 
 __device__ __forceinline__ bool finite_bits(float x) { return (__float_as_uint(x) & 0x7f800000u) != 0x7f800000u; }
@@ -173,29 +177,57 @@ __device__ __forceinline__ Slice row_slice(int V) {
   return Slice{g, min(n4, g + per)};
 }
 
-// The row's largest logit, and the bins of a selection.
+// The row's largest logit, and the bins of a selection: of a mass, equal steps down from z_ref; of a count, 512 equal steps
+// over r0, 256 over what follows up to r1, 254 over the rest, then one bin for the smallest logit.
 struct CutBinning {
-  float z_max, s_max;  // largest logit; the same times 1/T
-  float scale;         // bins per unit of the logit
-  bool ok;             // the largest score is finite ...
-  __device__ __forceinline__ int bin(float z) const { return (int)fminf((z_max - z) * scale, (float)(kCutBins - 1)); }
+  float z_max, s_max;  // largest logit of the order; the same times 1/T
+  float z_ref;         // where the bins begin
+  float scale, scale1, scale2;  // bins per unit of the logit
+  float r0, r1;
+  uint32_t floor;      // bits of the row's smallest logit: masked tokens, mostly
+  bool all;            // mass: no token has any (the largest score is not a finite number, or rounded by more than 22)
+  template <bool kMass>
+  __device__ __forceinline__ int bin(float z) const {
+    const float t = z_ref - z;
+    if (kMass) return (int)fminf(t * scale, (float)(kCutBins - 1));  // of logits that have a mass
+    if (t < r0) return (int)fmaxf(t * scale, 0.f);  // +inf as well; never the smallest logit
+    if (__float_as_uint(z) == floor) return kCutBins - 1;
+    if (!finite_bits(z)) return (int)__float_as_uint(z) < 0 ? kCutBins - 2 : 0;  // by its place in the order
+    return (int)(t < r1 ? (t - r0) * scale1 + 512.f : fminf((t - r1) * scale2, 254.f) + 768.f);
+  }
 };
 __device__ __forceinline__ CutBinning cut_binning(const CutRow& row, int n_slices, float inv_t, bool mass) {
-  uint32_t kmax = 0, kmin = 0xffffffffu;
-  for (int i = 0; i < n_slices; ++i) {  // the same addresses for every lane
-    kmax = max(kmax, row.kmax[i]);
-    kmin = min(kmin, row.kmin[i]);
+  const int i = min((int)(threadIdx.x & (kCutSlices - 1)), n_slices - 1);  // both halves of a wave hold all slices
+  uint32_t kmax = row.kmax[i], kmin = row.kmin[i], fmax = row.fmax[i], fmin = row.fmin[i], two = row.two[i], four = row.four[i];
+#pragma unroll
+  for (int o = kCutSlices / 2; o > 0; o >>= 1) {
+    kmax = max(kmax, (uint32_t)__shfl_xor((int)kmax, o, kWave));
+    kmin = min(kmin, (uint32_t)__shfl_xor((int)kmin, o, kWave));
+    fmax = max(fmax, (uint32_t)__shfl_xor((int)fmax, o, kWave));
+    fmin = min(fmin, (uint32_t)__shfl_xor((int)fmin, o, kWave));
+    two = max(two, (uint32_t)__shfl_xor((int)two, o, kWave));
+    four = max(four, (uint32_t)__shfl_xor((int)four, o, kWave));
   }
   CutBinning b;
   b.z_max = order_value(kmax);
   b.s_max = __fmul_rn(b.z_max, inv_t);
-  // ... and known well enough that the largest logit's own weight is about 2^32 (scores beyond 10^7 round by more)
-  const float x0 = __fmaf_rn(b.z_max, inv_t, -b.s_max);
-  b.ok = finite_bits(b.z_max) && finite_bits(b.s_max) && finite_bits(inv_t) && x0 > -1.f && x0 < 0.3f;
-  float range = b.z_max - order_value(min(kmin, kmax));
-  if (mass) range = fminf(range, 22.5f / inv_t);
-  b.scale = range > 0.f ? (float)(kCutBins - 1) / range : 0.f;
-  if (!finite_bits(b.scale)) b.scale = 0.f;  // a range below 2^-118: one bin
+  b.all = mass && fexp_weight(__fmaf_rn(b.z_max, inv_t, -b.s_max)) == 0;
+  b.z_ref = order_value(fmax);
+  b.floor = __float_as_uint(order_value(kmin));
+  const auto steps = [](float n, float range) { const float q = n / range; return range > 0.f && finite_bits(q) ? q : 0.f; };
+  const float range = b.z_ref - order_value(fmin);  // NaN without a finite logit
+  b.r0 = b.r1 = b.scale1 = b.scale2 = 0.f;
+  if (mass) {
+    b.scale = steps(kCutBins - 1, fminf(range, 22.5f / inv_t));
+  } else {
+    const float d2 = b.z_ref - order_value(two), d4 = b.z_ref - order_value(four);
+    const float bulk = d2 > 0.f ? fminf(4.f * d4, 64.f * d2) : 4.f * d4;
+    b.r0 = bulk > 0.f ? fminf(range, bulk) : range;
+    b.r1 = fminf(range, 32.f * b.r0);
+    b.scale = steps(512.f, b.r0);
+    b.scale1 = steps(256.f, b.r1 - b.r0);
+    b.scale2 = steps(254.f, range - b.r1);
+  }
   return b;
 }
 
@@ -249,32 +281,88 @@ __device__ __forceinline__ unsigned long long mass_target(unsigned long long S, 
   return t < 1 ? 1 : t;
 }
 
-// grid (slices, rows): the slice's largest and smallest finite key; clears the row's histograms and counters.
+// grid (slices, rows): the slice's share of the row's range; clears the row's histograms and counters.
 __global__ __launch_bounds__(kCutThreads) void cut_range_kernel(const float* __restrict__ logits, int V, CutRow* __restrict__ ws) {
-  __shared__ uint32_t sh[2][kCutThreads / 64];
+  __shared__ uint32_t sh[6][kCutThreads / 64];
   const int r = blockIdx.y, tid = threadIdx.x;
   CutRow& row = ws[r];
   for (int i = blockIdx.x * kCutThreads + tid; i < 2 * kCutBins; i += gridDim.x * kCutThreads) (&row.hist[0][0])[i] = 0ull;
-  if (blockIdx.x == 0 && tid < 2) row.n_list[tid] = 0u;
+  if (blockIdx.x == 0 && tid < 2) { row.n_list[tid] = 0u; row.lo[tid] = 0xffffffffu; row.hi[tid] = 0u; }
   const Slice sl = row_slice(V);
-  uint32_t kmax = 0, kmin = 0xffffffffu;
-  for_each_token(logits + (size_t)r * V, sl.g_begin, sl.g_end, tid, kCutThreads, [&](int, float zi) {
-    const uint32_t k = order_key(zi);
-    kmax = max(kmax, k);
-    kmin = min(kmin, finite_bits(zi) ? k : 0xffffffffu);
+  uint32_t kmax = 0, kmin = 0xffffffffu, fmax = 0, fmin = 0xffffffffu;
+  float two = -INFINITY, four = -INFINITY;
+  for_each_group<4>(logits + (size_t)r * V, sl.g_begin, sl.g_end, tid, kCutThreads, [&](int, float4 v) {
+    const float zs[4] = {v.x, v.y, v.z, v.w};
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      const uint32_t k = order_key(zs[e]);
+      kmax = max(kmax, k);
+      kmin = min(kmin, k);
+      fmax = max(fmax, finite_bits(zs[e]) ? k : 0u);
+      fmin = min(fmin, finite_bits(zs[e]) ? k : 0xffffffffu);
+    }
+    const float a = fminf(v.x, v.y), b = fminf(v.z, v.w);
+    two = fmaxf(two, fmaxf(a, b));
+    four = fmaxf(four, fminf(a, b));
   });
+  uint32_t ktwo = order_key(two), kfour = order_key(four);
 #pragma unroll
   for (int o = 32; o > 0; o >>= 1) {
     kmax = max(kmax, (uint32_t)__shfl_xor((int)kmax, o, kWave));
     kmin = min(kmin, (uint32_t)__shfl_xor((int)kmin, o, kWave));
+    fmax = max(fmax, (uint32_t)__shfl_xor((int)fmax, o, kWave));
+    fmin = min(fmin, (uint32_t)__shfl_xor((int)fmin, o, kWave));
+    ktwo = max(ktwo, (uint32_t)__shfl_xor((int)ktwo, o, kWave));
+    kfour = max(kfour, (uint32_t)__shfl_xor((int)kfour, o, kWave));
   }
-  if ((tid & 63) == 0) { sh[0][tid >> 6] = kmax; sh[1][tid >> 6] = kmin; }
+  if ((tid & 63) == 0) { sh[0][tid >> 6] = kmax; sh[1][tid >> 6] = fmax; sh[2][tid >> 6] = fmin; sh[3][tid >> 6] = kfour; sh[4][tid >> 6] = kmin; sh[5][tid >> 6] = ktwo; }
   __syncthreads();
   if (tid == 0) {
-    for (int w = 1; w < kCutThreads / 64; ++w) { kmax = max(kmax, sh[0][w]); kmin = min(kmin, sh[1][w]); }
+    for (int w = 1; w < kCutThreads / 64; ++w) {
+      kmax = max(kmax, sh[0][w]);
+      fmax = max(fmax, sh[1][w]);
+      fmin = min(fmin, sh[2][w]);
+      kfour = max(kfour, sh[3][w]);
+      kmin = min(kmin, sh[4][w]);
+      ktwo = max(ktwo, sh[5][w]);
+    }
     row.kmax[blockIdx.x] = kmax;
     row.kmin[blockIdx.x] = kmin;
+    row.fmax[blockIdx.x] = fmax;
+    row.fmin[blockIdx.x] = fmin;
+    row.two[blockIdx.x] = ktwo;
+    row.four[blockIdx.x] = kfour;
   }
+}
+
+// h[bin[e]] += w[e], and with kCount n[bin[e]] += 1, for four tokens per lane; bin < 0: none.  Where all lanes' tokens go
+// to one bin (equal logits, or a crowd in one bin) they are added up first: a hundred thousand additions to one LDS word
+// would take longer than everything else.
+template <bool kCount>
+__device__ __forceinline__ void add_to_bins(unsigned long long* h, uint32_t* n, const int (&bin)[4], const unsigned long long (&w)[4]) {
+  if (bin[0] == bin[1] && bin[0] == bin[2] && bin[0] == bin[3]) {
+    if (bin[0] < 0) return;
+    unsigned long long sum = (w[0] + w[1]) + (w[2] + w[3]);
+    const int first = __builtin_amdgcn_readfirstlane(bin[0]);
+    if (__ballot(bin[0] == first) == ~0ull) {  // every lane of the wave
+#pragma unroll
+      for (int o = 32; o > 0; o >>= 1) sum += __shfl_xor(sum, o, kWave);
+      if ((threadIdx.x & 63) == 0) {
+        atomicAdd(&h[first], sum);
+        if (kCount) atomicAdd(&n[first], 256u);
+      }
+    } else {
+      atomicAdd(&h[bin[0]], sum);
+      if (kCount) atomicAdd(&n[bin[0]], 4u);
+    }
+    return;
+  }
+#pragma unroll
+  for (int e = 0; e < 4; ++e)
+    if (bin[e] >= 0) {
+      atomicAdd(&h[bin[e]], w[e]);
+      if (kCount) atomicAdd(&n[bin[e]], 1u);
+    }
 }
 
 // grid (slices, rows): the slice's share of the histogram of selection kMass, among the tokens that `use_k`'s cut keeps.
@@ -285,20 +373,31 @@ __global__ __launch_bounds__(kCutThreads) void cut_hist_kernel(const float* __re
   const int r = blockIdx.y, tid = threadIdx.x;
   CutRow& row = ws[r];
   const CutBinning cb = cut_binning(row, gridDim.x, inv_t, kMass);
-  if (!cb.ok) return;  // block-uniform: sample_finish takes the row
+  if (cb.all) return;  // block-uniform: nothing is cut off
   const OrderCut allowed = use_k ? row.cut_k : OrderCut{0u, 0x7fffffff};
   for (int b = tid; b < kCutBins; b += kCutThreads) lh[b] = 0ull;
   __syncthreads();
   const Slice sl = row_slice(V);
-  for_each_token(logits + (size_t)r * V, sl.g_begin, sl.g_end, tid, kCutThreads, [&](int i, float zi) {
-    unsigned long long w = 1ull;
-    if (kMass) {
-      const float x = __fmaf_rn(zi, inv_t, -cb.s_max);
-      if (!(x > -22.0f)) return;  // weight zero
-      w = fexp_weight(x);
+  for_each_group<4>(logits + (size_t)r * V, sl.g_begin, sl.g_end, tid, kCutThreads, [&](int i0, float4 v) {
+    const float zs[4] = {v.x, v.y, v.z, v.w};
+    if constexpr (kMass) {
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const float x = __fmaf_rn(zs[e], inv_t, -cb.s_max);
+        if (!(x > -22.0f)) continue;  // weight zero
+        if (use_k && !kept_by(allowed, order_key(zs[e]), i0 + e)) continue;
+        atomicAdd(&lh[cb.bin<true>(zs[e])], fexp_weight(x));
+      }
+    } else {
+      int bins[4];
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        bins[e] = cb.bin<false>(zs[e]);
+        if (bins[e] == kCutBins - 1) bins[e] = -1;  // a scan that does not reach its count before the last bin ends there
+      }
+      const unsigned long long w[4] = {1, 1, 1, 1};
+      add_to_bins<false>(lh, nullptr, bins, w);
     }
-    if (use_k && !kept_by(allowed, order_key(zi), i)) return;
-    atomicAdd(&lh[cb.bin(zi)], w);
   });
   __syncthreads();
   for (int b = tid; b < kCutBins; b += kCutThreads)
@@ -365,21 +464,19 @@ struct DrawArgs {
 };
 
 // grid (slices, rows): names the cut's bin, lists the slice's tokens in it and (kDraw) draws among the slice's tokens of
-// earlier bins.  The draw's partials are written even where the row goes to radix_cut (and are not read there).
+// earlier bins.
 template <bool kMass, bool kDraw>
 __global__ __launch_bounds__(kCutThreads) void cut_gather_kernel(const float* __restrict__ logits, int V, float inv_t, int use_k,
                                                                  unsigned long long target, unsigned long long p_fixed,
                                                                  CutRow* __restrict__ ws, DrawArgs da) {
-  constexpr int kOwn = 1024;  // a block's own list, so that the row's counter sees one addition per block
   __shared__ CutSel sh_sel;
   __shared__ Draw sh_draw[kCutThreads / 64];
   constexpr int kKept = kDraw ? 2048 : 1;  // certainly kept tokens, drawn among after the scan with all lanes busy
-  __shared__ uint2 sh_list[kOwn], sh_kept[kKept];
-  __shared__ uint32_t sh_n, sh_at, sh_nk;
+  __shared__ uint2 sh_list[kCutList], sh_kept[kKept];
+  __shared__ uint32_t sh_n, sh_at, sh_nk, sh_lo, sh_hi;
   const int r = blockIdx.y, tid = threadIdx.x;
   CutRow& row = ws[r];
   const CutBinning cb = cut_binning(row, gridDim.x, inv_t, kMass);
-  if (!cb.ok) return;  // block-uniform: sample_finish takes the row
   const OrderCut allowed = use_k ? row.cut_k : OrderCut{0u, 0x7fffffff};
   if (tid < 64) {
     const unsigned long long* h = row.hist[kMass];
@@ -387,7 +484,8 @@ __global__ __launch_bounds__(kCutThreads) void cut_gather_kernel(const float* __
     sel.bin = scan_select_n<false, kCutBins / 64>(h, [&](unsigned long long S) { return kMass ? mass_target(S, p_fixed) : target; }, tid, &sel.rem);
     if (tid == 0) {
       sh_sel = sel;
-      sh_n = sh_nk = 0u;
+      sh_n = sh_nk = sh_hi = 0u;
+      sh_lo = 0xffffffffu;
       if (blockIdx.x == 0) row.sel[kMass] = sel;
     }
   }
@@ -407,45 +505,66 @@ __global__ __launch_bounds__(kCutThreads) void cut_gather_kernel(const float* __
   auto draw_token = [&](int i, float zi) {
     d.add(i, zi, cb.z_max, inv_t, token_bits((uint32_t)i, pos, seq, da.seed_lo, da.seed_hi));
   };
-  auto put = [&](uint32_t at, uint2 e) { if (at < (uint32_t)kCutList) row.list[kMass][at] = e; };
-  for_each_group(z, sl.g_begin, sl.g_end, tid, kCutThreads, [&](int i0, float4 v) {
-    const float zs[4] = {v.x, v.y, v.z, v.w};
-    // most groups lie behind the cut's bin as a whole
-    const float top = fmaxf(fmaxf(v.x, v.y), fmaxf(v.z, v.w));
-    const bool any = cb.bin(top) <= cut_bin;  // a NaN is the largest key (row not ok) or the smallest: fmaxf skips it
-    if (kDraw && !any && f >= i0 && f < i0 + 4) da.forced_z[r] = -INFINITY;  // cut off: probability zero
-    if (!any) return;
+  if (cb.all) {  // block-uniform; nothing is cut off (only with kMass, and then kDraw)
+    for_each_group<4>(z, sl.g_begin, sl.g_end, tid, kCutThreads, [&](int i0, float4 v) {
+      const float zs[4] = {v.x, v.y, v.z, v.w};
+      uint32_t rnd[4];
+      philox4x32_10((uint32_t)i0 >> 2, pos, seq, 0u, da.seed_lo, da.seed_hi, rnd);
 #pragma unroll
-    for (int e = 0; e < 4; ++e) {
-      const int b = cb.bin(zs[e]);
-      const uint32_t k = order_key(zs[e]);
-      if (b > cut_bin || (use_k && !kept_by(allowed, k, i0 + e))) {
-        if (kDraw && f == i0 + e) da.forced_z[r] = -INFINITY;
-        continue;
+      for (int e = 0; e < 4; ++e) {
+        d.add(i0 + e, zs[e], cb.z_max, inv_t, rnd[e]);
+        if (kDraw && f == i0 + e) da.forced_z[r] = zs[e];
       }
-      if (b == cut_bin) {
-        if (kDraw && f == i0 + e) da.forced_z[r] = -INFINITY;  // unless sample_finish keeps it
-        if (kMass && !(__fmaf_rn(zs[e], inv_t, -cb.s_max) > -22.0f)) continue;  // weight zero: never the cut, always behind it
-        const uint32_t at = atomicAdd(&sh_n, 1u);
-        if (at < (uint32_t)kOwn) sh_list[at] = make_uint2(k, (uint32_t)(i0 + e));
-        else put(atomicAdd(&row.n_list[kMass], 1u), make_uint2(k, (uint32_t)(i0 + e)));
-        continue;
+    });
+  } else {
+    uint32_t lo = 0xffffffffu, hi = 0u;
+    for_each_group<4>(z, sl.g_begin, sl.g_end, tid, kCutThreads, [&](int i0, float4 v) {
+      const float zs[4] = {v.x, v.y, v.z, v.w};
+      // most groups lie behind the cut's bin as a whole; fmaxf skips a NaN, which the sum shows
+      const float top = fmaxf(fmaxf(v.x, v.y), fmaxf(v.z, v.w)), sum = (v.x + v.y) + (v.z + v.w);
+      const bool any = cb.bin<kMass>(top) <= cut_bin || (!kMass && sum != sum);
+      if (kDraw && !any && f >= i0 && f < i0 + 4) da.forced_z[r] = -INFINITY;  // cut off: probability zero
+      if (!any) return;
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const int b = cb.bin<kMass>(zs[e]);
+        const uint32_t k = order_key(zs[e]);
+        if (b > cut_bin || (use_k && !kept_by(allowed, k, i0 + e))) {
+          if (kDraw && f == i0 + e) da.forced_z[r] = -INFINITY;
+          continue;
+        }
+        if (b == cut_bin) {
+          if (kDraw && f == i0 + e) da.forced_z[r] = -INFINITY;  // unless sample_finish keeps it
+          if (kMass && !(__fmaf_rn(zs[e], inv_t, -cb.s_max) > -22.0f)) continue;  // weight zero: never the cut, always behind it
+          const uint32_t at = atomicAdd(&sh_n, 1u);
+          if (at < (uint32_t)kCutList) sh_list[at] = make_uint2(k, (uint32_t)(i0 + e));
+          lo = min(lo, k);
+          hi = max(hi, k);
+          continue;
+        }
+        if (kDraw) {
+          const uint32_t at = atomicAdd(&sh_nk, 1u);
+          if (at < (uint32_t)kKept) sh_kept[at] = make_uint2(__float_as_uint(zs[e]), (uint32_t)(i0 + e));
+          else draw_token(i0 + e, zs[e]);
+          if (f == i0 + e) da.forced_z[r] = zs[e];
+        }
       }
-      if (kDraw) {
-        const uint32_t at = atomicAdd(&sh_nk, 1u);
-        if (at < (uint32_t)kKept) sh_kept[at] = make_uint2(__float_as_uint(zs[e]), (uint32_t)(i0 + e));
-        else draw_token(i0 + e, zs[e]);
-        if (f == i0 + e) da.forced_z[r] = zs[e];
-      }
+    });
+    if (lo <= hi) { atomicMin(&sh_lo, lo); atomicMax(&sh_hi, hi); }
+    __syncthreads();
+    const uint32_t n_own = sh_n;
+    if (tid == 0 && n_own > 0) {
+      sh_at = atomicAdd(&row.n_list[kMass], n_own);
+      atomicMin(&row.lo[kMass], sh_lo);
+      atomicMax(&row.hi[kMass], sh_hi);
     }
-  });
-  __syncthreads();
-  const uint32_t n_own = min(sh_n, (uint32_t)kOwn);
-  if (tid == 0 && n_own > 0) sh_at = atomicAdd(&row.n_list[kMass], n_own);
-  __syncthreads();
-  for (uint32_t t = tid; t < n_own; t += kCutThreads) put(sh_at + t, sh_list[t]);
+    __syncthreads();
+    if (n_own > 0)
+      for (uint32_t t = tid; t < min(n_own, (uint32_t)kCutList) && sh_at + t < (uint32_t)kCutList; t += kCutThreads) row.list[kMass][sh_at + t] = sh_list[t];
+    if (kDraw)
+      for (uint32_t t = tid; t < min(sh_nk, (uint32_t)kKept); t += kCutThreads) draw_token((int)sh_kept[t].y, __uint_as_float(sh_kept[t].x));
+  }
   if (!kDraw) return;
-  for (uint32_t t = tid; t < min(sh_nk, (uint32_t)kKept); t += kCutThreads) draw_token((int)sh_kept[t].y, __uint_as_float(sh_kept[t].x));
   d = block_draw<kCutThreads>(d, sh_draw);
   if (tid == 0) {
     float* p = da.part + ((size_t)r * gridDim.x + blockIdx.x) * kSamplePartFloats;
@@ -454,198 +573,226 @@ __global__ __launch_bounds__(kCutThreads) void cut_gather_kernel(const float* __
   }
 }
 
-// Four (bin, count-or-mass) entries in registers.  The top digit of the order key takes only a handful of values over
-// a row of logits, so in the first stage nearly every token would hit the same few LDS words; a thread collects them
-// here and adds each entry to the histogram once.
-struct BinCache {
-  int bin[4];
-  unsigned long long val[4];
-  int next;
-  __device__ __forceinline__ void init() {
-#pragma unroll
-    for (int e = 0; e < 4; ++e) { bin[e] = -1; val[e] = 0; }
-    next = 0;
-  }
-  __device__ __forceinline__ void add(int b, unsigned long long w, unsigned long long* h) {
-    bool hit = false;
-#pragma unroll
-    for (int e = 0; e < 4; ++e)
-      if (bin[e] == b) { val[e] += w; hit = true; }
-    if (hit) return;
-#pragma unroll
-    for (int e = 0; e < 4; ++e)
-      if (next == e) {
-        if (bin[e] >= 0) atomicAdd(&h[bin[e]], val[e]);
-        bin[e] = b;
-        val[e] = w;
-      }
-    next = (next + 1) & 3;
-  }
-  __device__ __forceinline__ void flush(unsigned long long* h) {
-#pragma unroll
-    for (int e = 0; e < 4; ++e)
-      if (bin[e] >= 0) atomicAdd(&h[bin[e]], val[e]);
-  }
-};
+// A token's place in the order as one number, descending: its key and, below it, its index from the end.
+constexpr int kIndexBits = 22;  // vocabularies are below 2^22
+constexpr uint32_t kIndexMask = (1u << kIndexBits) - 1;
+typedef unsigned long long place_t;
+__device__ __forceinline__ place_t place_of(uint32_t key, uint32_t i) { return ((place_t)key << kIndexBits) | (kIndexMask - i); }
+__device__ __forceinline__ OrderCut cut_at(place_t c) { return OrderCut{(uint32_t)(c >> kIndexBits), (int32_t)(kIndexMask - ((uint32_t)c & kIndexMask))}; }
 
 constexpr int kFinishThreads = 1024;
-struct FinishLds {
-  __align__(16) unsigned long long hist[kRadixBins];
-  uint2 list[kCutList];
-  Draw draw[kFinishThreads / 64];
-  unsigned long long rem;
-  uint32_t lo, hi, n;
-  OrderCut cut;
-};
-
-// The cut of a whole row by one block, digit by digit of the order key from the top (11, 11, 10 bits) and then of the
-// index (11, 11 bits, ascending) among the tokens that share the cut's key: count or mass per digit, scanned until the
-// target is reached.  Any row, whatever its values.  Every thread returns the cut.
-template <bool kMass>
-__device__ OrderCut radix_cut(const float* __restrict__ z, int V, float inv_t, float s_max, unsigned long long target,
-                              unsigned long long p_fixed, OrderCut allowed, FinishLds& sh) {
-  const int tid = threadIdx.x, lane = tid & 63;
-  uint32_t prefix = 0, iprefix = 0;
-  unsigned long long rem = target;
-  for (int stage = 0; stage < 5; ++stage) {
-    const int shift = stage == 0 ? 21 : stage == 1 ? 10 : stage == 2 ? 0 : stage == 3 ? 11 : 0;
-    const int width = stage == 2 ? 10 : 11;
-    const uint32_t mask = (1u << width) - 1;
-    __syncthreads();
-    for (int b = tid; b < kRadixBins; b += kFinishThreads) sh.hist[b] = 0ull;
-    __syncthreads();
-    if (stage == 0) {
-      BinCache bc;
-      bc.init();
-      for_each_token(z, 0, V >> 2, tid, kFinishThreads, [&](int i, float zi) {
-        const uint32_t k = order_key(zi);
-        if (!kept_by(allowed, k, i)) return;
-        bc.add((int)(k >> shift), kMass ? fexp_weight(__fmaf_rn(zi, inv_t, -s_max)) : 1ull, sh.hist);
-      });
-      bc.flush(sh.hist);
-    } else {
-      for_each_token(z, 0, V >> 2, tid, kFinishThreads, [&](int i, float zi) {
-        const uint32_t k = order_key(zi);
-        if (!kept_by(allowed, k, i)) return;
-        if (stage < 3) {
-          if ((k >> (shift + width)) != (prefix >> (shift + width))) return;
-          atomicAdd(&sh.hist[(k >> shift) & mask], kMass ? fexp_weight(__fmaf_rn(zi, inv_t, -s_max)) : 1ull);
-        } else {
-          if (k != prefix || (stage == 4 && ((uint32_t)i >> 11) != (iprefix >> 11))) return;
-          atomicAdd(&sh.hist[((uint32_t)i >> shift) & mask], 1ull);
-        }
-      });
-    }
-    __syncthreads();
-    const auto covered = [&](unsigned long long S) { return kMass && stage == 0 ? mass_target(S, p_fixed) : rem; };
-    unsigned long long rem_out;  // the same in every wave
-    if (stage < 3) {
-      const int b = stage == 2 ? scan_select_n<true, 16>(sh.hist, covered, lane, &rem_out) : scan_select_n<true, 32>(sh.hist, covered, lane, &rem_out);
-      prefix |= (uint32_t)b << shift;
-      if (stage == 2) {  // key complete: tokens with this key, in ascending index order -- how many are needed
-        if (kMass) {
-          const unsigned long long w = fexp_weight(__fmaf_rn(order_value(prefix), inv_t, -s_max));
-          rem_out = w > 0 ? (rem_out + w - 1) / w : 1ull;
-        }
-        if (rem_out < 1) rem_out = 1;
-      }
-    } else {
-      iprefix |= (uint32_t)scan_select_n<false, 32>(sh.hist, covered, lane, &rem_out) << shift;
-    }
-    rem = rem_out;
-  }
-  __syncthreads();
-  return OrderCut{prefix, (int32_t)iprefix};
-}
-
-// The cut inside the n listed tokens of its bin, of whose count or mass `rem` is to be covered: equal steps of the key
-// between the smallest and the largest, then the tokens of one step against each other.  False where a step holds more
-// than kCutFew tokens.  Leaves the list in sh.list.
+constexpr int kFinishWaves = kFinishThreads / 64;
 constexpr int kCutFew = 512;
-static_assert(kCutFew <= kFinishThreads && kCutFew <= kCutBins, "one thread each, in half of the histogram's place");
+struct FinishLds {
+  __align__(16) unsigned long long hist[kCutBins];
+  place_t few[kCutFew];
+  unsigned long long few_weight[kCutFew];
+  uint32_t count[kCutBins];
+  uint2 list[kCutList];
+  Draw draw[kFinishWaves];
+  place_t cut;
+  uint32_t n;
+  uint32_t found[2][4][kFinishWaves];
+};
+static_assert(kCutFew <= kFinishThreads, "one thread each");
+
 template <bool kMass>
-__device__ bool list_cut(const uint2* __restrict__ list, int n, unsigned long long rem, float inv_t, float s_max, FinishLds& sh,
-                         OrderCut* cut) {
-  const int tid = threadIdx.x, lane = tid & 63;
-  if (tid == 0) { sh.lo = 0xffffffffu; sh.hi = 0u; sh.n = 0u; }
-  for (int b = tid; b < kCutBins; b += kFinishThreads) sh.hist[b] = 0ull;
-  __syncthreads();
-  uint32_t lo = 0xffffffffu, hi = 0u;
-  for (int t = tid; t < n; t += kFinishThreads) {
-    const uint2 e = list[t];
-    sh.list[t] = e;
-    lo = min(lo, e.x);
-    hi = max(hi, e.x);
-  }
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) {
-    lo = min(lo, (uint32_t)__shfl_xor((int)lo, o, kWave));
-    hi = max(hi, (uint32_t)__shfl_xor((int)hi, o, kWave));
-  }
-  if (lane == 0) { atomicMin(&sh.lo, lo); atomicMax(&sh.hi, hi); }
-  __syncthreads();
-  hi = sh.hi;
-  const uint32_t span = hi - sh.lo;
-  const int shift = max(0, 32 - (int)__clz((int)span) - 10);  // span >> shift < kCutBins
-  auto weight = [&](uint32_t k) { return kMass ? fexp_weight(__fmaf_rn(order_value(k), inv_t, -s_max)) : 1ull; };
-  for (int t = tid; t < n; t += kFinishThreads) atomicAdd(&sh.hist[(hi - sh.list[t].x) >> shift], weight(sh.list[t].x));
-  __syncthreads();
-  unsigned long long left;
-  const uint32_t bin = (uint32_t)scan_select_n<false, kCutBins / 64>(sh.hist, [&](unsigned long long) { return rem; }, lane, &left);  // the same in every wave
-  // the tokens of that step and their weights, in the place of the histogram: the cut is the one whose own weight
-  // reaches what is left
-  uint2* const few = (uint2*)(sh.hist + kCutBins);
-  unsigned long long* const few_w = sh.hist;
-  __syncthreads();
-  for (int t = tid; t < n; t += kFinishThreads)
-    if (((hi - sh.list[t].x) >> shift) == bin) {
-      const uint32_t at = atomicAdd(&sh.n, 1u);
-      if (at < (uint32_t)kCutFew) { few[at] = sh.list[t]; few_w[at] = weight(sh.list[t].x); }
-    }
-  __syncthreads();
-  const int n_few = (int)sh.n;
-  if (n_few > kCutFew) return false;  // block-uniform
-  if (tid < n_few) {
-    const uint2 e = few[tid];
-    unsigned long long before = 0;
-    for (int u = 0; u < n_few; ++u) {
-      const uint2 o = few[u];
-      if (o.x > e.x || (o.x == e.x && o.y < e.y)) before += few_w[u];
-    }
-    if (before < left && left <= before + few_w[tid]) sh.cut = OrderCut{e.x, (int32_t)e.y};  // exactly one token
-  }
-  __syncthreads();
-  *cut = sh.cut;
-  return true;
+__device__ __forceinline__ unsigned long long token_weight(uint32_t key, float inv_t, float s_max) {
+  return kMass ? fexp_weight(__fmaf_rn(order_value(key), inv_t, -s_max)) : 1ull;
 }
 
-// The row's cut of selection kMass, in every thread: from its list where that holds it, otherwise from the whole row.
-// Returns whether it came from the list, which is then in sh.list.
+// The cut among the n tokens of sh.list that lie in places lo .. hi, of whose count or mass `rem` is to be covered, in
+// every thread: equal steps of the place until a step holds few tokens (one round, unless more than kCutFew have the
+// same key), then those against each other.
 template <bool kMass>
-__device__ bool row_cut(const float* __restrict__ z, int V, float inv_t, const CutBinning& cb, const CutRow& row,
-                        unsigned long long target, unsigned long long p_fixed, OrderCut allowed, FinishLds& sh, OrderCut* cut) {
-  const uint32_t n = row.n_list[kMass];
-  if (cb.ok && n <= (uint32_t)kCutList && list_cut<kMass>(row.list[kMass], (int)n, row.sel[kMass].rem, inv_t, cb.s_max, sh, cut)) return true;
-  *cut = radix_cut<kMass>(z, V, inv_t, cb.s_max, target, p_fixed, allowed, sh);
-  return false;
+__device__ place_t list_cut(int n, place_t lo, place_t hi, unsigned long long rem, float inv_t, float s_max, FinishLds& sh) {
+  const int tid = threadIdx.x, lane = tid & 63;
+  int n_few;
+  do {
+    const int shift = max(0, 54 - (int)__clzll((long long)(hi - lo)));  // (hi - lo) >> shift < kCutBins
+    __syncthreads();
+    for (int b = tid; b < kCutBins; b += kFinishThreads) sh.hist[b] = 0ull;
+    if (tid == 0) sh.n = 0u;
+    __syncthreads();
+    for (int t = tid; t < n; t += kFinishThreads) {
+      const uint2 e = sh.list[t];
+      const place_t c = place_of(e.x, e.y);
+      if (c >= lo && c <= hi) atomicAdd(&sh.hist[(hi - c) >> shift], token_weight<kMass>(e.x, inv_t, s_max));
+    }
+    __syncthreads();
+    unsigned long long left;  // the same in every wave
+    const int step = scan_select_n<false, kCutBins / 64>(sh.hist, [&](unsigned long long) { return rem; }, lane, &left);
+    rem = left;
+    hi -= min((place_t)step << shift, hi - lo);
+    lo = max(lo, hi - min(hi, ((place_t)1 << shift) - 1));
+    for (int t = tid; t < n; t += kFinishThreads) {
+      const uint2 e = sh.list[t];
+      const place_t c = place_of(e.x, e.y);
+      if (c < lo || c > hi) continue;
+      const uint32_t at = atomicAdd(&sh.n, 1u);
+      if (at < (uint32_t)kCutFew) { sh.few[at] = c; sh.few_weight[at] = token_weight<kMass>(e.x, inv_t, s_max); }
+    }
+    __syncthreads();
+    n_few = (int)sh.n;
+  } while (n_few > kCutFew);  // a range shrinks to a 512th at least in every round, to a single place at last
+  if (tid == 0) sh.cut = lo;
+  __syncthreads();
+  if (tid < n_few) {
+    const place_t c = sh.few[tid];
+    unsigned long long before = 0;
+    for (int u = 0; u < n_few; ++u)
+      if (sh.few[u] > c) before += sh.few_weight[u];
+    if (before < rem && rem <= before + sh.few_weight[tid]) atomicMax(&sh.cut, c);  // one token
+  }
+  __syncthreads();
+  return sh.cut;
+}
+
+// The `need`-th token with this key (in the order of the index), found chunk by chunk from the row's start; in every
+// thread.  Where the row has fewer, the last index.
+__device__ place_t nth_of_key(const float* __restrict__ z, int V, uint32_t key, unsigned long long need, FinishLds& sh) {
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, n4 = V >> 2;
+  unsigned long long seen = 0;
+  if (tid == 0) sh.cut = place_of(key, kIndexMask);
+  int turn = 0;
+  for (int g0 = 0; g0 < n4; g0 += 4 * kFinishThreads, turn ^= 1) {  // the buffers in turn: one barrier per chunk
+    unsigned long long m[4][4];  // lanes whose element e of part p has the key
+#pragma unroll
+    for (int p = 0; p < 4; ++p) {
+      const int g = g0 + p * kFinishThreads + tid;
+      const float4 v = g < n4 ? ((const float4*)z)[g] : make_float4(0.f, 0.f, 0.f, 0.f);
+      m[p][0] = __ballot(g < n4 && order_key(v.x) == key);
+      m[p][1] = __ballot(g < n4 && order_key(v.y) == key);
+      m[p][2] = __ballot(g < n4 && order_key(v.z) == key);
+      m[p][3] = __ballot(g < n4 && order_key(v.w) == key);
+      if (lane == 0)
+        sh.found[turn][p][wave] = __builtin_popcountll(m[p][0]) + __builtin_popcountll(m[p][1]) + __builtin_popcountll(m[p][2]) + __builtin_popcountll(m[p][3]);
+    }
+    __syncthreads();
+    unsigned long long before = seen, mine[4];
+#pragma unroll
+    for (int p = 0; p < 4; ++p)
+      for (int w = 0; w < kFinishWaves; ++w) {
+        if (w == wave) mine[p] = before;
+        before += sh.found[turn][p][w];
+      }
+    if (before >= need) {  // block-uniform: it is in this chunk
+      const unsigned long long below = (1ull << lane) - 1;
+#pragma unroll
+      for (int p = 0; p < 4; ++p) {
+        unsigned long long at = mine[p];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) at += __builtin_popcountll(m[p][e] & below);
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+          if (m[p][e] >> lane & 1ull) {
+            if (++at == need) sh.cut = place_of(key, 4u * (uint32_t)(g0 + p * kFinishThreads + tid) + e);
+          }
+      }
+      break;
+    }
+    seen = before;
+  }
+  __syncthreads();
+  return sh.cut;
+}
+
+// The row's cut of selection kMass, in every thread.  The list of its bin, as far as the cut depends on it, is in sh.list
+// (*n_list tokens) afterwards; kept(i0, mask, z) is called for groups of four tokens of the bin of which those in the mask
+// are kept without being in the list.
+// A bin with more tokens than a list holds is narrowed first: 1024 steps of the key at a time, each a pass over the row,
+// until a list holds a step's tokens (one pass, hardly ever two), or all have one key, of which the index then decides.
+template <bool kMass, typename F>
+__device__ place_t row_cut(const float* __restrict__ z, int V, float inv_t, const CutBinning& cb, const CutRow& row, int use_k,
+                           FinishLds& sh, int* n_list, F kept) {
+  const int tid = threadIdx.x, lane = tid & 63;
+  uint32_t n = row.n_list[kMass], lo = row.lo[kMass], hi = row.hi[kMass];
+  unsigned long long rem = row.sel[kMass].rem;
+  if (n <= (uint32_t)kCutList) {
+    for (int t = tid; t < (int)n; t += kFinishThreads) sh.list[t] = row.list[kMass][t];
+    *n_list = (int)n;
+    return list_cut<kMass>((int)n, (place_t)lo << kIndexBits, place_of(hi, 0u), rem, inv_t, cb.s_max, sh);
+  }
+  const OrderCut allowed = use_k ? row.cut_k : OrderCut{0u, 0x7fffffff};
+  const uint32_t top = hi;
+  while (n > (uint32_t)kCutList && lo < hi) {
+    const int shift = max(0, 22 - (int)__clz((int)(hi - lo)));  // (hi - lo) >> shift < kCutBins
+    __syncthreads();
+    for (int b = tid; b < kCutBins; b += kFinishThreads) { sh.hist[b] = 0ull; sh.count[b] = 0u; }
+    __syncthreads();
+    for_each_group<4>(z, 0, V >> 2, tid, kFinishThreads, [&](int i0, float4 v) {
+      const float zs[4] = {v.x, v.y, v.z, v.w};
+      int bins[4];
+      unsigned long long w[4];
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const uint32_t k = order_key(zs[e]);
+        const bool use = hi - k <= hi - lo && (!use_k || kept_by(allowed, k, i0 + e));
+        bins[e] = use ? (int)((hi - k) >> shift) : -1;
+        w[e] = !kMass ? 1ull : use ? token_weight<kMass>(k, inv_t, cb.s_max) : 0ull;
+      }
+      add_to_bins<kMass>(sh.hist, sh.count, bins, w);
+    });
+    __syncthreads();
+    unsigned long long left;  // the same in every wave
+    const int step = scan_select_n<false, kCutBins / 64>(sh.hist, [&](unsigned long long) { return rem; }, lane, &left);
+    n = kMass ? sh.count[step] : (uint32_t)sh.hist[step];
+    rem = left;
+    hi -= min((uint32_t)step << shift, hi - lo);
+    lo = max(lo, hi - min(hi, (1u << shift) - 1));
+  }
+  __syncthreads();
+  place_t cut = (place_t)lo << kIndexBits;
+  int g_end = V >> 2;
+  const bool listed = n <= (uint32_t)kCutList;  // block-uniform
+  if (!listed) {
+    unsigned long long need = rem;
+    if (kMass) {
+      const unsigned long long w = token_weight<kMass>(lo, inv_t, cb.s_max);
+      need = w > 0 ? (rem + w - 1) / w : 1ull;
+    }
+    cut = nth_of_key(z, V, lo, need, sh);
+    if (top == lo) g_end = min(g_end, cut_at(cut).idx / 4 + 1);  // nothing behind it
+  }
+  if (tid == 0) sh.n = 0u;
+  __syncthreads();
+  for_each_group<4>(z, 0, g_end, tid, kFinishThreads, [&](int i0, float4 v) {
+    const float zs[4] = {v.x, v.y, v.z, v.w};
+    uint32_t mask = 0;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      const uint32_t k = order_key(zs[e]);
+      if (k < lo || k > top) continue;
+      if (k > hi || (!listed && place_of(k, (uint32_t)(i0 + e)) >= cut)) {
+        mask |= 1u << e;
+      } else if (listed && (!use_k || kept_by(allowed, k, i0 + e))) {
+        const uint32_t at = atomicAdd(&sh.n, 1u);
+        if (at < (uint32_t)kCutList) sh.list[at] = make_uint2(k, (uint32_t)(i0 + e));
+      }
+    }
+    if (mask) kept(i0, mask, zs);
+  });
+  __syncthreads();
+  *n_list = min((int)sh.n, kCutList);
+  return listed ? list_cut<kMass>(*n_list, (place_t)lo << kIndexBits, place_of(hi, 0u), rem, inv_t, cb.s_max, sh) : cut;
 }
 
 // grid (rows): the top-k cut of a row that a top-p cut will follow.
 __global__ __launch_bounds__(kFinishThreads) void cut_finish_kernel(const float* __restrict__ logits, int V, float inv_t, int n_slices,
-                                                                    unsigned long long target, CutRow* __restrict__ ws) {
+                                                                    CutRow* __restrict__ ws) {
   __shared__ FinishLds sh;
   CutRow& row = ws[blockIdx.x];
   const CutBinning cb = cut_binning(row, n_slices, inv_t, false);
-  OrderCut cut;
-  row_cut<false>(logits + (size_t)blockIdx.x * V, V, inv_t, cb, row, target, 0ull, OrderCut{0u, 0x7fffffff}, sh, &cut);
-  if (threadIdx.x == 0) row.cut_k = cut;
+  int n;
+  const place_t cut = row_cut<false>(logits + (size_t)blockIdx.x * V, V, inv_t, cb, row, 0, sh, &n,
+                                     [](int, uint32_t, const float*) {});
+  if (threadIdx.x == 0) row.cut_k = cut_at(cut);
 }
 
 // grid (rows): the final cut, the draw among the tokens of its bin, and the result.
 template <bool kMass>
 __global__ __launch_bounds__(kFinishThreads) void sample_finish_kernel(const float* __restrict__ logits, int V, float inv_t,
-                                                                       int n_slices, int use_k, unsigned long long target,
-                                                                       unsigned long long p_fixed, const CutRow* __restrict__ ws,
+                                                                       int n_slices, int use_k, const CutRow* __restrict__ ws,
                                                                        DrawArgs da, int32_t* __restrict__ out_tok,
                                                                        float* __restrict__ out_lp, int32_t* __restrict__ last_tok) {
   __shared__ FinishLds sh;
@@ -653,41 +800,35 @@ __global__ __launch_bounds__(kFinishThreads) void sample_finish_kernel(const flo
   const CutRow& row = ws[r];
   const float* z = logits + (size_t)r * V;
   const CutBinning cb = cut_binning(row, n_slices, inv_t, kMass);
-  const OrderCut allowed = use_k ? row.cut_k : OrderCut{0u, 0x7fffffff};
   const RowMeta rm = da.rows[r];
   const uint32_t pos = (uint32_t)(rm.pos + da.pos_offset), seq = (uint32_t)rm.seq;
   const int f = da.forced ? da.forced[r] : -1;
   __shared__ float sh_fz;
   Draw d = empty_draw();
   if (tid == 0 && f >= 0 && f < V) sh_fz = da.forced_z[r];
-  OrderCut cut;
-  if (!row_cut<kMass>(z, V, inv_t, cb, row, target, p_fixed, allowed, sh, &cut)) {
-    for_each_group(z, 0, V >> 2, tid, kFinishThreads, [&](int i0, float4 v) {
-      const float zs[4] = {v.x, v.y, v.z, v.w};
+  if (!cb.all) {  // block-uniform
+    int n;
+    const place_t cut = row_cut<kMass>(z, V, inv_t, cb, row, use_k, sh, &n, [&](int i0, uint32_t before, const float (&zs)[4]) {
       uint32_t rnd[4];
       philox4x32_10((uint32_t)i0 >> 2, pos, seq, 0u, da.seed_lo, da.seed_hi, rnd);
 #pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        const bool kept = kept_by(cut, order_key(zs[e]), i0 + e);
-        if (i0 + e == f) sh_fz = kept ? zs[e] : -INFINITY;
-        if (kept) d.add(i0 + e, zs[e], cb.z_max, inv_t, rnd[e]);
-      }
+      for (int e = 0; e < 4; ++e)
+        if (before >> e & 1u) {
+          d.add(i0 + e, zs[e], cb.z_max, inv_t, rnd[e]);
+          if (i0 + e == f) sh_fz = zs[e];
+        }
     });
-  } else {
-    for (int t = tid; t < (int)row.n_list[kMass]; t += kFinishThreads) {
+    for (int t = tid; t < n; t += kFinishThreads) {
       const uint2 e = sh.list[t];
-      if (!kept_by(cut, e.x, (int)e.y)) continue;
+      if (place_of(e.x, e.y) < cut) continue;
       const float zi = order_value(e.x);
       d.add((int)e.y, zi, cb.z_max, inv_t, token_bits(e.y, pos, seq, da.seed_lo, da.seed_hi));
       if ((int)e.y == f) sh_fz = zi;
     }
-    for (int t = tid; t < n_slices; t += kFinishThreads) {
-      const float* p = da.part + ((size_t)r * n_slices + t) * kSamplePartFloats;
-      Draw o;
-      o.best = Best{p[0], __float_as_int(p[1]), p[2]};
-      o.sum = *(const unsigned long long*)(p + 4);
-      d.merge(o);
-    }
+  }
+  for (int t = tid; t < n_slices; t += kFinishThreads) {
+    const float* p = da.part + ((size_t)r * n_slices + t) * kSamplePartFloats;
+    d.merge(Draw{Best{p[0], __float_as_int(p[1]), p[2]}, *(const unsigned long long*)(p + 4)});
   }
   d = block_draw<kFinishThreads>(d, sh.draw);  // its barrier also publishes sh_fz
   if (tid == 0) {
@@ -721,15 +862,15 @@ void launch_sample_cut(hipStream_t st, const float* logits, int M, int V, float 
     cut_hist_kernel<false><<<grid, kCutThreads, 0, st>>>(logits, V, inv_t, 0, ws);
     if (!use_p) {
       cut_gather_kernel<false, true><<<grid, kCutThreads, 0, st>>>(logits, V, inv_t, 0, K, 0ull, ws, da);
-      sample_finish_kernel<false><<<M, kFinishThreads, 0, st>>>(logits, V, inv_t, slices, 0, K, 0ull, ws, da, out_tokens, out_logprobs, last_tok);
+      sample_finish_kernel<false><<<M, kFinishThreads, 0, st>>>(logits, V, inv_t, slices, 0, ws, da, out_tokens, out_logprobs, last_tok);
       return;
     }
     cut_gather_kernel<false, false><<<grid, kCutThreads, 0, st>>>(logits, V, inv_t, 0, K, 0ull, ws, da);
-    cut_finish_kernel<<<M, kFinishThreads, 0, st>>>(logits, V, inv_t, slices, K, ws);
+    cut_finish_kernel<<<M, kFinishThreads, 0, st>>>(logits, V, inv_t, slices, ws);
   }
   cut_hist_kernel<true><<<grid, kCutThreads, 0, st>>>(logits, V, inv_t, use_k, ws);
   cut_gather_kernel<true, true><<<grid, kCutThreads, 0, st>>>(logits, V, inv_t, use_k, 0ull, P, ws, da);
-  sample_finish_kernel<true><<<M, kFinishThreads, 0, st>>>(logits, V, inv_t, slices, use_k, 1ull, P, ws, da, out_tokens, out_logprobs, last_tok);
+  sample_finish_kernel<true><<<M, kFinishThreads, 0, st>>>(logits, V, inv_t, slices, use_k, ws, da, out_tokens, out_logprobs, last_tok);
 }
 
 }  // namespace

@@ -1500,6 +1500,110 @@ def test_truncated_sampler_rows_that_leave_the_list_path(amd):
     ro.close()
 
 
+def _masked_rows(V):
+    """Rows whose cut's bin holds thousands of tokens, or whose smallest logits are masks: name -> row."""
+    lowest = float(np.finfo(np.float32).min)
+    base = ri.normal((16, V), 3.0, 8, 75)
+    pick = np.random.default_rng(75).random((16, V))
+    out = {}
+
+    def row(name, edit):
+        z = base[len(out)].clone()
+        edit(z, torch.from_numpy(pick[len(out)]))
+        out[name] = z
+
+    def fill(z, where, value):
+        z[where] = value
+
+    row("one banned", lambda z, u: fill(z, 7, -1e9))
+    row("one at the lowest", lambda z, u: fill(z, 7, lowest))
+    row("half at -1e9", lambda z, u: fill(z, u < 0.5, -1e9))
+    row("half at -inf", lambda z, u: fill(z, u < 0.5, float("-inf")))
+    row("ten allowed, the rest at -1e9", lambda z, u: fill(z, slice(10, None), -1e9))
+    row("ten allowed, the rest at the lowest", lambda z, u: fill(z, slice(10, None), lowest))
+    row("ten allowed, the rest at -inf", lambda z, u: fill(z, slice(10, None), float("-inf")))
+    row("some allowed, the rest at -1e9 and -inf", lambda z, u: (fill(z, u > 0.2, -1e9), fill(z, u > 0.9, float("-inf"))))
+    row("a twentieth allowed", lambda z, u: fill(z, u > 0.05, -1e9))
+    row("rounded to 16 bits", lambda z, u: z.copy_(z.bfloat16().float()))
+    row("rounded to quarters", lambda z, u: z.copy_(torch.round(z * 4) / 4))
+    row("three values", lambda z, u: z.copy_(torch.where(u < 0.1, 2.0, torch.where(u < 0.6, 1.0, -1.0))))
+    row("all equal", lambda z, u: z.fill_(0.25))
+    row("zeros of both signs", lambda z, u: z.copy_(torch.where(u < 0.5, 0.0, -0.0)))
+    row("a narrow crowd below one outlier", lambda z, u: (z.mul_(1e-4), fill(z, 11, 9.0)))
+    row("one infinity", lambda z, u: fill(z, 77, float("inf")))
+    return out
+
+
+def test_truncated_sampler_masked_tied_and_crowded_rows(amd):
+    """Rows whose cut falls among masked, equal or crowded logits, more of them than a list holds: the drawn tokens, the
+    log-probabilities and the kept set (probed by forced tokens on both sides of the cut) are the oracle's."""
+    V = 40000
+    shape = dict(ri.SHAPES["tiny"], n_layers=1, vocab=V)
+    w, _ = make_both(shape, 11)
+    rows = _masked_rows(V)
+    n = len(rows)
+    ro = amd.Rollout(shape, to_device(w), max_seqs=64, max_ctx=64, max_rows=n, kv_pages=8)
+    z = torch.stack(list(rows.values()))
+    zd = z.to(DEV)
+    seqs, poss = list(range(3, 3 + n)), [5 * i for i in range(n)]
+    for T, k, p in [(0.6, 0, 0.95), (0.7, 50, 0.0), (1.0, 9000, 0.0), (0.7, 1000, 0.9), (20.0, 30000, 0.8), (1.0, 1, 0.0), (1.0, V - 1, 0.0)]:
+        inside, outside = [], []
+        for r in range(n):
+            keep = orc.truncation(z[r].numpy(), float(np.float32(1.0) / np.float32(T)), k, p).astype(bool)
+            keys = z[r].numpy().view(np.int32).astype(np.int64)
+            keys = np.where(keys < 0, -(keys & 0x7fffffff) - 1, keys)
+            order = np.lexsort((np.arange(V), -keys))
+            kept = int(keep.sum())
+            assert keep[order[:kept]].all()
+            inside.append(int(order[kept - 1]))
+            outside.append(int(order[kept]) if kept < V else -1)
+        for forced in (None, inside, outside):
+            f = None if forced is None else torch.tensor(forced, dtype=torch.int32, device=DEV)
+            tok, lp = ro.rl_sample_logits(zd, seqs, poss, T, 9, forced=f, top_k=k, top_p=p)
+            torch.cuda.synchronize()
+            for r, name in enumerate(rows):
+                t_ref, lp_ref, _ = orc.sample_truncated(z[r].numpy(), T, k, p, 9, seqs[r], poss[r], forced=-1 if forced is None else forced[r])
+                assert int(tok[r]) == t_ref, (T, k, p, name)
+                if abs(lp_ref) > float(np.finfo(np.float32).max):  # of the lowest float at T < 1: no fp32 number
+                    lp_ref = float("-inf")
+                if name == "one infinity":
+                    continue
+                if np.isfinite(lp_ref):
+                    assert abs(float(lp[r]) - lp_ref) < 1e-5 * max(1.0, abs(lp_ref)), (T, k, p, name, float(lp[r]), lp_ref)
+                else:
+                    assert float(lp[r]) == lp_ref, (T, k, p, name)
+    ro.close()
+
+
+def test_truncated_sampler_masked_rows_are_not_slow(amd):
+    """A masked token, or a top-k cut that falls among masked ones, must not send a row to one block's passes over the whole
+    vocabulary: at one row it takes about as long as a plain row (1.0 to 1.3 times; five times is the limit for noise)."""
+    V = 151936
+    ro = _sampler_model(amd, V, True)
+    g = torch.Generator(device=DEV)
+    g.manual_seed(76)
+    plain = torch.randn(1, V, generator=g, device=DEV) * 3.0
+    banned, ten = plain.clone(), plain.clone()
+    banned[0, 7] = -1e9
+    ten[0, 10:] = float(np.finfo(np.float32).min)
+
+    def best(z):
+        times = []
+        for _ in range(5):
+            a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            a.record()
+            for _ in range(10):
+                ro.rl_sample_logits(z, [3], [5], 0.7, 9, top_k=50)
+            b.record()
+            torch.cuda.synchronize()
+            times.append(a.elapsed_time(b))
+        return min(times)
+
+    t = best(plain)
+    assert best(banned) < 5 * t and best(ten) < 5 * t
+    ro.close()
+
+
 def test_truncated_logprobs_have_the_same_bits_in_every_call_and_batch(amd):
     """Tokens and log-probabilities of truncated sampling depend on the row alone: repeated calls, and batches of 128,
     20 and 1 rows (which cut a row into slices of other sizes), give the same bits."""
