@@ -39,30 +39,46 @@ __device__ __forceinline__ float wave_sums(const float (&v)[R], int lane) {
   return a[0];
 }
 
-// One wave per output column n (4 waves per block) and R rows: lane l takes VEC elements from VEC l on of every 64 VEC.
-// K % VEC == 0.  VEC is 4 except for the O projection of an odd number of heads whose head_dim is no multiple of four:
-// there K is only even, rows begin on 8-byte boundaries, and a group of four would reach into the next row.
+// One wave per C output columns from C n on (4 waves per block) and R rows: lane l takes VEC elements from VEC l on of
+// every 64 VEC.  K % VEC == 0.  VEC is 4 except for the O projection of an odd number of heads whose head_dim is no
+// multiple of four: there K is only even, rows begin on 8-byte boundaries, and a group of four would reach into the next row.
 // kEpiSwiGLU: W has 2N rows (gate then up); out[m][n] = silu(gate)*up.  kEpiResidual: out[m][n] += product.
 // gain (may be null): the rows are RMS-normalised first, x * rsqrt(mean(x^2) + eps) * gain; every wave forms the row's
-// mean square from the elements it holds anyway.  A row's result depends neither on R nor on the rows beside it.
-template <int EPI, int R, int VEC>
+// mean square from the elements it holds anyway.  A row's result depends neither on R and C nor on the rows beside it.
+template <int EPI, int R, int C, int VEC>
 __global__ __launch_bounds__(256) void gemm_f32_kernel(const float* __restrict__ X, const float* __restrict__ W,
-                                                       float* __restrict__ out, int M, int N, int K,
+                                                       float* __restrict__ out, int M, int N, int K, int m_tiles,
                                                        const float* __restrict__ gain, float eps) {
   typedef float vec_t __attribute__((ext_vector_type(VEC)));
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-  const int n = blockIdx.x * 4 + wave, m0 = blockIdx.y * R;
+  // Consecutive blocks go to the eight dies in turn: the row tiles of one column tile follow each other on one die, whose
+  // L2 then gives the weights to all but the first of them.
+  const int j = blockIdx.x >> 3;
+  const int m0 = j % m_tiles * R, n = (((j / m_tiles) * 8 + (blockIdx.x & 7)) * 4 + wave) * C;
   if (n >= N) return;
-  const float* w0 = W + (size_t)n * K;
-  const float* w1 = W + (size_t)(n + N) * K;  // only read for SwiGLU
-  float a0[R], a1[R], ss[R];
+  const float* w0[C];
+  const float* w1[C];  // only read for SwiGLU
 #pragma unroll
-  for (int i = 0; i < R; ++i) a0[i] = a1[i] = ss[i] = 0.f;
-#pragma unroll 4
+  for (int c = 0; c < C; ++c) {
+    w0[c] = W + (size_t)min(n + c, N - 1) * K;
+    w1[c] = w0[c] + (size_t)N * K;
+  }
+  float a0[C][R], a1[C][R], ss[R];
+#pragma unroll
+  for (int i = 0; i < R; ++i) {
+    ss[i] = 0.f;
+#pragma unroll
+    for (int c = 0; c < C; ++c) a0[c][i] = a1[c][i] = 0.f;
+  }
+#pragma unroll(C == 1 ? 4 : 2)
   for (int k = VEC * lane; k < K; k += 64 * VEC) {
-    const vec_t u = *(const vec_t*)(w0 + k);
-    vec_t v = 0.f, g = 1.f;
-    if (EPI == kEpiSwiGLU) v = *(const vec_t*)(w1 + k);
+    vec_t u[C], v[C], g = 1.f;
+#pragma unroll
+    for (int c = 0; c < C; ++c) {
+      u[c] = *(const vec_t*)(w0[c] + k);
+      v[c] = 0.f;
+      if (EPI == kEpiSwiGLU) v[c] = *(const vec_t*)(w1[c] + k);
+    }
     if (gain) g = *(const vec_t*)(gain + k);
 #pragma unroll
     for (int i = 0; i < R; ++i) {
@@ -73,25 +89,31 @@ __global__ __launch_bounds__(256) void gemm_f32_kernel(const float* __restrict__
         x *= g;
       }
 #pragma unroll
-      for (int e = VEC - 1; e >= 0; --e) {
-        a0[i] = fmaf(u[e], x[e], a0[i]);
-        if (EPI == kEpiSwiGLU) a1[i] = fmaf(v[e], x[e], a1[i]);
-      }
+      for (int c = 0; c < C; ++c)
+#pragma unroll
+        for (int e = VEC - 1; e >= 0; --e) {
+          a0[c][i] = fmaf(u[c][e], x[e], a0[c][i]);
+          if (EPI == kEpiSwiGLU) a1[c][i] = fmaf(v[c][e], x[e], a1[c][i]);
+        }
     }
   }
-  float s0 = wave_sums<R>(a0, lane), s1 = 0.f;
-  if (EPI == kEpiSwiGLU) s1 = wave_sums<R>(a1, lane);
-  if (gain) {
-    const float inv = 1.0f / sqrtf(wave_sums<R>(ss, lane) / (float)K + eps);
-    s0 *= inv;
-    s1 *= inv;
+  float inv = 1.f;
+  if (gain) inv = 1.0f / sqrtf(wave_sums<R>(ss, lane) / (float)K + eps);
+#pragma unroll
+  for (int c = 0; c < C; ++c) {
+    float s0 = wave_sums<R>(a0[c], lane), s1 = 0.f;
+    if (EPI == kEpiSwiGLU) s1 = wave_sums<R>(a1[c], lane);
+    if (gain) {
+      s0 *= inv;
+      s1 *= inv;
+    }
+    const int m = m0 + lane;
+    if (lane >= R || m >= M || n + c >= N) continue;
+    float* o = out + (size_t)m * N + n + c;
+    if (EPI == kEpiSwiGLU) *o = s0 / (1.0f + expf(-s0)) * s1;
+    else if (EPI == kEpiResidual) *o += s0;
+    else *o = s0;
   }
-  const int m = m0 + lane;
-  if (lane >= R || m >= M) return;
-  float* o = out + (size_t)m * N + n;
-  if (EPI == kEpiSwiGLU) *o = s0 / (1.0f + expf(-s0)) * s1;
-  else if (EPI == kEpiResidual) *o += s0;
-  else *o = s0;
 }
 
 struct F32Append {
@@ -192,25 +214,31 @@ __global__ __launch_bounds__(256) void attn_f32_kernel(const float* __restrict__
   }
 }
 
-template <int R, int VEC>
+template <int R, int C, int VEC>
 void launch_gemm_rows(hipStream_t s, const float* X, const float* W, float* out, int M, int N, int K, int epi, const float* gain,
                       float eps) {
-  const dim3 grid((N + 3) / 4, (M + R - 1) / R);
+  const int m_tiles = (M + R - 1) / R, n_tiles = (N + 4 * C - 1) / (4 * C);
+  const dim3 grid((n_tiles + 7) / 8 * 8 * m_tiles);
   if (epi == kEpiSwiGLU)
-    gemm_f32_kernel<kEpiSwiGLU, R, VEC><<<grid, 256, 0, s>>>(X, W, out, M, N, K, gain, eps);
+    gemm_f32_kernel<kEpiSwiGLU, R, C, VEC><<<grid, 256, 0, s>>>(X, W, out, M, N, K, m_tiles, gain, eps);
   else if (epi == kEpiResidual)
-    gemm_f32_kernel<kEpiResidual, R, VEC><<<grid, 256, 0, s>>>(X, W, out, M, N, K, gain, eps);
+    gemm_f32_kernel<kEpiResidual, R, C, VEC><<<grid, 256, 0, s>>>(X, W, out, M, N, K, m_tiles, gain, eps);
   else
-    gemm_f32_kernel<kEpiPartial, R, VEC><<<grid, 256, 0, s>>>(X, W, out, M, N, K, gain, eps);
+    gemm_f32_kernel<kEpiPartial, R, C, VEC><<<grid, 256, 0, s>>>(X, W, out, M, N, K, m_tiles, gain, eps);
 }
 
 template <int VEC>
 void launch_gemm_vec(hipStream_t s, const float* X, const float* W, float* out, int M, int N, int K, int epi, const float* gain,
                      float eps) {
-  // rows per wave: the smallest of 1, 4 and 8 that holds the batch (rows beyond it would be computed for nothing), 8 beyond
-  if (M == 1) launch_gemm_rows<1, VEC>(s, X, W, out, M, N, K, epi, gain, eps);
-  else if (M <= 4) launch_gemm_rows<4, VEC>(s, X, W, out, M, N, K, epi, gain, eps);
-  else launch_gemm_rows<8, VEC>(s, X, W, out, M, N, K, epi, gain, eps);
+  // rows per wave: the smallest of 1, 4 and 8 that holds the batch (rows beyond it would be computed for nothing), 8 beyond,
+  // where a wave also takes two columns: the rows then come from L1 once for both, and so does the mean square.  With two
+  // layers of 2048 hidden dimensions a decode step of 64 rows takes 1.26 ms (3.15 with one column, 3.48 with the row tiles
+  // one after the other as well) and a prefill of 900 tokens 9.9 ms (22.1, 26.0); of 256 dimensions 0.09 and 0.64 ms
+  // (0.13, 0.93).  Four columns: 1.00, 8.4, 0.10, 0.65.
+  if (M == 1) launch_gemm_rows<1, 1, VEC>(s, X, W, out, M, N, K, epi, gain, eps);
+  else if (M <= 4) launch_gemm_rows<4, 1, VEC>(s, X, W, out, M, N, K, epi, gain, eps);
+  else if (M <= 8) launch_gemm_rows<8, 1, VEC>(s, X, W, out, M, N, K, epi, gain, eps);
+  else launch_gemm_rows<8, 2, VEC>(s, X, W, out, M, N, K, epi, gain, eps);
 }
 
 }  // namespace
