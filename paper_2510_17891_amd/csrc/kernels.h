@@ -54,9 +54,9 @@ __host__ __device__ inline size_t weight_offset(int r, int k, int k_blocks, int 
 void launch_embed(hipStream_t s, int dtype, const void* embed, const int32_t* tokens, float* x, int M, int H, int V,
                   const RowMeta* rows = nullptr, const int32_t* last_tok = nullptr);
 
-// x[r] += sum_{s<S} part[s][r][:] (part may be null);  capture (may be null) gets x;  if gain != null,
-// h = x * rsqrt(mean(x^2)+eps) * gain written as fp32 row-major (kF32) or f16 fragment-major (kBF16 models).
-void launch_residual_norm(hipStream_t s, int dtype, float* x, const float* part, int S, const void* gain,
+// bf16 models: x[r] += sum_{s<S} part[s][r][:] (part may be null);  capture (may be null) gets x;  if gain != null,
+// h = x * rsqrt(mean(x^2)+eps) * gain written as f16 fragment-major.
+void launch_residual_norm(hipStream_t s, float* x, const float* part, int S, const void* gain,
                           void* h_out, float* capture, int M, int H, float eps);
 
 // Sum the split partials of the QKV projection, apply per-head RMSNorm (q,k) and the rotation (q,k) at

@@ -107,7 +107,7 @@ void compute_layout(const rl_model_config& c, Layout* L) {
   L->ring = take(kRing * L->slot_bytes);
   L->x = take(R * H * 4);
   L->x_last = take(R * H * 4);
-  L->h = take(Rp * H * act);
+  L->h = take(c.dtype == RL_BF16 ? Rp * H * act : 256);  // fp32 projections normalise their rows themselves
   size_t part_elems;
   if (c.dtype == RL_BF16) {
     size_t a1 = (size_t)gemm_bf16_splits((int)nqkv, (int)H, kEpiPartial) * R * nqkv;
@@ -233,7 +233,12 @@ struct SharedAttn {  // device pointers into the metadata slot of the call (empt
   bool window = false;  // every row is in a set, and the sets cover all segments of their rows
 };
 
-// one_row_per_seq: the batch is a decode step, which lets the bf16 attention kernel take over the rotation and the
+// A layer boundary of a capture (may be null) where no norm writes it: the residual stream as it is.
+void copy_capture(hipStream_t st, float* cap, const float* x, int M, int H) {
+  if (cap) (void)hipMemcpyAsync(cap, x, (size_t)M * H * 4, hipMemcpyDeviceToDevice, st);  // an error stays for hipGetLastError
+}
+
+// one_row_per_seq: the batch is a decode step, which lets the attention kernel take over the rotation and the
 // KV append (a row's block is then the only reader of the key it writes).
 int run_layers(rl_model* m, hipStream_t st, int M, const RowMeta* rows, int max_ctx_in_batch,
                const SharedAttn& sa = SharedAttn(), bool one_row_per_seq = false) {
@@ -252,9 +257,11 @@ int run_layers(rl_model* m, hipStream_t st, int M, const RowMeta* rows, int max_
   int pend = 0;
   for (int l = 0; l < g.n_layers; ++l) {
     float* cap = m->capture ? m->capture + (size_t)l * m->cfg.max_rows * H : nullptr;
-    if (bf || cap) {  // fp32: the projections normalise their rows themselves; this only copies x for a capture
+    if (bf) {
       Timer t(m, st, K_NORM);
-      launch_residual_norm(st, g.dtype, x, pend ? part : nullptr, pend, bf ? m->attn_norm[l] : nullptr, h, cap, M, H, g.rms_eps);
+      launch_residual_norm(st, x, pend ? part : nullptr, pend, m->attn_norm[l], h, cap, M, H, g.rms_eps);
+    } else {
+      copy_capture(st, cap, x, M, H);
     }
     int s_qkv = 1;
     { Timer t(m, st, K_QKV);
@@ -289,7 +296,7 @@ int run_layers(rl_model* m, hipStream_t st, int M, const RowMeta* rows, int max_
       else { launch_gemm_f32(st, (const float*)o, (const float*)m->wo[l], x, M, H, nqd, kEpiResidual); s_o = 0; } }
     if (bf) {
       Timer t(m, st, K_NORM);
-      launch_residual_norm(st, g.dtype, x, s_o ? part : nullptr, s_o, m->mlp_norm[l], h, nullptr, M, H, g.rms_eps);
+      launch_residual_norm(st, x, s_o ? part : nullptr, s_o, m->mlp_norm[l], h, nullptr, M, H, g.rms_eps);
     }
     { Timer t(m, st, K_GATEUP);
       if (bf) launch_gemm_bf16(st, h, m->w_gate_up[l], a, M, F, H, kEpiSwiGLU);
@@ -313,9 +320,11 @@ void run_head(rl_model* m, hipStream_t st, int M, float* xbuf, int pend, const R
   float* logits = m->wsp<float>(m->lay.logits);
   float* cap = m->capture ? m->capture + (size_t)g.n_layers * m->cfg.max_rows * g.hidden : nullptr;
   const bool bf = g.dtype == kBF16;
-  if (bf || cap) {
+  if (bf) {
     Timer t(m, st, K_NORM);
-    launch_residual_norm(st, g.dtype, xbuf, pend ? part : nullptr, pend, bf ? m->final_norm : nullptr, h, cap, M, g.hidden, g.rms_eps);
+    launch_residual_norm(st, xbuf, pend ? part : nullptr, pend, m->final_norm, h, cap, M, g.hidden, g.rms_eps);
+  } else {
+    copy_capture(st, cap, xbuf, M, g.hidden);
   }
   float* spart = m->wsp<float>(m->lay.samp_part);
   float* fz = m->wsp<float>(m->lay.forced_z);
@@ -819,9 +828,12 @@ rl_status rl_decode_hidden(rl_model* m, void* stream, int32_t n, const int32_t* 
   HIP_TRY(hipMemcpyAsync(x, hidden_in, bytes, hipMemcpyDeviceToDevice, st));
   int pend = run_layers(m, st, n, rows, max_ctx_in_batch, sa, true);
   float* cap = m->capture ? m->capture + (size_t)m->geo.n_layers * m->cfg.max_rows * m->geo.hidden : nullptr;
-  if (pend || cap) {
+  if (pend) {
     Timer t(m, st, K_NORM);
-    launch_residual_norm(st, m->geo.dtype, x, m->wsp<float>(m->lay.part), pend, nullptr, nullptr, cap, n, m->geo.hidden, m->geo.rms_eps); }
+    launch_residual_norm(st, x, m->wsp<float>(m->lay.part), pend, nullptr, nullptr, cap, n, m->geo.hidden, m->geo.rms_eps);
+  } else {
+    copy_capture(st, cap, x, n, m->geo.hidden);
+  }
   HIP_TRY(hipMemcpyAsync(hidden_out, x, bytes, hipMemcpyDeviceToDevice, st));
   HIP_TRY(hipGetLastError());
   for (int i = 0; i < n; ++i) m->table->set_len(seq_ids[i], m->table->len(seq_ids[i]) + 1);
@@ -951,9 +963,12 @@ static rl_status prefill_impl(rl_model* m, hipStream_t st, int32_t n_prompts, in
     int pend = run_layers(m, st, M, rows, max_ctx, sa);
     // fold the pending partials into x, then keep the rows that end a prompt (one copy per group member)
     float* cap = m->capture ? m->capture + (size_t)m->geo.n_layers * m->cfg.max_rows * H : nullptr;
-    if (pend || cap) {
+    if (pend) {
       Timer t(m, st, K_NORM);
-      launch_residual_norm(st, m->geo.dtype, x, m->wsp<float>(m->lay.part), pend, nullptr, nullptr, cap, M, H, m->geo.rms_eps); }
+      launch_residual_norm(st, x, m->wsp<float>(m->lay.part), pend, nullptr, nullptr, cap, M, H, m->geo.rms_eps);
+    } else {
+      copy_capture(st, cap, x, M, H);
+    }
     for (const Last& l : lasts)
       for (int j = 0; j < group; ++j)
         HIP_TRY(hipMemcpyAsync(x_last + (size_t)(l.prompt * group + j) * H, x + (size_t)l.row * H, (size_t)H * 4, hipMemcpyDeviceToDevice, st));

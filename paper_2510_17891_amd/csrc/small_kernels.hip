@@ -31,10 +31,10 @@ void launch_embed(hipStream_t s, int dtype, const void* embed, const int32_t* to
 // ------------------------------------------------------------------------------------------------
 // Residual update + RMSNorm.  One block per row, one float4 per thread and pass (H/4 threads, at most 1024), so
 // that the few dependent memory round trips of this latency-bound step are as short as possible.  The split
-// partials of the preceding projection are summed in a fixed order, so results do not depend on the batch.
+// partials of the preceding projection are summed in a fixed order, so results do not depend on the batch.  bf16 models
+// only: fp32 projections normalise their rows and add to the residual stream themselves.
 // ------------------------------------------------------------------------------------------------
-// gain: H gains; without a norm (has_gain = 0) any readable H-element array of the model's dtype.
-template <bool BF16>
+// gain: H bf16 gains; without a norm (has_gain = 0) any readable H-element array.
 __global__ __launch_bounds__(1024) void residual_norm_kernel(float* __restrict__ x, const float* __restrict__ part,
                                                              int S, size_t split_stride, const void* __restrict__ gain,
                                                              int has_gain, void* __restrict__ h_out,
@@ -45,19 +45,14 @@ __global__ __launch_bounds__(1024) void residual_norm_kernel(float* __restrict__
   float ss = 0.f;
   constexpr int kMaxPass = 2;  // H <= 1024 threads * 4 * kMaxPass, checked by the host
   float4 keep[kMaxPass];
-  // Gains are requested together with the data, as stored (bf16: two words per thread), and first touched after the
+  // Gains are requested together with the data, as stored (two words per thread), and first touched after the
   // sums: converting them here would make the compiler wait for them before it even asks for the data.
-  uint4 graw[kMaxPass];
+  uint2 graw[kMaxPass];
 #pragma unroll
   for (int pass = 0; pass < kMaxPass; ++pass) {
     const int i0 = (pass * nthr + threadIdx.x) * 4;
     const int ig = i0 < H ? i0 : 0;  // unconditional loads (a branch here costs a wait); `gain` is always readable
-    if (BF16) {
-      const uint2 gb = *(const uint2*)((const uint16_t*)gain + ig);
-      graw[pass] = make_uint4(gb.x, gb.y, 0u, 0u);
-    } else {
-      graw[pass] = *(const uint4*)((const float*)gain + ig);
-    }
+    graw[pass] = *(const uint2*)((const uint16_t*)gain + ig);
   }
 #pragma unroll
   for (int pass = 0; pass < kMaxPass; ++pass) {
@@ -79,7 +74,7 @@ __global__ __launch_bounds__(1024) void residual_norm_kernel(float* __restrict__
   if (!has_gain) return;
 #pragma unroll
   for (int pass = 0; pass < kMaxPass; ++pass)
-    asm volatile("" : "+v"(graw[pass].x), "+v"(graw[pass].y), "+v"(graw[pass].z), "+v"(graw[pass].w));
+    asm volatile("" : "+v"(graw[pass].x), "+v"(graw[pass].y));
   ss = wave_sum(ss);
   if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = ss;
   __syncthreads();
@@ -91,33 +86,20 @@ __global__ __launch_bounds__(1024) void residual_norm_kernel(float* __restrict__
     const int i0 = (pass * nthr + threadIdx.x) * 4;
     if (i0 >= H) continue;
     const float4 v = keep[pass];
-    float4 g;
-    if (BF16) {
-      g = make_float4(bf2f(graw[pass].x & 0xffffu), bf2f(graw[pass].x >> 16), bf2f(graw[pass].y & 0xffffu), bf2f(graw[pass].y >> 16));
-    } else {
-      g = make_float4(__uint_as_float(graw[pass].x), __uint_as_float(graw[pass].y), __uint_as_float(graw[pass].z),
-                      __uint_as_float(graw[pass].w));
-    }
-    if (BF16) {
-      *(uint2*)((uint16_t*)h_out + frag_offset(r, i0, H >> 6)) =
-          make_uint2(pack2h(v.x * inv * g.x, v.y * inv * g.y), pack2h(v.z * inv * g.z, v.w * inv * g.w));
-    } else {
-      *(float4*)((float*)h_out + (size_t)r * H + i0) = make_float4(v.x * inv * g.x, v.y * inv * g.y, v.z * inv * g.z, v.w * inv * g.w);
-    }
+    const float4 g = make_float4(bf2f(graw[pass].x & 0xffffu), bf2f(graw[pass].x >> 16), bf2f(graw[pass].y & 0xffffu), bf2f(graw[pass].y >> 16));
+    *(uint2*)((uint16_t*)h_out + frag_offset(r, i0, H >> 6)) =
+        make_uint2(pack2h(v.x * inv * g.x, v.y * inv * g.y), pack2h(v.z * inv * g.z, v.w * inv * g.w));
   }
 }
 
-void launch_residual_norm(hipStream_t s, int dtype, float* x, const float* part, int S, const void* gain,
+void launch_residual_norm(hipStream_t s, float* x, const float* part, int S, const void* gain,
                           void* h_out, float* capture, int M, int H, float eps) {
   size_t stride = (size_t)M * H;
   int threads = ((H / 4 + 63) / 64) * 64;
   if (threads > 1024) threads = 1024;
   const int has_gain = gain != nullptr;
   const void* g = has_gain ? gain : x;  // read and ignored without a norm
-  if (dtype == kBF16)
-    residual_norm_kernel<true><<<M, threads, 0, s>>>(x, part, S, stride, g, has_gain, h_out, capture, H, eps);
-  else
-    residual_norm_kernel<false><<<M, threads, 0, s>>>(x, part, S, stride, g, has_gain, h_out, capture, H, eps);
+  residual_norm_kernel<<<M, threads, 0, s>>>(x, part, S, stride, g, has_gain, h_out, capture, H, eps);
 }
 
 // One wave per (row, head), four heads per block.  Lane i < d/2 owns the rotary pair (i, i + d/2).

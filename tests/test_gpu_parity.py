@@ -1676,6 +1676,30 @@ def test_f32_steps_for_other_head_dims_and_batch_sizes(amd, over):
         assert rel_inf(z1[0].cpu().numpy(), zr) < 1e-4
 
 
+def test_f32_capture_holds_every_layer_boundary(amd):
+    """The capture of an fp32 model: what goes into the first layer, what one layer alone makes of it, and what comes out of
+    the last, for a decode of hidden rows and (the prompt's rows) a prefill."""
+    shape = dict(ri.SHAPES["tiny"])
+    w, _ = make_both(shape, 23)
+    wd = to_device(w)
+    x = ri.normal((3, shape["hidden"]), 1.0, 9, 77).to(DEV)
+    ro = amd.Rollout(shape, wd, max_seqs=3, max_ctx=64, max_rows=8, kv_pages=12)
+    one = amd.Rollout(dict(shape, n_layers=1), dict(wd, layers=wd["layers"][:1]), max_seqs=3, max_ctx=64, max_rows=8, kv_pages=12)
+    prompts = [[5], [6], [7]]
+    cap, cap1 = ro.rl_set_capture(True), one.rl_set_capture(True)
+    ro.rl_prefill([0, 1, 2], prompts, 0.0, 1)
+    one.rl_prefill([0, 1, 2], prompts, 0.0, 1)
+    torch.cuda.synchronize()
+    embedded = wd["embed"][torch.tensor([5, 6, 7], device=DEV)]
+    assert torch.equal(cap[0, :3], embedded) and torch.equal(cap1[0, :3], embedded)
+    assert torch.equal(cap[1, :3], cap1[1, :3]) and not torch.equal(cap[2, :3], cap[1, :3])
+    out, out1 = ro.rl_decode_hidden([0, 1, 2], x), one.rl_decode_hidden([0, 1, 2], x)
+    torch.cuda.synchronize()
+    assert torch.equal(cap[0, :3], x) and torch.equal(cap[1, :3], out1) and torch.equal(cap[2, :3], out)
+    ro.close()
+    one.close()
+
+
 def test_f32_wide_rows_share_their_weights(amd):
     """fp32 projections of many rows read their weights once, not once per eight rows: a step of 64 rows through a layer of
     2048 hidden dimensions takes 2.2 times as long as one of 8 rows (6.0 times when every row tile fetched them)."""
