@@ -30,29 +30,35 @@ HBM_PEAK_GBS = 8000.0
 
 # HBM traffic of the dominant kernels from rocprofv3 --pmc FETCH_SIZE / WRITE_SIZE runs (profiles/hbm_traffic_counters.md),
 # stored as measured bytes / algorithmic bytes of the same launches, each counter scaled by what it reads for a plain
-# 1 GiB device copy (FETCH_SIZE x 2.0000, WRITE_SIZE x 1.0000).  An entry is used only while the kernel's source
-# file still has the hash it had when the counters were taken; otherwise "traffic" is null.
+# 1 GiB device copy (FETCH_SIZE x 2.0000, WRITE_SIZE x 1.0000).  An entry is used only while the code of the kernel's
+# source file (comments aside) still has the hash it had when the counters were taken; otherwise "traffic" is null.
 TRAFFIC_RATIO = {
     # one layer at the launch shape of the 128-sequence wave (16 groups x 8 samples, 2048 shared + 7168 private tokens)
-    ("wave", "attn_decode"): (1.044, "attn_bf16.hip", "bf9a68219783273c"),
-    ("layer", "attn_decode"): (1.044, "attn_bf16.hip", "bf9a68219783273c"),
-    ("full", "attn_decode"): (1.040, "attn_bf16.hip", "bf9a68219783273c"),
-    ("full", "gemm_gate_up_swiglu"): (1.011, "gemm_bf16.hip", "c85762f8c6f26887"),
+    ("wave", "attn_decode"): (1.043, "attn_bf16.hip", "08978da6b40b3c17"),
+    ("layer", "attn_decode"): (1.043, "attn_bf16.hip", "08978da6b40b3c17"),
+    ("full", "attn_decode"): (1.040, "attn_bf16.hip", "08978da6b40b3c17"),
+    ("full", "gemm_gate_up_swiglu"): (1.010, "gemm_bf16.hip", "354abb6d32887075"),
 }
 
 
-def measured_traffic(workload, kernel, algorithmic_bytes):
+def code_hash(src):
+    """Of a kernel source file without its comments and with white space evened out."""
     import hashlib
+    import re
+    with open(os.path.join(ROOT, "paper_2510_17891_amd", "csrc", src)) as f:
+        code = re.sub(r"//[^\n]*", " ", f.read())
+    return hashlib.sha256(" ".join(code.split()).encode()).hexdigest()[:16]
+
+
+def measured_traffic(workload, kernel, algorithmic_bytes):
     ent = TRAFFIC_RATIO.get((workload, kernel))
     if ent is None:
         return None
     ratio, src, sha = ent
-    path = os.path.join(ROOT, "paper_2510_17891_amd", "csrc", src)
     try:
-        cur = hashlib.sha256(open(path, "rb").read()).hexdigest()[:16]
+        return ratio * algorithmic_bytes if code_hash(src) == sha else None
     except OSError:
         return None
-    return ratio * algorithmic_bytes if cur == sha else None
 
 
 def parse():

@@ -346,6 +346,14 @@ def test_bench_refuses_more_than_one_gpu():
         assert r.returncode == 2 and "one GPU" in r.stderr and r.stdout.strip() == ""
 
 
+def test_bench_traffic_ratios_belong_to_the_present_kernels():
+    """The measured traffic of the bench line is that of the present code: a kernel whose code has changed since its
+    counters were taken would leave the field empty (comments may change)."""
+    import bench
+    for (workload, kernel), (ratio, src, sha) in bench.TRAFFIC_RATIO.items():
+        assert bench.measured_traffic(workload, kernel, 1e9) == ratio * 1e9, (workload, kernel, src, bench.code_hash(src), sha)
+
+
 def test_binding_fails_loudly_without_the_library():
     """No fallback: when the shared library is not there, the first call through the binding raises and names the
     build command."""
