@@ -1068,14 +1068,19 @@ __global__ __launch_bounds__(512, 1) void gemm_bf16_lds8r3_kernel(const u32x4_t*
 //     leaves its matrix core idle (16 matrix instructions and 16 fragment reads take 577 cycles, with four LDS writes and
 //     four weight loads in a row 852, spread out 670);
 //   - the barrier does not wait for LDS reads in flight: a stage is rewritten one barrier after its last read;
-//   - two blocks per compute unit (256 registers per lane), which hides each other's barriers, quarter sums and ends.
+//   - two blocks per compute unit (256 registers per lane), which hides each other's barriers, quarter sums and ends.  The
+//     instances that keep no running sums have them (48 or 36 KB of LDS), and so have three row blocks with sums (68 KB);
+//     four row blocks with sums (O and down at 1024 rows) take 112 KB, so that one block with one wave per SIMD is alone
+//     on a unit: down runs at 0.81 PFLOP/s where gate/up runs at 1.0.
+// Waves without batch rows (two of twelve at 301 rows) execute all matrix instructions of the last rows along with the
+// others and drop the result.
 // The quarter sums keep a row's bits those of the K-split kernels: every K quarter in an accumulator of its own, added
 // in order; then, where the plan splits K, the splits in order, kept in LDS between them.  So a QKV, O or down product
 // leaves no split partials: QKV writes its sum once (100 MB less written and 75 MB less read at 1024 rows), O and down
 // add theirs to the residual stream themselves (kEpiResidual), in the order in which the norm kernel would.
-// Measured inside scoring, prefill and decode passes, against the kernels before: gate/up 120 -> 92 us at 301 rows, 139 -> 115 at 512, 208 -> 209
-// at 1024; QKV 44 -> 37, 55 -> 43, 88 -> 68; O 53 -> 48 and down 118 -> 124 at 1024, with the norm behind each 21 -> 11;
-// output projection with sampling 1403 -> 1321.
+// Measured inside scoring, prefill and decode passes, against the kernels before: gate/up 129 -> 93 us at 301 rows, 139 ->
+// 115 at 512, 218 -> 204 at 1024; QKV 46 -> 39, 56 -> 44, 93 -> 67; at 1024 rows O 55 -> 48, but down 125 -> 128 (one block
+// per unit), with the norm behind each 21 -> 11; output projection with sampling 1472 -> 1289.
 __device__ __forceinline__ __amdgpu_buffer_rsrc_t buffer_of(const void* base, uint32_t bytes) {
   return __builtin_amdgcn_make_buffer_rsrc((void*)base, 0, bytes, 0x00020000);
 }
