@@ -1295,6 +1295,39 @@ def test_decode_graph_steps_equal_eager_steps(amd, kv_fp8, G, wide):
     rb.close()
 
 
+@pytest.mark.parametrize("kind", ["tiny_f32", "small_bf16"])
+@pytest.mark.parametrize("top_k,top_p", [(0, 0.95), (50, 0.0), (300, 0.9)])
+def test_truncated_decode_graph_steps_equal_eager_steps(amd, kind, top_k, top_p):
+    """Graph steps with top-k / top-p against eager steps of a second instance, bit for bit, over 12 replays with eager
+    work and synchronisations in between: the cut's kernels clear what they count in, and the fp32 step appends inside
+    its attention."""
+    import ctypes as C
+    b = amd.binding
+    shape = dict(ri.SHAPES["tiny"]) if kind == "tiny_f32" else dict(ri.SHAPES["layer8b"], n_layers=2, hidden=512, n_q=4, n_kv=1, ffn=768, vocab=8192)
+    w, _ = make_both(shape, 66, std=0.05)
+    wd = to_device(w)
+    ids = list(range(5))
+    prompts = [ri.tokens((n,), shape["vocab"], 66, 960 + i).tolist() for i, n in enumerate([20, 33, 5, 47, 1])]
+    kw = dict(max_seqs=5, max_ctx=96, max_rows=64, kv_pages=30)
+    ra, rb = amd.Rollout(shape, wd, **kw), amd.Rollout(shape, wd, **kw)
+    for r in (ra, rb):
+        r.rl_prefill(ids, prompts, 1.0, 9)
+    tok, lp = torch.empty(5, dtype=torch.int32, device=DEV), torch.empty(5, device=DEV)
+    sp, g, captures = b.rl_sampling(1.0, top_k, 9, top_p, 0), C.c_void_p(), C.c_int64()
+    b.check(b.lib().rl_decode_graph_create(ra.h, 5, b._i32(ids), C.byref(sp), b._ptr(tok), b._ptr(lp), C.byref(g)))
+    torch.cuda.synchronize()
+    side = torch.cuda.Stream()
+    with torch.cuda.stream(side):
+        for step in range(12):
+            b.check(b.lib().rl_decode_graph_step(g, b._stream(), C.byref(captures)))
+            te, le = rb.rl_decode_step(ids, None, 1.0, 9, top_k=top_k, top_p=top_p)
+            torch.cuda.synchronize()
+            assert torch.equal(tok, te) and torch.equal(lp, le), step
+    b.lib().rl_decode_graph_destroy(g)
+    ra.close()
+    rb.close()
+
+
 # ------------------------------------------------------------------------------- fp8 keys and values (opt-in)
 def _e4m3_exact(shape_, seed, tid):
     """Random values that every fp8 e4m3 variant represents exactly: multiples of 0.25 in [-2, 2]."""
@@ -1573,6 +1606,26 @@ def test_truncated_sampler_masked_tied_and_crowded_rows(amd):
                 else:
                     assert float(lp[r]) == lp_ref, (T, k, p, name)
     ro.close()
+
+
+def test_truncated_sampler_at_the_smallest_and_largest_vocabulary(amd):
+    """Four entries, and the last multiple of four below 2^22: plain, equal and masked rows against the oracle."""
+    for V, ks in ((4, (1, 3)), ((1 << 22) - 4, (50, 3000000))):
+        shape = dict(ri.SHAPES["tiny"], n_layers=1, hidden=8, n_q=1, n_kv=1, head_dim=8, ffn=8, vocab=V)
+        w, _ = make_both(shape, 12)
+        ro = amd.Rollout(shape, to_device(w), max_seqs=8, max_ctx=16, max_rows=3, kv_pages=4)
+        z = torch.stack([ri.normal((V,), 3.0, 9, 78), torch.full((V,), -1.5), ri.normal((V,), 3.0, 9, 79)])
+        z[2, V // 4:] = -1e9
+        seqs, poss = [1, 2, 3], [4, 0, 9]
+        zd = z.to(DEV)
+        for T, k, p in [(1.0, ks[0], 0.0), (1.0, ks[1], 0.0), (0.7, 0, 0.9), (1.0, ks[1], 0.5)]:
+            tok, lp = ro.rl_sample_logits(zd, seqs, poss, T, 3, top_k=k, top_p=p)
+            torch.cuda.synchronize()
+            for r in range(3):
+                t_ref, lp_ref, kept = orc.sample_truncated(z[r].numpy(), T, k, p, 3, seqs[r], poss[r])
+                assert int(tok[r]) == t_ref, (V, T, k, p, r, kept)
+                assert abs(float(lp[r]) - lp_ref) < 1e-5 * max(1.0, abs(lp_ref)), (V, T, k, p, r, float(lp[r]), lp_ref)
+        ro.close()
 
 
 def test_truncated_sampler_masked_rows_are_not_slow(amd):
