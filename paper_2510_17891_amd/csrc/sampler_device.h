@@ -111,7 +111,7 @@ __device__ __forceinline__ void lse_merge(float& m, float& s, float m2, float s2
   s = s * __expf(m - mn) + s2 * __expf(m2 - mn);
   m = mn;
 }
-// lse_merge(m, s, t, 1) with one exponential instead of two; the same bits.
+// lse_merge(m, s, t, 1) with one exponential instead of two; the same bits for a finite t.
 __device__ __forceinline__ void lse_add(float& m, float& s, float t) {
   if (t > m) {
     s = s * __expf(m - t) + 1.0f;
