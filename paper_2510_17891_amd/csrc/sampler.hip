@@ -123,8 +123,9 @@ __global__ __launch_bounds__(1024) void sample_stage2_kernel(const float* __rest
 // row.  A radix selection over the digits of the key took five passes, each with its own scan, and a draw over every
 // entry.  Rows of 151936 entries, that selection -> these passes: 0.6 / 0.95 at 128 rows 217 -> 74 us, at one row 65 -> 33;
 // top-k 50 198 -> 69 and 56 -> 31, also with masked tokens or logits rounded to 16 bits; a top-k cut among masked tokens
-// 323 -> 97 and 58 -> 41.  Slower at few rows are a crowd 30000 times narrower than the distance of an outlier above it
-// (top-k: 197 -> 140 at 128 rows, 56 -> 76 at one) and the mass of equal logits (360 -> 270, 63 -> 160).
+// 323 -> 97 and 58 -> 41; equal logits 360 -> 78 and 63 -> 26 (the cut follows from their number).  Slower at few rows is a
+// crowd 30000 times narrower than the distance of an outlier above it (top-k: 197 -> 140 at 128 rows, 56 -> 76 at one):
+// steps that follow such a crowd cost plain rows 5 % at 256 rows.
 // ------------------------------------------------------------------------------------------------
 constexpr int kCutBins = 1024;
 constexpr int kCutList = 4096;
@@ -186,6 +187,7 @@ struct CutBinning {
   float r0, r1;
   uint32_t floor;      // bits of the row's smallest logit: masked tokens, mostly
   bool all;            // mass: no token has any (the largest score is not a finite number, or rounded by more than 22)
+  bool equal;          // all logits are equal
   template <bool kMass>
   __device__ __forceinline__ int bin(float z) const {
     const float t = z_ref - z;
@@ -195,6 +197,9 @@ struct CutBinning {
     if (!finite_bits(z)) return (int)__float_as_uint(z) < 0 ? kCutBins - 2 : 0;  // by its place in the order
     return (int)(t < r1 ? (t - r0) * scale1 + 512.f : fminf((t - r1) * scale2, 254.f) + 768.f);
   }
+  // Leading tokens that are kept where that follows without a search (every token, or so many of the equal ones), or -1.
+  template <bool kMass>
+  __device__ __forceinline__ int prefix(int n_allowed, int V, float inv_t, unsigned long long target, unsigned long long p_fixed) const;
 };
 __device__ __forceinline__ CutBinning cut_binning(const CutRow& row, int n_slices, float inv_t, bool mass) {
   const int i = min((int)(threadIdx.x & (kCutSlices - 1)), n_slices - 1);  // both halves of a wave hold all slices
@@ -214,6 +219,7 @@ __device__ __forceinline__ CutBinning cut_binning(const CutRow& row, int n_slice
   b.all = mass && fexp_weight(__fmaf_rn(b.z_max, inv_t, -b.s_max)) == 0;
   b.z_ref = order_value(fmax);
   b.floor = __float_as_uint(order_value(kmin));
+  b.equal = kmin == kmax;
   const auto steps = [](float n, float range) { const float q = n / range; return range > 0.f && finite_bits(q) ? q : 0.f; };
   const float range = b.z_ref - order_value(fmin);  // NaN without a finite logit
   b.r0 = b.r1 = b.scale1 = b.scale2 = 0.f;
@@ -279,6 +285,17 @@ __device__ __forceinline__ int scan_select_n(const unsigned long long* hist, F t
 __device__ __forceinline__ unsigned long long mass_target(unsigned long long S, unsigned long long p_fixed) {
   const unsigned long long t = (__umul64hi(S, p_fixed) << 32) | ((S * p_fixed) >> 32);  // S < 2^50, p_fixed < 2^32
   return t < 1 ? 1 : t;
+}
+
+template <bool kMass>
+__device__ __forceinline__ int CutBinning::prefix(int n_allowed, int V, float inv_t, unsigned long long target,
+                                                  unsigned long long p_fixed) const {
+  if (all) return V;
+  if (!equal) return -1;
+  if (!kMass) return (int)target;
+  const unsigned long long w = fexp_weight(__fmaf_rn(z_max, inv_t, -s_max));  // not zero
+  const unsigned long long n = (mass_target(w * (unsigned long long)n_allowed, p_fixed) + w - 1) / w;
+  return (int)min(max(n, 1ull), (unsigned long long)n_allowed);  // scores beyond 10^9 may round to a weight that overflows
 }
 
 // grid (slices, rows): the slice's share of the row's range; clears the row's histograms and counters.
@@ -373,7 +390,7 @@ __global__ __launch_bounds__(kCutThreads) void cut_hist_kernel(const float* __re
   const int r = blockIdx.y, tid = threadIdx.x;
   CutRow& row = ws[r];
   const CutBinning cb = cut_binning(row, gridDim.x, inv_t, kMass);
-  if (cb.all) return;  // block-uniform: nothing is cut off
+  if (cb.all || cb.equal) return;  // block-uniform: no search
   const OrderCut allowed = use_k ? row.cut_k : OrderCut{0u, 0x7fffffff};
   for (int b = tid; b < kCutBins; b += kCutThreads) lh[b] = 0ull;
   __syncthreads();
@@ -505,15 +522,22 @@ __global__ __launch_bounds__(kCutThreads) void cut_gather_kernel(const float* __
   auto draw_token = [&](int i, float zi) {
     d.add(i, zi, cb.z_max, inv_t, token_bits((uint32_t)i, pos, seq, da.seed_lo, da.seed_hi));
   };
-  if (cb.all) {  // block-uniform; nothing is cut off (only with kMass, and then kDraw)
+  // block-uniform
+  const int n_prefix = cb.prefix<kMass>(use_k ? allowed.idx + 1 : V, V, inv_t, target, p_fixed);
+  if (n_prefix >= 0 && !kDraw) {
+    if (blockIdx.x == 0 && tid == 0) row.cut_k = OrderCut{order_key(cb.z_max), n_prefix - 1};
+    return;
+  }
+  if (n_prefix >= 0) {
     for_each_group<4>(z, sl.g_begin, sl.g_end, tid, kCutThreads, [&](int i0, float4 v) {
       const float zs[4] = {v.x, v.y, v.z, v.w};
       uint32_t rnd[4];
       philox4x32_10((uint32_t)i0 >> 2, pos, seq, 0u, da.seed_lo, da.seed_hi, rnd);
 #pragma unroll
       for (int e = 0; e < 4; ++e) {
-        d.add(i0 + e, zs[e], cb.z_max, inv_t, rnd[e]);
-        if (kDraw && f == i0 + e) da.forced_z[r] = zs[e];
+        const bool kept = i0 + e < n_prefix;
+        if (kept) d.add(i0 + e, zs[e], cb.z_max, inv_t, rnd[e]);
+        if (f == i0 + e) da.forced_z[r] = kept ? zs[e] : -INFINITY;
       }
     });
   } else {
@@ -749,7 +773,7 @@ __device__ place_t row_cut(const float* __restrict__ z, int V, float inv_t, cons
     unsigned long long need = rem;
     if (kMass) {
       const unsigned long long w = token_weight<kMass>(lo, inv_t, cb.s_max);
-      need = w > 0 ? (rem + w - 1) / w : 1ull;
+      need = w > 0 ? max((rem + w - 1) / w, 1ull) : 1ull;
     }
     cut = nth_of_key(z, V, lo, need, sh);
     if (top == lo) g_end = min(g_end, cut_at(cut).idx / 4 + 1);  // nothing behind it
@@ -783,6 +807,7 @@ __global__ __launch_bounds__(kFinishThreads) void cut_finish_kernel(const float*
   __shared__ FinishLds sh;
   CutRow& row = ws[blockIdx.x];
   const CutBinning cb = cut_binning(row, n_slices, inv_t, false);
+  if (cb.equal) return;  // cut_gather wrote the cut
   int n;
   const place_t cut = row_cut<false>(logits + (size_t)blockIdx.x * V, V, inv_t, cb, row, 0, sh, &n,
                                      [](int, uint32_t, const float*) {});
@@ -806,7 +831,7 @@ __global__ __launch_bounds__(kFinishThreads) void sample_finish_kernel(const flo
   __shared__ float sh_fz;
   Draw d = empty_draw();
   if (tid == 0 && f >= 0 && f < V) sh_fz = da.forced_z[r];
-  if (!cb.all) {  // block-uniform
+  if (!cb.all && !cb.equal) {  // block-uniform
     int n;
     const place_t cut = row_cut<kMass>(z, V, inv_t, cb, row, use_k, sh, &n, [&](int i0, uint32_t before, const float (&zs)[4]) {
       uint32_t rnd[4];
