@@ -17,8 +17,8 @@ int set_error(int status, const char* fmt, ...) __attribute__((format(printf, 2,
 struct RowMeta {
   int32_t seq;   // sequence id (row of the block table, RNG stream)
   int32_t pos;   // absolute position of the token fed in this row
-  int32_t page;  // KV page that holds position pos (the host knows it; saves the append kernel a dependent load)
-  int32_t pad;   // row 0 of a decode call: number of page grants uploaded with the rows; otherwise 0
+  int32_t page;  // KV page that holds position pos (what the append and, at a page's first position, the block table need)
+  int32_t pad;
 };
 
 enum Dtype : int { kF32 = 0, kBF16 = 1 };
@@ -49,14 +49,37 @@ __host__ __device__ inline size_t weight_offset(int r, int k, int k_blocks, int 
 }
 
 // ---- elementwise / small kernels (both dtypes) -------------------------------------------------
-// x[r][:] = E[tok[r]][:] widened to fp32 (ids clamped to [0, V)).
-// tokens == null: row r is fed last_tok[rows[r].seq] (the token the sampler recorded for that sequence).
-void launch_embed(hipStream_t s, int dtype, const void* embed, const int32_t* tokens, float* x, int M, int H, int V,
-                  const RowMeta* rows = nullptr, const int32_t* last_tok = nullptr);
+// What the first kernel of a call moves from the pinned slot of the call to its slot in the workspace, in units of 16
+// bytes: the rows from the start of the slot, then up to three more regions.  block_table (may be null): rows at the
+// first position of a page are entered there.
+struct SlotUpload {
+  const uint4* src = nullptr;  // host memory, read by the kernel: may be rewritten once the kernel has finished
+  uint4* dst = nullptr;
+  int n_rows = 0;
+  int at[3] = {0, 0, 0}, n[3] = {0, 0, 0};
+  int32_t* block_table = nullptr;
+  int max_blocks = 0;
+};
+// Where the rows of a call come from.  from_table: row r is src[token] (model dtype, V rows of H; ids are clamped to
+// [0, V)) with token = tokens[r], or, with tokens == null, last_tok[rows[r].seq] (what the sampler recorded for that
+// sequence).  Otherwise src is fp32 [M][H].
+struct RowSource {
+  const void* src = nullptr;
+  int from_table = 0;
+  const int32_t* tokens = nullptr;
+  const int32_t* last_tok = nullptr;
+  const RowMeta* rows = nullptr;  // in host memory: the slot's
+  int V = 0;
+};
+// First kernel of a call: moves the metadata slot, x = the rows of the call, and in bf16 models capture (may be null) = x
+// and h_out = the normalised rows.
+void launch_entry(hipStream_t s, int dtype, const RowSource& in, const SlotUpload& up, float* x, const void* gain, void* h_out,
+                  float* capture, int M, int H, float eps);
 
-// bf16 models: x[r] += sum_{s<S} part[s][r][:] (part may be null);  capture (may be null) gets x;  if gain != null,
-// h = x * rsqrt(mean(x^2)+eps) * gain written as f16 fragment-major.
-void launch_residual_norm(hipStream_t s, float* x, const float* part, int S, const void* gain,
+// bf16 models: x_out[r] = x_in[r] + sum_{s<S} part[s][r][:] (x_out may be x_in and is not written when S == 0; part may
+// then be null);  capture (may be null) gets that row;  if gain != null, h = row * rsqrt(mean(row^2)+eps) * gain written
+// as f16 fragment-major.  x_in, x_out 16-byte aligned.
+void launch_residual_norm(hipStream_t s, const float* x_in, float* x_out, const float* part, int S, const void* gain,
                           void* h_out, float* capture, int M, int H, float eps);
 
 // Sum the split partials of the QKV projection, apply per-head RMSNorm (q,k) and the rotation (q,k) at
@@ -179,11 +202,5 @@ void launch_sample_merge(hipStream_t s, const float* part, int n_tiles, int M, i
 
 // out[idx[i]] = src[i] for idx[i] >= 0.
 void launch_scatter_f32(hipStream_t s, const float* src, const int32_t* idx, float* out, int n);
-
-// block_table[upd[3i]][upd[3i+1]] = upd[3i+2] for i < n (device-side mirror update of newly granted pages).
-void launch_table_update(hipStream_t s, int32_t* block_table, int max_blocks, const int32_t* upd, int n);
-// The same for at most n_max entries, of which the first rows[0].pad (read on the device) are applied.
-void launch_table_update_counted(hipStream_t s, int32_t* block_table, int max_blocks, const int32_t* upd,
-                                 const RowMeta* rows, int n_max);
 
 }  // namespace rl

@@ -49,6 +49,11 @@ namespace {
 
 constexpr int kRing = 64;  // per-call metadata slots in the workspace
 constexpr int kRingCalls = kRing - 2;  // slots that ordinary calls cycle through; the last two belong to a decode graph
+// One event covers this many uses of the slots (an event on every call costs the device 2.8 us between two kernels and the
+// host 3 us).  Calls of a model are ordered one after another, on whatever streams, because they share the workspace:
+// an event behind a later call is behind the earlier ones too.
+constexpr int kEpochUses = 12, kEpochs = 8;
+static_assert((kEpochs - 1) * kEpochUses > kRingCalls, "the event of a slot's last use is not recorded anew before the slot comes round");
 constexpr int T_MAX_SCORE = 4096;  // sequences per scoring call
 
 size_t align_up(size_t v, size_t a = 256) { return (v + a - 1) / a * a; }
@@ -138,8 +143,8 @@ void compute_layout(const rl_model_config& c, Layout* L) {
   L->total = off;
 }
 
-enum Kind { K_META, K_EMBED, K_NORM, K_QKV, K_ROPE_APPEND, K_ATTN, K_ATTN_MERGE, K_OPROJ, K_GATEUP, K_DOWN, K_LMHEAD, K_SAMPLE, K_COUNT };
-const char* const kKindNames[K_COUNT] = {"meta", "embed", "residual_norm", "gemm_qkv", "qk_rope_append", "attn_decode", "attn_merge",
+enum Kind { K_EMBED, K_NORM, K_QKV, K_ROPE_APPEND, K_ATTN, K_ATTN_MERGE, K_OPROJ, K_GATEUP, K_DOWN, K_LMHEAD, K_SAMPLE, K_COUNT };
+const char* const kKindNames[K_COUNT] = {"embed", "residual_norm", "gemm_qkv", "qk_rope_append", "attn_decode", "attn_merge",
                                         "gemm_o", "gemm_gate_up_swiglu", "gemm_down", "gemm_lm_head", "sample"};
 
 }  // namespace
@@ -157,9 +162,11 @@ struct rl_model {
   size_t layer_kv_bytes, kv_block_bytes;  // one layer of the pool; one K (or V) block of a (page, kv head)
   // pinned host ring for per-call metadata
   char* host_ring = nullptr;
-  hipEvent_t ring_ev[kRing];
-  bool ring_used[kRing];
   int ring_next = 0;
+  hipEvent_t epoch_ev[kEpochs];
+  int64_t epoch = 0, epoch_done = -1;  // the epoch that is filling; the last one the host has seen finished
+  int epoch_uses = 0;
+  int64_t slot_epoch[kRing];  // epoch of a slot's last use, -1: never used
   float* capture = nullptr;
   bool graph_alive = false;     // a decode graph owns the last two metadata slots
   int attn_segs_per_block = 4;  // segments per attention block of contexts beyond 4096 keys (one per wave)
@@ -214,12 +221,25 @@ struct Timer {
 rl_status ring_acquire(rl_model* m, int* slot_out) {
   int s = m->ring_next;
   m->ring_next = (s + 1) % kRingCalls;
-  if (m->ring_used[s]) {  // the device is kRingCalls calls behind: the host has nothing better to do than wait
+  const int64_t e = m->slot_epoch[s];
+  if (e > m->epoch_done) {  // the device is up to kRingCalls calls behind: the host has nothing better to do than wait
     const auto t0 = std::chrono::steady_clock::now();
-    HIP_TRY(hipEventSynchronize(m->ring_ev[s]));
+    if (e == m->epoch) HIP_TRY(hipDeviceSynchronize());  // only if recording the epoch's event has failed
+    else HIP_TRY(hipEventSynchronize(m->epoch_ev[e % kEpochs]));
+    if (e < m->epoch) m->epoch_done = e;
     m->host_us[3] += std::chrono::duration<double, std::micro>(std::chrono::steady_clock::now() - t0).count();
   }
   *slot_out = s;
+  return RL_OK;
+}
+
+// The work that reads the host side of a slot has been enqueued.
+rl_status slot_in_use(rl_model* m, hipStream_t st, int slot) {
+  m->slot_epoch[slot] = m->epoch;
+  if (++m->epoch_uses < kEpochUses) return RL_OK;
+  HIP_TRY(hipEventRecord(m->epoch_ev[m->epoch % kEpochs], st));
+  m->epoch += 1;
+  m->epoch_uses = 0;
   return RL_OK;
 }
 
@@ -238,6 +258,7 @@ void copy_capture(hipStream_t st, float* cap, const float* x, int M, int H) {
   if (cap) (void)hipMemcpyAsync(cap, x, (size_t)M * H * 4, hipMemcpyDeviceToDevice, st);  // an error stays for hipGetLastError
 }
 
+// The rows and their first norm (bf16: in h) are there: launch_entry ran.
 // one_row_per_seq: the batch is a decode step, which lets the attention kernel take over the rotation and the
 // KV append (a row's block is then the only reader of the key it writes).
 int run_layers(rl_model* m, hipStream_t st, int M, const RowMeta* rows, int max_ctx_in_batch,
@@ -257,11 +278,11 @@ int run_layers(rl_model* m, hipStream_t st, int M, const RowMeta* rows, int max_
   int pend = 0;
   for (int l = 0; l < g.n_layers; ++l) {
     float* cap = m->capture ? m->capture + (size_t)l * m->cfg.max_rows * H : nullptr;
-    if (bf) {
-      Timer t(m, st, K_NORM);
-      launch_residual_norm(st, x, pend ? part : nullptr, pend, m->attn_norm[l], h, cap, M, H, g.rms_eps);
-    } else {
+    if (!bf) {
       copy_capture(st, cap, x, M, H);
+    } else if (l > 0) {
+      Timer t(m, st, K_NORM);
+      launch_residual_norm(st, x, x, pend ? part : nullptr, pend, m->attn_norm[l], h, cap, M, H, g.rms_eps);
     }
     int s_qkv = 1;
     { Timer t(m, st, K_QKV);
@@ -296,7 +317,7 @@ int run_layers(rl_model* m, hipStream_t st, int M, const RowMeta* rows, int max_
       else { launch_gemm_f32(st, (const float*)o, (const float*)m->wo[l], x, M, H, nqd, kEpiResidual); s_o = 0; } }
     if (bf) {
       Timer t(m, st, K_NORM);
-      launch_residual_norm(st, x, s_o ? part : nullptr, s_o, m->mlp_norm[l], h, nullptr, M, H, g.rms_eps);
+      launch_residual_norm(st, x, x, s_o ? part : nullptr, s_o, m->mlp_norm[l], h, nullptr, M, H, g.rms_eps);
     }
     { Timer t(m, st, K_GATEUP);
       if (bf) launch_gemm_bf16(st, h, m->w_gate_up[l], a, M, F, H, kEpiSwiGLU);
@@ -322,7 +343,7 @@ void run_head(rl_model* m, hipStream_t st, int M, float* xbuf, int pend, const R
   const bool bf = g.dtype == kBF16;
   if (bf) {
     Timer t(m, st, K_NORM);
-    launch_residual_norm(st, xbuf, pend ? part : nullptr, pend, m->final_norm, h, cap, M, g.hidden, g.rms_eps);
+    launch_residual_norm(st, xbuf, xbuf, pend ? part : nullptr, pend, m->final_norm, h, cap, M, g.hidden, g.rms_eps);
   } else {
     copy_capture(st, cap, xbuf, M, g.hidden);
   }
@@ -355,8 +376,8 @@ void run_head(rl_model* m, hipStream_t st, int M, float* xbuf, int pend, const R
   }
 }
 
-// Checks shared by decode calls; on success `grants` holds the pages handed out and lens are NOT yet advanced.
-rl_status admit_decode(rl_model* m, int32_t n, const int32_t* seq_ids, std::vector<PageGrant>* grants) {
+// Checks shared by decode calls; on success the pages are handed out and lens are NOT yet advanced.
+rl_status admit_decode(rl_model* m, int32_t n, const int32_t* seq_ids) {
   if (n < 1 || n > (int32_t)m->cfg.max_rows) return fail(RL_ERR_INVALID_ARG, "n_seqs %d outside [1, max_rows=%u]", n, m->cfg.max_rows);
   if (!seq_ids) return fail(RL_ERR_INVALID_ARG, "seq_ids is NULL");
   SeqTable& T = *m->table;
@@ -371,23 +392,61 @@ rl_status admit_decode(rl_model* m, int32_t n, const int32_t* seq_ids, std::vect
     need += T.pages_missing(s, T.len(s) + 1);
   }
   if (need > T.free_pages()) return fail(RL_ERR_KV_FULL, "need %lld pages, %lld free", (long long)need, (long long)T.free_pages());
-  for (int i = 0; i < n; ++i) T.reserve(seq_ids[i], T.len(seq_ids[i]) + 1, grants);
+  for (int i = 0; i < n; ++i) T.reserve(seq_ids[i], T.len(seq_ids[i]) + 1, nullptr);
   return RL_OK;
 }
 
-// Copy a plan of shared attention into the metadata slot (host side hs, device side ds) and describe it in *sa.
-rl_status upload_attn_plan(rl_model* m, hipStream_t st, char* hs, char* ds, int n, const AttnPlan& plan, SharedAttn* sa) {
+// The upload of a call's rows from its host slot hs to its device slot ds; more regions of the slot are added to it.
+// table: the rows enter their pages in the block table.
+SlotUpload slot_upload(const rl_model* m, const char* hs, char* ds, int n_rows, bool table) {
+  static_assert(sizeof(RowMeta) == 16, "one unit per row");
+  SlotUpload up;
+  up.src = (const uint4*)hs;
+  up.dst = (uint4*)ds;
+  up.n_rows = n_rows;
+  up.block_table = table ? m->wsp<int32_t>(m->lay.block_table) : nullptr;
+  up.max_blocks = m->geo.max_blocks;
+  return up;
+}
+void add_region(SlotUpload* up, size_t at, size_t bytes) {  // regions start and are padded at multiples of 256 bytes
+  int k = 0;
+  while (up->n[k]) ++k;
+  up->at[k] = (int)(at / 16);
+  up->n[k] = (int)((bytes + 15) / 16);
+}
+
+// Copy a plan of shared attention into the host slot, add it to the upload and describe it (device pointers) in *sa.
+void place_attn_plan(rl_model* m, char* hs, char* ds, int n, const AttnPlan& plan, SharedAttn* sa, SlotUpload* up) {
   *sa = SharedAttn();
-  if (plan.sets.empty()) return RL_OK;
+  if (plan.sets.empty()) return;
   memcpy(hs + m->lay.slot_skip, plan.skip.data(), (size_t)n * 4);
   memcpy(hs + m->lay.slot_sets, plan.sets.data(), plan.sets.size() * sizeof(AttnShared));
-  HIP_TRY(hipMemcpyAsync(ds + m->lay.slot_skip, hs + m->lay.slot_skip, (size_t)n * 4, hipMemcpyHostToDevice, st));
-  HIP_TRY(hipMemcpyAsync(ds + m->lay.slot_sets, hs + m->lay.slot_sets, plan.sets.size() * sizeof(AttnShared), hipMemcpyHostToDevice, st));
+  add_region(up, m->lay.slot_skip, (size_t)n * 4);
+  add_region(up, m->lay.slot_sets, plan.sets.size() * sizeof(AttnShared));
   sa->skip = (const int32_t*)(ds + m->lay.slot_skip);
   sa->sets = (const AttnShared*)(ds + m->lay.slot_sets);
   sa->n_sets = (int)plan.sets.size();
   sa->max_segs = plan.max_shared_segs;
-  return RL_OK;
+}
+
+// First kernel of a call: the upload, the rows into the residual stream, the first norm.  Marks the slot as in use until
+// the kernel has read it.
+rl_status enter_rows(rl_model* m, hipStream_t st, int slot, const RowSource& in, const SlotUpload& up, int M) {
+  float* cap = m->geo.dtype == kBF16 ? m->capture : nullptr;  // layer 0's boundary; fp32: copied in run_layers
+  { Timer t(m, st, K_EMBED);
+    launch_entry(st, m->geo.dtype, in, up, m->wsp<float>(m->lay.x), m->attn_norm[0], m->wsp<void>(m->lay.h), cap, M, m->geo.hidden, m->geo.rms_eps); }
+  return slot_in_use(m, st, slot);
+}
+
+RowSource table_rows(const rl_model* m, const char* hs, const int32_t* tokens) {
+  RowSource in;
+  in.src = m->embed;
+  in.from_table = 1;
+  in.tokens = tokens;
+  in.last_tok = m->wsp<int32_t>(m->lay.last_tok);
+  in.rows = (const RowMeta*)hs;
+  in.V = m->geo.vocab;
+  return in;
 }
 
 // Rows per set for a call of n rows (the test switch can ask for the wide sets always or never, whatever the size).
@@ -398,14 +457,14 @@ int rows_per_set(const rl_model* m, int n) {
 }
 
 // Sets of neighbouring rows of one sequence for a chunk of prefill or scoring rows (bf16 only).
-rl_status upload_window_plan(rl_model* m, hipStream_t st, char* hs, char* ds, int n, const RowMeta* hr, SharedAttn* sa) {
+void place_window_plan(rl_model* m, char* hs, char* ds, int n, const RowMeta* hr, SharedAttn* sa, SlotUpload* up) {
   *sa = SharedAttn();
-  if (m->geo.dtype != kBF16 || !m->share_attention) return RL_OK;
+  if (m->geo.dtype != kBF16 || !m->share_attention) return;
   std::vector<int32_t> seq(n), pos(n);
   for (int i = 0; i < n; ++i) { seq[i] = hr[i].seq; pos[i] = hr[i].pos; }
   AttnPlan plan;
   plan_window_sets(n, seq.data(), pos.data(), rows_per_set(m, n), &plan);
-  if (plan.sets.empty()) return RL_OK;  // every row on its own
+  if (plan.sets.empty()) return;  // every row on its own
   // The rows left over become sets of one, so that the launch needs no row blocks; the longest contexts come first, so
   // that the blocks still running at its end are short ones.
   for (int i = 0; i < n; ++i) {
@@ -419,15 +478,13 @@ rl_status upload_window_plan(rl_model* m, hipStream_t st, char* hs, char* ds, in
     plan.max_shared_segs = std::max(plan.max_shared_segs, s.n_segs);
   }
   std::stable_sort(plan.sets.begin(), plan.sets.end(), [&](const AttnShared& a, const AttnShared& b) { return pos[a.rows[0]] > pos[b.rows[0]]; });
-  const rl_status rs = upload_attn_plan(m, st, hs, ds, n, plan, sa);
+  place_attn_plan(m, hs, ds, n, plan, sa, up);
   sa->window = sa->n_sets > 0;
-  return rs;
 }
 
-// Write the rows, page grants and shared-attention plan of one decode call into the host slot hs and describe them
-// (device pointers relative to the device slot ds).  Returns the bytes of the slot in use.
-size_t build_decode_meta(rl_model* m, int32_t n, const int32_t* seq_ids, const std::vector<PageGrant>& grants, char* hs,
-                         char* ds, int* max_ctx_out, SharedAttn* sa) {
+// Write the rows and the shared-attention plan of one decode call into the host slot hs and describe them (device
+// pointers relative to the device slot ds).  Returns the upload that brings them there.
+SlotUpload build_decode_meta(rl_model* m, int32_t n, const int32_t* seq_ids, char* hs, char* ds, int* max_ctx_out, SharedAttn* sa) {
   RowMeta* hr = (RowMeta*)hs;
   int max_ctx = 0;
   for (int i = 0; i < n; ++i) {
@@ -437,10 +494,7 @@ size_t build_decode_meta(rl_model* m, int32_t n, const int32_t* seq_ids, const s
     hr[i].pad = 0;
     if (hr[i].pos + 1 > max_ctx) max_ctx = hr[i].pos + 1;
   }
-  int32_t* hu = (int32_t*)(hs + m->lay.slot_upd);
-  for (size_t i = 0; i < grants.size(); ++i) { hu[3 * i] = grants[i].seq; hu[3 * i + 1] = grants[i].block; hu[3 * i + 2] = grants[i].page; }
   // rows of sequences that hold prompt pages in common and stand at the same position share those segments
-  *sa = SharedAttn();
   AttnPlan plan;
   if (m->geo.dtype == kBF16 && m->share_attention) {
     std::vector<int64_t> fam(n);
@@ -454,59 +508,43 @@ size_t build_decode_meta(rl_model* m, int32_t n, const int32_t* seq_ids, const s
     }
     if (any) plan_shared_attention(n, fam.data(), fam_blocks.data(), pos.data(), rows_per_set(m, n), &plan);
   }
-  hr[0].pad = (int32_t)grants.size();
-  // One upload for everything the step needs: the slot's regions lie at fixed offsets, so the copy runs from the rows
-  // to the end of the last region in use (a few KB; what lies between is not read).
-  size_t used = (size_t)n * sizeof(RowMeta);
-  if (!grants.empty()) used = m->lay.slot_upd + grants.size() * 12;
-  if (!plan.sets.empty()) {
-    memcpy(hs + m->lay.slot_skip, plan.skip.data(), (size_t)n * 4);
-    memcpy(hs + m->lay.slot_sets, plan.sets.data(), plan.sets.size() * sizeof(AttnShared));
-    used = m->lay.slot_sets + plan.sets.size() * sizeof(AttnShared);
-    sa->skip = (const int32_t*)(ds + m->lay.slot_skip);
-    sa->sets = (const AttnShared*)(ds + m->lay.slot_sets);
-    sa->n_sets = (int)plan.sets.size();
-    sa->max_segs = plan.max_shared_segs;
-  }
+  SlotUpload up = slot_upload(m, hs, ds, n, true);
+  place_attn_plan(m, hs, ds, n, plan, sa, &up);
   *max_ctx_out = max_ctx;
-  return used;
+  return up;
 }
 
-// Build and upload the rows (and page grants) of one decode call; returns device pointers into the slot.
-rl_status upload_decode_meta(rl_model* m, hipStream_t st, int32_t n, const int32_t* seq_ids,
-                             const std::vector<PageGrant>& grants, const RowMeta** rows_dev, int* max_ctx_out,
-                             SharedAttn* sa) {
+// Build the rows of one decode call in a metadata slot of their own; *rows_dev and *sa are device pointers into it, valid once the
+// upload has run.
+struct DecodeMeta {
   int slot;
-  rl_status rs = ring_acquire(m, &slot);
+  char* hs;
+  SlotUpload up;
+  const RowMeta* rows_dev;
+  int max_ctx;
+  SharedAttn sa;
+};
+rl_status prepare_decode_meta(rl_model* m, int32_t n, const int32_t* seq_ids, DecodeMeta* dm) {
+  rl_status rs = ring_acquire(m, &dm->slot);
   if (rs != RL_OK) return rs;
-  char* hs = m->host_ring + (size_t)slot * m->lay.slot_bytes;
-  char* ds = m->ws + m->lay.ring + (size_t)slot * m->lay.slot_bytes;
-  const size_t used = build_decode_meta(m, n, seq_ids, grants, hs, ds, max_ctx_out, sa);
-  Timer t(m, st, K_META);
-  HIP_TRY(hipMemcpyAsync(ds, hs, used, hipMemcpyHostToDevice, st));
-  if (!grants.empty())
-    launch_table_update(st, m->wsp<int32_t>(m->lay.block_table), m->geo.max_blocks, (const int32_t*)(ds + m->lay.slot_upd), (int)grants.size());
-  HIP_TRY(hipEventRecord(m->ring_ev[slot], st));
-  m->ring_used[slot] = true;
-  *rows_dev = (const RowMeta*)ds;
+  dm->hs = m->host_ring + (size_t)dm->slot * m->lay.slot_bytes;
+  char* ds = m->ws + m->lay.ring + (size_t)dm->slot * m->lay.slot_bytes;
+  dm->up = build_decode_meta(m, n, seq_ids, dm->hs, ds, &dm->max_ctx, &dm->sa);
+  dm->rows_dev = (const RowMeta*)ds;
   return RL_OK;
 }
 
-// The kernels of one decode step for n rows whose metadata is on the device: embedding, layers, head.
+// The kernels of one decode step behind its first: layers and head.
 void decode_enqueue(rl_model* m, hipStream_t st, int n, const RowMeta* rows, int max_ctx_in_batch, const SharedAttn& sa,
-                    const int32_t* in_tokens, const int32_t* forced_next, const rl_sampling* sp, int32_t* out_tokens,
-                    float* out_logprobs, float* debug_logits) {
-  float* x = m->wsp<float>(m->lay.x);
-  { Timer t(m, st, K_EMBED);
-    launch_embed(st, m->geo.dtype, m->embed, in_tokens, x, n, m->geo.hidden, m->geo.vocab, rows, m->wsp<int32_t>(m->lay.last_tok)); }
+                    const int32_t* forced_next, const rl_sampling* sp, int32_t* out_tokens, float* out_logprobs, float* debug_logits) {
   int pend = run_layers(m, st, n, rows, max_ctx_in_batch, sa, true);
-  run_head(m, st, n, x, pend, rows, 1, forced_next, sp, out_tokens, out_logprobs, debug_logits);
+  run_head(m, st, n, m->wsp<float>(m->lay.x), pend, rows, 1, forced_next, sp, out_tokens, out_logprobs, debug_logits);
 }
 
 }  // namespace
 
-// A decode step of a fixed batch as a HIP graph.  What changes from step to step is data (rows, page grants, the
-// shared-attention plan: one upload from a pinned buffer that the graph's copy node reads at every launch) except for
+// A decode step of a fixed batch as a HIP graph.  What changes from step to step is data (rows and the
+// shared-attention plan: one upload from a pinned buffer that the graph's first kernel reads at every launch) except for
 // three launch shapes, which form the key of the captured graph: the 1024-key bracket of the longest context (block
 // count and shared-memory size of the attention launch), the number of row sets, and the blocks the sets need.  When
 // the key changes -- once per 1024 steps for a batch in lock step -- the step is captured again.  Two buffers and two
@@ -585,7 +623,8 @@ rl_status rl_init_model(const rl_model_config* c, const rl_weights* w, rl_model*
   m->layer_kv_bytes = (size_t)n_pages * c->n_kv_heads * 2 * m->kv_block_bytes;
   m->table = new SeqTable((int)c->max_seqs, (int)c->max_ctx, n_pages);
   for (int i = 0; i < K_COUNT; ++i) { m->prof_ms[i] = 0; m->prof_n[i] = 0; }
-  for (int i = 0; i < kRing; ++i) { m->ring_ev[i] = nullptr; m->ring_used[i] = false; }
+  for (int i = 0; i < kRing; ++i) m->slot_epoch[i] = -1;
+  for (int i = 0; i < kEpochs; ++i) m->epoch_ev[i] = nullptr;
 
   auto bail = [&](hipError_t e, const char* what) {
     rl_status r = fail(RL_ERR_DEVICE, "%s: %s", what, hipGetErrorString(e));
@@ -594,8 +633,8 @@ rl_status rl_init_model(const rl_model_config* c, const rl_weights* w, rl_model*
   };
   hipError_t e;
   if ((e = hipHostMalloc((void**)&m->host_ring, kRing * L.slot_bytes, hipHostMallocDefault)) != hipSuccess) return bail(e, "hipHostMalloc");
-  for (int i = 0; i < kRing; ++i)
-    if ((e = hipEventCreateWithFlags(&m->ring_ev[i], hipEventDisableTiming)) != hipSuccess) return bail(e, "hipEventCreate");
+  for (int i = 0; i < kEpochs; ++i)
+    if ((e = hipEventCreateWithFlags(&m->epoch_ev[i], hipEventDisableTiming)) != hipSuccess) return bail(e, "hipEventCreate");
   // Stale slots of recycled pages are multiplied by zero weights, so the pool must never hold NaN/Inf patterns.
   if ((e = hipMemset(m->kv_pool, 0, (size_t)n_pages * page_bytes)) != hipSuccess) return bail(e, "hipMemset(kv_pool)");
   if ((e = hipMemset(m->ws + L.block_table, 0, (size_t)c->max_seqs * (c->max_ctx / 16) * 4)) != hipSuccess) return bail(e, "hipMemset(block_table)");
@@ -620,7 +659,7 @@ void rl_destroy_model(rl_model* m) {
   if (!m) return;
   for (auto& p : m->pending) { (void)hipEventDestroy(p.a); (void)hipEventDestroy(p.b); }
   for (auto ev : m->ev_pool) (void)hipEventDestroy(ev);
-  for (int i = 0; i < kRing; ++i) if (m->ring_ev[i]) (void)hipEventDestroy(m->ring_ev[i]);
+  for (int i = 0; i < kEpochs; ++i) if (m->epoch_ev[i]) (void)hipEventDestroy(m->epoch_ev[i]);
   if (m->host_ring) (void)hipHostFree(m->host_ring);
   delete m->table;
   delete m;
@@ -691,18 +730,17 @@ rl_status rl_decode_step(rl_model* m, void* stream, int32_t n, const int32_t* se
   if (m->geo.vocab == 0) return fail(RL_ERR_UNSUPPORTED, "model has no vocabulary");
   hipStream_t st = (hipStream_t)stream;
   const auto t0 = std::chrono::steady_clock::now();
-  std::vector<PageGrant> grants;
-  rl_status rs = admit_decode(m, n, seq_ids, &grants);
+  rl_status rs = admit_decode(m, n, seq_ids);
   if (rs != RL_OK) return rs;
   const auto t1 = std::chrono::steady_clock::now();
   const double waited = m->host_us[3];
-  const RowMeta* rows;
-  int max_ctx_in_batch;
-  SharedAttn sa;
-  rs = upload_decode_meta(m, st, n, seq_ids, grants, &rows, &max_ctx_in_batch, &sa);
+  DecodeMeta dm;
+  rs = prepare_decode_meta(m, n, seq_ids, &dm);
   if (rs != RL_OK) return rs;
   const auto t2 = std::chrono::steady_clock::now();
-  decode_enqueue(m, st, n, rows, max_ctx_in_batch, sa, in_tokens, forced_next, sp, out_tokens, out_logprobs, debug_logits);
+  rs = enter_rows(m, st, dm.slot, table_rows(m, dm.hs, in_tokens), dm.up, n);
+  if (rs != RL_OK) return rs;
+  decode_enqueue(m, st, n, dm.rows_dev, dm.max_ctx, dm.sa, forced_next, sp, out_tokens, out_logprobs, debug_logits);
   HIP_TRY(hipGetLastError());
   for (int i = 0; i < n; ++i) m->table->set_len(seq_ids[i], m->table->len(seq_ids[i]) + 1);
   const auto t3 = std::chrono::steady_clock::now();
@@ -766,8 +804,7 @@ rl_status rl_decode_graph_step(rl_decode_graph* g, void* stream, int64_t* captur
   rl_model* m = g->m;
   hipStream_t st = (hipStream_t)stream;
   const int n = (int)g->ids.size();
-  std::vector<PageGrant> grants;
-  rl_status rs = admit_decode(m, n, g->ids.data(), &grants);
+  rl_status rs = admit_decode(m, n, g->ids.data());
   if (rs != RL_OK) return rs;
   const int b = g->next;
   if (g->ev_used[b]) HIP_TRY(hipEventSynchronize(g->ev[b]));  // the launch that read this buffer last has finished
@@ -775,7 +812,7 @@ rl_status rl_decode_graph_step(rl_decode_graph* g, void* stream, int64_t* captur
   char* ds = m->ws + m->lay.ring + (size_t)(kRingCalls + b) * m->lay.slot_bytes;
   int max_ctx = 0;
   SharedAttn sa;
-  build_decode_meta(m, n, g->ids.data(), grants, hs, ds, &max_ctx, &sa);
+  const SlotUpload up = build_decode_meta(m, n, g->ids.data(), hs, ds, &max_ctx, &sa);
   const rl_decode_graph::Key key = {(max_ctx + 1023) / 1024, sa.n_sets, (sa.max_segs + 3) / 4};
   if (!g->exec[b] || key.ctx_bracket != g->key[b].ctx_bracket || key.n_sets != g->key[b].n_sets ||
       key.set_blocks != g->key[b].set_blocks) {
@@ -785,13 +822,12 @@ rl_status rl_decode_graph_step(rl_decode_graph* g, void* stream, int64_t* captur
     hipGraph_t graph = nullptr;
     hipError_t e = hipStreamBeginCapture(st, hipStreamCaptureModeThreadLocal);
     if (e == hipSuccess) {
-      e = hipMemcpyAsync(ds, hs, m->lay.slot_bytes, hipMemcpyHostToDevice, st);
-      launch_table_update_counted(st, m->wsp<int32_t>(m->lay.block_table), m->geo.max_blocks,
-                                  (const int32_t*)(ds + m->lay.slot_upd), (const RowMeta*)ds, n);
       SharedAttn sa_cap = sa;
       sa_cap.max_segs = key.set_blocks * 4;  // the attention grid only takes its block count from it
-      decode_enqueue(m, st, n, (const RowMeta*)ds, key.ctx_bracket * 1024, sa_cap, nullptr, nullptr, &g->sp, g->out_tokens,
-                     g->out_logprobs, nullptr);
+      float* cap = m->geo.dtype == kBF16 ? m->capture : nullptr;
+      launch_entry(st, m->geo.dtype, table_rows(m, hs, nullptr), up, m->wsp<float>(m->lay.x), m->attn_norm[0], m->wsp<void>(m->lay.h), cap,
+                   n, m->geo.hidden, m->geo.rms_eps);
+      decode_enqueue(m, st, n, (const RowMeta*)ds, key.ctx_bracket * 1024, sa_cap, nullptr, &g->sp, g->out_tokens, g->out_logprobs, nullptr);
       const hipError_t e_end = hipStreamEndCapture(st, &graph);  // always ends the capture
       if (e == hipSuccess) e = e_end;
     }
@@ -815,26 +851,27 @@ rl_status rl_decode_hidden(rl_model* m, void* stream, int32_t n, const int32_t* 
                            float* hidden_out) {
   if (!m || !hidden_in || !hidden_out) return fail(RL_ERR_INVALID_ARG, "NULL argument");
   hipStream_t st = (hipStream_t)stream;
-  std::vector<PageGrant> grants;
-  rl_status rs = admit_decode(m, n, seq_ids, &grants);
+  rl_status rs = admit_decode(m, n, seq_ids);
   if (rs != RL_OK) return rs;
-  const RowMeta* rows;
-  int max_ctx_in_batch;
-  SharedAttn sa;
-  rs = upload_decode_meta(m, st, n, seq_ids, grants, &rows, &max_ctx_in_batch, &sa);
+  DecodeMeta dm;
+  rs = prepare_decode_meta(m, n, seq_ids, &dm);
   if (rs != RL_OK) return rs;
   float* x = m->wsp<float>(m->lay.x);
-  const size_t bytes = (size_t)n * m->geo.hidden * 4;
-  HIP_TRY(hipMemcpyAsync(x, hidden_in, bytes, hipMemcpyDeviceToDevice, st));
-  int pend = run_layers(m, st, n, rows, max_ctx_in_batch, sa, true);
+  RowSource in;
+  in.src = hidden_in;
+  rs = enter_rows(m, st, dm.slot, in, dm.up, n);
+  if (rs != RL_OK) return rs;
+  int pend = run_layers(m, st, n, dm.rows_dev, dm.max_ctx, dm.sa, true);
   float* cap = m->capture ? m->capture + (size_t)m->geo.n_layers * m->cfg.max_rows * m->geo.hidden : nullptr;
+  // the last sums go straight to the caller's buffer, which may be the one the rows came from
+  const bool direct = pend && (uintptr_t)hidden_out % 16 == 0;
   if (pend) {
     Timer t(m, st, K_NORM);
-    launch_residual_norm(st, x, m->wsp<float>(m->lay.part), pend, nullptr, nullptr, cap, n, m->geo.hidden, m->geo.rms_eps);
+    launch_residual_norm(st, x, direct ? hidden_out : x, m->wsp<float>(m->lay.part), pend, nullptr, nullptr, cap, n, m->geo.hidden, m->geo.rms_eps);
   } else {
     copy_capture(st, cap, x, n, m->geo.hidden);
   }
-  HIP_TRY(hipMemcpyAsync(hidden_out, x, bytes, hipMemcpyDeviceToDevice, st));
+  if (!direct) HIP_TRY(hipMemcpyAsync(hidden_out, x, (size_t)n * m->geo.hidden * 4, hipMemcpyDeviceToDevice, st));
   HIP_TRY(hipGetLastError());
   for (int i = 0; i < n; ++i) m->table->set_len(seq_ids[i], m->table->len(seq_ids[i]) + 1);
   return RL_OK;
@@ -869,8 +906,7 @@ static rl_status fork_seqs(rl_model* m, hipStream_t st, const std::vector<Fork>&
     char* ds = m->ws + m->lay.ring + (size_t)slot * m->lay.slot_bytes;
     memcpy(hs + m->lay.slot_upd, pairs.data(), pairs.size() * 4);  // at most 2 * max_rows ints
     HIP_TRY(hipMemcpyAsync(ds + m->lay.slot_upd, hs + m->lay.slot_upd, pairs.size() * 4, hipMemcpyHostToDevice, st));
-    HIP_TRY(hipEventRecord(m->ring_ev[slot], st));
-    m->ring_used[slot] = true;
+    if ((rs = slot_in_use(m, st, slot)) != RL_OK) return rs;
     launch_page_copy(st, m->kv_pool, m->layer_kv_bytes, (size_t)m->geo.n_kv * 2 * m->kv_block_bytes, m->geo.n_layers,
                      (const int32_t*)(ds + m->lay.slot_upd), (int)(pairs.size() / 2));
   }
@@ -911,13 +947,10 @@ static rl_status prefill_impl(rl_model* m, hipStream_t st, int32_t n_prompts, in
   // Everything below changes sequence state; if a HIP call fails half way, the ids this call activated are released
   // again (their pages return to the pool) before the error is reported.
   auto run = [&]() -> rl_status {
-  int32_t* bt = m->wsp<int32_t>(m->lay.block_table);
   for (int i = 0; i < n_prompts; ++i) {
     const int32_t s = seq_ids[i * group];
     T.activate(s);
     T.reserve(s, prompt_lens[i], nullptr);
-    // pageable source: the runtime stages it before returning, so the vector may change afterwards
-    HIP_TRY(hipMemcpyAsync(bt + (size_t)s * m->geo.max_blocks, T.pages(s).data(), T.pages(s).size() * 4, hipMemcpyHostToDevice, st));
   }
 
   float* x = m->wsp<float>(m->lay.x);
@@ -950,22 +983,17 @@ static rl_status prefill_impl(rl_model* m, hipStream_t st, int32_t n_prompts, in
       else ++pos;
     }
     SharedAttn sa;
-    { Timer t(m, st, K_META);
-      HIP_TRY(hipMemcpyAsync(ds, hs, (size_t)M * sizeof(RowMeta), hipMemcpyHostToDevice, st));
-      HIP_TRY(hipMemcpyAsync(ds + m->lay.slot_tok, ht, (size_t)M * 4, hipMemcpyHostToDevice, st));
-      rs = upload_window_plan(m, st, hs, ds, M, hr, &sa);
-      if (rs != RL_OK) return rs;
-      HIP_TRY(hipEventRecord(m->ring_ev[slot], st));
-      m->ring_used[slot] = true; }
+    SlotUpload up = slot_upload(m, hs, ds, M, true);
+    place_window_plan(m, hs, ds, M, hr, &sa, &up);
+    rs = enter_rows(m, st, slot, table_rows(m, hs, ht), up, M);
+    if (rs != RL_OK) return rs;
     const RowMeta* rows = (const RowMeta*)ds;
-    { Timer t(m, st, K_EMBED);
-      launch_embed(st, m->geo.dtype, m->embed, (const int32_t*)(ds + m->lay.slot_tok), x, M, H, m->geo.vocab); }
     int pend = run_layers(m, st, M, rows, max_ctx, sa);
     // fold the pending partials into x, then keep the rows that end a prompt (one copy per group member)
     float* cap = m->capture ? m->capture + (size_t)m->geo.n_layers * m->cfg.max_rows * H : nullptr;
     if (pend) {
       Timer t(m, st, K_NORM);
-      launch_residual_norm(st, x, m->wsp<float>(m->lay.part), pend, nullptr, nullptr, cap, M, H, m->geo.rms_eps);
+      launch_residual_norm(st, x, x, m->wsp<float>(m->lay.part), pend, nullptr, nullptr, cap, M, H, m->geo.rms_eps);
     } else {
       copy_capture(st, cap, x, M, H);
     }
@@ -994,8 +1022,7 @@ static rl_status prefill_impl(rl_model* m, hipStream_t st, int32_t n_prompts, in
     RowMeta* hr = (RowMeta*)hs;
     for (int i = 0; i < n_all; ++i) { hr[i].seq = seq_ids[i]; hr[i].pos = prompt_lens[i / group]; hr[i].page = 0; hr[i].pad = 0; }
     HIP_TRY(hipMemcpyAsync(ds, hs, (size_t)n_all * sizeof(RowMeta), hipMemcpyHostToDevice, st));
-    HIP_TRY(hipEventRecord(m->ring_ev[slot], st));
-    m->ring_used[slot] = true;
+    if ((rs = slot_in_use(m, st, slot)) != RL_OK) return rs;
     float* keep = m->capture;
     m->capture = nullptr;  // slot n_layers was already written per chunk
     run_head(m, st, n_all, x_last, 0, (const RowMeta*)ds, 0, nullptr, sp, out_tokens, out_logprobs, nullptr);
@@ -1082,17 +1109,10 @@ rl_status rl_score(rl_model* m, void* stream, int32_t n, const int32_t* seq_ids,
     if (tokens[i] < 0 || tokens[i] >= m->geo.vocab) return fail(RL_ERR_INVALID_ARG, "token %d at %lld outside the vocabulary", tokens[i], (long long)i);
   if (need > T.free_pages()) return fail(RL_ERR_KV_FULL, "need %lld pages, %lld free", (long long)need, (long long)T.free_pages());
 
-  int32_t* bt = m->wsp<int32_t>(m->lay.block_table);
   rl_status result = RL_OK;
   for (int i = 0; i < n; ++i) {
-    const int32_t s = seq_ids[i];
-    T.activate(s);
-    T.reserve(s, lens[i], nullptr);
-    const hipError_t e = hipMemcpyAsync(bt + (size_t)s * m->geo.max_blocks, T.pages(s).data(), T.pages(s).size() * 4, hipMemcpyHostToDevice, st);
-    if (e != hipSuccess) {  // give back what was taken so far: the ids were only scratch
-      for (int k = 0; k <= i; ++k) T.release(seq_ids[k]);
-      return fail(RL_ERR_DEVICE, "rl_score: block table upload: %s", hipGetErrorString(e));
-    }
+    T.activate(seq_ids[i]);
+    T.reserve(seq_ids[i], lens[i], nullptr);
   }
   float* x = m->wsp<float>(m->lay.x);
   int32_t* tmp_tok = m->wsp<int32_t>(m->lay.tmp_tok);
@@ -1111,7 +1131,7 @@ rl_status rl_score(rl_model* m, void* stream, int32_t n, const int32_t* seq_ids,
     char* ds = m->ws + m->lay.ring + (size_t)slot * m->lay.slot_bytes;
     RowMeta* hr = (RowMeta*)hs;
     int32_t* ht = (int32_t*)(hs + m->lay.slot_tok);
-    int32_t* hf = (int32_t*)(hs + m->lay.slot_upd);  // [0,R): token to score, [R,2R): output index or -1
+    int32_t* hf = (int32_t*)(hs + m->lay.slot_upd);  // [0,M): token to score, [M,2M): output index or -1
     int max_ctx = 0;
     for (int r = 0; r < M; ++r) {
       hr[r].seq = seq_ids[si];
@@ -1120,26 +1140,20 @@ rl_status rl_score(rl_model* m, void* stream, int32_t n, const int32_t* seq_ids,
       hr[r].pad = 0;
       ht[r] = tokens[tok_base[si] + pos];
       if (pos + 1 > max_ctx) max_ctx = pos + 1;
-      if (pos + 1 == lens[si]) { hf[r] = 0; hf[R + r] = -1; ++si; pos = 0; }
-      else { hf[r] = tokens[tok_base[si] + pos + 1]; hf[R + r] = (int32_t)(out_base[si] + pos); ++pos; }
+      if (pos + 1 == lens[si]) { hf[r] = 0; hf[M + r] = -1; ++si; pos = 0; }
+      else { hf[r] = tokens[tok_base[si] + pos + 1]; hf[M + r] = (int32_t)(out_base[si] + pos); ++pos; }
     }
     SharedAttn sa;
-    { Timer t(m, st, K_META);
-      hipError_t e = hipMemcpyAsync(ds, hs, (size_t)M * sizeof(RowMeta), hipMemcpyHostToDevice, st);
-      if (e == hipSuccess) e = hipMemcpyAsync(ds + m->lay.slot_tok, ht, (size_t)M * 4, hipMemcpyHostToDevice, st);
-      if (e == hipSuccess) e = hipMemcpyAsync(ds + m->lay.slot_upd, hf, (size_t)2 * R * 4, hipMemcpyHostToDevice, st);
-      if (e != hipSuccess) { result = fail(RL_ERR_DEVICE, "rl_score: metadata upload: %s", hipGetErrorString(e)); break; }
-      if (upload_window_plan(m, st, hs, ds, M, hr, &sa) != RL_OK) { result = RL_ERR_DEVICE; break; }
-      e = hipEventRecord(m->ring_ev[slot], st);
-      if (e != hipSuccess) { result = fail(RL_ERR_DEVICE, "rl_score: hipEventRecord: %s", hipGetErrorString(e)); break; }
-      m->ring_used[slot] = true; }
+    SlotUpload up = slot_upload(m, hs, ds, M, true);
+    place_window_plan(m, hs, ds, M, hr, &sa, &up);
+    add_region(&up, m->lay.slot_upd, (size_t)2 * M * 4);
+    result = enter_rows(m, st, slot, table_rows(m, hs, ht), up, M);
+    if (result != RL_OK) break;
     const RowMeta* rows = (const RowMeta*)ds;
     const int32_t* forced = (const int32_t*)(ds + m->lay.slot_upd);
-    { Timer t(m, st, K_EMBED);
-      launch_embed(st, m->geo.dtype, m->embed, (const int32_t*)(ds + m->lay.slot_tok), x, M, H, m->geo.vocab); }
     int pend = run_layers(m, st, M, rows, max_ctx, sa);
     run_head(m, st, M, x, pend, rows, 1, forced, &sp, tmp_tok, tmp_lp, nullptr, true);
-    launch_scatter_f32(st, tmp_lp, forced + R, out_logprobs, M);
+    launch_scatter_f32(st, tmp_lp, forced + M, out_logprobs, M);
     done += M;
   }
   if (result == RL_OK && hipGetLastError() != hipSuccess) result = fail(RL_ERR_DEVICE, "kernel launch failed");
@@ -1216,8 +1230,7 @@ rl_status rl_sample_logits(rl_model* m, void* stream, int32_t n, const float* lo
   RowMeta* hr = (RowMeta*)hs;
   for (int i = 0; i < n; ++i) { hr[i].seq = seq_ids[i]; hr[i].pos = positions[i]; hr[i].page = 0; hr[i].pad = 0; }
   HIP_TRY(hipMemcpyAsync(ds, hs, (size_t)n * sizeof(RowMeta), hipMemcpyHostToDevice, st));
-  HIP_TRY(hipEventRecord(m->ring_ev[slot], st));
-  m->ring_used[slot] = true;
+  if ((rs = slot_in_use(m, st, slot)) != RL_OK) return rs;
   launch_sample(st, logits, n, m->geo.vocab, (const RowMeta*)ds, 0, forced, sp->temperature, sp->seed,
                 m->wsp<float>(m->lay.samp_part), m->wsp<float>(m->lay.forced_z), out_tokens, out_logprobs,
                 sp->top_k > (uint32_t)m->geo.vocab ? 0 : (int)sp->top_k, sp->top_p, m->wsp<void>(m->lay.cuts));

@@ -1,5 +1,7 @@
-// Embedding gather, residual + RMSNorm, per-head norm + rotary + KV append, KV import, weight packing.
+// First kernel of a call, residual + RMSNorm, per-head norm + rotary + KV append, KV import, weight packing.
 // These move little data per step; they are written for few launches and simple indexing.
+#include <algorithm>
+
 #include "device_utils.h"
 #include "kernels.h"
 #include "rope_device.h"
@@ -7,25 +9,55 @@
 namespace rl {
 
 // ------------------------------------------------------------------------------------------------
-// Embedding gather (rollout step "x = E[token]").
+// First kernel of a call: the call's metadata slot (rows, tokens, attention plan) moves from pinned host memory to the
+// device, new pages are entered in the block table, and the rows enter the residual stream (from the embedding table or
+// from the caller's buffer) and, in bf16 models, the first layer's RMSNorm.
+//
+// Each of these used to be a launch of its own: a copy of the slot (a blit kernel, 2 to 4 us), the table update, the
+// copy of the caller's rows and the norm are a chain in which every link costs a launch and at least one round trip to
+// memory.  Here a few leading blocks read the slot while the others work on their rows.  Together with the last copy (the
+// sums behind the last layer go straight to the caller's buffer) and one event per twelve calls instead of per call: one
+// layer on one row 109.9 -> 99.5 us, on 64 rows 205.0 -> 194.0, on 512 rows 492 -> 463.
 // ------------------------------------------------------------------------------------------------
-template <typename T>
-__global__ __launch_bounds__(256) void embed_kernel(const T* __restrict__ E, const int32_t* __restrict__ tok,
-                                                    float* __restrict__ x, int H, int V, const RowMeta* __restrict__ rows,
-                                                    const int32_t* __restrict__ last_tok) {
-  const int r = blockIdx.x;
-  const int fed = tok != nullptr ? tok[r] : last_tok[rows[r].seq];
-  const int t = min(max(fed, 0), V - 1);  // ids come from device memory the host cannot inspect
-  const size_t base = (size_t)t * H;
-  for (int i = threadIdx.x; i < H; i += 256) x[(size_t)r * H + i] = load_as_float(E, base + i);
+__device__ __forceinline__ void upload_slot(const SlotUpload& u, int first, int stride) {
+  const int total = u.n_rows + u.n[0] + u.n[1] + u.n[2];
+  for (int i = first; i < total; i += stride) {
+    int at = i, left = i - u.n_rows;
+    if (left >= 0) {
+#pragma unroll
+      for (int k = 0; k < 3; ++k) {
+        if (left >= 0 && left < u.n[k]) at = u.at[k] + left;
+        left -= u.n[k];
+      }
+    }
+    const uint4 v = u.src[at];
+    u.dst[at] = v;
+    // A row at the first position of a page names that page (RowMeta: seq, pos, page): its block-table entry.  Every page
+    // a sequence grows into gets its first row before any row reads it, so this is all the table needs.
+    if (i < u.n_rows && u.block_table && (v.y & (kPageTokens - 1)) == 0) u.block_table[(size_t)v.x * u.max_blocks + (v.y >> 4)] = (int32_t)v.z;
+  }
 }
 
-void launch_embed(hipStream_t s, int dtype, const void* embed, const int32_t* tokens, float* x, int M, int H, int V,
-                  const RowMeta* rows, const int32_t* last_tok) {
-  if (dtype == kBF16)
-    embed_kernel<uint16_t><<<M, 256, 0, s>>>((const uint16_t*)embed, tokens, x, H, V, rows, last_tok);
-  else
-    embed_kernel<float><<<M, 256, 0, s>>>((const float*)embed, tokens, x, H, V, rows, last_tok);
+// Token of row r: read by one lane per block, because the tokens of a prompt (and the rows of a step that feeds itself) lie in host memory.
+__device__ __forceinline__ int fetch_token(const RowSource& in, int r, int* shared) {
+  if (threadIdx.x == 0) {
+    const int fed = in.tokens != nullptr ? in.tokens[r] : in.last_tok[in.rows[r].seq];
+    *shared = min(max(fed, 0), in.V - 1);  // ids come from device memory the host cannot inspect
+  }
+  __syncthreads();
+  return *shared;
+}
+
+template <typename T>
+__global__ __launch_bounds__(256) void entry_rows_kernel(RowSource in, SlotUpload up, int up_blocks, float* __restrict__ x, int H) {
+  __shared__ int token;
+  if ((int)blockIdx.x < up_blocks) {
+    upload_slot(up, blockIdx.x * 256 + threadIdx.x, up_blocks * 256);
+    return;
+  }
+  const int r = blockIdx.x - up_blocks;
+  const size_t base = (size_t)(in.from_table ? fetch_token(in, r, &token) : r) * H;
+  for (int i = threadIdx.x; i < H; i += 256) x[(size_t)r * H + i] = load_as_float((const T*)in.src, base + i);
 }
 
 // ------------------------------------------------------------------------------------------------
@@ -34,14 +66,24 @@ void launch_embed(hipStream_t s, int dtype, const void* embed, const int32_t* to
 // partials of the preceding projection are summed in a fixed order, so results do not depend on the batch.  bf16 models
 // only: fp32 projections normalise their rows and add to the residual stream themselves.
 // ------------------------------------------------------------------------------------------------
-// gain: H bf16 gains; without a norm (has_gain = 0) any readable H-element array.
-__global__ __launch_bounds__(1024) void residual_norm_kernel(float* __restrict__ x, const float* __restrict__ part,
+// SRC 0: x = xi + split sums;  1: the rows of a call from the caller's fp32 buffer;  2: from the embedding table (bf16).
+// The last two are the first kernel of a call: x is always written, and leading blocks move the metadata slot.
+// xo may be xi.  gain: H bf16 gains; without a norm (has_gain = 0) any readable H-element array.
+template <int SRC>
+__global__ __launch_bounds__(1024) void residual_norm_kernel(const float* xi, float* xo, const float* __restrict__ part,
                                                              int S, size_t split_stride, const void* __restrict__ gain,
                                                              int has_gain, void* __restrict__ h_out,
-                                                             float* __restrict__ capture, int H, float eps) {
+                                                             float* __restrict__ capture, int H, float eps, RowSource in,
+                                                             SlotUpload up, int up_blocks) {
   __shared__ float red[16];
-  const int r = blockIdx.x, nthr = blockDim.x;
-  float* xr = x + (size_t)r * H;
+  __shared__ int token;
+  const int nthr = blockDim.x;
+  if (SRC > 0 && (int)blockIdx.x < up_blocks) {
+    upload_slot(up, blockIdx.x * nthr + threadIdx.x, up_blocks * nthr);
+    return;
+  }
+  const int r = SRC > 0 ? (int)blockIdx.x - up_blocks : (int)blockIdx.x;
+  const float* xr = xi + (size_t)r * H;
   float ss = 0.f;
   constexpr int kMaxPass = 2;  // H <= 1024 threads * 4 * kMaxPass, checked by the host
   float4 keep[kMaxPass];
@@ -54,18 +96,24 @@ __global__ __launch_bounds__(1024) void residual_norm_kernel(float* __restrict__
     const int ig = i0 < H ? i0 : 0;  // unconditional loads (a branch here costs a wait); `gain` is always readable
     graw[pass] = *(const uint2*)((const uint16_t*)gain + ig);
   }
+  const uint16_t* er = SRC == 2 ? (const uint16_t*)in.src + (size_t)fetch_token(in, r, &token) * H : nullptr;
 #pragma unroll
   for (int pass = 0; pass < kMaxPass; ++pass) {
     const int i0 = (pass * nthr + threadIdx.x) * 4;
     float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
     if (i0 < H) {
-      v = *(const float4*)(xr + i0);
+      if (SRC == 2) {
+        const uint2 e = *(const uint2*)(er + i0);
+        v = make_float4(bf2f(e.x & 0xffffu), bf2f(e.x >> 16), bf2f(e.y & 0xffffu), bf2f(e.y >> 16));
+      } else {
+        v = *(const float4*)(xr + i0);
+      }
 #pragma unroll 4
       for (int sp = 0; sp < S; ++sp) {
         const float4 p = *(const float4*)(part + sp * split_stride + (size_t)r * H + i0);
         v.x += p.x; v.y += p.y; v.z += p.z; v.w += p.w;
       }
-      if (S > 0) *(float4*)(xr + i0) = v;
+      if (SRC > 0 || S > 0) *(float4*)(xo + (size_t)r * H + i0) = v;
       if (capture) *(float4*)(capture + (size_t)r * H + i0) = v;
     }
     keep[pass] = v;
@@ -92,14 +140,34 @@ __global__ __launch_bounds__(1024) void residual_norm_kernel(float* __restrict__
   }
 }
 
-void launch_residual_norm(hipStream_t s, float* x, const float* part, int S, const void* gain,
+static int norm_threads(int H) { return std::min(((H / 4 + 63) / 64) * 64, 1024); }
+
+void launch_residual_norm(hipStream_t s, const float* x_in, float* x_out, const float* part, int S, const void* gain,
                           void* h_out, float* capture, int M, int H, float eps) {
-  size_t stride = (size_t)M * H;
-  int threads = ((H / 4 + 63) / 64) * 64;
-  if (threads > 1024) threads = 1024;
   const int has_gain = gain != nullptr;
-  const void* g = has_gain ? gain : x;  // read and ignored without a norm
-  residual_norm_kernel<<<M, threads, 0, s>>>(x, part, S, stride, g, has_gain, h_out, capture, H, eps);
+  const void* g = has_gain ? gain : x_in;  // read and ignored without a norm
+  residual_norm_kernel<0><<<M, norm_threads(H), 0, s>>>(x_in, x_out, part, S, (size_t)M * H, g, has_gain, h_out, capture, H, eps,
+                                                       RowSource{}, SlotUpload{}, 0);
+}
+
+void launch_entry(hipStream_t s, int dtype, const RowSource& in, const SlotUpload& up, float* x, const void* gain, void* h_out,
+                  float* capture, int M, int H, float eps) {
+  const int words = up.n_rows + up.n[0] + up.n[1] + up.n[2];
+  // The fused kernel reads 16 bytes of an fp32 row or 8 of a table row at a time; the caller's buffer or a table that is
+  // not aligned to that goes element by element, and a norm of its own follows.
+  const bool fused = dtype == kBF16 && (uintptr_t)in.src % (in.from_table ? 8 : 16) == 0;
+  if (!fused) {
+    const int up_blocks = (words + 255) / 256;
+    if (in.from_table && dtype == kBF16) entry_rows_kernel<uint16_t><<<M + up_blocks, 256, 0, s>>>(in, up, up_blocks, x, H);
+    else entry_rows_kernel<float><<<M + up_blocks, 256, 0, s>>>(in, up, up_blocks, x, H);
+    if (dtype == kBF16) launch_residual_norm(s, x, x, nullptr, 0, gain, h_out, capture, M, H, eps);
+    return;
+  }
+  const int threads = norm_threads(H), up_blocks = (words + threads - 1) / threads;
+  if (in.from_table)
+    residual_norm_kernel<2><<<M + up_blocks, threads, 0, s>>>(nullptr, x, nullptr, 0, 0, gain, 1, h_out, capture, H, eps, in, up, up_blocks);
+  else
+    residual_norm_kernel<1><<<M + up_blocks, threads, 0, s>>>((const float*)in.src, x, nullptr, 0, 0, gain, 1, h_out, capture, H, eps, in, up, up_blocks);
 }
 
 // One wave per (row, head), four heads per block.  Lane i < d/2 owns the rotary pair (i, i + d/2).
@@ -279,33 +347,6 @@ __global__ __launch_bounds__(256) void pack_weight_kernel(const uint4* __restric
 void launch_pack_weight_bf16(hipStream_t s, const void* src, void* dst, int N, int K, int seg) {
   size_t total = (size_t)N * (K >> 3);
   pack_weight_kernel<<<(unsigned)((total + 255) / 256), 256, 0, s>>>((const uint4*)src, (uint4*)dst, N, K, seg);
-}
-
-}  // namespace rl
-
-namespace rl {
-
-__global__ void table_update_kernel(int32_t* __restrict__ bt, int max_blocks, const int32_t* __restrict__ upd, int n) {
-  const int i = blockIdx.x * 64 + threadIdx.x;
-  if (i < n) bt[(size_t)upd[3 * i] * max_blocks + upd[3 * i + 1]] = upd[3 * i + 2];
-}
-
-void launch_table_update(hipStream_t s, int32_t* block_table, int max_blocks, const int32_t* upd, int n) {
-  if (n <= 0) return;
-  table_update_kernel<<<(n + 63) / 64, 64, 0, s>>>(block_table, max_blocks, upd, n);
-}
-
-// The same with the number of entries read on the device (rows[0].pad), for launches whose shape must not depend
-// on it: a grid for n_max entries, of which the first rows[0].pad are applied.
-__global__ void table_update_counted_kernel(int32_t* __restrict__ bt, int max_blocks, const int32_t* __restrict__ upd,
-                                            const RowMeta* __restrict__ rows) {
-  const int i = blockIdx.x * 64 + threadIdx.x;
-  if (i < rows[0].pad) bt[(size_t)upd[3 * i] * max_blocks + upd[3 * i + 1]] = upd[3 * i + 2];
-}
-
-void launch_table_update_counted(hipStream_t s, int32_t* block_table, int max_blocks, const int32_t* upd,
-                                 const RowMeta* rows, int n_max) {
-  table_update_counted_kernel<<<(n_max + 63) / 64, 64, 0, s>>>(block_table, max_blocks, upd, rows);
 }
 
 }  // namespace rl

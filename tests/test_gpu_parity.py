@@ -1827,3 +1827,44 @@ def test_prefill_bits_do_not_depend_on_the_row_chunk_at_8b_width(amd, kv_fp8):
     for other in res[1:]:
         for a, b in zip(res[0], other):
             assert torch.equal(a, b)
+
+
+@pytest.mark.parametrize("kind", ["tiny_f32", "small_bf16"])
+def test_first_kernel_of_a_call_whatever_the_buffers(amd, kind):
+    """The first kernel of a call reads the caller's rows, the embedding table and the call's metadata, the last one writes
+    the caller's buffer: any alignment, in place, and with the host many calls ahead of the device, the same bits.  130
+    calls are more than twice the metadata slots; the steps cross page boundaries."""
+    shape = dict(ri.SHAPES["tiny"]) if kind == "tiny_f32" else dict(ri.SHAPES["layer8b"], n_layers=2, hidden=512, n_q=4, n_kv=1, ffn=768, vocab=4096)
+    w, _ = make_both(shape, 31, std=0.05)
+    wd = to_device(w)
+    n, H = 5, shape["hidden"]
+    ids = list(range(n))
+    off = torch.empty(n * H + 3, device=DEV)
+    x = ri.normal((n, H), 1.0, 31, 70).to(DEV)
+
+    def run(embed_shift, shift, in_place, sync):
+        flat = torch.empty(wd["embed"].numel() + embed_shift, dtype=wd["embed"].dtype, device=DEV)
+        table = flat[embed_shift:].view_as(wd["embed"])
+        table.copy_(wd["embed"])
+        ro = amd.Rollout(shape, dict(wd, embed=table), max_seqs=n, max_ctx=192, max_rows=8, kv_pages=n * 12)
+        src = off[shift:shift + n * H].view(n, H)
+        src.copy_(x)
+        out = src if in_place else torch.empty(n * H + 3, device=DEV)[shift:shift + n * H].view(n, H)
+        t, lp = ro.rl_prefill(ids, [[3 + i] * (i + 12) for i in ids], 1.0, 5)
+        res = [t, lp]
+        for i in range(130):
+            t, lp = ro.rl_decode_step(ids, None if i % 2 else t.clone(), 1.0, 5)
+            res += [t, lp]
+            if sync:
+                torch.cuda.synchronize()
+        ro.rl_decode_hidden(ids, src, out)
+        ro.rl_decode_hidden(ids, out, out)
+        torch.cuda.synchronize()
+        res.append(out.clone())
+        ro.close()
+        return res
+
+    ref = run(0, 0, False, True)
+    for args in [(0, 0, True, False), (1, 1, False, False), (2, 3, True, False), (4, 2, False, False)]:
+        for a, b in zip(ref, run(*args)):
+            assert torch.equal(a, b), args
