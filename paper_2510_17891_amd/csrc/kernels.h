@@ -50,13 +50,14 @@ __host__ __device__ inline size_t weight_offset(int r, int k, int k_blocks, int 
 
 // ---- elementwise / small kernels (both dtypes) -------------------------------------------------
 // What the first kernel of a call moves from the pinned slot of the call to its slot in the workspace, in units of 16
-// bytes: the rows from the start of the slot, then up to three more regions.  block_table (may be null): rows at the
+// bytes: the rows from the start of the slot, then up to kSlotRegions more regions.  block_table (may be null): rows at the
 // first position of a page are entered there.
+constexpr int kSlotRegions = 5;
 struct SlotUpload {
   const uint4* src = nullptr;  // host memory, read by the kernel: may be rewritten once the kernel has finished
   uint4* dst = nullptr;
   int n_rows = 0;
-  int at[3] = {0, 0, 0}, n[3] = {0, 0, 0};
+  int at[kSlotRegions] = {}, n[kSlotRegions] = {};
   int32_t* block_table = nullptr;
   int max_blocks = 0;
 };
@@ -79,8 +80,14 @@ void launch_entry(hipStream_t s, int dtype, const RowSource& in, const SlotUploa
 // bf16 models: x_out[r] = x_in[r] + sum_{s<S} part[s][r][:] (x_out may be x_in and is not written when S == 0; part may
 // then be null);  capture (may be null) gets that row;  if gain != null, h = row * rsqrt(mean(row^2)+eps) * gain written
 // as f16 fragment-major.  x_in, x_out 16-byte aligned.
+// group > 1: the M rows are the rows r / group of x_in and part (which then hold M / group rows); x_out is another buffer.
 void launch_residual_norm(hipStream_t s, const float* x_in, float* x_out, const float* part, int S, const void* gain,
-                          void* h_out, float* capture, int M, int H, float eps);
+                          void* h_out, float* capture, int M, int H, float eps, int group = 1);
+
+// For the n pairs (row, slot): x_out[slot] = x[row] (H floats), q_out[slot] = q[row] (D floats).
+void launch_put_aside(hipStream_t s, const int32_t* pairs, int n, const float* x, float* x_out, int H, const float* q, float* q_out, int D);
+// out[r] = in[r / group], M rows of H floats.
+void launch_repeat_rows(hipStream_t s, const float* in, float* out, int M, int H, int group);
 
 // Sum the split partials of the QKV projection, apply per-head RMSNorm (q,k) and the rotation (q,k) at
 // each row's position, write q as fp32 [M][n_q][d] and append k,v to the row's KV page (rows[r].page).
@@ -93,10 +100,16 @@ void launch_qk_rope_append(hipStream_t s, const Geometry& g, const float* qkv_pa
 void launch_kv_import(hipStream_t s, const Geometry& g, const void* k_src, const void* v_src, int first_pos, int n_tokens,
                       const int32_t* block_table_row, void* k_pool_layer, void* v_pool_layer);
 
-// Copy whole KV pages (all layers): pool byte layout [layer][page][page_bytes]; pairs = n x (src page, dst page)
-// in device memory.
-void launch_page_copy(hipStream_t s, void* kv_pool, size_t layer_bytes, size_t page_bytes, int n_layers,
-                      const int32_t* pairs, int n_pairs);
+// Sequences that continue others: the first `full` block-table entries of dst become those of src, and with page >= 0 the
+// source's next page (partly filled) is copied, in all layers, into `page`, which becomes dst's next entry.  Pool byte
+// layout [layer][page][page_bytes].  The descriptors travel as kernel arguments.
+constexpr int kForkBatch = 128;
+struct ForkBatch {
+  struct One { int32_t src, dst, full, page; } f[kForkBatch];
+  int n;
+};
+void launch_fork(hipStream_t s, const ForkBatch& batch, int32_t* block_table, int max_blocks, void* kv_pool, size_t layer_bytes,
+                 size_t page_bytes, int n_layers);
 
 // ---- attention -----------------------------------------------------------------------------------
 // bf16, head_dim 128: decode attention over paged KV (MFMA), one block per (row, kv head), context cut into

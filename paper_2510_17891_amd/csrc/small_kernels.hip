@@ -19,13 +19,19 @@ namespace rl {
 // sums behind the last layer go straight to the caller's buffer) and one event per twelve calls instead of per call: one
 // layer on one row 109.9 -> 99.5 us, on 64 rows 205.0 -> 194.0, on 512 rows 492 -> 463.
 // ------------------------------------------------------------------------------------------------
+__host__ __device__ inline int slot_units(const SlotUpload& u) {
+  int n = u.n_rows;
+  for (int k = 0; k < kSlotRegions; ++k) n += u.n[k];
+  return n;
+}
+
 __device__ __forceinline__ void upload_slot(const SlotUpload& u, int first, int stride) {
-  const int total = u.n_rows + u.n[0] + u.n[1] + u.n[2];
+  const int total = slot_units(u);
   for (int i = first; i < total; i += stride) {
     int at = i, left = i - u.n_rows;
     if (left >= 0) {
 #pragma unroll
-      for (int k = 0; k < 3; ++k) {
+      for (int k = 0; k < kSlotRegions; ++k) {
         if (left >= 0 && left < u.n[k]) at = u.at[k] + left;
         left -= u.n[k];
       }
@@ -66,24 +72,25 @@ __global__ __launch_bounds__(256) void entry_rows_kernel(RowSource in, SlotUploa
 // partials of the preceding projection are summed in a fixed order, so results do not depend on the batch.  bf16 models
 // only: fp32 projections normalise their rows and add to the residual stream themselves.
 // ------------------------------------------------------------------------------------------------
-// SRC 0: x = xi + split sums;  1: the rows of a call from the caller's fp32 buffer;  2: from the embedding table (bf16).
-// The last two are the first kernel of a call: x is always written, and leading blocks move the metadata slot.
+// SRC 0: x = xi + split sums, 3: the same with row r from row r / group;  1: the rows of a call from the caller's fp32 buffer;  2: from the embedding table (bf16).
+// 1 and 2 are the first kernel of a call: x is always written, and leading blocks move the metadata slot.
 // xo may be xi.  gain: H bf16 gains; without a norm (has_gain = 0) any readable H-element array.
 template <int SRC>
 __global__ __launch_bounds__(1024) void residual_norm_kernel(const float* xi, float* xo, const float* __restrict__ part,
                                                              int S, size_t split_stride, const void* __restrict__ gain,
                                                              int has_gain, void* __restrict__ h_out,
                                                              float* __restrict__ capture, int H, float eps, RowSource in,
-                                                             SlotUpload up, int up_blocks) {
+                                                             SlotUpload up, int up_blocks, int group) {
   __shared__ float red[16];
   __shared__ int token;
   const int nthr = blockDim.x;
-  if (SRC > 0 && (int)blockIdx.x < up_blocks) {
+  constexpr bool kEntry = SRC == 1 || SRC == 2;
+  if (kEntry && (int)blockIdx.x < up_blocks) {
     upload_slot(up, blockIdx.x * nthr + threadIdx.x, up_blocks * nthr);
     return;
   }
-  const int r = SRC > 0 ? (int)blockIdx.x - up_blocks : (int)blockIdx.x;
-  const float* xr = xi + (size_t)r * H;
+  const int r = kEntry ? (int)blockIdx.x - up_blocks : (int)blockIdx.x, ri = SRC == 3 ? r / group : r;
+  const float* xr = xi + (size_t)ri * H;
   float ss = 0.f;
   constexpr int kMaxPass = 2;  // H <= 1024 threads * 4 * kMaxPass, checked by the host
   float4 keep[kMaxPass];
@@ -110,10 +117,10 @@ __global__ __launch_bounds__(1024) void residual_norm_kernel(const float* xi, fl
       }
 #pragma unroll 4
       for (int sp = 0; sp < S; ++sp) {
-        const float4 p = *(const float4*)(part + sp * split_stride + (size_t)r * H + i0);
+        const float4 p = *(const float4*)(part + sp * split_stride + (size_t)ri * H + i0);
         v.x += p.x; v.y += p.y; v.z += p.z; v.w += p.w;
       }
-      if (SRC > 0 || S > 0) *(float4*)(xo + (size_t)r * H + i0) = v;
+      if (kEntry || S > 0) *(float4*)(xo + (size_t)r * H + i0) = v;
       if (capture) *(float4*)(capture + (size_t)r * H + i0) = v;
     }
     keep[pass] = v;
@@ -143,16 +150,19 @@ __global__ __launch_bounds__(1024) void residual_norm_kernel(const float* xi, fl
 static int norm_threads(int H) { return std::min(((H / 4 + 63) / 64) * 64, 1024); }
 
 void launch_residual_norm(hipStream_t s, const float* x_in, float* x_out, const float* part, int S, const void* gain,
-                          void* h_out, float* capture, int M, int H, float eps) {
+                          void* h_out, float* capture, int M, int H, float eps, int group) {
   const int has_gain = gain != nullptr;
   const void* g = has_gain ? gain : x_in;  // read and ignored without a norm
-  residual_norm_kernel<0><<<M, norm_threads(H), 0, s>>>(x_in, x_out, part, S, (size_t)M * H, g, has_gain, h_out, capture, H, eps,
-                                                       RowSource{}, SlotUpload{}, 0);
+  const size_t stride = (size_t)(M / group) * H;
+  if (group > 1)
+    residual_norm_kernel<3><<<M, norm_threads(H), 0, s>>>(x_in, x_out, part, S, stride, g, has_gain, h_out, capture, H, eps, RowSource{}, SlotUpload{}, 0, group);
+  else
+    residual_norm_kernel<0><<<M, norm_threads(H), 0, s>>>(x_in, x_out, part, S, stride, g, has_gain, h_out, capture, H, eps, RowSource{}, SlotUpload{}, 0, 1);
 }
 
 void launch_entry(hipStream_t s, int dtype, const RowSource& in, const SlotUpload& up, float* x, const void* gain, void* h_out,
                   float* capture, int M, int H, float eps) {
-  const int words = up.n_rows + up.n[0] + up.n[1] + up.n[2];
+  const int words = slot_units(up);
   // The fused kernel reads 16 bytes of an fp32 row or 8 of a table row at a time; the caller's buffer or a table that is
   // not aligned to that goes element by element, and a norm of its own follows.
   const bool fused = dtype == kBF16 && (uintptr_t)in.src % (in.from_table ? 8 : 16) == 0;
@@ -165,9 +175,29 @@ void launch_entry(hipStream_t s, int dtype, const RowSource& in, const SlotUploa
   }
   const int threads = norm_threads(H), up_blocks = (words + threads - 1) / threads;
   if (in.from_table)
-    residual_norm_kernel<2><<<M + up_blocks, threads, 0, s>>>(nullptr, x, nullptr, 0, 0, gain, 1, h_out, capture, H, eps, in, up, up_blocks);
+    residual_norm_kernel<2><<<M + up_blocks, threads, 0, s>>>(nullptr, x, nullptr, 0, 0, gain, 1, h_out, capture, H, eps, in, up, up_blocks, 1);
   else
-    residual_norm_kernel<1><<<M + up_blocks, threads, 0, s>>>((const float*)in.src, x, nullptr, 0, 0, gain, 1, h_out, capture, H, eps, in, up, up_blocks);
+    residual_norm_kernel<1><<<M + up_blocks, threads, 0, s>>>((const float*)in.src, x, nullptr, 0, 0, gain, 1, h_out, capture, H, eps, in, up, up_blocks, 1);
+}
+
+__global__ __launch_bounds__(256) void put_aside_kernel(const int32_t* __restrict__ pairs, const float* __restrict__ x, float* __restrict__ x_out,
+                                                       int H, const float* __restrict__ q, float* __restrict__ q_out, int D) {
+  const size_t from = pairs[2 * blockIdx.x], to = pairs[2 * blockIdx.x + 1];
+  for (int i = threadIdx.x; i < H; i += 256) x_out[to * H + i] = x[from * H + i];
+  for (int i = threadIdx.x; i < D; i += 256) q_out[to * D + i] = q[from * D + i];
+}
+
+void launch_put_aside(hipStream_t s, const int32_t* pairs, int n, const float* x, float* x_out, int H, const float* q, float* q_out, int D) {
+  if (n > 0) put_aside_kernel<<<n, 256, 0, s>>>(pairs, x, x_out, H, q, q_out, D);
+}
+
+__global__ __launch_bounds__(256) void repeat_rows_kernel(const float* __restrict__ in, float* __restrict__ out, int H, int group) {
+  const size_t r = blockIdx.x;
+  for (int i = threadIdx.x; i < H; i += 256) out[r * H + i] = in[r / group * H + i];
+}
+
+void launch_repeat_rows(hipStream_t s, const float* in, float* out, int M, int H, int group) {
+  repeat_rows_kernel<<<M, 256, 0, s>>>(in, out, H, group);
 }
 
 // One wave per (row, head), four heads per block.  Lane i < d/2 owns the rotary pair (i, i + d/2).
@@ -353,21 +383,28 @@ void launch_pack_weight_bf16(hipStream_t s, const void* src, void* dst, int N, i
 
 namespace rl {
 
-// grid: x = layer, y = pair.  Copies one page (all kv heads, K and V: contiguous inside a layer) with 16-byte accesses.
-__global__ __launch_bounds__(256) void page_copy_kernel(char* __restrict__ pool, size_t layer_bytes, size_t page_bytes,
-                                                        const int32_t* __restrict__ pairs) {
-  const int32_t src = pairs[2 * blockIdx.y], dst = pairs[2 * blockIdx.y + 1];
+// grid: x = layer (its copy of the partial page), then one more for the block-table row; y = fork.
+__global__ __launch_bounds__(256) void fork_kernel(ForkBatch batch, int32_t* __restrict__ bt, int max_blocks, char* __restrict__ pool,
+                                                   size_t layer_bytes, size_t page_bytes, int n_layers) {
+  const ForkBatch::One f = batch.f[blockIdx.y];
+  const int32_t* from = bt + (size_t)f.src * max_blocks;
+  if ((int)blockIdx.x == n_layers) {
+    int32_t* to = bt + (size_t)f.dst * max_blocks;
+    for (int b = threadIdx.x; b < f.full; b += 256) to[b] = from[b];
+    if (threadIdx.x == 0 && f.page >= 0) to[f.full] = f.page;
+    return;
+  }
+  if (f.page < 0) return;
   char* base = pool + (size_t)blockIdx.x * layer_bytes;
-  const uint4* s = (const uint4*)(base + (size_t)src * page_bytes);
-  uint4* d = (uint4*)(base + (size_t)dst * page_bytes);
+  const uint4* s = (const uint4*)(base + (size_t)from[f.full] * page_bytes);
+  uint4* d = (uint4*)(base + (size_t)f.page * page_bytes);
+#pragma unroll 4
   for (size_t i = threadIdx.x; i < page_bytes / 16; i += 256) d[i] = s[i];
 }
 
-void launch_page_copy(hipStream_t s, void* kv_pool, size_t layer_bytes, size_t page_bytes, int n_layers,
-                      const int32_t* pairs, int n_pairs) {
-  if (n_pairs <= 0) return;
-  dim3 grid(n_layers, n_pairs);
-  page_copy_kernel<<<grid, 256, 0, s>>>((char*)kv_pool, layer_bytes, page_bytes, pairs);
+void launch_fork(hipStream_t s, const ForkBatch& batch, int32_t* block_table, int max_blocks, void* kv_pool, size_t layer_bytes,
+                 size_t page_bytes, int n_layers) {
+  fork_kernel<<<dim3(n_layers + 1, batch.n), 256, 0, s>>>(batch, block_table, max_blocks, (char*)kv_pool, layer_bytes, page_bytes, n_layers);
 }
 
 }  // namespace rl

@@ -1868,3 +1868,42 @@ def test_first_kernel_of_a_call_whatever_the_buffers(amd, kind):
     for args in [(0, 0, True, False), (1, 1, False, False), (2, 3, True, False), (4, 2, False, False)]:
         for a, b in zip(ref, run(*args)):
             assert torch.equal(a, b), args
+
+
+@pytest.mark.parametrize("kind", ["tiny_f32", "small_bf16"])
+def test_prompt_ends_of_many_chunks_and_forks_beyond_one_launch(amd, kind):
+    """Prompts that end inside, at the edge of and one row into a chunk, with one token, and with full and partial last
+    pages: their rows pass the end of the last layer together, with the same bits as when every prompt is a call of its
+    own and when the layer boundaries are captured.  140 forks are more than one launch takes."""
+    shape = dict(ri.SHAPES["tiny"]) if kind == "tiny_f32" else dict(ri.SHAPES["layer8b"], n_layers=2, hidden=512, n_q=4, n_kv=1, ffn=768, vocab=4096)
+    w, _ = make_both(shape, 37, std=0.05)
+    wd = to_device(w)
+    lens = [16, 1, 15, 33, 48, 2]  # chunks of 32 rows
+    prompts = [ri.tokens((n,), shape["vocab"], 37, 800 + i).tolist() for i, n in enumerate(lens)]
+
+    def run(how):
+        ro = amd.Rollout(shape, wd, max_seqs=160, max_ctx=96, max_rows=32 if how != "single" else 160, kv_pages=600)
+        if how == "captured":
+            ro.rl_set_capture(True)
+        g = 3
+        ids = list(range(len(lens) * g))
+        if how == "single":
+            parts = [ro.rl_prefill_groups(ids[i * g:i * g + g], g, [p], 1.0, 5) for i, p in enumerate(prompts)]
+            out = [torch.cat([p[k] for p in parts]) for k in (0, 1)]
+        else:
+            out = list(ro.rl_prefill_groups(ids, g, prompts, 1.0, 5))
+        for _ in range(3):
+            out += list(ro.rl_decode_step(ids, None, 1.0, 5))
+        if how == "single":  # forks of a sequence with a partial last page: they all go on as it does
+            logits = torch.empty(141, shape["vocab"], device=DEV)
+            ro.rl_seq_fork(3 * g, list(range(18, 158)))
+            ro.rl_decode_step([3 * g] + list(range(18, 158)), torch.full((141,), 7, dtype=torch.int32, device=DEV), 0.0, 5, debug_logits=logits)
+            assert torch.equal(logits, logits[:1].expand_as(logits))
+        torch.cuda.synchronize()
+        ro.close()
+        return out
+
+    ref = run("single")
+    for how in ("together", "captured"):
+        for a, b in zip(ref, run(how)):
+            assert torch.equal(a, b), how
