@@ -38,6 +38,15 @@
 // keys are read once per set instead of once per row.  Up to four segments (1024 keys) are merged by the set's own block,
 // one wave per segment: at 1024 rows the merge launch (20 us) and 68 MB of partials written and read back are gone.
 //
+// What the rows of sets have left behind the shared segments is often one segment, i.e. work for one wave.  In large
+// launches these segments are packed four to a block, one per wave (plan_packs): a layer of 128 rows with 1024 of 1100
+// keys shared 182 -> 167 us, of 512 rows 462 -> 443; with two or three segments left no faster and no slower.
+// A block of a short context spends as long on its way to the first step as on its steps.  So the first step's keys are
+// requested before the queries are formed, the queries lie in LDS with a stride that spreads 16 columns over the banks, one
+// split is not loaded four times over, segment bounds take no divisions, and a step exists in three copies instead of five
+// (every block runs most of this kernel once, from a cold instruction cache).  Together, per launch: 16.4 -> 15.1 us at 32
+// rows of 1025 keys (a 36-layer step 3981 -> 3917), 128-row wave 818 -> 810 (layer), 256 fp8 rows 931 -> 921.
+//
 // Decode steps (one row per sequence) run the variant that also does what would otherwise be a kernel of its own
 // before this one: it sums the QKV projection's split partials, normalises and rotates the heads of its columns, and
 // appends the row's new key and value to the cache.  The only consumer of a row's new key and value inside the launch
@@ -66,6 +75,8 @@ constexpr int kPartStride = kD + 2;           // floats per (row, head, segment)
 // side by side.
 __device__ __forceinline__ size_t part_o(int max_segs, int seg) { return (size_t)seg * kD; }
 __device__ __forceinline__ size_t part_ml(int max_segs, int seg) { return (size_t)max_segs * kD + 2 * (size_t)seg; }
+constexpr int kQStride = kD + 4;              // floats per column of the queries in LDS: 16 columns read at once hit different banks
+constexpr int kPackPages = 32;                // room for the page list of a wave of a pack
 constexpr int kLdsSegs = 16;                  // contexts up to 4096 keep their segment partials in LDS
 
 constexpr int kPairU4(bool kv8) { return kv8 ? 2 * kPageElems / 16 : 2 * kPageElems / 8; }  // 16-byte units of one (page, kv head): K and V
@@ -78,20 +89,29 @@ struct PagePair {
   u32x4_t v[2][4];  // [page a|b][jj]: dims 32jj..32jj+31 (two 16-dim blocks) x this lane's 4 keys
 };
 
-__device__ __forceinline__ void load_pair(PagePair& pp, const u32x4_t* kbase, const u32x4_t* vbase, int64_t page_a,
-                                          int64_t page_b, int n_kv, int lane) {
-  // per layer the pool is [page][kv head][K | V]: the K and V blocks of a (page, head) are adjacent
-  const size_t oa = (size_t)page_a * n_kv * (2 * kPageElems / 8) + lane;
-  const size_t ob = (size_t)page_b * n_kv * (2 * kPageElems / 8) + lane;
+// Per layer the pool is [page][kv head][K | V]: the K and V blocks of a (page, head) are adjacent.  A step reads those of
+// two pages, the same for the whole wave, as two buffers (scalar base, the lane's offset, a constant); a buffer of no
+// bytes (past = true) costs no traffic, which keeps the loads of the pipeline unconditional.
+template <bool KV8>
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t pair_of(const u32x4_t* kbase, int page, int n_kv, bool past) {
+  const u32x4_t* p = kbase + (size_t)(unsigned)page * (unsigned)(n_kv * kPairU4(KV8));
+  return __builtin_amdgcn_make_buffer_rsrc((void*)p, 0, past ? 0 : kPairU4(KV8) * 16, 0x00020000);
+}
+__device__ __forceinline__ u32x4_t load16_nt(__amdgpu_buffer_rsrc_t r, unsigned voff, unsigned soff) {
+  return __builtin_bit_cast(u32x4_t, __builtin_amdgcn_raw_buffer_load_b128(r, voff, soff, 2 /* non-temporal */));
+}
+
+__device__ __forceinline__ void load_pair(PagePair& pp, const u32x4_t* kbase, int page_a, int page_b, int n_kv, unsigned lane, bool past) {
+  const auto ra = pair_of<false>(kbase, page_a, n_kv, past), rb = pair_of<false>(kbase, page_b, n_kv, past);
 #pragma unroll
   for (int s = 0; s < 4; ++s) {
-    pp.k[0][s] = __builtin_nontemporal_load(kbase + oa + s * 64);
-    pp.k[1][s] = __builtin_nontemporal_load(kbase + ob + s * 64);
+    pp.k[0][s] = load16_nt(ra, lane * 16 + s * 1024, 0);
+    pp.k[1][s] = load16_nt(rb, lane * 16 + s * 1024, 0);
   }
 #pragma unroll
   for (int s = 0; s < 4; ++s) {
-    pp.v[0][s] = __builtin_nontemporal_load(vbase + oa + s * 64);
-    pp.v[1][s] = __builtin_nontemporal_load(vbase + ob + s * 64);
+    pp.v[0][s] = load16_nt(ra, lane * 16 + s * 1024, 2 * kPageElems);
+    pp.v[1][s] = load16_nt(rb, lane * 16 + s * 1024, 2 * kPageElems);
   }
 }
 
@@ -101,19 +121,17 @@ struct PagePair8 {
   u32x4_t v[2][2];  // [page a|b][J]: word 2*(jj&1) + par = this lane's 4 keys of dim 32jj + 16par + dl, jj = 2J + (jj&1)
 };
 
-__device__ __forceinline__ void load_pair(PagePair8& pp, const u32x4_t* kbase, const u32x4_t* vbase, int64_t page_a,
-                                          int64_t page_b, int n_kv, int lane) {
-  const size_t oa = (size_t)page_a * n_kv * kPairU4(true) + lane;
-  const size_t ob = (size_t)page_b * n_kv * kPairU4(true) + lane;
+__device__ __forceinline__ void load_pair(PagePair8& pp, const u32x4_t* kbase, int page_a, int page_b, int n_kv, unsigned lane, bool past) {
+  const auto ra = pair_of<true>(kbase, page_a, n_kv, past), rb = pair_of<true>(kbase, page_b, n_kv, past);
 #pragma unroll
   for (int c = 0; c < 2; ++c) {
-    pp.k[0][c] = __builtin_nontemporal_load(kbase + oa + c * 64);
-    pp.k[1][c] = __builtin_nontemporal_load(kbase + ob + c * 64);
+    pp.k[0][c] = load16_nt(ra, lane * 16 + c * 1024, 0);
+    pp.k[1][c] = load16_nt(rb, lane * 16 + c * 1024, 0);
   }
 #pragma unroll
   for (int c = 0; c < 2; ++c) {
-    pp.v[0][c] = __builtin_nontemporal_load(vbase + oa + c * 64);
-    pp.v[1][c] = __builtin_nontemporal_load(vbase + ob + c * 64);
+    pp.v[0][c] = load16_nt(ra, lane * 16 + c * 1024, kPageElems);
+    pp.v[1][c] = load16_nt(rb, lane * 16 + c * 1024, kPageElems);
   }
 }
 
@@ -161,12 +179,30 @@ __device__ __forceinline__ void widen(PagePair& out, const PagePair8& in) {
 // launch; the partials and their merge do not depend on it).
 __host__ __device__ inline int attn_num_splits(int n_seg, int spb) { return n_seg <= kLdsSegs ? 1 : (n_seg + spb - 1) / spb; }
 
+// attn_seg_begin with the division as a multiplication: exact, since sgm * n_it <= 256 * 2048 and m exceeds 2^32 / n_seg by
+// less than one.
+struct SegBounds {
+  unsigned n_it, m;
+  __device__ __forceinline__ SegBounds(int n_it_, int n_seg) : n_it(n_it_), m(0xffffffffu / (unsigned)n_seg + 1) {}
+  __device__ __forceinline__ int begin(int sgm) const { return (int)__umulhi((unsigned)sgm * n_it, m); }
+};
+// Bit c: segment c (c < n_seg <= kLdsSegs) has keys.  Only contexts of fewer than four steps leave some without.
+__device__ __forceinline__ unsigned segs_with_keys(int n_it, int n_seg) {
+  unsigned mask = (1u << n_seg) - 1;
+  if (n_it < n_seg) {  // n_seg is four then
+    for (int c = 0; c < 4; ++c)
+      if (attn_seg_begin(c + 1, n_it, 4) == attn_seg_begin(c, n_it, 4)) mask &= ~(1u << c);
+  }
+  return mask;
+}
+
 // Flat merge of the (at most kLdsSegs) segments of one head: running maximum, weights exp(m_c - M), sums in index
 // order; the lane owns dims 2*lane, 2*lane+1.  o_ptr(c) -> O(128), ml_ptr(c) -> (max, sum) of segment c (LDS or
 // workspace); all loads are issued before the arithmetic.  Returns the two normalised outputs packed as f16 (the operand type
 // of the output projection).
 template <typename F, typename G>
 __device__ __forceinline__ uint32_t merge_short(F o_ptr, G ml_ptr, int n_seg, int n_it, int lane) {
+  const unsigned with_keys = segs_with_keys(n_it, n_seg);
   float mx[kLdsSegs], lx[kLdsSegs];
   float2 vx[kLdsSegs];
 #pragma unroll
@@ -174,7 +210,7 @@ __device__ __forceinline__ uint32_t merge_short(F o_ptr, G ml_ptr, int n_seg, in
     mx[c] = -INFINITY;  // marks an absent or empty segment (nothing was written for it)
     lx[c] = 0.f;
     vx[c] = make_float2(0.f, 0.f);
-    if (c < n_seg && attn_seg_begin(c + 1, n_it, n_seg) != attn_seg_begin(c, n_it, n_seg)) {
+    if (with_keys >> c & 1) {
       const float* pm = ml_ptr(c);
       mx[c] = pm[0];
       lx[c] = pm[1];
@@ -240,13 +276,20 @@ __global__ __launch_bounds__(256, KV8 ? 3 : 2) void attn_decode_bf16_kernel(cons
   const bool is_set = (int)blockIdx.y >= n_rows;  // block-uniform
   // column c of the matrix operand: member c / group of the set (the row itself in a row block), head c % group.
   // Lane (j, g) holds column j and, in a set of more than 16 columns, column j + 16 of a second operand as well.
-  int r, n_members = 1, skip = 0, shared_segs = 0;
+  // A pack's columns are the heads of its (up to four) rows like those of a set, and every wave multiplies its own row's
+  // keys by all of them and uses its row's columns: row, context and segments are then those of the wave.
+  const int uw = __builtin_amdgcn_readfirstlane(wave);  // lets the compiler see what is the same for the whole wave
+  int r, n_members = 1, skip = 0, shared_segs = 0, pack_seg = 0;
   int col_row[2];
+  bool is_pack = false;  // block-uniform
   if (is_set) {
     const AttnShared* sh = shared + (blockIdx.y - n_rows);
     n_members = sh->n_rows;
     shared_segs = sh->n_segs;
-    r = sh->rows[0];
+    is_pack = shared_segs == 0;
+    if (is_pack && (blockIdx.z > 0 || n_members == 0)) return;  // block-uniform
+    r = __builtin_amdgcn_readfirstlane(sh->rows[is_pack ? uw : 0]);
+    pack_seg = __builtin_amdgcn_readfirstlane(sh->rows[kAttnPackSegs + uw]);
 #pragma unroll
     for (int c = 0; c < 2; ++c) {
       const int mj = (j + 16 * c) / group;
@@ -259,18 +302,23 @@ __global__ __launch_bounds__(256, KV8 ? 3 : 2) void attn_decode_bf16_kernel(cons
   }
   const int n_cols = n_members * group;   // <= 32 (fp8 pages: <= 16)
   const bool wide = !KV8 && n_cols > 16;  // block-uniform: the set fills a second group of 16 columns
-  const bool col_valid[2] = {j < n_cols, j + 16 < n_cols};
+  const bool col_there = j < n_cols;
+  const bool col_valid[2] = {col_there && (!is_pack || j / group == wave), j + 16 < n_cols};
   const int col_head[2] = {hk * group + j % group, hk * group + (j + 16) % group};
   const RowMeta rm = rows[r];
   const int ctx = rm.pos + 1;  // keys 0..pos; the row's own key is in its page already, or (APPEND) formed here
   // A set's members may stand at different positions of one 32-key window (rows of one sequence): same steps and
   // segments, and each column is masked at its own length.  r is the member with the longest context.
-  const int ctx_col[2] = {is_set ? rows[col_row[0]].pos + 1 : ctx, is_set ? rows[col_row[1]].pos + 1 : ctx};
+  const bool own_ctx = is_set && !is_pack;
+  const int ctx_col[2] = {own_ctx ? rows[col_row[0]].pos + 1 : ctx, own_ctx ? rows[col_row[1]].pos + 1 : ctx};
   const int n_seg = attn_num_segments(ctx);
   const bool in_lds = !is_set && skip == 0 && n_seg <= kLdsSegs;  // merged by this block
   // this block's segments [lo, hi)
   int lo, hi;
-  if (is_set) {
+  if (is_pack) {
+    lo = pack_seg;
+    hi = pack_seg + (uw < n_members ? 1 : 0);
+  } else if (is_set) {
     lo = blockIdx.z * 4;
     hi = min(lo + 4, shared_segs);
   } else {
@@ -279,34 +327,61 @@ __global__ __launch_bounds__(256, KV8 ? 3 : 2) void attn_decode_bf16_kernel(cons
     lo = max((int)blockIdx.z * per, skip);
     hi = min((int)blockIdx.z * per + per, n_seg);
   }
-  if (lo >= hi) return;  // block-uniform: nothing left for this block
+  if (!is_pack && lo >= hi) return;  // block-uniform: nothing left for this block
   const int n_blk = (ctx + 15) >> 4;
   const int n_it = (ctx + 31) >> 5;  // 32-key steps
-  auto seg_begin = [&](int sgm) { return attn_seg_begin(sgm, n_it, n_seg); };
+  const SegBounds bounds(n_it, n_seg);
+  auto seg_begin = [&](int sgm) { return bounds.begin(sgm); };
   // A set that covers every segment of its rows (neighbouring rows of one sequence) and has them all in this block, one
   // per wave, is merged here: the partials stay in registers until the waves are done, then meet in LDS.
   const bool set_merges = !APPEND && is_set && shared_segs == n_seg && n_seg <= 4;  // block-uniform
-  int seg = lo + (wave * (hi - lo)) / 4;  // contiguous, balanced share of the block's segments
+  int seg = is_pack ? lo : lo + (uw * (hi - lo)) / 4;  // contiguous, balanced share of the block's segments
   const int first_seg = seg;
-  const int seg_end = lo + ((wave + 1) * (hi - lo)) / 4;
+  const int seg_end = is_pack ? hi : lo + ((uw + 1) * (hi - lo)) / 4;
   const int it_begin = seg_begin(seg), it_end = seg_begin(seg_end);
   const u32x4_t* kb = k_pool + (size_t)hk * kPairU4(KV8);
-  const u32x4_t* vb = v_pool + (size_t)hk * kPairU4(KV8);
+  // Entry n_blk duplicates the last page (odd page counts).  A wave of a pack has a list of its own, of the (at most 18)
+  // pages of its segment.
+  const int page0 = is_pack ? uw * kPackPages - 2 * it_begin : 0;
+  const int32_t* const bt = block_table + (size_t)rm.seq * max_blocks;
+  // The keys and values of the wave's first step are requested before the queries are formed: their pages are looked up
+  // directly, and they arrive while the queries are summed, normalised and rotated (a wave without steps asks for what
+  // its neighbour asks for).  The list's first 256 entries are requested before them and stored behind them, so that
+  // nothing in between waits for the keys; for the same reason the barriers up to the first step order LDS alone.
+  const int first_a = __builtin_amdgcn_readfirstlane(bt[min(2 * it_begin, n_blk - 1)]);
+  const int first_b = __builtin_amdgcn_readfirstlane(bt[min(2 * it_begin + 1, n_blk - 1)]);
+  const int page_early = bt[min(is_pack ? 2 * it_begin + lane : (int)threadIdx.x, n_blk - 1)];
+  auto put_pages = [&]() __attribute__((always_inline)) {
+    if (is_pack) {
+      if (lane < kPackPages) pages[uw * kPackPages + lane] = page_early;
+    } else {
+      if ((int)threadIdx.x <= n_blk) pages[threadIdx.x] = page_early;
+      for (int i = threadIdx.x + 256; i <= n_blk; i += 256) pages[i] = bt[min(i, n_blk - 1)];
+    }
+  };
+  auto lds_barrier = []() __attribute__((always_inline)) {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+    __builtin_amdgcn_s_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+  };
+  typedef typename std::conditional<KV8, PagePair8, PagePair>::type Buf;  // registers of a step as loaded
+  Buf pa;
   if (!APPEND) {
-    for (int i = threadIdx.x; i <= n_blk; i += 256)  // entry n_blk duplicates the last page (odd page counts)
-      pages[i] = block_table[(size_t)rm.seq * max_blocks + (i < n_blk ? i : n_blk - 1)];
+    load_pair(pa, kb, first_a, first_b, n_kv, lane, false);
+    __builtin_amdgcn_sched_barrier(0);
+    put_pages();
   }
 
   // ---- APPEND: queries of this block's columns into LDS, the row's new key and value for the appending wave ----
   bool appends = false;  // wave-uniform: this wave owns the row's last step and with it the new key and value
   float* const lds_part = (float*)(pages + lds_part_offset);
-  float* const lds_q = (float*)(pages + lds_q_offset);  // [16 columns][128], APPEND only
-  // A set block keeps no partials in LDS; in a wide one that area holds the queries of columns 16.. ([16][128],
+  float* const lds_q = (float*)(pages + lds_q_offset);  // [16 columns][kQStride], APPEND only
+  // A set block keeps no partials in LDS; in a wide one that area holds the queries of columns 16.. ([16][kQStride],
   // APPEND only) and behind them the q operands of both column groups ([group][hi | lo][matrix-core step][lane]):
   // with two accumulators per lane there are no registers left for them.
   float* const lds_q1 = lds_part;
-  u32x4_t* const lds_qopw = (u32x4_t*)(lds_part + 16 * kD);
-  uint16_t* const lds_new = (uint16_t*)(lds_q + 16 * kD);  // the row's new key [128] and value [128] as bf16, APPEND only
+  u32x4_t* const lds_qopw = (u32x4_t*)(lds_part + 16 * kQStride);
+  uint16_t* const lds_new = (uint16_t*)(lds_q + 16 * kQStride) + (is_pack ? wave * 2 * kD : 0);  // the row's new key [128] and value [128] as bf16, APPEND only
   // KV8: the q operand lives in LDS ([hi | lo][matrix-core step][lane], 8 KiB) instead of 32 registers per lane, which
   // lets three blocks share a compute unit.  It takes the place of the fp32 queries once those have been read.
   u32x4_t* const lds_qop = (u32x4_t*)lds_q;
@@ -327,10 +402,17 @@ __global__ __launch_bounds__(256, KV8 ? 3 : 2) void attn_decode_bf16_kernel(cons
       const int c = m & 1 ? set_rows[5] : set_rows[4], d = m & 1 ? set_rows[7] : set_rows[6];
       return m & 4 ? (m & 2 ? d : c) : (m & 2 ? b : a);
     };
-    const int uw = __builtin_amdgcn_readfirstlane(wave);  // lets the compiler see that the task choice is per wave
-    appends = !is_set && hi == n_seg && uw == 3;
+    appends = hi == n_seg && (is_pack ? uw < n_members : !is_set && uw == 3);
     const int n_tot = (n_q + 2 * n_kv) * kD;
-    float2 cs = ap.rope[(size_t)rm.pos * (kD / 2) + lane];  // the rows of a set have one position
+    float2 cs = ap.rope[(size_t)rm.pos * (kD / 2) + lane];
+    float2 cs_q[4] = {cs, cs, cs, cs};  // the rows of a set have one position, those of a pack each their own
+    if (is_pack) {
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        const int m = min((uw + 4 * u) / group, n_members - 1);
+        cs_q[u] = ap.rope[(size_t)rows[member_row(m)].pos * (kD / 2) + lane];
+      }
+    }
     uint32_t gq0 = 0, gq1 = 0, gk0 = 0, gk1 = 0;            // gains as stored (bf16)
     if (ap.q_gain) { gq0 = ((const uint16_t*)ap.q_gain)[lane]; gq1 = ((const uint16_t*)ap.q_gain)[lane + kD / 2]; }
     HeadPairLoads lq[4] = {}, lk = {}, lv = {};  // slots without a task stay zero
@@ -350,8 +432,19 @@ __global__ __launch_bounds__(256, KV8 ? 3 : 2) void attn_decode_bf16_kernel(cons
       head_pair_issue(lv, row_part + (size_t)(n_q + n_kv + hk) * kD, ap.S, ap.split_stride, kD, lane);
       if (ap.k_gain) { gk0 = ((const uint16_t*)ap.k_gain)[lane]; gk1 = ((const uint16_t*)ap.k_gain)[lane + kD / 2]; }
     }
-    for (int i = threadIdx.x; i <= n_blk; i += 256)  // entry n_blk duplicates the last page (odd page counts)
-      pages[i] = block_table[(size_t)rm.seq * max_blocks + (i < n_blk ? i : n_blk - 1)];
+    HeadPairLoads lw[4] = {};
+    if (wide) {  // block-uniform: the columns 16.. of a wide set
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        const int t = 16 + uw + 4 * u;
+        if (t < n_cols)
+          head_pair_issue(lw[u], ap.qkv_part + (size_t)member_row(t / group) * n_tot + (size_t)(hk * group + t % group) * kD, ap.S,
+                          ap.split_stride, kD, lane);
+      }
+    }
+    __builtin_amdgcn_sched_barrier(0);
+    load_pair(pa, kb, first_a, first_b, n_kv, lane, false);
+    __builtin_amdgcn_sched_barrier(0);
     // Everything loaded above is first touched below this line: the empty statements keep the compiler from moving
     // the arithmetic (and with it the waits) up between the loads.
     asm volatile("" : "+v"(cs.x), "+v"(cs.y), "+v"(gq0), "+v"(gq1), "+v"(gk0), "+v"(gk1));
@@ -361,7 +454,7 @@ __global__ __launch_bounds__(256, KV8 ? 3 : 2) void attn_decode_bf16_kernel(cons
 #pragma unroll
     for (int u = 0; u < 4; ++u) {
       hold(lq[u]);
-      hp[u].cs = cs; hp[u].g0 = bf2f(gq0); hp[u].g1 = bf2f(gq1);
+      hp[u].cs = cs_q[u]; hp[u].g0 = bf2f(gq0); hp[u].g1 = bf2f(gq1);
       head_pair_sum(hp[u], lq[u], ap.S);
     }
     hold(lk);
@@ -385,8 +478,8 @@ __global__ __launch_bounds__(256, KV8 ? 3 : 2) void attn_decode_bf16_kernel(cons
     for (int u = 0; u < 4; ++u) {
       const int t = uw + 4 * u;
       if (t < n_cols) {
-        lds_q[t * kD + lane] = hp[u].v0;
-        lds_q[t * kD + kD / 2 + lane] = hp[u].v1;
+        lds_q[t * kQStride + lane] = hp[u].v0;
+        lds_q[t * kQStride + kD / 2 + lane] = hp[u].v1;
       }
     }
     if (appends) {  // the new key and value, rounded, wait in LDS for this wave's last step
@@ -405,15 +498,7 @@ __global__ __launch_bounds__(256, KV8 ? 3 : 2) void attn_decode_bf16_kernel(cons
         lds_new[kD + lane + kD / 2] = (uint16_t)f2bf(hv.v1);
       }
     }
-    if (wide) {  // block-uniform: the same for the columns 16.. of a wide set, in the same arithmetic
-      HeadPairLoads lw[4] = {};
-#pragma unroll
-      for (int u = 0; u < 4; ++u) {
-        const int t = 16 + uw + 4 * u;
-        if (t < n_cols)
-          head_pair_issue(lw[u], ap.qkv_part + (size_t)member_row(t / group) * n_tot + (size_t)(hk * group + t % group) * kD, ap.S,
-                          ap.split_stride, kD, lane);
-      }
+    if (wide) {  // the same for its columns, in the same arithmetic
       HeadPair hw[4];
 #pragma unroll
       for (int u = 0; u < 4; ++u) {
@@ -426,12 +511,13 @@ __global__ __launch_bounds__(256, KV8 ? 3 : 2) void attn_decode_bf16_kernel(cons
       for (int u = 0; u < 4; ++u) {
         const int t = uw + 4 * u;  // column 16 + t
         if (16 + t < n_cols) {
-          lds_q1[t * kD + lane] = hw[u].v0;
-          lds_q1[t * kD + kD / 2 + lane] = hw[u].v1;
+          lds_q1[t * kQStride + lane] = hw[u].v0;
+          lds_q1[t * kQStride + kD / 2 + lane] = hw[u].v1;
         }
       }
     }
-    __syncthreads();  // pages[] and the queries are in LDS
+    put_pages();
+    lds_barrier();  // pages[] and the queries are in LDS
   }
 
   // ---- q operand: hi/lo bf16 split; columns beyond the set are zero -------------------------------
@@ -453,22 +539,22 @@ __global__ __launch_bounds__(256, KV8 ? 3 : 2) void attn_decode_bf16_kernel(cons
   };
   u32x4_t q_hi[KV8 ? 1 : 4], q_lo[KV8 ? 1 : 4];  // KV8: the step this wave builds for the block
   {
-    const float* qh = APPEND ? lds_q + j * kD : q + ((size_t)col_row[0] * n_q + col_head[0]) * kD;
+    const float* qh = APPEND ? lds_q + j * kQStride : q + ((size_t)col_row[0] * n_q + col_head[0]) * kD;
     if constexpr (KV8) {
-      split_q(qh, col_valid[0], wave, q_hi[0], q_lo[0]);  // one step per wave, shared through LDS
+      split_q(qh, col_there, wave, q_hi[0], q_lo[0]);  // one step per wave, shared through LDS
     } else {
 #pragma unroll
-      for (int s = 0; s < 4; ++s) split_q(qh, col_valid[0], s, q_hi[s], q_lo[s]);
+      for (int s = 0; s < 4; ++s) split_q(qh, col_there, s, q_hi[s], q_lo[s]);
     }
   }
   if constexpr (KV8) {
-    if (APPEND) __syncthreads();  // every wave has read the fp32 queries that the operand overwrites
+    if (APPEND) lds_barrier();  // every wave has read the fp32 queries that the operand overwrites
     lds_qop[wave * 64 + lane] = q_hi[0];
     lds_qop[256 + wave * 64 + lane] = q_lo[0];
   }
   if constexpr (!KV8) {
     if (wide) {  // both groups' operands go through LDS, wave w storing step w
-      const float* qh = APPEND ? lds_q1 + j * kD : q + ((size_t)col_row[1] * n_q + col_head[1]) * kD;
+      const float* qh = APPEND ? lds_q1 + j * kQStride : q + ((size_t)col_row[1] * n_q + col_head[1]) * kD;
       u32x4_t w_hi, w_lo;
       split_q(qh, col_valid[1], wave, w_hi, w_lo);
       const u32x4_t h0 = wave == 0 ? q_hi[0] : wave == 1 ? q_hi[1] : wave == 2 ? q_hi[2] : q_hi[3];
@@ -479,12 +565,11 @@ __global__ __launch_bounds__(256, KV8 ? 3 : 2) void attn_decode_bf16_kernel(cons
       lds_qopw[768 + wave * 64 + lane] = w_lo;
     }
   }
-  if (!APPEND || KV8 || wide) __syncthreads();  // pages[] is filled; the q operands kept in LDS are complete
+  if (!APPEND || KV8 || wide) lds_barrier();  // pages[] is filled; the q operands kept in LDS are complete
 
   // Segment partials of short contexts (<= kLdsSegs segments) stay in LDS; longer ones and the shared ones go
-  // through the workspace.  pcol: this lane's column, indexed by the absolute segment number.
-  float* const gcol = part + ((size_t)col_row[0] * n_q + col_head[0]) * max_segs * kPartStride;
-  float* const pcol[2] = {in_lds ? lds_part + (size_t)j * n_seg * kPartStride : gcol,
+  // through the workspace.  gcol: this lane's column there; both are indexed by the absolute segment number.
+  float* const gcol[2] = {part + ((size_t)col_row[0] * n_q + col_head[0]) * max_segs * kPartStride,
                           part + ((size_t)col_row[1] * n_q + col_head[1]) * max_segs * kPartStride};
   // per column group (the second one only in a wide set)
   f32x4_t o_acc[2][8];
@@ -520,15 +605,15 @@ __global__ __launch_bounds__(256, KV8 ? 3 : 2) void attn_decode_bf16_kernel(cons
       const bf16x8_t qa = __builtin_bit_cast(bf16x8_t, q_in_lds ? qop[s * 64 + lane] : q_hi[KV8 ? 0 : s]);
       const bf16x8_t ql = __builtin_bit_cast(bf16x8_t, q_in_lds ? qop[256 + s * 64 + lane] : q_lo[KV8 ? 0 : s]);
       sa[0] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, pp.k[0][s]), qa, sa[0], 0, 0, 0);
-      sa[0] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, pp.k[0][s]), ql, sa[0], 0, 0, 0);
       sb[0] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, pp.k[1][s]), qa, sb[0], 0, 0, 0);
+      sa[0] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, pp.k[0][s]), ql, sa[0], 0, 0, 0);
       sb[0] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, pp.k[1][s]), ql, sb[0], 0, 0, 0);
       if constexpr (NG == 2) {
         const bf16x8_t wa = __builtin_bit_cast(bf16x8_t, lds_qopw[512 + s * 64 + lane]);
         const bf16x8_t wl = __builtin_bit_cast(bf16x8_t, lds_qopw[768 + s * 64 + lane]);
         sa[1] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, pp.k[0][s]), wa, sa[1], 0, 0, 0);
-        sa[1] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, pp.k[0][s]), wl, sa[1], 0, 0, 0);
         sb[1] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, pp.k[1][s]), wa, sb[1], 0, 0, 0);
+        sa[1] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, pp.k[0][s]), wl, sa[1], 0, 0, 0);
         sb[1] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, pp.k[1][s]), wl, sb[1], 0, 0, 0);
       }
     }
@@ -595,15 +680,20 @@ __global__ __launch_bounds__(256, KV8 ? 3 : 2) void attn_decode_bf16_kernel(cons
         float l_tot = l_run[c] + __shfl_xor(l_run[c], 16, kWave);
         l_tot += __shfl_xor(l_tot, 32, kWave);
         if (col_valid[c]) {
-          const bool lds_rec = c == 0 && in_lds;  // block-uniform
-          float* p = pcol[c] + (lds_rec ? (size_t)seg * kPartStride : part_o(max_segs, seg));
-          float* pm = lds_rec ? p + kD : pcol[c] + part_ml(max_segs, seg);
+          if (c == 0 && in_lds) {  // block-uniform
+            float* p = lds_part + (j * n_seg + seg) * kPartStride;  // on 8-byte boundaries
 #pragma unroll
-          for (int b = 0; b < 8; ++b) {
-            p[16 * b + 4 * g] = o_acc[c][b][0]; p[16 * b + 4 * g + 1] = o_acc[c][b][1];
-            p[16 * b + 4 * g + 2] = o_acc[c][b][2]; p[16 * b + 4 * g + 3] = o_acc[c][b][3];
+            for (int b = 0; b < 8; ++b) {
+              *(float2*)(p + 16 * b + 4 * g) = make_float2(o_acc[c][b][0], o_acc[c][b][1]);
+              *(float2*)(p + 16 * b + 4 * g + 2) = make_float2(o_acc[c][b][2], o_acc[c][b][3]);
+            }
+            if (g == 0) *(float2*)(p + kD) = make_float2(m_run[c], l_tot);
+          } else {
+            float* p = gcol[c] + part_o(max_segs, seg);
+#pragma unroll
+            for (int b = 0; b < 8; ++b) *(f32x4_t*)(p + 16 * b + 4 * g) = o_acc[c][b];
+            if (g == 0) *(float2*)(gcol[c] + part_ml(max_segs, seg)) = make_float2(m_run[c], l_tot);
           }
-          if (g == 0) { pm[0] = m_run[c]; pm[1] = l_tot; }
         }
       }
       // Stores and loads share one counter and may finish out of order, so a store that may be pending makes the
@@ -617,9 +707,9 @@ __global__ __launch_bounds__(256, KV8 ? 3 : 2) void attn_decode_bf16_kernel(cons
       boundary = seg < seg_end ? seg_begin(seg + 1) : it_end;
     }
   };
-  typedef typename std::conditional<KV8, PagePair8, PagePair>::type Buf;  // registers of a step as loaded
   auto fetch = [&](Buf& pp, int it) __attribute__((always_inline)) {
-    load_pair(pp, kb, vb, pages[2 * it], pages[2 * it + 1], n_kv, lane);
+    const int i = page0 + 2 * min(it, it_end - 1);
+    load_pair(pp, kb, __builtin_amdgcn_readfirstlane(pages[i]), __builtin_amdgcn_readfirstlane(pages[i + 1]), n_kv, lane, it >= it_end);
   };
   auto consume = [&](const Buf& pp, int it, auto ng) __attribute__((always_inline)) {
     if constexpr (KV8) {
@@ -714,30 +804,26 @@ __global__ __launch_bounds__(256, KV8 ? 3 : 2) void attn_decode_bf16_kernel(cons
   };
 
   // Two register buffers, refilled unconditionally inside the loop so that the compiler's wait counts let the
-  // other buffer's 16 loads stay in flight while one is consumed; the ragged end is peeled off below.
+  // other buffer's 16 loads stay in flight while one is consumed.  Three copies of a step: every block runs most of this
+  // kernel once, from a cold instruction cache.
   auto run = [&](auto ng) __attribute__((always_inline)) {
     constexpr bool kRow = decltype(ng)::value == 1;  // only a row block appends
     if (it_begin < it_end) {
-      Buf pa, pb;
-      fetch(pa, it_begin);
+      Buf pb;
+      if constexpr (!kRow) fetch(pa, it_begin);  // once more, from the caches: there are no registers to hold it from above
       int it = it_begin;
-      for (; it + 2 < it_end; it += 2) {
+      for (; it + 1 < it_end; it += 2) {
         fetch(pb, it + 1);
         __builtin_amdgcn_sched_barrier(0);
         consume(pa, it, ng);
         __builtin_amdgcn_sched_barrier(0);
         fetch(pa, it + 2);
         __builtin_amdgcn_sched_barrier(0);
+        if (APPEND && kRow && appends && it + 2 == it_end) patch_new(pb);
         consume(pb, it + 1, ng);
         __builtin_amdgcn_sched_barrier(0);
       }
-      if (it + 1 < it_end) {  // two steps left
-        fetch(pb, it + 1);
-        __builtin_amdgcn_sched_barrier(0);
-        consume(pa, it, ng);
-        if (APPEND && kRow && appends) patch_new(pb);
-        consume(pb, it + 1, ng);
-      } else {  // one step left
+      if (it < it_end) {
         if (APPEND && kRow && appends) patch_new(pa);
         consume(pa, it, ng);
       }
@@ -800,10 +886,11 @@ __global__ __launch_bounds__(256, KV8 ? 3 : 2) void attn_decode_bf16_kernel(cons
 // For the latter the segment weights exp(m_c - M) are formed by the lanes in parallel (max and denominator by the wave's fixed
 // butterfly), then the O partials are accumulated in index order, eight loads in flight at a time.  Rows with
 // short contexts were finished by the first kernel.
-__global__ __launch_bounds__(64) void attn_merge_bf16_kernel(const float* __restrict__ part, const RowMeta* __restrict__ rows,
+__global__ __launch_bounds__(256) void attn_merge_bf16_kernel(const float* __restrict__ part, const RowMeta* __restrict__ rows,
                                                              int max_segs, uint16_t* __restrict__ o_out, int n_q,
                                                              const int32_t* __restrict__ skip_segs) {
-  const int head = blockIdx.x, r = blockIdx.y, lane = threadIdx.x;
+  const int head = blockIdx.x * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), r = blockIdx.y, lane = threadIdx.x & 63;
+  if (head >= n_q) return;
   const int ctx = rows[r].pos + 1;
   const int n_seg = attn_num_segments(ctx);
   const float* p = part + ((size_t)r * n_q + head) * max_segs * kPartStride;
@@ -871,24 +958,25 @@ bool launch_attn_decode_bf16(hipStream_t s, const Geometry& g, const float* q, c
                              const int32_t* block_table, void* k_pool_layer, void* v_pool_layer, float* part,
                              int max_segs_alloc, int max_ctx_in_batch, void* o_out, int M, const int32_t* skip_segs,
                              const AttnShared* shared, int n_shared, int max_shared_segs, const AttnAppend* append,
-                             int segs_per_block, bool window_sets) {
+                             int segs_per_block, bool window_sets, bool packs, bool all_packed) {
   const int n_seg_max = attn_num_segments(max_ctx_in_batch);
   const int spb = std::min(std::max(segs_per_block, 1), kLdsSegs);
-  const int page_ints = ((max_ctx_in_batch + 15) / 16 + 1 + 3) & ~3;  // keeps the partials 16-byte aligned
+  int page_ints = ((max_ctx_in_batch + 15) / 16 + 1 + 3) & ~3;  // keeps the partials 16-byte aligned
+  if (packs) page_ints = std::max(page_ints, 4 * kPackPages);
   if (n_shared <= 0) { skip_segs = nullptr; n_shared = 0; max_shared_segs = 0; }
   // Window sets hold every row: no row blocks (at 1024 rows 8192 blocks that only find out that they have nothing to do,
   // 70 -> 52 us for up to 1024 keys, the longest contexts first).
-  const int row_blocks = n_shared > 0 && window_sets ? 0 : M;
+  const int row_blocks = n_shared > 0 && (window_sets || all_packed) ? 0 : M;
   const int z = std::max(row_blocks > 0 ? attn_num_splits(n_seg_max, spb) : 1, (max_shared_segs + 3) / 4);
   dim3 grid(g.n_kv, row_blocks + n_shared, z);
   const int segs = n_seg_max > kLdsSegs ? kLdsSegs : n_seg_max;
   int part_floats = (g.n_q / g.n_kv) * segs * kPartStride;  // a multiple of 4
   // a set of more than 16 columns keeps the queries of its columns 16.. and the two q operands there
-  if (n_shared > 0 && !g.kv_fp8) part_floats = std::max(part_floats, 3 * 16 * kD);
+  if (n_shared > 0 && !g.kv_fp8) part_floats = std::max(part_floats, 16 * kQStride + 2 * 16 * kD);
   // ... and one that covers all (up to four) segments of its rows their partials, afterwards
   if (n_shared > 0 && window_sets) part_floats = std::max(part_floats, (g.kv_fp8 ? 16 : 32) * 4 * kPartStride);
   // the queries of up to 16 columns, the new key and value (bf16); fp8 pages: the q operand (in the queries' place)
-  const int q_ints = append ? 16 * kD + kD : g.kv_fp8 ? 16 * kD : 0;
+  const int q_ints = append ? 16 * kQStride + (packs ? 4 : 1) * kD : g.kv_fp8 ? 16 * kD : 0;
   const size_t lds = (size_t)(page_ints + part_floats + q_ints) * 4;
   const float scale = 1.0f / sqrtf((float)g.head_dim);
   AppendArgs ap = {};
@@ -916,7 +1004,7 @@ bool launch_attn_decode_bf16(hipStream_t s, const Geometry& g, const float* q, c
 void launch_attn_merge_bf16(hipStream_t s, const Geometry& g, const RowMeta* rows, float* part, int max_segs_alloc,
                             void* o_out, int M, const int32_t* skip_segs, int n_shared) {
   if (n_shared <= 0) skip_segs = nullptr;
-  attn_merge_bf16_kernel<<<dim3(g.n_q, M), 64, 0, s>>>(part, rows, max_segs_alloc, (uint16_t*)o_out, g.n_q, skip_segs);
+  attn_merge_bf16_kernel<<<dim3((g.n_q + 3) / 4, M), 256, 0, s>>>(part, rows, max_segs_alloc, (uint16_t*)o_out, g.n_q, skip_segs);
 }
 
 }  // namespace rl

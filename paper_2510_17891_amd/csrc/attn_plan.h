@@ -26,8 +26,9 @@ RL_HOST_DEVICE inline int attn_seg_begin(int sgm, int n_it, int n_seg) {
 }
 
 // Rows of equal context length whose leading pages are the same physical pages: their first n_segs segments are
-// computed once for the set.
-constexpr int kAttnSetRows = 8;
+// computed once for the set.  n_segs == 0: a pack of up to four (row, segment) pairs, pair w being rows[w] and
+// rows[kAttnPackSegs + w] (unused pairs repeat the first).
+constexpr int kAttnSetRows = 8, kAttnPackSegs = 4;
 struct AttnShared {
   int32_t rows[kAttnSetRows];  // entries beyond n_rows repeat rows[0]
   int32_t n_rows;
@@ -58,6 +59,8 @@ struct AttnPlan {
   std::vector<int32_t> skip;     // per row: leading segments some set covers
   std::vector<AttnShared> sets;
   int max_shared_segs = 0;
+  int packs = 0;            // entries at the end of `sets` that are packs
+  bool all_packed = false;  // no row is left to a block of its own
 };
 
 // prefix_id[i] != 0 names the page-sharing family of row i (equal ids: the first prefix_blocks[i] pages are the
@@ -95,6 +98,56 @@ inline void plan_shared_attention(int n, const int64_t* prefix_id, const int32_t
     }
     i = e;
   }
+}
+
+// Rows of sets with one to three segments left behind the shared ones: a block of their own would keep as many of its
+// four waves busy, and a large launch lasts as many rounds of blocks as there are rows.  These segments are packed
+// four to a block instead, one per wave.  A packed row's skip is one more than its segments (no row block does
+// anything for it, and the merge does not take it for a row that a set has finished).  Nothing is packed in launches
+// that put less than `min_pairs` (row, kv head) pairs on the chip, where each row's wave has a compute unit to itself,
+// or where the list would outgrow `max_entries`.  padded: empty packs (n_rows == 0) follow, as many as make the number
+// of entries depend on the packed rows alone and not on how many segments they have left (a graph's launch shape).
+inline void plan_packs(int n, const int32_t* pos, int n_kv, int group, int min_pairs, int max_entries, bool padded, AttnPlan* plan) {
+  plan->packs = 0;
+  plan->all_packed = false;
+  if (plan->sets.empty() || n * n_kv < min_pairs || group * 4 > 16) return;  // the four rows' heads share one operand
+  int units = 0, rows = 0;
+  const auto left = [&](int r) { return plan->skip[r] ? attn_num_segments(pos[r] + 1) - plan->skip[r] : 0; };
+  const auto packed = [&](int r) { return left(r) >= 1 && left(r) <= 3; };
+  bool all = true;
+  for (int r = 0; r < n; ++r) {
+    if (!packed(r)) {
+      all = false;
+      continue;
+    }
+    units += left(r);
+    rows += 1;
+  }
+  const int entries = ((padded ? 3 * rows : units) + 3) / 4;
+  if (!units || (int)plan->sets.size() + entries > max_entries) return;
+  AttnShared s = {};  // no rows, no shared segments
+  for (int r = 0; r < n; ++r) {
+    if (!packed(r)) continue;
+    const int n_seg = attn_num_segments(pos[r] + 1);
+    for (int sgm = plan->skip[r]; sgm < n_seg; ++sgm) {
+      for (int k = s.n_rows; k < kAttnPackSegs; ++k) {
+        s.rows[k] = s.n_rows ? s.rows[0] : r;
+        s.rows[kAttnPackSegs + k] = s.n_rows ? s.rows[kAttnPackSegs] : sgm;
+      }
+      s.rows[s.n_rows] = r;
+      s.rows[kAttnPackSegs + s.n_rows] = sgm;
+      if (++s.n_rows == kAttnPackSegs) {
+        plan->sets.push_back(s);
+        s.n_rows = 0;
+      }
+    }
+    plan->skip[r] = n_seg + 1;
+  }
+  if (s.n_rows) plan->sets.push_back(s);
+  s.n_rows = 0;
+  for (int e = (units + 3) / 4; e < entries; ++e) plan->sets.push_back(s);
+  plan->packs = entries;
+  plan->all_packed = all;
 }
 
 // Rows that feed consecutive positions of one sequence (prefill, scoring).  Positions inside one aligned window of

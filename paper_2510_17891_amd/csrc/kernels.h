@@ -125,6 +125,7 @@ int attn_bf16_max_segments(int max_ctx);
 // only one that needs the row's new key, and it takes it from registers, not from the page.  The arithmetic is the
 // one of launch_qk_rope_append, bit for bit.
 // window_sets: every row is in a set, and every set in `shared` covers all segments of its rows.
+// packs: some entries of `shared` are packs of single segments;  all_packed: they cover all that the sets leave of every row.
 // segs_per_block (1..16): segments one block takes of a context of more than 16 segments (> 4096 keys); results do
 // not depend on it.
 constexpr int kAttnAppendMaxSplits = 4;
@@ -142,7 +143,7 @@ bool launch_attn_decode_bf16(hipStream_t s, const Geometry& g, const float* q, c
                              float* part, int max_segs_alloc, int max_ctx_in_batch, void* o_out, int M,
                              const int32_t* skip_segs = nullptr, const AttnShared* shared = nullptr, int n_shared = 0,
                              int max_shared_segs = 0, const AttnAppend* append = nullptr, int segs_per_block = 16,
-                             bool window_sets = false);
+                             bool window_sets = false, bool packs = false, bool all_packed = false);
 void launch_attn_merge_bf16(hipStream_t s, const Geometry& g, const RowMeta* rows, float* part, int max_segs_alloc,
                             void* o_out, int M, const int32_t* skip_segs, int n_shared);
 // fp32, even head_dim <= 128: one block per (row, q head), whole context, output fp32 row-major [M][n_q*d].  append (may

@@ -54,6 +54,7 @@ constexpr int kRingCalls = kRing - 2;  // slots that ordinary calls cycle throug
 // an event behind a later call is behind the earlier ones too.
 constexpr int kEpochUses = 12, kEpochs = 8;
 static_assert((kEpochs - 1) * kEpochUses > kRingCalls, "the event of a slot's last use is not recorded anew before the slot comes round");
+constexpr int kPackMinPairs = 1024;  // (row, kv head) pairs of a decode step from which left-over segments are packed
 constexpr int T_MAX_SCORE = 4096;  // sequences per scoring call
 
 size_t align_up(size_t v, size_t a = 256) { return (v + a - 1) / a * a; }
@@ -254,6 +255,7 @@ struct SharedAttn {  // device pointers into the metadata slot of the call (empt
   const AttnShared* sets = nullptr;
   int n_sets = 0, max_segs = 0;
   bool window = false;  // every row is in a set, and the sets cover all segments of their rows
+  bool packs = false, all_packed = false;  // some sets are packs of single segments; no row is left to a block of its own
 };
 
 // A layer boundary of a capture (may be null) where no norm writes it: the residual stream as it is.
@@ -279,7 +281,7 @@ int finish_layer(rl_model* m, hipStream_t st, int l, int M, const RowMeta* rows,
     bool merge;
     { Timer t(m, st, K_ATTN);
       merge = launch_attn_decode_bf16(st, g, q, rows, bt, m->k_pool(l), m->v_pool(l), apart, m->lay.max_segs, max_ctx_in_batch,
-                                      o, M, sa.skip, sa.sets, sa.n_sets, sa.max_segs, ap, m->attn_segs_per_block, sa.window); }
+                                      o, M, sa.skip, sa.sets, sa.n_sets, sa.max_segs, ap, m->attn_segs_per_block, sa.window, sa.packs, sa.all_packed); }
     if (merge) {
       Timer t(m, st, K_ATTN_MERGE);
       launch_attn_merge_bf16(st, g, rows, apart, m->lay.max_segs, o, M, sa.skip, sa.n_sets);
@@ -461,6 +463,8 @@ void place_attn_plan(rl_model* m, char* hs, char* ds, int n, const AttnPlan& pla
   sa->sets = (const AttnShared*)(ds + m->lay.slot_sets);
   sa->n_sets = (int)plan.sets.size();
   sa->max_segs = plan.max_shared_segs;
+  sa->packs = plan.packs > 0;
+  sa->all_packed = plan.all_packed;
 }
 
 // First kernel of a call: the upload, the rows into the residual stream, the first norm.  Marks the slot as in use until
@@ -518,7 +522,9 @@ void place_window_plan(rl_model* m, char* hs, char* ds, int n, const RowMeta* hr
 
 // Write the rows and the shared-attention plan of one decode call into the host slot hs and describe them (device
 // pointers relative to the device slot ds).  Returns the upload that brings them there.
-SlotUpload build_decode_meta(rl_model* m, int32_t n, const int32_t* seq_ids, char* hs, char* ds, int* max_ctx_out, SharedAttn* sa) {
+// fixed_shape: the launch shape changes as rarely as it can (decode graphs).
+SlotUpload build_decode_meta(rl_model* m, int32_t n, const int32_t* seq_ids, char* hs, char* ds, int* max_ctx_out, SharedAttn* sa,
+                             bool fixed_shape = false) {
   RowMeta* hr = (RowMeta*)hs;
   int max_ctx = 0;
   for (int i = 0; i < n; ++i) {
@@ -540,7 +546,10 @@ SlotUpload build_decode_meta(rl_model* m, int32_t n, const int32_t* seq_ids, cha
       pos[i] = hr[i].pos;
       any |= fam[i] != 0;
     }
-    if (any) plan_shared_attention(n, fam.data(), fam_blocks.data(), pos.data(), rows_per_set(m, n), &plan);
+    if (any) {
+      plan_shared_attention(n, fam.data(), fam_blocks.data(), pos.data(), rows_per_set(m, n), &plan);
+      plan_packs(n, pos.data(), m->geo.n_kv, m->geo.n_q / m->geo.n_kv, m->share_attention == 2 ? 0 : m->share_attention == 3 ? 1 << 30 : kPackMinPairs, n, fixed_shape, &plan);
+    }
   }
   SlotUpload up = slot_upload(m, hs, ds, n, true);
   place_attn_plan(m, hs, ds, n, plan, sa, &up);
@@ -579,8 +588,9 @@ void decode_enqueue(rl_model* m, hipStream_t st, int n, const RowMeta* rows, int
 
 // A decode step of a fixed batch as a HIP graph.  What changes from step to step is data (rows and the
 // shared-attention plan: one upload from a pinned buffer that the graph's first kernel reads at every launch) except for
-// three launch shapes, which form the key of the captured graph: the 1024-key bracket of the longest context (block
-// count and shared-memory size of the attention launch), the number of row sets, and the blocks the sets need.  When
+// four launch shapes, which form the key of the captured graph: the 1024-key bracket of the longest context (block
+// count and shared-memory size of the attention launch), the number of row sets, the blocks the sets need, and whether
+// some or all of what the sets leave of their rows is packed.  When
 // the key changes -- once per 1024 steps for a batch in lock step -- the step is captured again.  Two buffers and two
 // graphs alternate, so the host may prepare step k + 1 while step k runs.
 struct rl_decode_graph {
@@ -593,7 +603,7 @@ struct rl_decode_graph {
   hipEvent_t ev[2] = {nullptr, nullptr};
   bool ev_used[2] = {false, false};
   hipGraphExec_t exec[2] = {nullptr, nullptr};
-  struct Key { int ctx_bracket, n_sets, set_blocks; } key[2] = {{-1, -1, -1}, {-1, -1, -1}};
+  struct Key { int ctx_bracket, n_sets, set_blocks, packs; } key[2] = {{-1, -1, -1, -1}, {-1, -1, -1, -1}};
   int next = 0;
   int64_t captures = 0;
 };
@@ -846,10 +856,10 @@ rl_status rl_decode_graph_step(rl_decode_graph* g, void* stream, int64_t* captur
   char* ds = m->ws + m->lay.ring + (size_t)(kRingCalls + b) * m->lay.slot_bytes;
   int max_ctx = 0;
   SharedAttn sa;
-  const SlotUpload up = build_decode_meta(m, n, g->ids.data(), hs, ds, &max_ctx, &sa);
-  const rl_decode_graph::Key key = {(max_ctx + 1023) / 1024, sa.n_sets, (sa.max_segs + 3) / 4};
+  const SlotUpload up = build_decode_meta(m, n, g->ids.data(), hs, ds, &max_ctx, &sa, true);
+  const rl_decode_graph::Key key = {(max_ctx + 1023) / 1024, sa.n_sets, (sa.max_segs + 3) / 4, sa.packs + sa.all_packed};
   if (!g->exec[b] || key.ctx_bracket != g->key[b].ctx_bracket || key.n_sets != g->key[b].n_sets ||
-      key.set_blocks != g->key[b].set_blocks) {
+      key.set_blocks != g->key[b].set_blocks || key.packs != g->key[b].packs) {
     if (g->exec[b]) { (void)hipGraphExecDestroy(g->exec[b]); g->exec[b] = nullptr; }
     const bool prof = m->prof_on;
     m->prof_on = false;  // no event pairs inside a captured step

@@ -106,15 +106,19 @@ __device__ __forceinline__ HeadPair head_pair_load(const float* __restrict__ hea
 }
 
 // The same sums for callers that want the loads of several heads in flight at once: head_pair_issue only loads
-// (S <= kHeadPairMaxS; the slots beyond S repeat the last split and are not used), head_pair_sum adds in split order.
+// (S <= kHeadPairMaxS; with one split nothing else is loaded, otherwise the slots beyond S repeat the last split; neither is
+// used), head_pair_sum adds in split order.
 constexpr int kHeadPairMaxS = 4;
 struct HeadPairLoads { float a[kHeadPairMaxS][2]; };
 
 __device__ __forceinline__ void head_pair_issue(HeadPairLoads& ld, const float* __restrict__ head_part, int S,
                                                 size_t split_stride, int d, int i) {
   const int half = d >> 1;
+  ld.a[0][0] = head_part[i];
+  ld.a[0][1] = head_part[i + half];
+  if (S == 1) return;
 #pragma unroll
-  for (int sp = 0; sp < kHeadPairMaxS; ++sp) {
+  for (int sp = 1; sp < kHeadPairMaxS; ++sp) {
     const float* p = head_part + (sp < S ? sp : S - 1) * split_stride;
     ld.a[sp][0] = p[i];
     ld.a[sp][1] = p[i + half];

@@ -59,6 +59,25 @@ int st_plan_shared(void* t, int n, const int* seq_ids, const int* pos, int rows_
   return (int)plan.sets.size();
 }
 
+// what is left behind the shared segments of n rows (skip[r] of them, 0: in no set): skip is updated, sets_out gets the packs
+// behind n_sets sets; returns the entries, and in *all whether no row is left
+int st_plan_packs(int n, const int* pos, int n_kv, int group, int min_pairs, int max_entries, int padded, int n_sets, int* skip,
+                  int* sets_out, int* all) {
+  rl::AttnPlan plan;
+  plan.skip.assign(skip, skip + n);
+  plan.sets.resize(n_sets);
+  rl::plan_packs(n, pos, n_kv, group, min_pairs, max_entries, padded != 0, &plan);
+  for (int i = 0; i < n; ++i) skip[i] = plan.skip[i];
+  for (size_t k = n_sets; k < plan.sets.size(); ++k) {
+    int* o = sets_out + 10 * (k - n_sets);
+    for (int e = 0; e < rl::kAttnSetRows; ++e) o[e] = plan.sets[k].rows[e];
+    o[8] = plan.sets[k].n_rows;
+    o[9] = plan.sets[k].n_segs;
+  }
+  *all = plan.all_packed;
+  return plan.packs;
+}
+
 int st_plan_windows(int n, const int* seq, const int* pos, int rows_per_set, int* skip_out, int* sets_out, int max_sets) {
   rl::AttnPlan plan;
   rl::plan_window_sets(n, seq, pos, rows_per_set, &plan);

@@ -1140,6 +1140,38 @@ def test_shared_attention_set_widths_agree_for_other_head_groupings(amd, n_q, n_
         r.close()
 
 
+@pytest.mark.parametrize("kv_fp8", [False, True])
+def test_packed_segments_behind_shared_prompts_keep_their_bits(amd, kv_fp8):
+    """Three samples each of prompts of one to nine shared segments (odd numbers of left-over segments; one beyond 4096 keys,
+    one with rows of their own beside the packs) and one sequence alone, over a change of the segments left and of the page:
+    with sets and packs, and with every row on its own, the same bits."""
+    shape = dict(ri.SHAPES["layer8b"], n_layers=2, hidden=512, n_q=8, n_kv=2, ffn=768, vocab=8192)
+    w, _ = make_both(shape, 67, std=0.05)
+    wd = to_device(w)
+    seed, G = 11, 3
+    lens = [33, 90, 1030, 4180]
+    prompts = [ri.tokens((n,), shape["vocab"], 67, 970 + i).tolist() for i, n in enumerate(lens)]
+    ids = list(range(len(lens) * G + 1))
+    kw = dict(max_seqs=16, max_ctx=4240, max_rows=64, kv_pages=480, kv_fp8=kv_fp8)
+    ra, rb = amd.Rollout(shape, wd, **kw), amd.Rollout(shape, wd, **kw)
+    ra.rl_debug_share_attention(2)
+    rb.rl_debug_share_attention(0)
+    for r in (ra, rb):
+        r.rl_prefill_groups(ids[:-1], G, prompts, 1.0, seed)
+        r.rl_prefill([ids[-1]], [prompts[1]], 1.0, seed)
+    V = shape["vocab"]
+    tok = torch.tensor(ri.tokens((len(ids),), V, 67, 990).tolist(), dtype=torch.int32, device=DEV)
+    for step in range(40):
+        za, zb = torch.empty(len(ids), V, device=DEV), torch.empty(len(ids), V, device=DEV)
+        ta, la = ra.rl_decode_step(ids, tok, 1.0, seed, debug_logits=za)
+        tb, lb = rb.rl_decode_step(ids, tok, 1.0, seed, debug_logits=zb)
+        torch.cuda.synchronize()
+        assert torch.equal(za, zb) and torch.equal(ta, tb) and torch.equal(la, lb), step
+        tok = ta.clone()
+    ra.close()
+    rb.close()
+
+
 def test_prefill_and_score_bits_do_not_depend_on_the_row_chunk(amd):
     """Prompts pushed through the layers 1024, 320 or 48 rows at a time (max_rows): the first tokens, their
     log-probabilities, the teacher-forced scores and the decode steps that follow are the same bits."""

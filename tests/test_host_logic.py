@@ -67,6 +67,8 @@ def st(tmp_path_factory):
     L.st_prefix_id.restype = C.c_longlong
     L.st_prefix_id.argtypes = [C.c_void_p, C.c_int]
     L.st_prefix_blocks.argtypes = [C.c_void_p, C.c_int]
+    L.st_plan_packs.argtypes = [C.c_int, C.POINTER(C.c_int), C.c_int, C.c_int, C.c_int, C.c_int, C.c_int, C.c_int, C.POINTER(C.c_int),
+                                C.POINTER(C.c_int), C.POINTER(C.c_int)]
     L.st_plan_shared.argtypes = [C.c_void_p, C.c_int, C.POINTER(C.c_int), C.POINTER(C.c_int), C.c_int,
                                  C.POINTER(C.c_int), C.POINTER(C.c_int), C.c_int]
     return L
@@ -238,6 +240,41 @@ def test_shared_attention_plan(st):
     st.st_activate(t, 8)
     assert st.st_prefix_id(t, 8) == 0
     st.st_destroy(t)
+
+
+@pytest.mark.parametrize("padded", [False, True])
+def test_packs_cover_what_sets_leave(st, padded):
+    """Every segment behind the shared ones of a row with one to three of them left is in exactly one pack, packs hold four
+    (row, segment) pairs and repeat the first in unused places, and rows with more left, or in no set, keep their own block."""
+    ctxs = [1100, 1100, 1200, 300, 5000, 1100, 2048, 97, 33]
+    segs = [st.st_attn_num_segments(c) for c in ctxs]
+    left = [1, 2, 3, 1, 2, 0, 4, 1, 3]                # 0: in no set
+    pos = [c - 1 for c in ctxs]
+    n = len(ctxs)
+
+    def plan(left, pairs=1, n_kv=8, group=4, most=64):
+        skip = (C.c_int * n)(*[s - k if k else 0 for s, k in zip(segs, left)])
+        sets, every = (C.c_int * (10 * 64))(), C.c_int()
+        k = st.st_plan_packs(n, (C.c_int * n)(*pos), n_kv, group, pairs, most, int(padded), 3, skip, sets, C.byref(every))
+        return list(skip), [list(sets[10 * i:10 * i + 10]) for i in range(k)], bool(every.value)
+
+    skip, packs, every = plan(left)
+    assert not every
+    got = []
+    for p in packs:
+        assert p[9] == 0 and 0 <= p[8] <= 4
+        got += [(p[w], p[4 + w]) for w in range(p[8])]
+        if p[8]:
+            assert all((p[w], p[4 + w]) == (p[0], p[4]) for w in range(p[8], 4))
+    assert sorted(got) == sorted((r, s) for r in range(n) if 1 <= left[r] <= 3 for s in range(segs[r] - left[r], segs[r]))
+    for r in range(n):
+        assert skip[r] == (segs[r] + 1 if 1 <= left[r] <= 3 else segs[r] - left[r] if left[r] else 0)
+    rows = sum(1 <= k <= 3 for k in left)
+    assert len(packs) == -(-(3 * rows if padded else len(got)) // 4)
+    assert plan([1] * n)[2]                           # no row block needed
+    for kw in (dict(pairs=n * 8 + 1), dict(group=8), dict(most=3 + len(packs) - 1)):
+        skip, packs_, every = plan(left, **kw)
+        assert not packs_ and not every and max(s - t for s, t in zip(skip, segs)) <= 0
 
 
 def test_window_sets_of_prefill_rows(st):
