@@ -638,8 +638,8 @@ __global__ __launch_bounds__(256, KV8 ? 3 : 2) void attn_decode_bf16_kernel(cons
       }
 #pragma unroll
       for (int e = 0; e < 4; ++e) mx = fmaxf(mx, fmaxf(sc[e], sc[4 + e]));
-      mx = fmaxf(mx, __shfl_xor(mx, 16, kWave));
-      mx = fmaxf(mx, __shfl_xor(mx, 32, kWave));
+      mx = lane_max(mx, 16);
+      mx = lane_max(mx, 32);
       const float m_new = fmaxf(m_run[c], mx);  // finite: key it*32 is inside every column's context
       alpha[c] = __expf(m_run[c] - m_new);
       m_run[c] = m_new;
@@ -677,8 +677,8 @@ __global__ __launch_bounds__(256, KV8 ? 3 : 2) void attn_decode_bf16_kernel(cons
     if (it + 1 == boundary) {  // wave-uniform
 #pragma unroll
       for (int c = 0; c < NG; ++c) {
-        float l_tot = l_run[c] + __shfl_xor(l_run[c], 16, kWave);
-        l_tot += __shfl_xor(l_tot, 32, kWave);
+        float l_tot = lane_add(l_run[c], 16);
+        l_tot = lane_add(l_tot, 32);
         if (col_valid[c]) {
           if (c == 0 && in_lds) {  // block-uniform
             float* p = lds_part + (j * n_seg + seg) * kPartStride;  // on 8-byte boundaries
@@ -840,8 +840,8 @@ __global__ __launch_bounds__(256, KV8 ? 3 : 2) void attn_decode_bf16_kernel(cons
     if (it_begin < it_end) {
 #pragma unroll
       for (int c = 0; c < (KV8 ? 1 : 2); ++c) {
-        float l_tot = l_run[c] + __shfl_xor(l_run[c], 16, kWave);
-        l_tot += __shfl_xor(l_tot, 32, kWave);
+        float l_tot = lane_add(l_run[c], 16);
+        l_tot = lane_add(l_tot, 32);
         if (col_valid[c]) {  // never in the second group of a set that is not wide
           float* p = lds_part + ((size_t)(j + 16 * c) * n_seg + first_seg) * kPartStride;
 #pragma unroll

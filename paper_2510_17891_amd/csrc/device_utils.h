@@ -46,14 +46,64 @@ __device__ __forceinline__ float load_as_float(const uint16_t* p, size_t i) { re
 __device__ __forceinline__ void store_from_float(float* p, size_t i, float v) { p[i] = v; }
 __device__ __forceinline__ void store_from_float(uint16_t* p, size_t i, float v) { p[i] = (uint16_t)f2bf(v); }
 
+// Values of the lanes `mask` apart (a power of two, a constant once loops are unrolled; all 64 lanes active).  Within 16 lanes
+// these are data-parallel-primitive moves, beyond them gfx950's swaps of 16- and 32-lane halves: a few cycles, where an
+// exchange through the LDS crossbar (__shfl_xor) takes over a hundred, and a reduction chains six of them.
+struct LanePair {
+  uint32_t a, b;  // own and other value, in an order that is the same in both lanes for masks 16 and 32
+};
+__device__ __forceinline__ LanePair lane_pair_bits(uint32_t v, int mask) {
+  const int x = (int)v;
+  switch (mask) {
+    case 1: return {v, (uint32_t)__builtin_amdgcn_update_dpp(0, x, 0xB1, 0xf, 0xf, true)};  // quad_perm 1 0 3 2
+    case 2: return {v, (uint32_t)__builtin_amdgcn_update_dpp(0, x, 0x4E, 0xf, 0xf, true)};  // quad_perm 2 3 0 1
+    case 4: {  // row_half_mirror (lane ^ 7), then quad_perm 3 2 1 0 (lane ^ 3)
+      const int h = __builtin_amdgcn_update_dpp(0, x, 0x141, 0xf, 0xf, true);
+      return {v, (uint32_t)__builtin_amdgcn_update_dpp(0, h, 0x1B, 0xf, 0xf, true)};
+    }
+    case 8: return {v, (uint32_t)__builtin_amdgcn_update_dpp(0, x, 0x128, 0xf, 0xf, true)};  // row_ror 8
+    case 16: {
+      const auto r = __builtin_amdgcn_permlane16_swap(v, v, false, false);
+      return {r[0], r[1]};
+    }
+    default: {
+      const auto r = __builtin_amdgcn_permlane32_swap(v, v, false, false);
+      return {r[0], r[1]};
+    }
+  }
+}
+__device__ __forceinline__ uint32_t lane_xor(uint32_t v, int mask) {
+  const LanePair p = lane_pair_bits(v, mask);
+  return mask >= 16 && (threadIdx.x & mask) ? p.a : p.b;
+}
+__device__ __forceinline__ int lane_xor(int v, int mask) { return (int)lane_xor((uint32_t)v, mask); }
+__device__ __forceinline__ float lane_xor(float v, int mask) { return __uint_as_float(lane_xor(__float_as_uint(v), mask)); }
+__device__ __forceinline__ unsigned long long lane_xor(unsigned long long v, int mask) {
+  return ((unsigned long long)lane_xor((uint32_t)(v >> 32), mask) << 32) | lane_xor((uint32_t)v, mask);
+}
+// v of this lane and the one `mask` apart: sum and maximum.
+__device__ __forceinline__ float lane_add(float v, int mask) {
+  const LanePair p = lane_pair_bits(__float_as_uint(v), mask);
+  return __uint_as_float(p.a) + __uint_as_float(p.b);
+}
+__device__ __forceinline__ float lane_max(float v, int mask) {
+  const LanePair p = lane_pair_bits(__float_as_uint(v), mask);
+  return fmaxf(__uint_as_float(p.a), __uint_as_float(p.b));
+}
+
+// fn(kFirst), fn(kFirst / 2), ..., fn(1): the steps of a reduction, each with its mask as a constant.
+template <int kFirst = 32, typename F>
+__device__ __forceinline__ void each_mask(F fn) {
+  fn(kFirst);
+  if constexpr (kFirst > 1) each_mask<kFirst / 2>(fn);
+}
+
 __device__ __forceinline__ float wave_sum(float v) {
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, kWave);
+  each_mask([&](int o) __attribute__((always_inline)) { v = lane_add(v, o); });
   return v;
 }
 __device__ __forceinline__ float wave_max(float v) {
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) v = fmaxf(v, __shfl_xor(v, o, kWave));
+  each_mask([&](int o) __attribute__((always_inline)) { v = lane_max(v, o); });
   return v;
 }
 

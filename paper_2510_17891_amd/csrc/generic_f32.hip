@@ -29,11 +29,11 @@ __device__ __forceinline__ float wave_sums(const float (&v)[R], int lane) {
       for (int i = 0; i < R / 2; ++i)
         if (i < n / 2) {
           const float keep = up ? a[2 * i + 1] : a[2 * i], send = up ? a[2 * i] : a[2 * i + 1];
-          a[i] = keep + __shfl_xor(send, mask, kWave);
+          a[i] = keep + lane_xor(send, mask);
         }
       n >>= 1;
     } else {
-      a[0] += __shfl_xor(a[0], mask, kWave);
+      a[0] = lane_add(a[0], mask);
     }
   }
   return a[0];

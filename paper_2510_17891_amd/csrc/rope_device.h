@@ -148,14 +148,10 @@ __device__ __forceinline__ void head_pairs_finish(HeadPair (&hp)[N], int d, bool
     float ss[N];
 #pragma unroll
     for (int n = 0; n < N; ++n) ss[n] = __builtin_fmaf(hp[n].v0, hp[n].v0, hp[n].v1 * hp[n].v1);
+    each_mask([&](int o) __attribute__((always_inline)) {  // the butterfly of wave_sum
 #pragma unroll
-    for (int o = 32; o > 0; o >>= 1) {  // the butterfly of wave_sum
-      float other[N];
-#pragma unroll
-      for (int n = 0; n < N; ++n) other[n] = __shfl_xor(ss[n], o, kWave);
-#pragma unroll
-      for (int n = 0; n < N; ++n) ss[n] += other[n];
-    }
+      for (int n = 0; n < N; ++n) ss[n] = lane_add(ss[n], o);
+    });
 #pragma unroll
     for (int n = 0; n < N; ++n) {
       const float mean = ss[n] / (float)d;

@@ -42,11 +42,10 @@ __global__ __launch_bounds__(256) void sample_stage1_kernel(const float* __restr
       if (i == f) forced_z[r] = zi;
     }
   }
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) {
+  each_mask([&](int o) __attribute__((always_inline)) {
     best = better(best, shfl_xor_best(best, o));
-    lse_merge(m, s, __shfl_xor(m, o, kWave), __shfl_xor(s, o, kWave));
-  }
+    lse_merge(m, s, lane_xor(m, o), lane_xor(s, o));
+  });
   const int wave = threadIdx.x >> 6;
   if ((threadIdx.x & 63) == 0) { sh_y[wave] = best.y; sh_i[wave] = best.idx; sh_z[wave] = best.z; sh_m[wave] = m; sh_s[wave] = s; }
   __syncthreads();
@@ -80,11 +79,10 @@ __global__ __launch_bounds__(1024) void sample_stage2_kernel(const float* __rest
     best = better(best, Best{a.x, __float_as_int(a.y), a.z});
     lse_merge(m, s, b.x, b.y);
   }
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) {
+  each_mask([&](int o) __attribute__((always_inline)) {
     best = better(best, shfl_xor_best(best, o));
-    lse_merge(m, s, __shfl_xor(m, o, kWave), __shfl_xor(s, o, kWave));
-  }
+    lse_merge(m, s, lane_xor(m, o), lane_xor(s, o));
+  });
   if (lane == 0) { sh_y[wave] = best.y; sh_i[wave] = best.idx; sh_z[wave] = best.z; sh_m[wave] = m; sh_s[wave] = s; }
   __syncthreads();
   if (threadIdx.x == 0) {
@@ -204,15 +202,14 @@ struct CutBinning {
 __device__ __forceinline__ CutBinning cut_binning(const CutRow& row, int n_slices, float inv_t, bool mass) {
   const int i = min((int)(threadIdx.x & (kCutSlices - 1)), n_slices - 1);  // both halves of a wave hold all slices
   uint32_t kmax = row.kmax[i], kmin = row.kmin[i], fmax = row.fmax[i], fmin = row.fmin[i], two = row.two[i], four = row.four[i];
-#pragma unroll
-  for (int o = kCutSlices / 2; o > 0; o >>= 1) {
-    kmax = max(kmax, (uint32_t)__shfl_xor((int)kmax, o, kWave));
-    kmin = min(kmin, (uint32_t)__shfl_xor((int)kmin, o, kWave));
-    fmax = max(fmax, (uint32_t)__shfl_xor((int)fmax, o, kWave));
-    fmin = min(fmin, (uint32_t)__shfl_xor((int)fmin, o, kWave));
-    two = max(two, (uint32_t)__shfl_xor((int)two, o, kWave));
-    four = max(four, (uint32_t)__shfl_xor((int)four, o, kWave));
-  }
+  each_mask<kCutSlices / 2>([&](int o) __attribute__((always_inline)) {
+    kmax = max(kmax, lane_xor(kmax, o));
+    kmin = min(kmin, lane_xor(kmin, o));
+    fmax = max(fmax, lane_xor(fmax, o));
+    fmin = min(fmin, lane_xor(fmin, o));
+    two = max(two, lane_xor(two, o));
+    four = max(four, lane_xor(four, o));
+  });
   CutBinning b;
   b.z_max = order_value(kmax);
   b.s_max = __fmul_rn(b.z_max, inv_t);
@@ -323,15 +320,14 @@ __global__ __launch_bounds__(kCutThreads) void cut_range_kernel(const float* __r
     four = fmaxf(four, fminf(a, b));
   });
   uint32_t ktwo = order_key(two), kfour = order_key(four);
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) {
-    kmax = max(kmax, (uint32_t)__shfl_xor((int)kmax, o, kWave));
-    kmin = min(kmin, (uint32_t)__shfl_xor((int)kmin, o, kWave));
-    fmax = max(fmax, (uint32_t)__shfl_xor((int)fmax, o, kWave));
-    fmin = min(fmin, (uint32_t)__shfl_xor((int)fmin, o, kWave));
-    ktwo = max(ktwo, (uint32_t)__shfl_xor((int)ktwo, o, kWave));
-    kfour = max(kfour, (uint32_t)__shfl_xor((int)kfour, o, kWave));
-  }
+  each_mask([&](int o) __attribute__((always_inline)) {
+    kmax = max(kmax, lane_xor(kmax, o));
+    kmin = min(kmin, lane_xor(kmin, o));
+    fmax = max(fmax, lane_xor(fmax, o));
+    fmin = min(fmin, lane_xor(fmin, o));
+    ktwo = max(ktwo, lane_xor(ktwo, o));
+    kfour = max(kfour, lane_xor(kfour, o));
+  });
   if ((tid & 63) == 0) { sh[0][tid >> 6] = kmax; sh[1][tid >> 6] = fmax; sh[2][tid >> 6] = fmin; sh[3][tid >> 6] = kfour; sh[4][tid >> 6] = kmin; sh[5][tid >> 6] = ktwo; }
   __syncthreads();
   if (tid == 0) {
@@ -362,8 +358,7 @@ __device__ __forceinline__ void add_to_bins(unsigned long long* h, uint32_t* n, 
     unsigned long long sum = (w[0] + w[1]) + (w[2] + w[3]);
     const int first = __builtin_amdgcn_readfirstlane(bin[0]);
     if (__ballot(bin[0] == first) == ~0ull) {  // every lane of the wave
-#pragma unroll
-      for (int o = 32; o > 0; o >>= 1) sum += __shfl_xor(sum, o, kWave);
+      each_mask([&](int o) __attribute__((always_inline)) { sum += lane_xor(sum, o); });
       if ((threadIdx.x & 63) == 0) {
         atomicAdd(&h[first], sum);
         if (kCount) atomicAdd(&n[first], 256u);
@@ -459,11 +454,10 @@ __device__ __forceinline__ Draw empty_draw() { return Draw{Best{-INFINITY, -1, 0
 // The block's draw, in thread 0.
 template <int kThreads>
 __device__ __forceinline__ Draw block_draw(Draw d, Draw (&sh)[kThreads / 64]) {
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) {
+  each_mask([&](int o) __attribute__((always_inline)) {
     d.best = better(d.best, shfl_xor_best(d.best, o));
-    d.sum = Draw::plus(d.sum, __shfl_xor(d.sum, o, kWave));
-  }
+    d.sum = Draw::plus(d.sum, lane_xor(d.sum, o));
+  });
   if ((threadIdx.x & 63) == 0) sh[threadIdx.x >> 6] = d;
   __syncthreads();
   if (threadIdx.x == 0)

@@ -122,7 +122,7 @@ __device__ __forceinline__ void lse_add(float& m, float& s, float t) {
 }
 
 __device__ __forceinline__ Best shfl_xor_best(Best b, int o) {
-  return Best{__shfl_xor(b.y, o, kWave), __shfl_xor(b.idx, o, kWave), __shfl_xor(b.z, o, kWave)};
+  return Best{lane_xor(b.y, o), lane_xor(b.idx, o), lane_xor(b.z, o)};
 }
 
 }  // namespace rl
