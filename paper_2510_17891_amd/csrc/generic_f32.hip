@@ -3,8 +3,11 @@
 // chain of launches that each last about as long as a few dependent memory round trips.  They are therefore written for
 // few launches (norm and residual inside the projections, rotation and KV append inside the attention) and for having
 // all loads of a launch in flight at once.  A decode step of 4 rows through two layers of 256 hidden dimensions, sampling
-// included: 73 us in 15 launches, where separate norms, rotation and append, projections with one 4-byte load per lane
-// and 48 exchanges per 8 sums, and a single wave per attention head took 150 us in 23.
+// included: 48 us in 13 launches (150 us in 23 with separate norms, rotation and append, projections with one 4-byte load
+// per lane and a single wave per attention head; 57 us with weights that waited pass by pass, an attention that asked for
+// keys and values behind the query, and two launches of the sampler).
+#include <type_traits>
+
 #include "device_utils.h"
 #include "kernels.h"
 #include "rope_device.h"
@@ -63,26 +66,48 @@ __global__ __launch_bounds__(256) void gemm_f32_kernel(const float* __restrict__
     w0[c] = W + (size_t)min(n + c, N - 1) * K;
     w1[c] = w0[c] + (size_t)N * K;
   }
-  float a0[C][R], a1[C][R], ss[R];
+  float a0[C][R], a1[C][R], ss[R], old[C];
+#pragma unroll
+  for (int c = 0; c < C; ++c)  // what the product is added to, requested ahead of it
+    old[c] = EPI == kEpiResidual ? out[(size_t)min(m0 + min(lane, R - 1), M - 1) * N + min(n + c, N - 1)] : 0.f;
 #pragma unroll
   for (int i = 0; i < R; ++i) {
     ss[i] = 0.f;
 #pragma unroll
     for (int c = 0; c < C; ++c) a0[c][i] = a1[c][i] = 0.f;
   }
-#pragma unroll(C == 1 ? 4 : 2)
-  for (int k = VEC * lane; k < K; k += 64 * VEC) {
-    vec_t u[C], v[C], g = 1.f;
+  // One pass: 64 VEC elements of the weights and of the rows, requested together and used together, up to kFlight passes at
+  // a time (a pass that waits for the one before costs a round trip to memory).  Elements past the end are read from
+  // the row's start and count as zero.
+  struct Pass { vec_t u[C], v[C], g, x[R]; };
+  const float* const gains = gain ? gain : w0[0];  // read and not used without a norm
+  auto load = [&](Pass& p, int k, bool all) __attribute__((always_inline)) {
+    const bool in = all || k < K;
+    const int kk = in ? k : 0;
 #pragma unroll
     for (int c = 0; c < C; ++c) {
-      u[c] = *(const vec_t*)(w0[c] + k);
-      v[c] = 0.f;
-      if (EPI == kEpiSwiGLU) v[c] = *(const vec_t*)(w1[c] + k);
+      p.u[c] = *(const vec_t*)(w0[c] + kk);
+      p.v[c] = 0.f;
+      if (EPI == kEpiSwiGLU) p.v[c] = *(const vec_t*)(w1[c] + kk);
     }
-    if (gain) g = *(const vec_t*)(gain + k);
+    p.g = *(const vec_t*)(gains + kk);
+#pragma unroll
+    for (int i = 0; i < R; ++i) p.x[i] = *(const vec_t*)(X + (size_t)min(m0 + i, M - 1) * K + kk);
+  };
+  auto use = [&](Pass& p, int k, bool all) __attribute__((always_inline)) {
+    if (!all && k >= K) {
+#pragma unroll
+      for (int c = 0; c < C; ++c) p.u[c] = p.v[c] = 0.f;
+#pragma unroll
+      for (int i = 0; i < R; ++i) p.x[i] = 0.f;
+      p.g = 0.f;
+    }
+    const vec_t g = p.g;
+    const auto& u = p.u;
+    const auto& v = p.v;
 #pragma unroll
     for (int i = 0; i < R; ++i) {
-      vec_t x = *(const vec_t*)(X + (size_t)min(m0 + i, M - 1) * K + k);
+      vec_t x = p.x[i];
       if (gain) {
 #pragma unroll
         for (int e = VEC - 1; e >= 0; --e) ss[i] = fmaf(x[e], x[e], ss[i]);
@@ -96,7 +121,25 @@ __global__ __launch_bounds__(256) void gemm_f32_kernel(const float* __restrict__
           if (EPI == kEpiSwiGLU) a1[c][i] = fmaf(v[c][e], x[e], a1[c][i]);
         }
     }
+  };
+  constexpr int kFlight = C == 1 ? 4 : 2, kPass = 64 * VEC;
+  int k = VEC * lane, left = (K + kPass - 1) / kPass;
+  auto passes = [&](auto nc) __attribute__((always_inline)) {
+    constexpr int n = decltype(nc)::value;
+    Pass p[n];
+#pragma unroll
+    for (int e = 0; e < n; ++e) load(p[e], k + e * kPass, e + 1 < n);
+#pragma unroll
+    for (int e = 0; e < n; ++e) use(p[e], k + e * kPass, e + 1 < n);
+    k += n * kPass;
+    left -= n;
+  };
+  while (left >= kFlight) passes(std::integral_constant<int, kFlight>{});
+  if constexpr (kFlight > 2) {
+    if (left == 3) passes(std::integral_constant<int, 3>{});
+    else if (left == 2) passes(std::integral_constant<int, 2>{});
   }
+  if (left == 1) passes(std::integral_constant<int, 1>{});
   float inv = 1.f;
   if (gain) inv = 1.0f / sqrtf(wave_sums<R>(ss, lane) / (float)K + eps);
 #pragma unroll
@@ -111,7 +154,7 @@ __global__ __launch_bounds__(256) void gemm_f32_kernel(const float* __restrict__
     if (lane >= R || m >= M || n + c >= N) continue;
     float* o = out + (size_t)m * N + n + c;
     if (EPI == kEpiSwiGLU) *o = s0 / (1.0f + expf(-s0)) * s1;
-    else if (EPI == kEpiResidual) *o += s0;
+    else if (EPI == kEpiResidual) *o = old[c] + s0;
     else *o = s0;
   }
 }
@@ -125,15 +168,21 @@ struct F32Append {
 };
 
 // One block of four waves per (row, q head), keys in tiles of 256: one key per thread for the scores; for the weighted
-// sum a thread owns VEC dims and every (256 / (d / VEC))-th key; online softmax across tiles.  d <= 128, d % VEC == 0.
+// sum a thread owns VEC dims and every (256 / (d / VEC))-th key; online softmax across tiles.  d <= VEC * ND, d % VEC == 0.
 // APPEND (one row per sequence): the block forms its query and the row's new key and value from the QKV projection, uses
 // the latter two from LDS, and the first head of the group writes them to the row's page.
-template <bool APPEND, int VEC>
-__global__ __launch_bounds__(256) void attn_f32_kernel(const float* __restrict__ q, const RowMeta* __restrict__ rows,
+// What bounds it is the chain of round trips, not the bytes: a thread's key and its first kFirst values are requested
+// together, for the first tile before the query is formed (7.5 -> 6.8 us at 4 rows of 64 to 96 keys; 64 rows of 900 keys of
+// 62 dims, two layers, 364 -> 323; keys beyond the context repeat the last one and have no
+// weight, dims beyond d repeat the last ones and are not used), and there is one copy of everything, because a
+// block runs this code once, from a cold instruction cache.
+template <bool APPEND, int VEC, int ND>
+__global__ __launch_bounds__(256, 2) void attn_f32_kernel(const float* __restrict__ q, const RowMeta* __restrict__ rows,
                                                        const int32_t* __restrict__ block_table, int max_blocks,
                                                        float* k_pool, float* v_pool, float* __restrict__ o_out, int n_q,
                                                        int n_kv, int d, float scale, F32Append ap) {
   typedef float vec_t __attribute__((ext_vector_type(VEC)));
+  constexpr int kFirst = 8;
   __shared__ __align__(16) float qs[128], kn[128], vn[128], ps[256], part[256 * VEC];
   __shared__ float red[8];
   const int h = blockIdx.x, r = blockIdx.y, tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
@@ -141,45 +190,67 @@ __global__ __launch_bounds__(256) void attn_f32_kernel(const float* __restrict__
   const int ctx = rm.pos + 1, group = n_q / n_kv, hk = h / group;
   const int32_t* bt = block_table + (size_t)rm.seq * max_blocks;
   const size_t page_elems = (size_t)kPageTokens * d;
-  if (APPEND) {
-    if (wave < 3) {  // query, new key, new value: one wave each
-      const int half = d >> 1;
-      const int head = wave == 0 ? h : wave == 1 ? n_q + hk : n_q + n_kv + hk;
-      const bool norm = ap.q_gain != nullptr && wave < 2;
-      HeadPair hp = head_pair_load<false>(ap.qkv + ((size_t)r * (n_q + 2 * n_kv) + head) * d, 1, 0, d, lane, wave < 2,
-                                          ap.rope + (size_t)rm.pos * half, norm ? (wave == 0 ? ap.q_gain : ap.k_gain) : nullptr);
-      head_pair_finish(hp, d, wave < 2, norm, ap.eps);
-      if (lane < half) {
-        float* s = wave == 0 ? qs : wave == 1 ? kn : vn;
-        s[lane] = hp.v0;
-        s[lane + half] = hp.v1;
-        if (wave > 0 && h == hk * group) {
-          float* p = (wave == 1 ? k_pool : v_pool) + ((size_t)rm.page * n_kv + hk) * 2 * page_elems + (size_t)(rm.pos & 15) * d;
-          p[lane] = hp.v0;
-          p[lane + half] = hp.v1;
-        }
-      }
-    }
-  } else {
-    for (int i = tid; i < d; i += 256) qs[i] = q[((size_t)r * n_q + h) * d + i];
-  }
-  __syncthreads();
   const int nd = d / VEC, groups = 256 / nd, dim = (tid % nd) * VEC, grp = tid / nd;
+  const auto row_of = [&](const float* pool, int key, int page) __attribute__((always_inline)) {
+    return pool + ((size_t)page * n_kv + hk) * 2 * page_elems + (size_t)(key & 15) * d;
+  };
   vec_t acc = 0.f;
   float m_run = -INFINITY, l_run = 0.f;
   for (int kb = 0; kb < ctx; kb += 256) {
-    const int key = kb + tid;
-    float sc = -INFINITY;
-    if (key < ctx) {
-      const float* kp = APPEND && key == rm.pos ? kn : k_pool + ((size_t)bt[key >> 4] * n_kv + hk) * 2 * page_elems + (size_t)(key & 15) * d;
-      vec_t dot = 0.f;
-#pragma unroll 8
-      for (int i = 0; i < d; i += VEC) dot += *(const vec_t*)(qs + i) * *(const vec_t*)(kp + i);
-      float s = dot[0];
+    const int key = min(kb + tid, ctx - 1), k_page = bt[key >> 4];
+    int v_key[kFirst], v_page[kFirst];
 #pragma unroll
-      for (int e = 1; e < VEC; ++e) s += dot[e];
-      sc = s * scale;
+    for (int i = 0; i < kFirst; ++i) {
+      v_key[i] = min(kb + grp + i * groups, ctx - 1);
+      v_page[i] = bt[v_key[i] >> 4];
     }
+    HeadPair hp;
+    const bool forms = APPEND && kb == 0 && wave < 3;  // query, new key, new value: one wave each
+    const bool norm = ap.q_gain != nullptr && wave < 2;
+    const int half = d >> 1;
+    if (forms) {
+      const int head = wave == 0 ? h : wave == 1 ? n_q + hk : n_q + n_kv + hk;
+      hp = head_pair_load<false>(ap.qkv + ((size_t)r * (n_q + 2 * n_kv) + head) * d, 1, 0, d, lane, wave < 2,
+                                 ap.rope + (size_t)rm.pos * half, norm ? (wave == 0 ? ap.q_gain : ap.k_gain) : nullptr);
+    }
+    vec_t kr[ND], vr[kFirst];
+    {
+      const float* kp = row_of(k_pool, key, k_page);
+#pragma unroll
+      for (int i = 0; i < ND; ++i) kr[i] = *(const vec_t*)(kp + min(i, nd - 1) * VEC);
+#pragma unroll
+      for (int i = 0; i < kFirst; ++i) vr[i] = *(const vec_t*)(row_of(v_pool, v_key[i], v_page[i]) + dim);
+    }
+    if (kb == 0) {
+      if (forms) {
+        head_pair_finish(hp, d, wave < 2, norm, ap.eps);
+        if (lane < half) {
+          float* s = wave == 0 ? qs : wave == 1 ? kn : vn;
+          s[lane] = hp.v0;
+          s[lane + half] = hp.v1;
+          if (wave > 0 && h == hk * group) {
+            float* p = (wave == 1 ? k_pool : v_pool) + ((size_t)rm.page * n_kv + hk) * 2 * page_elems + (size_t)(rm.pos & 15) * d;
+            p[lane] = hp.v0;
+            p[lane + half] = hp.v1;
+          }
+        }
+      }
+      if (!APPEND)
+        for (int i = tid; i < d; i += 256) qs[i] = q[((size_t)r * n_q + h) * d + i];
+      __syncthreads();
+    }
+    if (APPEND && key == rm.pos) {  // the new key is not in its page yet
+#pragma unroll
+      for (int i = 0; i < ND; ++i) kr[i] = *(const vec_t*)(kn + min(i, nd - 1) * VEC);
+    }
+    vec_t dot = 0.f;
+#pragma unroll
+    for (int i = 0; i < ND; ++i)
+      if (i < nd) dot += *(const vec_t*)(qs + i * VEC) * kr[i];
+    float sc = dot[0];
+#pragma unroll
+    for (int e = 1; e < VEC; ++e) sc += dot[e];
+    sc = kb + tid < ctx ? sc * scale : -INFINITY;
     float mx = wave_max(sc);
     if (lane == 0) red[wave] = mx;
     __syncthreads();
@@ -195,11 +266,15 @@ __global__ __launch_bounds__(256) void attn_f32_kernel(const float* __restrict__
     acc *= alpha;
     if (grp < groups) {
       const int nk = min(256, ctx - kb);
+#pragma unroll
+      for (int i = 0; i < kFirst; ++i) {
+        const int t = grp + i * groups;
+        if (t < nk) acc += ps[t] * (APPEND && kb + t == rm.pos ? *(const vec_t*)(vn + dim) : vr[i]);
+      }
 #pragma unroll 4
-      for (int t = grp; t < nk; t += groups) {
+      for (int t = grp + kFirst * groups; t < nk; t += groups) {
         const int kt = kb + t;
-        const float* vp = APPEND && kt == rm.pos ? vn : v_pool + ((size_t)bt[kt >> 4] * n_kv + hk) * 2 * page_elems + (size_t)(kt & 15) * d;
-        acc += ps[t] * *(const vec_t*)(vp + dim);
+        acc += ps[t] * *(const vec_t*)((APPEND && kt == rm.pos ? vn : row_of(v_pool, kt, bt[kt >> 4])) + dim);
       }
     }
     __syncthreads();
@@ -255,14 +330,20 @@ void launch_attn_f32(hipStream_t s, const Geometry& g, const float* q, const Row
   F32Append ap = {};
   if (append) ap = F32Append{append->qkv_part, (const float*)append->q_gain, (const float*)append->k_gain, append->rope_table, g.rms_eps};
   const float scale = 1.0f / sqrtf((float)g.head_dim);
-#define RL_ATTN_F32(APP, VEC)                                                                                       \
-  attn_f32_kernel<APP, VEC><<<grid, 256, 0, s>>>(q, rows, block_table, g.max_blocks, (float*)k_pool_layer,          \
-                                                 (float*)v_pool_layer, o_out, g.n_q, g.n_kv, g.head_dim, scale, ap)
-  if (g.head_dim % 4 == 0) {
-    if (append) RL_ATTN_F32(true, 4); else RL_ATTN_F32(false, 4);
-  } else {  // an even head_dim: pairs keep the loads aligned
-    if (append) RL_ATTN_F32(true, 2); else RL_ATTN_F32(false, 2);
-  }
+#define RL_ATTN_F32(VEC, ND)                                                                                         \
+  do {                                                                                                               \
+    if (append)                                                                                                      \
+      attn_f32_kernel<true, VEC, ND><<<grid, 256, 0, s>>>(q, rows, block_table, g.max_blocks, (float*)k_pool_layer,  \
+                                                          (float*)v_pool_layer, o_out, g.n_q, g.n_kv, g.head_dim, scale, ap); \
+    else                                                                                                             \
+      attn_f32_kernel<false, VEC, ND><<<grid, 256, 0, s>>>(q, rows, block_table, g.max_blocks, (float*)k_pool_layer, \
+                                                           (float*)v_pool_layer, o_out, g.n_q, g.n_kv, g.head_dim, scale, ap); \
+  } while (0)
+  // the key registers of a thread: 64 floats for heads of up to 64 dims, 128 beyond
+  if (g.head_dim % 4 == 0 && g.head_dim <= 64) RL_ATTN_F32(4, 16);
+  else if (g.head_dim % 4 == 0) RL_ATTN_F32(4, 32);
+  else if (g.head_dim <= 64) RL_ATTN_F32(2, 32);  // an even head_dim: pairs keep the loads aligned
+  else RL_ATTN_F32(2, 64);
 #undef RL_ATTN_F32
 }
 

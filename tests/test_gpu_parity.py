@@ -64,6 +64,31 @@ def test_sampler_bit_exact_and_logprob(amd, vocab, bf16):
     ro.close()
 
 
+@pytest.mark.parametrize("vocab", [4, 64, 260, 4100, 8192, 8196])
+def test_sampler_at_the_edges_of_one_block_per_row(amd, vocab):
+    """One thread, one wave, a few threads of a second, a second pass, the last vocabulary that one block takes, the first
+    that it does not; and logits on a 4-byte boundary, which go to the kernels that read them one by one."""
+    ro = _sampler_model(amd, vocab, False)
+    n = 5
+    z = ri.normal((n, vocab), 1.3, 6, 71)
+    z[1, vocab - 1] = z[1, 2] = 9.0
+    z[2, :] = 0.25
+    z[3, 0] = float("-inf")
+    shifted = torch.empty(n * vocab + 1, device=DEV)[1:].view(n, vocab)
+    shifted.copy_(z)
+    seqs, poss = [3, 0, 7, 63, 1], [0, 1, 65535, 77, 2048]
+    forced = torch.tensor([vocab - 1, -1, 0, 3, -1], dtype=torch.int32, device=DEV)
+    for zd in (z.to(DEV), shifted):
+        for T, f in ((1.0, None), (0.0, None), (0.7, forced)):
+            tok, lp = ro.rl_sample_logits(zd, seqs, poss, T, 77, forced=f)
+            torch.cuda.synchronize()
+            for r in range(n):
+                t_ref, lp_ref = orc.sample(z[r].numpy(), T, 77, seqs[r], poss[r], forced=-1 if f is None else int(f[r]))
+                assert int(tok[r]) == t_ref, (T, r)
+                assert abs(float(lp[r]) - lp_ref) < 1e-5 * max(1.0, abs(lp_ref)), (T, r)
+    ro.close()
+
+
 # ------------------------------------------------------------------------------- fp32 tiny model, end to end
 def test_tiny_fp32_greedy_rollout_matches_oracle(amd):
     """4 prompts x 64 tokens, greedy decode of 32 tokens: every token identical, logits within 1e-4."""
