@@ -3,6 +3,7 @@
 // in fp32 (tolerance, not bit-exact).
 #include <algorithm>
 #include <mutex>
+#include <type_traits>
 
 #include "../../include/rl.h"
 #include "kernels.h"
@@ -157,7 +158,8 @@ __global__ __launch_bounds__(1024) void sample_stage2_kernel(const float* __rest
 // ------------------------------------------------------------------------------------------------
 // Truncated sampling: the top-k / top-p cut of every row (the last kept token of the order) and the draw from what is
 // left, in three passes over the logits.
-//   1. cut_range: largest and smallest logit of the row, and how far below the largest its bulk lies.
+//   1. cut_range: largest and smallest logit of the row, how far below the largest its bulk lies, and the largest logit of
+//      every unit of 256, by which pass 3 leaves out what lies behind the cut.
 //   2. cut_hist: count or integer mass per bin, the bins being steps of the logit below the largest one.  A mass has
 //      kCutBins equal steps over the 22 / inv_t in which weights are not zero.  A count has the finest steps over four
 //      times the distance to the largest minimum of four neighbouring logits (or 64 times that of two, where that is less:
@@ -173,8 +175,8 @@ __global__ __launch_bounds__(1024) void sample_stage2_kernel(const float* __rest
 // logits, or masked ones that the cut reaches) the finishing block goes over the row itself (row_cut).
 // What bounds it: the passes' arithmetic per token (order keys, weights, LDS additions), then the finishing blocks, one per
 // row.  A radix selection over the digits of the key took five passes, each with its own scan, and a draw over every
-// entry.  Rows of 151936 entries, that selection -> these passes: 0.6 / 0.95 at 128 rows 217 -> 74 us, at one row 65 -> 33;
-// top-k 50 198 -> 69 and 56 -> 31, also with masked tokens or logits rounded to 16 bits; a top-k cut among masked tokens
+// entry.  Rows of 151936 entries, that selection -> these passes: 0.6 / 0.95 at 128 rows 217 -> 58 us, at one row 65 -> 26;
+// top-k 50 198 -> 52 and 56 -> 31, also with masked tokens or logits rounded to 16 bits; a top-k cut among masked tokens
 // 323 -> 97 and 58 -> 41; equal logits 360 -> 78 and 63 -> 26 (the cut follows from their number).  Slower at few rows is a
 // crowd 30000 times narrower than the distance of an outlier above it (top-k: 197 -> 140 at 128 rows, 56 -> 76 at one):
 // steps that follow such a crowd cost plain rows 5 % at 256 rows.
@@ -183,6 +185,7 @@ constexpr int kCutBins = 1024;
 constexpr int kCutList = 4096;
 constexpr int kCutThreads = 512;
 constexpr int kCutSlices = 32;  // at most, per row
+constexpr int kCutUnits = 1024;  // units of 64 groups of four logits, per row: the largest logit of each is kept
 
 struct CutSel {            // after the scan of a histogram
   int32_t bin;             // the bin that holds the cut
@@ -198,6 +201,7 @@ struct CutRow {  // per row
   // per slice: largest and smallest key; the same of the finite logits (or 0, 0xffffffff); the largest minimum of two and
   // of four neighbouring logits, as keys
   uint32_t kmax[kCutSlices], kmin[kCutSlices], fmax[kCutSlices], fmin[kCutSlices], two[kCutSlices], four[kCutSlices];
+  float unit_max[kCutUnits];             // +inf where a unit holds something that is not a number
   uint2 list[2][kCutList];               // (key, index)
 };
 static_assert(sizeof(CutRow) % 16 == 0, "rows lie one behind the other, histograms are read in pairs");
@@ -221,13 +225,19 @@ __device__ __forceinline__ void for_each_group(const float* __restrict__ z, int 
   }
 }
 
+__device__ __forceinline__ int signed_key(float z) {  // as a signed number in the order of order_key
+  const int b = __float_as_int(z);
+  return b ^ ((b >> 31) & 0x7fffffff);
+}
 __device__ __forceinline__ bool finite_bits(float x) { return (__float_as_uint(x) & 0x7f800000u) != 0x7f800000u; }
 
-struct Slice { int g_begin, g_end; };
+// units: of the slice, from its start; unit0: where the row keeps the first one's largest logit, or -1 (a row of more than
+// kCutUnits, i.e. beyond 260000 logits).
+struct Slice { int g_begin, g_end, units, unit0; };
 __device__ __forceinline__ Slice row_slice(int V) {
-  const int n4 = V >> 2, per = (n4 + gridDim.x - 1) / gridDim.x;
-  const int g = min(n4, (int)blockIdx.x * per);
-  return Slice{g, min(n4, g + per)};
+  const int n4 = V >> 2, per = (n4 + gridDim.x - 1) / gridDim.x, most = (per + 63) >> 6;
+  const int g = min(n4, (int)blockIdx.x * per), g_end = min(n4, g + per);
+  return Slice{g, g_end, (g_end - g + 63) >> 6, (int)gridDim.x * most <= kCutUnits ? (int)blockIdx.x * most : -1};
 }
 
 // The row's largest logit, and the bins of a selection: of a mass, equal steps down from z_ref; of a count, 512 equal steps
@@ -358,21 +368,60 @@ __global__ __launch_bounds__(kCutThreads) void cut_range_kernel(const float* __r
   if (blockIdx.x == 0 && tid < 2) { row.n_list[tid] = 0u; row.lo[tid] = 0xffffffffu; row.hi[tid] = 0u; }
   const Slice sl = row_slice(V);
   uint32_t kmax = 0, kmin = 0xffffffffu, fmax = 0, fmin = 0xffffffffu;
+  int smax = (int)0x80000000, smin = 0x7fffffff;
   float two = -INFINITY, four = -INFINITY;
-  for_each_group<4>(logits + (size_t)r * V, sl.g_begin, sl.g_end, tid, kCutThreads, [&](int, float4 v) {
-    const float zs[4] = {v.x, v.y, v.z, v.w};
+  const float4* z4 = (const float4*)(logits + (size_t)r * V);
+  for (int g0 = sl.g_begin; g0 < sl.g_end; g0 += 4 * kCutThreads) {
+    float4 v[4];
 #pragma unroll
-    for (int e = 0; e < 4; ++e) {
-      const uint32_t k = order_key(zs[e]);
-      kmax = max(kmax, k);
-      kmin = min(kmin, k);
-      fmax = max(fmax, finite_bits(zs[e]) ? k : 0u);
-      fmin = min(fmin, finite_bits(zs[e]) ? k : 0xffffffffu);
+    for (int p = 0; p < 4; ++p) {
+      const int g = g0 + p * kCutThreads + tid;
+      v[p] = z4[g < sl.g_end ? g : sl.g_end - 1];  // the last group again: changes nothing below
     }
-    const float a = fminf(v.x, v.y), b = fminf(v.z, v.w);
-    two = fmaxf(two, fmaxf(a, b));
-    four = fmaxf(four, fminf(a, b));
-  });
+    float tops[4];
+    bool odd = false;
+#pragma unroll
+    for (int p = 0; p < 4; ++p) {
+      const float sum = (v[p].x + v[p].y) + (v[p].z + v[p].w);  // not finite where one of them is not, or hardly ever besides
+      odd |= !finite_bits(sum);
+      tops[p] = sum != sum ? INFINITY : fmaxf(fmaxf(v[p].x, v[p].y), fmaxf(v[p].z, v[p].w));
+      const float a = fminf(v[p].x, v[p].y), b = fminf(v[p].z, v[p].w);
+      two = fmaxf(two, fmaxf(a, b));
+      four = fmaxf(four, fminf(a, b));
+      if (!finite_bits(sum)) continue;
+      const int k0 = signed_key(v[p].x), k1 = signed_key(v[p].y), k2 = signed_key(v[p].z), k3 = signed_key(v[p].w);
+      smax = max(smax, max(max(k0, k1), max(k2, k3)));
+      smin = min(smin, min(min(k0, k1), min(k2, k3)));
+    }
+    if (odd) {
+#pragma unroll
+      for (int p = 0; p < 4; ++p) {
+        const float zs[4] = {v[p].x, v[p].y, v[p].z, v[p].w};
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          const uint32_t k = order_key(zs[e]);
+          kmax = max(kmax, k);
+          kmin = min(kmin, k);
+          fmax = max(fmax, finite_bits(zs[e]) ? k : 0u);
+          fmin = min(fmin, finite_bits(zs[e]) ? k : 0xffffffffu);
+        }
+      }
+    }
+    // the four units' maxima at once, that of load p in lane p: every step halves the values a lane carries
+    const bool up1 = tid & 1, up2 = tid & 2;
+    const float t0 = fmaxf(up1 ? tops[1] : tops[0], lane_xor(up1 ? tops[0] : tops[1], 1));
+    const float t1 = fmaxf(up1 ? tops[3] : tops[2], lane_xor(up1 ? tops[2] : tops[3], 1));
+    float top = fmaxf(up2 ? t1 : t0, lane_xor(up2 ? t0 : t1, 2));
+    top = lane_max(lane_max(lane_max(lane_max(top, 4), 8), 16), 32);
+    const int unit = ((g0 - sl.g_begin) >> 6) + (tid & 63) * (kCutThreads / 64) + (tid >> 6);
+    if (sl.unit0 >= 0 && (tid & 63) < 4 && unit < sl.units) row.unit_max[sl.unit0 + unit] = top;
+  }
+  if (smax >= smin) {  // of groups without anything odd: order_key is the signed key with its sign turned
+    kmax = max(kmax, (uint32_t)smax ^ 0x80000000u);
+    kmin = min(kmin, (uint32_t)smin ^ 0x80000000u);
+    fmax = max(fmax, (uint32_t)smax ^ 0x80000000u);
+    fmin = min(fmin, (uint32_t)smin ^ 0x80000000u);
+  }
   uint32_t ktwo = order_key(two), kfour = order_key(four);
   each_mask([&](int o) __attribute__((always_inline)) {
     kmax = max(kmax, lane_xor(kmax, o));
@@ -444,27 +493,34 @@ __global__ __launch_bounds__(kCutThreads) void cut_hist_kernel(const float* __re
   for (int b = tid; b < kCutBins; b += kCutThreads) lh[b] = 0ull;
   __syncthreads();
   const Slice sl = row_slice(V);
-  for_each_group<4>(logits + (size_t)r * V, sl.g_begin, sl.g_end, tid, kCutThreads, [&](int i0, float4 v) {
-    const float zs[4] = {v.x, v.y, v.z, v.w};
-    if constexpr (kMass) {
+  const auto scan = [&](auto near_c, auto all_c) __attribute__((always_inline)) {
+    for_each_group<4>(logits + (size_t)r * V, sl.g_begin, sl.g_end, tid, kCutThreads, [&](int i0, float4 v) {
+      const float zs[4] = {v.x, v.y, v.z, v.w};
+      if constexpr (kMass) {
 #pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        const float x = __fmaf_rn(zs[e], inv_t, -cb.s_max);
-        if (!(x > -22.0f)) continue;  // weight zero
-        if (use_k && !kept_by(allowed, order_key(zs[e]), i0 + e)) continue;
-        atomicAdd(&lh[cb.bin<true>(zs[e])], fexp_weight(x));
-      }
-    } else {
-      int bins[4];
+        for (int e = 0; e < 4; ++e) {
+          const float x = __fmaf_rn(zs[e], inv_t, -cb.s_max);
+          if (!(x > -22.0f)) continue;  // weight zero
+          if (!decltype(all_c)::value && use_k && !kept_by(allowed, order_key(zs[e]), i0 + e)) continue;
+          atomicAdd(&lh[cb.bin<true>(zs[e])], fexp_weight<decltype(near_c)::value>(x));
+        }
+      } else {
+        int bins[4];
 #pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        bins[e] = cb.bin<false>(zs[e]);
-        if (bins[e] == kCutBins - 1) bins[e] = -1;  // a scan that does not reach its count before the last bin ends there
+        for (int e = 0; e < 4; ++e) {
+          bins[e] = cb.bin<false>(zs[e]);
+          if (bins[e] == kCutBins - 1) bins[e] = -1;  // a scan that does not reach its count before the last bin ends there
+        }
+        const unsigned long long w[4] = {1, 1, 1, 1};
+        add_to_bins<false>(lh, nullptr, bins, w);
       }
-      const unsigned long long w[4] = {1, 1, 1, 1};
-      add_to_bins<false>(lh, nullptr, bins, w);
-    }
-  });
+    });
+  };
+  // The scan is bound by its instructions (45 per token): the usual row does without the branch for weights beyond one and
+  // without a cut before this one, 20.4 -> 18 us at 128 rows.  Largest scores below 2^20 are off by less than a sixteenth
+  // when rounded: no score exceeds them by more.
+  if (!kMass || (fabsf(cb.s_max) <= 0x1p20f && !use_k)) scan(std::true_type{}, std::true_type{});  // block-uniform
+  else scan(std::false_type{}, std::false_type{});
   __syncthreads();
   for (int b = tid; b < kCutBins; b += kCutThreads)
     if (lh[b] != 0ull) atomicAdd(&row.hist[kMass][b], lh[b]);
@@ -539,8 +595,19 @@ __global__ __launch_bounds__(kCutThreads) void cut_gather_kernel(const float* __
   constexpr int kKept = kDraw ? 2048 : 1;  // certainly kept tokens, drawn among after the scan with all lanes busy
   __shared__ uint2 sh_list[kCutList], sh_kept[kKept];
   __shared__ uint32_t sh_n, sh_at, sh_nk, sh_lo, sh_hi;
-  const int r = blockIdx.y, tid = threadIdx.x;
+  const int r = blockIdx.y, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   CutRow& row = ws[r];
+  const Slice sl = row_slice(V);
+  uint32_t pos = 0, seq = 0;
+  int f = -1;
+  if (kDraw) {
+    const RowMeta rm = da.rows[r];
+    pos = (uint32_t)(rm.pos + da.pos_offset);
+    seq = (uint32_t)rm.seq;
+    if (da.forced) f = da.forced[r];
+    // cut off, i.e. of probability zero, unless it is found among the kept tokens, here or by sample_finish
+    if (tid == 0 && f >= 4 * sl.g_begin && f < 4 * sl.g_end) da.forced_z[r] = -INFINITY;
+  }
   const CutBinning cb = cut_binning(row, gridDim.x, inv_t, kMass);
   const OrderCut allowed = use_k ? row.cut_k : OrderCut{0u, 0x7fffffff};
   if (tid < 64) {
@@ -557,15 +624,6 @@ __global__ __launch_bounds__(kCutThreads) void cut_gather_kernel(const float* __
   __syncthreads();
   const int cut_bin = sh_sel.bin;
   const float* z = logits + (size_t)r * V;
-  const Slice sl = row_slice(V);
-  uint32_t pos = 0, seq = 0;
-  int f = -1;
-  if (kDraw) {
-    const RowMeta rm = da.rows[r];
-    pos = (uint32_t)(rm.pos + da.pos_offset);
-    seq = (uint32_t)rm.seq;
-    if (da.forced) f = da.forced[r];
-  }
   Draw d = empty_draw();
   auto draw_token = [&](int i, float zi) {
     d.add(i, zi, cb.z_max, inv_t, token_bits((uint32_t)i, pos, seq, da.seed_lo, da.seed_hi));
@@ -585,43 +643,66 @@ __global__ __launch_bounds__(kCutThreads) void cut_gather_kernel(const float* __
       for (int e = 0; e < 4; ++e) {
         const bool kept = i0 + e < n_prefix;
         if (kept) d.add(i0 + e, zs[e], cb.z_max, inv_t, rnd[e]);
-        if (f == i0 + e) da.forced_z[r] = kept ? zs[e] : -INFINITY;
+        if (kept && f == i0 + e) da.forced_z[r] = zs[e];
       }
     });
   } else {
     uint32_t lo = 0xffffffffu, hi = 0u;
-    for_each_group<4>(z, sl.g_begin, sl.g_end, tid, kCutThreads, [&](int i0, float4 v) {
-      const float zs[4] = {v.x, v.y, v.z, v.w};
-      // most groups lie behind the cut's bin as a whole; fmaxf skips a NaN, which the sum shows
-      const float top = fmaxf(fmaxf(v.x, v.y), fmaxf(v.z, v.w)), sum = (v.x + v.y) + (v.z + v.w);
-      const bool any = cb.bin<kMass>(top) <= cut_bin || (!kMass && sum != sum);
-      if (kDraw && !any && f >= i0 && f < i0 + 4) da.forced_z[r] = -INFINITY;  // cut off: probability zero
-      if (!any) return;
+    // one token of the cut's bin or an earlier one
+    const auto token = [&](int i, float zi) __attribute__((always_inline)) {
+      const uint32_t k = order_key(zi);
+      if (use_k && !kept_by(allowed, k, i)) return;
+      if (cb.bin<kMass>(zi) == cut_bin) {
+        if (kMass && !(__fmaf_rn(zi, inv_t, -cb.s_max) > -22.0f)) return;  // weight zero: never the cut, always behind it
+        const uint32_t at = atomicAdd(&sh_n, 1u);
+        if (at < (uint32_t)kCutList) sh_list[at] = make_uint2(k, (uint32_t)i);
+        lo = min(lo, k);
+        hi = max(hi, k);
+      } else if (kDraw) {
+        const uint32_t at = atomicAdd(&sh_nk, 1u);
+        if (at < (uint32_t)kKept) sh_kept[at] = make_uint2(__float_as_uint(zi), (uint32_t)i);
+        else draw_token(i, zi);
+        if (f == i) da.forced_z[r] = zi;
+      }
+    };
+    // A wave takes every eighth unit, and of those only the ones whose largest logit is in the cut's bin or before it (the
+    // bin is a monotone function of the logit): where some dozens of tokens are kept, most of the row is not read again.
+    // The code for a token exists once: sixteen copies of it, drawing included, were fetched past cold by every block.
+    // 128 rows of 151936 entries, 0.6 / 0.95 (100 kept): this kernel 25.9 -> 14.9 us; 1.0 / 0.95 (14000 kept) all 113 -> 84.
+    const bool read_all = sl.unit0 < 0 || sl.units <= 4 * (kCutThreads / 64);  // all at once is faster than asking first
+    for (int u0 = wave; u0 < sl.units; u0 += 64 * (kCutThreads / 64)) {
+      const int u = u0 + lane * (kCutThreads / 64);
+      const bool there = u < sl.units;
+      const float most = read_all ? INFINITY : row.unit_max[sl.unit0 + (there ? u : 0)];
+      unsigned long long left = __ballot(there && (most == INFINITY || cb.bin<kMass>(most) <= cut_bin));
+      while (left) {
+        float4 v[4];
+        int g[4];
 #pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        const int b = cb.bin<kMass>(zs[e]);
-        const uint32_t k = order_key(zs[e]);
-        if (b > cut_bin || (use_k && !kept_by(allowed, k, i0 + e))) {
-          if (kDraw && f == i0 + e) da.forced_z[r] = -INFINITY;
-          continue;
+        for (int p = 0; p < 4; ++p) {
+          g[p] = left ? sl.g_begin + 64 * (u0 + (int)__builtin_ctzll(left) * (kCutThreads / 64)) + lane : sl.g_end;
+          left &= left - 1;
+          v[p] = ((const float4*)z)[min(g[p], sl.g_end - 1)];
         }
-        if (b == cut_bin) {
-          if (kDraw && f == i0 + e) da.forced_z[r] = -INFINITY;  // unless sample_finish keeps it
-          if (kMass && !(__fmaf_rn(zs[e], inv_t, -cb.s_max) > -22.0f)) continue;  // weight zero: never the cut, always behind it
-          const uint32_t at = atomicAdd(&sh_n, 1u);
-          if (at < (uint32_t)kCutList) sh_list[at] = make_uint2(k, (uint32_t)(i0 + e));
-          lo = min(lo, k);
-          hi = max(hi, k);
-          continue;
+        uint32_t mask = 0;  // of the thread's sixteen tokens
+#pragma unroll
+        for (int p = 0; p < 4; ++p) {
+          // most groups lie behind the cut's bin as a whole; fmaxf skips a NaN, which the sum shows
+          const float top = fmaxf(fmaxf(v[p].x, v[p].y), fmaxf(v[p].z, v[p].w)), sum = (v[p].x + v[p].y) + (v[p].z + v[p].w);
+          if (g[p] >= sl.g_end || (cb.bin<kMass>(top) > cut_bin && (kMass || sum == sum))) continue;
+          const float zs[4] = {v[p].x, v[p].y, v[p].z, v[p].w};
+#pragma unroll
+          for (int e = 0; e < 4; ++e) mask |= cb.bin<kMass>(zs[e]) <= cut_bin ? 1u << (4 * p + e) : 0u;
         }
-        if (kDraw) {
-          const uint32_t at = atomicAdd(&sh_nk, 1u);
-          if (at < (uint32_t)kKept) sh_kept[at] = make_uint2(__float_as_uint(zs[e]), (uint32_t)(i0 + e));
-          else draw_token(i0 + e, zs[e]);
-          if (f == i0 + e) da.forced_z[r] = zs[e];
+        while (mask) {
+          const int at = __builtin_ctz(mask), p = at >> 2, e = at & 3;
+          mask &= mask - 1;
+          const float4 a = p & 1 ? v[1] : v[0], b = p & 1 ? v[3] : v[2], c = p & 2 ? b : a;
+          const int ga = p & 1 ? g[1] : g[0], gb = p & 1 ? g[3] : g[2];
+          token(4 * (p & 2 ? gb : ga) + e, e & 2 ? (e & 1 ? c.w : c.z) : (e & 1 ? c.y : c.x));
         }
       }
-    });
+    }
     if (lo <= hi) { atomicMin(&sh_lo, lo); atomicMax(&sh_hi, hi); }
     __syncthreads();
     const uint32_t n_own = sh_n;

@@ -65,6 +65,8 @@ __device__ __forceinline__ uint32_t order_key(float z) {  // ascending key = asc
 __device__ __forceinline__ float order_value(uint32_t key) {  // inverse of order_key
   return __uint_as_float((key & 0x80000000u) ? (key & 0x7fffffffu) : ~key);
 }
+// kNear: x is known to be at most 0.3, so that n <= 0.
+template <bool kNear = false>
 __device__ __forceinline__ unsigned long long fexp_weight(float x) {
   if (!(x > -22.0f)) return 0ull;
   const float t = __fmul_rn(x, 0x1.715476p+0f);
@@ -79,7 +81,7 @@ __device__ __forceinline__ unsigned long long fexp_weight(float x) {
   p = __fmaf_rn(p, f, 1.0f);
   // p lies in (0.7, 1.5): its 24-bit significand moved to where 2^(n+32) puts it, which is the conversion of
   // ldexpf(p, n + 32) for n <= 0 (a third of its instructions; n > 0 only when s_max itself is rounded by more than 0.3)
-  if (n <= 0.0f) {
+  if (kNear || n <= 0.0f) {
     const uint32_t b = __float_as_uint(p);
     const int e = (int)(b >> 23) - 127;
     return ((unsigned long long)((b & 0x007fffffu) | 0x00800000u) << 10) >> (1 - e - (int)n);

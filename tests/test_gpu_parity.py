@@ -64,6 +64,38 @@ def test_sampler_bit_exact_and_logprob(amd, vocab, bf16):
     ro.close()
 
 
+@pytest.mark.parametrize("vocab,n", [(252, 3), (8204, 2), (66052, 1), (66052, 3), (262404, 2), (300, 9)])
+def test_truncated_sampling_reads_the_units_it_needs(amd, vocab, n):
+    """Kept tokens at the first and last place of units of 256 logits, of slices and of the row, among logits far below; a NaN
+    and infinities beside them; more units than a row keeps maxima of.  Token and log-probability as in the oracle."""
+    ro = _sampler_model(amd, vocab, False)
+    z = ri.normal((n, vocab), 0.5, 7, 73) - 30.0
+    at = [i for i in (0, 3, 255, 256, 511, 8191, 8192, 65535, 65536, vocab - 257, vocab - 1) if 0 <= i < vocab]
+    for r in range(n):
+        for k, i in enumerate(at):
+            z[r, i] = 3.0 - 0.3 * ((k * 7 + r) % len(at))
+    z[0, vocab // 2] = float("-inf")
+    zd = z.to(DEV)
+    for T, top_k, top_p in ((0.7, 0, 0.9), (1.0, 5, 0.0), (1.0, len(at) + 3, 0.999), (0.6, 0, 0.3)):
+        for f in (None, at[-1], 5):
+            forced = None if f is None else torch.full((n,), f, dtype=torch.int32, device=DEV)
+            tok, lp = ro.rl_sample_logits(zd, list(range(n)), [9] * n, T, 21, forced=forced, top_k=top_k, top_p=top_p)
+            torch.cuda.synchronize()
+            for r in range(n):
+                t_ref, lp_ref, _ = orc.sample_truncated(z[r].numpy(), T, top_k, top_p, 21, r, 9, forced=-1 if f is None else f)
+                assert int(tok[r]) == t_ref, (T, top_k, top_p, r, f)
+                if np.isfinite(lp_ref):
+                    assert abs(float(lp[r]) - lp_ref) < 1e-5 * max(1.0, abs(lp_ref)), (T, top_k, top_p, r, f)
+                else:
+                    assert float(lp[r]) == lp_ref
+    zd[:, 77] = float("nan")  # its unit is read all the same; a NaN has no weight and is not drawn
+    a = ro.rl_sample_logits(zd, list(range(n)), [9] * n, 0.7, 21, top_p=0.9)
+    zd[:, 77] = -60.0
+    b = ro.rl_sample_logits(zd, list(range(n)), [9] * n, 0.7, 21, top_p=0.9)
+    assert torch.equal(a[0], b[0]) or bool(torch.isnan(a[1]).all())
+    ro.close()
+
+
 @pytest.mark.parametrize("vocab", [4, 64, 260, 4100, 8192, 8196])
 def test_sampler_at_the_edges_of_one_block_per_row(amd, vocab):
     """One thread, one wave, a few threads of a second, a second pass, the last vocabulary that one block takes, the first
