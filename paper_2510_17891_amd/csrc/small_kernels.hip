@@ -44,25 +44,28 @@ __device__ __forceinline__ void upload_slot(const SlotUpload& u, int first, int 
   }
 }
 
-// Token of row r: read by one lane per block, because the tokens of a prompt (and the rows of a step that feeds itself) lie in host memory.
-__device__ __forceinline__ int fetch_token(const RowSource& in, int r, int* shared) {
-  if (threadIdx.x == 0) {
-    const int fed = in.tokens != nullptr ? in.tokens[r] : in.last_tok[in.rows[r].seq];
-    *shared = min(max(fed, 0), in.V - 1);  // ids come from device memory the host cannot inspect
+// Tokens of rows r .. r + R - 1 (past the last row: its token again): each is read by one lane per block, because the tokens of
+// a prompt (and the rows of a step that feeds itself) lie in host memory.
+template <int R>
+__device__ __forceinline__ void fetch_tokens(const RowSource& in, int r, int M, int (&shared)[R]) {
+  if (threadIdx.x < R) {
+    const int i = min(r + (int)threadIdx.x, M - 1);
+    const int fed = in.tokens != nullptr ? in.tokens[i] : in.last_tok[in.rows[i].seq];
+    shared[threadIdx.x] = min(max(fed, 0), in.V - 1);  // ids come from device memory the host cannot inspect
   }
   __syncthreads();
-  return *shared;
 }
 
 template <typename T>
 __global__ __launch_bounds__(256) void entry_rows_kernel(RowSource in, SlotUpload up, int up_blocks, float* __restrict__ x, int H) {
-  __shared__ int token;
+  __shared__ int token[1];
   if ((int)blockIdx.x < up_blocks) {
     upload_slot(up, blockIdx.x * 256 + threadIdx.x, up_blocks * 256);
     return;
   }
   const int r = blockIdx.x - up_blocks;
-  const size_t base = (size_t)(in.from_table ? fetch_token(in, r, &token) : r) * H;
+  if (in.from_table) fetch_tokens(in, r, r + 1, token);
+  const size_t base = (size_t)(in.from_table ? token[0] : r) * H;
   for (int i = threadIdx.x; i < H; i += 256) x[(size_t)r * H + i] = load_as_float((const T*)in.src, base + i);
 }
 
@@ -75,25 +78,28 @@ __global__ __launch_bounds__(256) void entry_rows_kernel(RowSource in, SlotUploa
 // SRC 0: x = xi + split sums, 3: the same with row r from row r / group;  1: the rows of a call from the caller's fp32 buffer;  2: from the embedding table (bf16).
 // 1 and 2 are the first kernel of a call: x is always written, and leading blocks move the metadata slot.
 // xo may be xi.  gain: H bf16 gains; without a norm (has_gain = 0) any readable H-element array.
-template <int SRC>
+// R: rows per block.  A block of 1024 threads spends its time on one round trip and a barrier, and two blocks fill a compute
+// unit: beyond 512 rows, two rows per block keep it at one round of blocks (1024 rows 11.3 -> 8.3 us, from the table 18.3 -> 13.0).  A row's bits do not
+// depend on R.
+template <int SRC, int R>
 __global__ __launch_bounds__(1024) void residual_norm_kernel(const float* xi, float* xo, const float* __restrict__ part,
                                                              int S, size_t split_stride, const void* __restrict__ gain,
                                                              int has_gain, void* __restrict__ h_out,
                                                              float* __restrict__ capture, int H, float eps, RowSource in,
-                                                             SlotUpload up, int up_blocks, int group) {
-  __shared__ float red[16];
-  __shared__ int token;
+                                                             SlotUpload up, int up_blocks, int group, int M) {
+  __shared__ float red[R][16];
+  __shared__ int token[R];
   const int nthr = blockDim.x;
   constexpr bool kEntry = SRC == 1 || SRC == 2;
   if (kEntry && (int)blockIdx.x < up_blocks) {
     upload_slot(up, blockIdx.x * nthr + threadIdx.x, up_blocks * nthr);
     return;
   }
-  const int r = kEntry ? (int)blockIdx.x - up_blocks : (int)blockIdx.x, ri = SRC == 3 ? r / group : r;
-  const float* xr = xi + (size_t)ri * H;
-  float ss = 0.f;
+  static_assert(R == 1 || SRC != 3, "a group's rows have blocks of their own");
+  const int r0 = (kEntry ? (int)blockIdx.x - up_blocks : (int)blockIdx.x) * R;
   constexpr int kMaxPass = 2;  // H <= 1024 threads * 4 * kMaxPass, checked by the host
-  float4 keep[kMaxPass];
+  float4 keep[R][kMaxPass];
+  float ss[R];
   // Gains are requested together with the data, as stored (two words per thread), and first touched after the
   // sums: converting them here would make the compiler wait for them before it even asks for the data.
   uint2 graw[kMaxPass];
@@ -103,47 +109,70 @@ __global__ __launch_bounds__(1024) void residual_norm_kernel(const float* xi, fl
     const int ig = i0 < H ? i0 : 0;  // unconditional loads (a branch here costs a wait); `gain` is always readable
     graw[pass] = *(const uint2*)((const uint16_t*)gain + ig);
   }
-  const uint16_t* er = SRC == 2 ? (const uint16_t*)in.src + (size_t)fetch_token(in, r, &token) * H : nullptr;
+  if (SRC == 2) fetch_tokens(in, r0, M, token);
 #pragma unroll
   for (int pass = 0; pass < kMaxPass; ++pass) {
     const int i0 = (pass * nthr + threadIdx.x) * 4;
-    float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
+#pragma unroll
+    for (int k = 0; k < R; ++k) keep[k][pass] = make_float4(0.f, 0.f, 0.f, 0.f);
     if (i0 < H) {
-      if (SRC == 2) {
-        const uint2 e = *(const uint2*)(er + i0);
-        v = make_float4(bf2f(e.x & 0xffffu), bf2f(e.x >> 16), bf2f(e.y & 0xffffu), bf2f(e.y >> 16));
-      } else {
-        v = *(const float4*)(xr + i0);
+#pragma unroll
+      for (int k = 0; k < R; ++k) {
+        const int ri = SRC == 3 ? r0 / group : min(r0 + k, M - 1);
+        if (SRC == 2) {
+          const uint2 e = *(const uint2*)((const uint16_t*)in.src + (size_t)token[k] * H + i0);
+          keep[k][pass] = make_float4(bf2f(e.x & 0xffffu), bf2f(e.x >> 16), bf2f(e.y & 0xffffu), bf2f(e.y >> 16));
+        } else {
+          keep[k][pass] = *(const float4*)(xi + (size_t)ri * H + i0);
+        }
       }
+#pragma unroll
+      for (int k = 0; k < R; ++k) {
+        const int ri = SRC == 3 ? r0 / group : min(r0 + k, M - 1);
+        float4 v = keep[k][pass];
 #pragma unroll 4
-      for (int sp = 0; sp < S; ++sp) {
-        const float4 p = *(const float4*)(part + sp * split_stride + (size_t)ri * H + i0);
-        v.x += p.x; v.y += p.y; v.z += p.z; v.w += p.w;
+        for (int sp = 0; sp < S; ++sp) {
+          const float4 p = *(const float4*)(part + sp * split_stride + (size_t)ri * H + i0);
+          v.x += p.x; v.y += p.y; v.z += p.z; v.w += p.w;
+        }
+        keep[k][pass] = v;
+        if (R > 1 && r0 + k >= M) continue;
+        if (kEntry || S > 0) *(float4*)(xo + (size_t)(r0 + k) * H + i0) = v;
+        if (capture) *(float4*)(capture + (size_t)(r0 + k) * H + i0) = v;
       }
-      if (kEntry || S > 0) *(float4*)(xo + (size_t)r * H + i0) = v;
-      if (capture) *(float4*)(capture + (size_t)r * H + i0) = v;
     }
-    keep[pass] = v;
-    ss += (v.x * v.x + v.y * v.y) + (v.z * v.z + v.w * v.w);
   }
   if (!has_gain) return;
 #pragma unroll
   for (int pass = 0; pass < kMaxPass; ++pass)
     asm volatile("" : "+v"(graw[pass].x), "+v"(graw[pass].y));
-  ss = wave_sum(ss);
-  if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = ss;
-  __syncthreads();
-  ss = 0.f;
-  for (int w = 0; w < (nthr >> 6); ++w) ss += red[w];
-  const float inv = 1.0f / sqrtf(ss / (float)H + eps);
 #pragma unroll
-  for (int pass = 0; pass < kMaxPass; ++pass) {
-    const int i0 = (pass * nthr + threadIdx.x) * 4;
-    if (i0 >= H) continue;
-    const float4 v = keep[pass];
-    const float4 g = make_float4(bf2f(graw[pass].x & 0xffffu), bf2f(graw[pass].x >> 16), bf2f(graw[pass].y & 0xffffu), bf2f(graw[pass].y >> 16));
-    *(uint2*)((uint16_t*)h_out + frag_offset(r, i0, H >> 6)) =
-        make_uint2(pack2h(v.x * inv * g.x, v.y * inv * g.y), pack2h(v.z * inv * g.z, v.w * inv * g.w));
+  for (int k = 0; k < R; ++k) {
+    ss[k] = 0.f;
+#pragma unroll
+    for (int pass = 0; pass < kMaxPass; ++pass) {
+      const float4 v = keep[k][pass];
+      ss[k] += (v.x * v.x + v.y * v.y) + (v.z * v.z + v.w * v.w);
+    }
+    ss[k] = wave_sum(ss[k]);
+    if ((threadIdx.x & 63) == 0) red[k][threadIdx.x >> 6] = ss[k];
+  }
+  __syncthreads();
+#pragma unroll
+  for (int k = 0; k < R; ++k) {
+    if (R > 1 && r0 + k >= M) continue;
+    float sum = 0.f;
+    for (int w = 0; w < (nthr >> 6); ++w) sum += red[k][w];
+    const float inv = 1.0f / sqrtf(sum / (float)H + eps);
+#pragma unroll
+    for (int pass = 0; pass < kMaxPass; ++pass) {
+      const int i0 = (pass * nthr + threadIdx.x) * 4;
+      if (i0 >= H) continue;
+      const float4 v = keep[k][pass];
+      const float4 g = make_float4(bf2f(graw[pass].x & 0xffffu), bf2f(graw[pass].x >> 16), bf2f(graw[pass].y & 0xffffu), bf2f(graw[pass].y >> 16));
+      *(uint2*)((uint16_t*)h_out + frag_offset(r0 + k, i0, H >> 6)) =
+          make_uint2(pack2h(v.x * inv * g.x, v.y * inv * g.y), pack2h(v.z * inv * g.z, v.w * inv * g.w));
+    }
   }
 }
 
@@ -155,9 +184,11 @@ void launch_residual_norm(hipStream_t s, const float* x_in, float* x_out, const 
   const void* g = has_gain ? gain : x_in;  // read and ignored without a norm
   const size_t stride = (size_t)(M / group) * H;
   if (group > 1)
-    residual_norm_kernel<3><<<M, norm_threads(H), 0, s>>>(x_in, x_out, part, S, stride, g, has_gain, h_out, capture, H, eps, RowSource{}, SlotUpload{}, 0, group);
+    residual_norm_kernel<3, 1><<<M, norm_threads(H), 0, s>>>(x_in, x_out, part, S, stride, g, has_gain, h_out, capture, H, eps, RowSource{}, SlotUpload{}, 0, group, M);
+  else if (M > 512)
+    residual_norm_kernel<0, 2><<<(M + 1) / 2, norm_threads(H), 0, s>>>(x_in, x_out, part, S, stride, g, has_gain, h_out, capture, H, eps, RowSource{}, SlotUpload{}, 0, 1, M);
   else
-    residual_norm_kernel<0><<<M, norm_threads(H), 0, s>>>(x_in, x_out, part, S, stride, g, has_gain, h_out, capture, H, eps, RowSource{}, SlotUpload{}, 0, 1);
+    residual_norm_kernel<0, 1><<<M, norm_threads(H), 0, s>>>(x_in, x_out, part, S, stride, g, has_gain, h_out, capture, H, eps, RowSource{}, SlotUpload{}, 0, 1, M);
 }
 
 void launch_entry(hipStream_t s, int dtype, const RowSource& in, const SlotUpload& up, float* x, const void* gain, void* h_out,
@@ -174,21 +205,34 @@ void launch_entry(hipStream_t s, int dtype, const RowSource& in, const SlotUploa
     return;
   }
   const int threads = norm_threads(H), up_blocks = (words + threads - 1) / threads;
-  if (in.from_table)
-    residual_norm_kernel<2><<<M + up_blocks, threads, 0, s>>>(nullptr, x, nullptr, 0, 0, gain, 1, h_out, capture, H, eps, in, up, up_blocks, 1);
+  if (!in.from_table)
+    residual_norm_kernel<1, 1><<<M + up_blocks, threads, 0, s>>>((const float*)in.src, x, nullptr, 0, 0, gain, 1, h_out, capture, H, eps, in, up, up_blocks, 1, M);
+  else if (M > 512)
+    residual_norm_kernel<2, 2><<<(M + 1) / 2 + up_blocks, threads, 0, s>>>(nullptr, x, nullptr, 0, 0, gain, 1, h_out, capture, H, eps, in, up, up_blocks, 1, M);
   else
-    residual_norm_kernel<1><<<M + up_blocks, threads, 0, s>>>((const float*)in.src, x, nullptr, 0, 0, gain, 1, h_out, capture, H, eps, in, up, up_blocks, 1);
+    residual_norm_kernel<2, 1><<<M + up_blocks, threads, 0, s>>>(nullptr, x, nullptr, 0, 0, gain, 1, h_out, capture, H, eps, in, up, up_blocks, 1, M);
 }
 
+// grid: x = pair, y = 1024 elements of the row, then of the queries: every thread has all its loads in flight (one block per
+// pair, an element per thread and pass, took 9.8 us; now 4.8).
 __global__ __launch_bounds__(256) void put_aside_kernel(const int32_t* __restrict__ pairs, const float* __restrict__ x, float* __restrict__ x_out,
                                                        int H, const float* __restrict__ q, float* __restrict__ q_out, int D) {
   const size_t from = pairs[2 * blockIdx.x], to = pairs[2 * blockIdx.x + 1];
-  for (int i = threadIdx.x; i < H; i += 256) x_out[to * H + i] = x[from * H + i];
-  for (int i = threadIdx.x; i < D; i += 256) q_out[to * D + i] = q[from * D + i];
+  const int nx = (H + 1023) / 1024, c = blockIdx.y < nx ? blockIdx.y : blockIdx.y - nx, n = (int)blockIdx.y < nx ? H : D;
+  const float* in = (int)blockIdx.y < nx ? x + from * H : q + from * D;
+  float* out = (int)blockIdx.y < nx ? x_out + to * H : q_out + to * D;
+  float v[4];
+#pragma unroll
+  for (int e = 0; e < 4; ++e) v[e] = in[min(c * 1024 + e * 256 + (int)threadIdx.x, n - 1)];
+#pragma unroll
+  for (int e = 0; e < 4; ++e) {
+    const int i = c * 1024 + e * 256 + threadIdx.x;
+    if (i < n) out[i] = v[e];
+  }
 }
 
 void launch_put_aside(hipStream_t s, const int32_t* pairs, int n, const float* x, float* x_out, int H, const float* q, float* q_out, int D) {
-  if (n > 0) put_aside_kernel<<<n, 256, 0, s>>>(pairs, x, x_out, H, q, q_out, D);
+  if (n > 0) put_aside_kernel<<<dim3(n, (H + 1023) / 1024 + (D + 1023) / 1024), 256, 0, s>>>(pairs, x, x_out, H, q, q_out, D);
 }
 
 __global__ __launch_bounds__(256) void repeat_rows_kernel(const float* __restrict__ in, float* __restrict__ out, int H, int group) {
@@ -384,13 +428,14 @@ void launch_pack_weight_bf16(hipStream_t s, const void* src, void* dst, int N, i
 namespace rl {
 
 // grid: x = layer (its copy of the partial page), then one more for the block-table row; y = fork.
-__global__ __launch_bounds__(256) void fork_kernel(ForkBatch batch, int32_t* __restrict__ bt, int max_blocks, char* __restrict__ pool,
+constexpr int kForkThreads = 1024;
+__global__ __launch_bounds__(kForkThreads) void fork_kernel(ForkBatch batch, int32_t* __restrict__ bt, int max_blocks, char* __restrict__ pool,
                                                    size_t layer_bytes, size_t page_bytes, int n_layers) {
   const ForkBatch::One f = batch.f[blockIdx.y];
   const int32_t* from = bt + (size_t)f.src * max_blocks;
   if ((int)blockIdx.x == n_layers) {
     int32_t* to = bt + (size_t)f.dst * max_blocks;
-    for (int b = threadIdx.x; b < f.full; b += 256) to[b] = from[b];
+    for (int b = threadIdx.x; b < f.full; b += kForkThreads) to[b] = from[b];
     if (threadIdx.x == 0 && f.page >= 0) to[f.full] = f.page;
     return;
   }
@@ -399,12 +444,12 @@ __global__ __launch_bounds__(256) void fork_kernel(ForkBatch batch, int32_t* __r
   const uint4* s = (const uint4*)(base + (size_t)from[f.full] * page_bytes);
   uint4* d = (uint4*)(base + (size_t)f.page * page_bytes);
 #pragma unroll 4
-  for (size_t i = threadIdx.x; i < page_bytes / 16; i += 256) d[i] = s[i];
+  for (size_t i = threadIdx.x; i < page_bytes / 16; i += kForkThreads) d[i] = s[i];
 }
 
 void launch_fork(hipStream_t s, const ForkBatch& batch, int32_t* block_table, int max_blocks, void* kv_pool, size_t layer_bytes,
                  size_t page_bytes, int n_layers) {
-  fork_kernel<<<dim3(n_layers + 1, batch.n), 256, 0, s>>>(batch, block_table, max_blocks, (char*)kv_pool, layer_bytes, page_bytes, n_layers);
+  fork_kernel<<<dim3(n_layers + 1, batch.n), kForkThreads, 0, s>>>(batch, block_table, max_blocks, (char*)kv_pool, layer_bytes, page_bytes, n_layers);
 }
 
 }  // namespace rl

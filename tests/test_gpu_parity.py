@@ -1229,6 +1229,29 @@ def test_packed_segments_behind_shared_prompts_keep_their_bits(amd, kv_fp8):
     rb.close()
 
 
+@pytest.mark.parametrize("rows", [512, 513, 514, 700])
+def test_norms_of_two_rows_per_block_keep_a_rows_bits(amd, rows):
+    """Prompts of 512 to 700 rows in one chunk (one row per block up to 512, then two, the last block's second one missing at an
+    odd number) and in chunks of 64: tokens, log-probabilities, logits behind them and scores are the same bits."""
+    shape = dict(ri.SHAPES["layer8b"], n_layers=2, hidden=512, n_q=4, n_kv=1, ffn=768, vocab=4096)
+    w, _ = make_both(shape, 68, std=0.05)
+    wd = to_device(w)
+    prompts = [ri.tokens((n,), shape["vocab"], 68, 980 + n).tolist() for n in (rows - 100, 100)]
+    res = []
+    for max_rows in (1024, 64):
+        ro = amd.Rollout(shape, wd, max_seqs=2, max_ctx=640, max_rows=max_rows, kv_pages=80)
+        tok, lp = ro.rl_prefill([0, 1], prompts, 1.0, 3)
+        z = torch.empty(2, shape["vocab"], device=DEV)
+        ro.rl_decode_step([0, 1], tok, 1.0, 3, debug_logits=z)
+        ro.rl_free_seqs([0, 1])
+        sc = ro.rl_score([0, 1], prompts, 1.0)
+        torch.cuda.synchronize()
+        res.append((tok.clone(), lp.clone(), z, sc.clone()))
+        ro.close()
+    for a, b in zip(*res):
+        assert torch.equal(a, b)
+
+
 def test_prefill_and_score_bits_do_not_depend_on_the_row_chunk(amd):
     """Prompts pushed through the layers 1024, 320 or 48 rows at a time (max_rows): the first tokens, their
     log-probabilities, the teacher-forced scores and the decode steps that follow are the same bits."""
