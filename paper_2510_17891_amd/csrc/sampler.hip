@@ -175,7 +175,7 @@ __global__ __launch_bounds__(1024) void sample_stage2_kernel(const float* __rest
 // logits, or masked ones that the cut reaches) the finishing block goes over the row itself (row_cut).
 // What bounds it: the passes' arithmetic per token (order keys, weights, LDS additions), then the finishing blocks, one per
 // row.  A radix selection over the digits of the key took five passes, each with its own scan, and a draw over every
-// entry.  Rows of 151936 entries, that selection -> these passes: 0.6 / 0.95 at 128 rows 217 -> 58 us, at one row 65 -> 26;
+// entry.  Rows of 151936 entries, that selection -> these passes: 0.6 / 0.95 at 128 rows 217 -> 57 us, at one row 65 -> 26;
 // top-k 50 198 -> 52 and 56 -> 31, also with masked tokens or logits rounded to 16 bits; a top-k cut among masked tokens
 // 323 -> 97 and 58 -> 41; equal logits 360 -> 78 and 63 -> 26 (the cut follows from their number).  Slower at few rows is a
 // crowd 30000 times narrower than the distance of an outlier above it (top-k: 197 -> 140 at 128 rows, 56 -> 76 at one):
@@ -1006,9 +1006,10 @@ void launch_sample_cut(hipStream_t st, const float* logits, int M, int V, float 
                        CutRow* ws, int32_t* out_tokens, float* out_logprobs, int32_t* last_tok) {
   const bool use_k = top_k > 0 && top_k < V, use_p = top_p > 0.0f && top_p < 1.0f;
   const unsigned long long K = (unsigned long long)top_k, P = (unsigned long long)(top_p * 4294967296.0f);  // exact scaling, truncated
-  // About two blocks per compute unit: every block clears, scans or flushes a histogram of its own (at 128 rows 4 slices
-  // of 512 threads 76 us, 8 slices 81, 4 of 1024 threads 77, 16 of 256 threads 90).
-  int slices = 512 / M;
+  // Two blocks per compute unit: every block clears, scans or flushes a histogram of its own.  Three, which is what the LDS of
+  // the third pass allows, where a block has enough of a long row (128 rows of 151936 entries at 1.0 / 0.95 83.4 -> 79.0 us, at
+  // 0.6 / 0.95 58.5 -> 57.4; four 63.0; at 40 rows three 34.0 against 33.7).
+  int slices = (M >= 64 && V > 65536 ? 768 : 512) / M;
   slices = std::max(1, std::min(std::min(slices, kCutSlices), (V + kSampleTile - 1) / kSampleTile));
   const dim3 grid(slices, M);
   cut_range_kernel<<<grid, kCutThreads, 0, st>>>(logits, V, ws);
