@@ -63,7 +63,10 @@ __global__ __launch_bounds__(256) void sample_stage1_kernel(const float* __restr
 
 constexpr int kSampleRowMax = 8192;
 // Both stages in one block per row, for vocabularies of a few thousand entries, where each launch lasts as long as its chain of
-// round trips whatever it does: 4 rows of 4096 entries 8.3 us in two launches, 4.7 in one.  Beyond, several blocks per row pay.
+// round trips whatever it does.  Kernel times, two launches -> one: 4 rows of 4096 entries 9.5 -> 5.9 us, 1 row of 8192 8.4 ->
+// 7.2, 1024 rows of 8192 27.5 -> 23.  At 12288 entries a row or two take as long either way, at 16384 8.4 in two launches and
+// 11.0 in one.  Which kernel runs depends on the vocabulary alone, and so do a row's bits: the loads need no alignment
+// beyond that of a float.
 __global__ __launch_bounds__(1024) void sample_row_kernel(const float* __restrict__ logits, int V, const RowMeta* __restrict__ rows,
                                                           int pos_offset, float inv_t, int greedy, uint32_t seed_lo, uint32_t seed_hi,
                                                           const int32_t* __restrict__ forced, int32_t* __restrict__ out_tok,
@@ -73,7 +76,8 @@ __global__ __launch_bounds__(1024) void sample_row_kernel(const float* __restric
   const int r = blockIdx.x, lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const float* z = logits + (size_t)r * V;
   const int first = threadIdx.x * 4, step = blockDim.x * 4;
-  float4 v = *(const float4*)(z + (first < V ? first : 0));  // V is a multiple of four, rows are 16-byte aligned
+  const auto load = [&](int i) __attribute__((always_inline)) { return make_float4(z[i], z[i + 1], z[i + 2], z[i + 3]); };  // one load
+  float4 v = load(first < V ? first : 0);  // V is a multiple of four
   const RowMeta rm = rows[r];
   const uint32_t pos = (uint32_t)(rm.pos + pos_offset), seq = (uint32_t)rm.seq;
   const int f = forced ? forced[r] : -1;
@@ -81,7 +85,7 @@ __global__ __launch_bounds__(1024) void sample_row_kernel(const float* __restric
   float m = -INFINITY, s = 0.f;
   for (int i0 = first; i0 < V; i0 += step) {
     const float zs[4] = {v.x, v.y, v.z, v.w};
-    if (i0 + step < V) v = *(const float4*)(z + i0 + step);
+    if (i0 + step < V) v = load(i0 + step);
     uint32_t rnd[4] = {0, 0, 0, 0};
     if (!greedy) philox4x32_10((uint32_t)i0 >> 2, pos, seq, 0u, seed_lo, seed_hi, rnd);
 #pragma unroll
@@ -1042,7 +1046,7 @@ void launch_sample(hipStream_t st, const float* logits, int M, int V, const RowM
                       (CutRow*)cut_buf, out_tokens, out_logprobs, last_tok);
     return;
   }
-  if (V <= kSampleRowMax && (uintptr_t)logits % 16 == 0) {
+  if (V <= kSampleRowMax) {
     sample_row_kernel<<<M, std::min(1024, (V / 4 + 63) / 64 * 64), 0, st>>>(logits, V, rows, pos_offset, inv_t, greedy, seed_lo, seed_hi, forced,
                                                                             out_tokens, out_logprobs, last_tok);
     return;
@@ -1063,7 +1067,7 @@ void launch_sample_merge(hipStream_t st, const float* part, int n_tiles, int M, 
 
 // ------------------------------------------------------------------------------------------------
 // The plain sampler for callers that cannot allocate (code under graph capture, serving loops, harnesses that forbid
-// it): the same two kernels as above, with the row metadata, the forced tokens' logits and the per-tile partials in
+// it): the same kernels as above, with the row metadata, the forced tokens' logits and the per-tile partials in
 // a file-scope device array instead of a model's workspace.  Each GPU has its own copy of the array at its own
 // address; that address is looked up once per device and used from then on (the array's name is not a device
 // address in host code).  Every call on a GPU uses that GPU's array, so calls that overlap on one GPU race.

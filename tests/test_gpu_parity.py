@@ -99,7 +99,7 @@ def test_truncated_sampling_reads_the_units_it_needs(amd, vocab, n):
 @pytest.mark.parametrize("vocab", [4, 64, 260, 4100, 8192, 8196])
 def test_sampler_at_the_edges_of_one_block_per_row(amd, vocab):
     """One thread, one wave, a few threads of a second, a second pass, the last vocabulary that one block takes, the first
-    that it does not; and logits on a 4-byte boundary, which go to the kernels that read them one by one."""
+    that it does not; and logits on a 4-byte boundary."""
     ro = _sampler_model(amd, vocab, False)
     n = 5
     z = ri.normal((n, vocab), 1.3, 6, 71)
@@ -118,6 +118,28 @@ def test_sampler_at_the_edges_of_one_block_per_row(amd, vocab):
                 t_ref, lp_ref = orc.sample(z[r].numpy(), T, 77, seqs[r], poss[r], forced=-1 if f is None else int(f[r]))
                 assert int(tok[r]) == t_ref, (T, r)
                 assert abs(float(lp[r]) - lp_ref) < 1e-5 * max(1.0, abs(lp_ref)), (T, r)
+    ro.close()
+
+
+@pytest.mark.parametrize("vocab", [4, 1000, 4096, 8192, 8196, 151936])
+def test_sampler_bits_do_not_depend_on_the_alignment_of_the_logits(amd, vocab):
+    """The same rows on a 16-byte boundary and 4, 8 and 12 bytes behind one: the same tokens, and log-probabilities that are
+    the same bit for bit; rl_sample_logits_static gives them too."""
+    ro = _sampler_model(amd, vocab, False)
+    n = 16
+    z = ri.normal((n, vocab), 1.3, 6, 72).to(DEV)
+    seqs, poss = list(range(n)), [17 * i for i in range(n)]
+    i32 = lambda v: torch.tensor(v, dtype=torch.int32, device=DEV)
+    for T, forced in ((1.0, None), (0.0, None), (0.7, i32([vocab - 1, -1] * (n // 2)))):
+        ref = ro.rl_sample_logits(z, seqs, poss, T, 77, forced=forced)
+        outs = [amd.binding.rl_sample_logits_static(z, i32(seqs), i32(poss), T, 77, forced=forced)]
+        for off in (1, 2, 3):
+            shifted = torch.empty(n * vocab + off, device=DEV)[off:].view(n, vocab)
+            shifted.copy_(z)
+            assert shifted.data_ptr() % 16 == 4 * off
+            outs.append(ro.rl_sample_logits(shifted, seqs, poss, T, 77, forced=forced))
+        for tok, lp in outs:
+            assert torch.equal(tok, ref[0]) and torch.equal(lp, ref[1]), (vocab, T)
     ro.close()
 
 
