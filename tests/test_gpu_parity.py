@@ -1742,6 +1742,47 @@ def test_truncated_sampler_masked_tied_and_crowded_rows(amd):
     ro.close()
 
 
+@pytest.mark.parametrize("V,n", [(151936, 128), (65536, 128), (65536, 40), (40004, 30)])
+def test_truncated_sampler_crowds_that_fill_whole_units(amd, V, n):
+    """A top-k cut among so many equal or nearly equal logits that a wave finds one to four whole units of 256 of them in
+    the cut's bin: with what fits the list, with what does not, and with units that only some of the tokens fill."""
+    ro = amd.Rollout(dict(ri.SHAPES["tiny"], n_layers=1, vocab=V), to_device(make_both(dict(ri.SHAPES["tiny"], n_layers=1, vocab=V), 11)[0]),
+                     max_seqs=n, max_ctx=64, max_rows=n, kv_pages=8)
+    z = ri.normal((n, V), 1.0, 8, 76)
+    z[0, 10:] = -1e9                          # masks that the cut reaches
+    z[1, 10:] = float("-inf")
+    z[2] *= 1e-4                              # a crowd below one token
+    z[2, V - 3] = 9.0
+    z[3:9] -= 30.0
+    z[3, 5000:7100] = 2.0                     # seven or eight whole units: they fit the list
+    z[4, 5000:7100] = 2.0 - ri.normal((2100,), 1e-7, 8, 77).abs()
+    z[5, 20001:20001 + 1300] = 2.0            # four at most
+    z[5, 17] = 3.0
+    z[6, 3000:3000 + 6000] = 2.0              # more than the list holds
+    z[7, 30000:30700] = 2.0                   # one or two
+    z[7, 30100] = 1.0
+    z[8, V - 1500:] = 2.0                     # up to the row's last, partly filled unit
+    zd = z.to(DEV)
+    seqs, poss = list(range(n)), [5 * i for i in range(n)]
+    for T, k, p in [(0.7, 50, 0.0), (1.0, 640, 0.0), (1.0, 1299, 0.9), (1.0, 2050, 0.0), (1.0, 7000, 0.0)]:
+        order = {r: np.argsort(-z[r].numpy().astype(np.float64), kind="stable") for r in range(10)}  # equal logits: lower ids first
+        inside, outside = [-1] * n, [-1] * n
+        for r in range(10):
+            inside[r], outside[r] = int(order[r][k - 1]), int(order[r][k])
+        for forced in (None, inside, outside):
+            f = None if forced is None else torch.tensor(forced, dtype=torch.int32, device=DEV)
+            tok, lp = ro.rl_sample_logits(zd, seqs, poss, T, 9, forced=f, top_k=k, top_p=p)
+            torch.cuda.synchronize()
+            for r in list(range(10)) + [n - 1]:
+                t_ref, lp_ref, _ = orc.sample_truncated(z[r].numpy(), T, k, p, 9, seqs[r], poss[r], forced=-1 if forced is None else forced[r])
+                assert int(tok[r]) == t_ref, (T, k, p, r)
+                if np.isfinite(lp_ref):
+                    assert abs(float(lp[r]) - lp_ref) < 1e-5 * max(1.0, abs(lp_ref)), (T, k, p, r, float(lp[r]), lp_ref)
+                else:
+                    assert float(lp[r]) == lp_ref, (T, k, p, r)
+    ro.close()
+
+
 def test_truncated_sampler_at_the_smallest_and_largest_vocabulary(amd):
     """Four entries, and the last multiple of four below 2^22: plain, equal and masked rows against the oracle."""
     for V, ks in ((4, (1, 3)), ((1 << 22) - 4, (50, 3000000))):
