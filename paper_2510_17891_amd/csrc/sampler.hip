@@ -6,6 +6,7 @@
 #include <type_traits>
 
 #include "../../include/rl.h"
+#include "cut_plan.h"
 #include "kernels.h"
 #include "sampler_device.h"
 
@@ -188,8 +189,7 @@ __global__ __launch_bounds__(1024) void sample_stage2_kernel(const float* __rest
 constexpr int kCutBins = 1024;
 constexpr int kCutList = 4096;
 constexpr int kCutThreads = 512;
-constexpr int kCutSlices = 32;  // at most, per row
-constexpr int kCutUnits = 1024;  // units of 64 groups of four logits, per row: the largest logit of each is kept
+static_assert(kCutTile >= kSampleTile, "a slice has a partial of its own");
 
 struct CutSel {            // after the scan of a histogram
   int32_t bin;             // the bin that holds the cut
@@ -236,12 +236,12 @@ __device__ __forceinline__ int signed_key(float z) {  // as a signed number in t
 __device__ __forceinline__ bool finite_bits(float x) { return (__float_as_uint(x) & 0x7f800000u) != 0x7f800000u; }
 
 // units: of the slice, from its start; unit0: where the row keeps the first one's largest logit, or -1 (a row of more than
-// kCutUnits, i.e. beyond 260000 logits).
+// kCutUnits, i.e. beyond 2^18 logits).
 struct Slice { int g_begin, g_end, units, unit0; };
 __device__ __forceinline__ Slice row_slice(int V) {
-  const int n4 = V >> 2, per = (n4 + gridDim.x - 1) / gridDim.x, most = (per + 63) >> 6;
+  const int n4 = V >> 2, per = cut_groups_per_slice(V, gridDim.x);
   const int g = min(n4, (int)blockIdx.x * per), g_end = min(n4, g + per);
-  return Slice{g, g_end, (g_end - g + 63) >> 6, (int)gridDim.x * most <= kCutUnits ? (int)blockIdx.x * most : -1};
+  return Slice{g, g_end, (g_end - g + 63) >> 6, cut_keeps_units(V, gridDim.x) ? (int)blockIdx.x * cut_units_per_slice(V, gridDim.x) : -1};
 }
 
 // The row's largest logit, and the bins of a selection: of a mass, equal steps down from z_ref; of a count, 512 equal steps
@@ -1047,11 +1047,7 @@ void launch_sample_cut(hipStream_t st, const float* logits, int M, int V, float 
                        CutRow* ws, int32_t* out_tokens, float* out_logprobs, int32_t* last_tok) {
   const bool use_k = top_k > 0 && top_k < V, use_p = top_p > 0.0f && top_p < 1.0f;
   const unsigned long long K = (unsigned long long)top_k, P = (unsigned long long)(top_p * 4294967296.0f);  // exact scaling, truncated
-  // Two blocks per compute unit: every block clears, scans or flushes a histogram of its own.  Three, which is what the LDS of
-  // the third pass allows, where a block has enough of a long row (128 rows of 151936 entries at 1.0 / 0.95 83.4 -> 79.0 us, at
-  // 0.6 / 0.95 58.5 -> 57.4; four 63.0; at 40 rows three 34.0 against 33.7).
-  int slices = (M >= 64 && V > 65536 ? 768 : 512) / M;
-  slices = std::max(1, std::min(std::min(slices, kCutSlices), (V + kSampleTile - 1) / kSampleTile));
+  const int slices = cut_slices(M, V);
   const dim3 grid(slices, M);
   cut_range_kernel<<<grid, kCutThreads, 0, st>>>(logits, V, ws);
   if (use_k) {

@@ -1,6 +1,7 @@
 // C wrappers around the host sequence table so that its logic can be exercised without a GPU.
 // Built with g++ into its own small library by the CPU tests; not part of the product library.
 #include "attn_plan.h"
+#include "cut_plan.h"
 #include "seq_table.h"
 #include "weight_order.h"
 
@@ -77,6 +78,11 @@ int st_plan_packs(int n, const int* pos, int n_kv, int group, int min_pairs, int
   *all = plan.all_packed;
   return plan.packs;
 }
+
+// slices of truncated sampling, units of 256 logits per slice, whether the units' largest logits are kept
+int st_cut_slices(int n_rows, int vocab) { return rl::cut_slices(n_rows, vocab); }
+int st_cut_units(int vocab, int slices) { return rl::cut_units_per_slice(vocab, slices); }
+int st_cut_keeps_units(int vocab, int slices) { return rl::cut_keeps_units(vocab, slices) ? 1 : 0; }
 
 int st_plan_windows(int n, const int* seq, const int* pos, int rows_per_set, int* skip_out, int* sets_out, int max_sets) {
   rl::AttnPlan plan;

@@ -405,3 +405,15 @@ def test_binding_fails_loudly_without_the_library():
             "    print('raised:', e)\n")
     r = subprocess.run([sys.executable, "-c", code], capture_output=True, text=True, cwd=root, timeout=120)
     assert r.returncode == 0 and "raised:" in r.stdout and "paper_2510_17891_amd.build" in r.stdout
+
+
+def test_truncated_sampling_keeps_the_units_of_every_row_of_up_to_2_18_logits(st):
+    """However a row is sliced, the place for its units' largest logits is enough, and no slice is empty of use: vocabularies
+    of 2^18 entries are real ones."""
+    for V in list(range(4, 1 << 18, 4 * 251)) + list(range((1 << 18) - 4 * 700, (1 << 18) + 1, 4)):
+        for slices in range(1, 33):
+            assert st.st_cut_keeps_units(V, slices) == 1, (V, slices)
+            assert st.st_cut_units(V, slices) * 64 * slices >= V // 4
+    for V in (4, 2048, 2052, 65536, 65540, 151936, 1 << 18, (1 << 22) - 4):
+        for n in (1, 2, 16, 63, 64, 95, 96, 128, 511, 512, 513, 767, 768, 769, 1024):
+            assert 1 <= st.st_cut_slices(n, V) <= min(32, (V + 2047) // 2048)
