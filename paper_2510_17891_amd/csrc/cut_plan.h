@@ -18,10 +18,12 @@ constexpr int kCutTile = 2048;  // logits of a slice, at least
 constexpr int kCutUnits = 1024 + kCutSlices;
 
 // Slices per row of a call of M rows.  Two blocks per compute unit: every block clears, scans or flushes a histogram of its own.
-// Three, which is what the LDS of the third pass allows, where a block has enough of a long row (128 rows of 151936 entries at
-// 1.0 / 0.95 83.4 -> 79.0 us, at 0.6 / 0.95 58.5 -> 57.4; four 63.0; at 40 rows three 34.0 against 33.7).
+// Three, which is what the LDS of the third pass allows, where there are logits enough for them.  Two -> three, us at 0.6 / 0.95
+// and at 1.0 / 0.95: 128 rows of 151936 entries 61.3 -> 60.1 and 86.9 -> 83.2, 95 of 102400 (9.7 M logits) 45.9 -> 45.4 and 58.5
+// -> 54.6, 64 of 151936 (9.7 M) 42.7 -> 42.9 and 53.7 -> 53.0, 72 of 128000 (9.2 M) no difference; but 64 of 128000 (8.2 M) 40.4
+// -> 41.9 and 49.6 -> 49.8, 128 of 65536 (8.4 M) 42.2 -> 44.1 and 50.1 -> 51.9, 48 of 151936 (7.3 M) 39.2 -> 41.8 and 46.7 -> 48.3.
 inline int cut_slices(int M, int V) {
-  const int slices = (M >= 64 && V > 65536 ? 768 : 512) / M;
+  const int slices = ((long long)M * V >= 9000000 ? 768 : 512) / M;
   return std::max(1, std::min(std::min(slices, kCutSlices), (V + kCutTile - 1) / kCutTile));
 }
 

@@ -417,3 +417,7 @@ def test_truncated_sampling_keeps_the_units_of_every_row_of_up_to_2_18_logits(st
     for V in (4, 2048, 2052, 65536, 65540, 151936, 1 << 18, (1 << 22) - 4):
         for n in (1, 2, 16, 63, 64, 95, 96, 128, 511, 512, 513, 767, 768, 769, 1024):
             assert 1 <= st.st_cut_slices(n, V) <= min(32, (V + 2047) // 2048)
+    # three blocks per compute unit only from nine million logits on
+    assert [st.st_cut_slices(n, 151936) for n in (48, 59, 60, 64, 96, 128, 256)] == [10, 8, 12, 12, 8, 6, 3]
+    assert [st.st_cut_slices(n, 65536) for n in (64, 96, 128, 137, 138, 256)] == [8, 5, 4, 3, 5, 3]
+    assert st.st_cut_slices(64, 102400) == 8 and st.st_cut_slices(64, 128000) == 8 and st.st_cut_slices(1024, (1 << 22) - 4) == 1
