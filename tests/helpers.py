@@ -74,3 +74,28 @@ class ArgmaxCount:
     def summary(self):
         return (f"argmax agreement {self.decided_agree}/{self.decided} on rows with a margin above the logit tolerance, "
                 f"{self.agree}/{self.rows} on all rows")
+
+
+# Truncated sampling (mirrored from csrc/cut_plan.h; a CPU test compares them): slices per row, and units of 256 logits per slice.
+CUT_UNITS_KEPT = 1056
+CUT_UNITS_READ_ALL = 32  # units of a slice up to which it is read without a look at their largest logits
+CUT_SHAPES = [(252, 3), (8204, 2), (66052, 1), (66052, 3), (300, 9), (300000, 64),                  # (vocabulary, rows): read whole
+              (262404, 2), (66052, 64), (151936, 30), (151936, 128), (262144, 96)]                   # unit by unit
+
+
+def cut_slices(n, vocab):
+    return max(1, min((768 if n * vocab >= 9000000 else 512) // n, 32, (vocab + 2047) // 2048))
+
+
+def cut_groups(n, vocab):  # of four logits, per slice
+    return -(-(vocab // 4) // cut_slices(n, vocab))
+
+
+def cut_units(n, vocab):
+    return -(-cut_groups(n, vocab) // 64)
+
+
+def cut_by_units(n, vocab):
+    """Whether the third pass of such a call looks at the units' largest logits."""
+    u = cut_units(n, vocab)
+    return u > CUT_UNITS_READ_ALL and cut_slices(n, vocab) * u <= CUT_UNITS_KEPT

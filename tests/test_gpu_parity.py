@@ -9,7 +9,7 @@ import pytest
 import torch
 
 import rollout_inputs as ri
-from helpers import ArgmaxCount, dims_of, make_both, rel_inf, to_device
+from helpers import ArgmaxCount, CUT_SHAPES, cut_groups, cut_slices, dims_of, make_both, rel_inf, to_device
 from oracle import oracle as orc
 
 pytestmark = pytest.mark.gpu
@@ -32,6 +32,11 @@ def _sampler_model(amd, vocab, bf16):
         shape = dict(ri.SHAPES["tiny"], n_layers=1, vocab=vocab)
     w, _ = make_both(shape, 11)
     return amd.Rollout(shape, to_device(w), max_seqs=64, max_ctx=64, max_rows=16, kv_pages=8)
+
+
+def _truncated_model(amd, vocab, rows):
+    shape = dict(ri.SHAPES["tiny"], n_layers=1, hidden=8, n_q=1, n_kv=1, head_dim=8, ffn=8, vocab=vocab)  # only its sampler is used
+    return amd.Rollout(shape, to_device(make_both(shape, 11)[0]), max_seqs=rows, max_ctx=16, max_rows=rows, kv_pages=4)
 
 
 @pytest.mark.parametrize("vocab,bf16", [(4096, False), (151936, True), (1000, False)])
@@ -64,35 +69,74 @@ def test_sampler_bit_exact_and_logprob(amd, vocab, bf16):
     ro.close()
 
 
-@pytest.mark.parametrize("vocab,n", [(252, 3), (8204, 2), (66052, 1), (66052, 3), (262404, 2), (300, 9)])
+@pytest.mark.parametrize("vocab,n", CUT_SHAPES)
 def test_truncated_sampling_reads_the_units_it_needs(amd, vocab, n):
-    """Kept tokens at the first and last place of units of 256 logits, of slices and of the row, among logits far below; a NaN
-    and infinities beside them; more units than a row keeps maxima of.  Token and log-probability as in the oracle."""
-    ro = _sampler_model(amd, vocab, False)
+    """Kept tokens at the first and last place of units of 256 logits, of slices and of the row, among logits far below;
+    units that are masked altogether; forced tokens in units that are read and in ones that are not.  Token and
+    log-probability as in the oracle, in shapes whose rows are read whole and in ones that are read unit by unit."""
+    ro = _truncated_model(amd, vocab, n)
     z = ri.normal((n, vocab), 0.5, 7, 73) - 30.0
-    at = [i for i in (0, 3, 255, 256, 511, 8191, 8192, 65535, 65536, vocab - 257, vocab - 1) if 0 <= i < vocab]
+    edge = [4 * cut_groups(n, vocab) * k for k in range(cut_slices(n, vocab))]  # of slices
+    last_unit = edge[-1] + (vocab - 1 - edge[-1]) // 256 * 256
+    at = {0, 3, 255, 256, 511, 8191, 8192, 65535, 65536, vocab - 257, vocab - 1, last_unit}
+    for e in edge[1:3] + edge[-1:]:
+        at |= {e - 1, e, e + 255, e + 256}
+    at = sorted(i for i in at if 0 <= i < vocab)
+    rows = range(n) if n < 10 else (0, 1, 2, n // 2, n - 1)
     for r in range(n):
         for k, i in enumerate(at):
             z[r, i] = 3.0 - 0.3 * ((k * 7 + r) % len(at))
     z[0, vocab // 2] = float("-inf")
+    if n > 1:
+        quiet = [u for u in range(0, vocab - 255, 256) if not any(u <= i < u + 256 for i in at)]
+        for u in quiet[::3]:
+            z[1, u:u + 256] = float("-inf")
+        for u in quiet[1::3]:
+            z[1, u:u + 256] = -1e9
     zd = z.to(DEV)
+    behind = next((i for i in range(600, vocab, 256) if not any(i // 256 == j // 256 for j in at)), 5)  # in a unit without a kept token
     for T, top_k, top_p in ((0.7, 0, 0.9), (1.0, 5, 0.0), (1.0, len(at) + 3, 0.999), (0.6, 0, 0.3)):
-        for f in (None, at[-1], 5):
+        for f in (None, at[-1], 5, behind):
             forced = None if f is None else torch.full((n,), f, dtype=torch.int32, device=DEV)
             tok, lp = ro.rl_sample_logits(zd, list(range(n)), [9] * n, T, 21, forced=forced, top_k=top_k, top_p=top_p)
             torch.cuda.synchronize()
-            for r in range(n):
+            for r in rows:
                 t_ref, lp_ref, _ = orc.sample_truncated(z[r].numpy(), T, top_k, top_p, 21, r, 9, forced=-1 if f is None else f)
                 assert int(tok[r]) == t_ref, (T, top_k, top_p, r, f)
                 if np.isfinite(lp_ref):
                     assert abs(float(lp[r]) - lp_ref) < 1e-5 * max(1.0, abs(lp_ref)), (T, top_k, top_p, r, f)
                 else:
                     assert float(lp[r]) == lp_ref
-    zd[:, 77] = float("nan")  # its unit is read all the same; a NaN has no weight and is not drawn
-    a = ro.rl_sample_logits(zd, list(range(n)), [9] * n, 0.7, 21, top_p=0.9)
-    zd[:, 77] = -60.0
-    b = ro.rl_sample_logits(zd, list(range(n)), [9] * n, 0.7, 21, top_p=0.9)
-    assert torch.equal(a[0], b[0]) or bool(torch.isnan(a[1]).all())
+    ro.close()
+
+
+@pytest.mark.parametrize("vocab,n", [(8204, 2), (66052, 64), (151936, 128)])
+def test_truncated_sampling_with_logits_that_are_not_numbers(amd, vocab, n):
+    """A NaN stands at the head of the order (its sign bit clear), so every cut keeps it: it is not drawn, and the
+    log-probability of whatever is drawn beside it is NaN.  A count finds it in a unit whose numbers all lie behind the cut; a
+    mass has no bins then and keeps every token.  Infinities beside it change neither."""
+    ro = _truncated_model(amd, vocab, n)
+    z = ri.normal((n, vocab), 1.0, 7, 74)
+    z[:, 512:768] = -40.0                     # a unit that a cut of a few tokens does not reach
+    odd, clean = z.clone(), z.clone()
+    odd[:, 600] = float("nan")
+    odd[1:, 601] = float("-inf")
+    clean[:, 600] = clean[1:, 601] = float("-inf")
+    od, seqs, poss = odd.to(DEV), list(range(n)), [9] * n
+    rows = sorted({0, 1, n // 2, n - 1})
+    for T, top_k, top_p in ((1.0, 6, 0.0), (0.7, 0, 0.9)):
+        tok, lp = ro.rl_sample_logits(od, seqs, poss, T, 21, top_k=top_k, top_p=top_p)
+        torch.cuda.synchronize()
+        assert bool(torch.isnan(lp).all()) and not bool((tok == 600).any()), (T, top_k, top_p)
+        for r in rows:
+            if top_k:                         # the NaN takes one of the six places
+                t_ref, _, _ = orc.sample_truncated(clean[r].numpy(), T, top_k - 1, 0.0, 21, r, 9)
+            else:
+                t_ref, _ = orc.sample(clean[r].numpy(), T, 21, r, 9)
+            assert int(tok[r]) == t_ref, (T, top_k, top_p, r)
+        for r in rows:                        # the row alone, which is read whole
+            one = ro.rl_sample_logits(od[r:r + 1], [r], [9], T, 21, top_k=top_k, top_p=top_p)
+            assert int(one[0][0]) == int(tok[r]) and bool(torch.isnan(one[1][0]))
     ro.close()
 
 
@@ -1746,8 +1790,7 @@ def test_truncated_sampler_masked_tied_and_crowded_rows(amd):
 def test_truncated_sampler_crowds_that_fill_whole_units(amd, V, n):
     """A top-k cut among so many equal or nearly equal logits that a wave finds one to four whole units of 256 of them in
     the cut's bin: with what fits the list, with what does not, and with units that only some of the tokens fill."""
-    ro = amd.Rollout(dict(ri.SHAPES["tiny"], n_layers=1, vocab=V), to_device(make_both(dict(ri.SHAPES["tiny"], n_layers=1, vocab=V), 11)[0]),
-                     max_seqs=n, max_ctx=64, max_rows=n, kv_pages=8)
+    ro = _truncated_model(amd, V, n)
     z = ri.normal((n, V), 1.0, 8, 76)
     z[0, 10:] = -1e9                          # masks that the cut reaches
     z[1, 10:] = float("-inf")

@@ -6,6 +6,8 @@ import subprocess
 
 import pytest
 
+import helpers as h
+
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 CSRC = os.path.join(ROOT, "paper_2510_17891_amd", "csrc")
 
@@ -421,3 +423,13 @@ def test_truncated_sampling_keeps_the_units_of_every_row_of_up_to_2_18_logits(st
     assert [st.st_cut_slices(n, 151936) for n in (48, 59, 60, 64, 96, 128, 256)] == [10, 8, 12, 12, 8, 6, 3]
     assert [st.st_cut_slices(n, 65536) for n in (64, 96, 128, 137, 138, 256)] == [8, 5, 4, 3, 5, 3]
     assert st.st_cut_slices(64, 102400) == 8 and st.st_cut_slices(64, 128000) == 8 and st.st_cut_slices(1024, (1 << 22) - 4) == 1
+
+
+def test_truncated_sampling_shapes_of_the_gpu_tests_reach_both_ways_of_the_third_pass(st):
+    """The slices that the GPU tests count on are the library's, and their shapes lie on both sides of the unit maxima."""
+    for V in (4, 252, 2052, 40004, 65536, 66052, 151936, 262144, 262404, 300000, (1 << 22) - 4):
+        for n in (1, 2, 3, 9, 16, 30, 60, 64, 96, 128, 150, 513, 1024):
+            assert h.cut_slices(n, V) == st.st_cut_slices(n, V), (V, n)
+            assert h.cut_units(n, V) == st.st_cut_units(V, st.st_cut_slices(n, V))
+            assert (h.cut_slices(n, V) * h.cut_units(n, V) <= h.CUT_UNITS_KEPT) == (st.st_cut_keeps_units(V, st.st_cut_slices(n, V)) == 1)
+    assert [h.cut_by_units(n, V) for V, n in h.CUT_SHAPES] == [False] * 6 + [True] * 5
