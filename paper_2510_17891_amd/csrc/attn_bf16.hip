@@ -200,13 +200,15 @@ __device__ __forceinline__ unsigned segs_with_keys(int n_it, int n_seg) {
 // order; the lane owns dims 2*lane, 2*lane+1.  o_ptr(c) -> O(128), ml_ptr(c) -> (max, sum) of segment c (LDS or
 // workspace); all loads are issued before the arithmetic.  Returns the two normalised outputs packed as f16 (the operand type
 // of the output projection).
-template <typename F, typename G>
+// kMost: segments at most, known to the compiler: with sixteen in the place of the four of a window set, whose rows are
+// merged one after another, a launch over 1024 rows of up to 1024 keys takes 62 us instead of 54.
+template <int kMost, typename F, typename G>
 __device__ __forceinline__ uint32_t merge_short(F o_ptr, G ml_ptr, int n_seg, int n_it, int lane) {
   const unsigned with_keys = segs_with_keys(n_it, n_seg);
-  float mx[kLdsSegs], lx[kLdsSegs];
-  float2 vx[kLdsSegs];
+  float mx[kMost], lx[kMost];
+  float2 vx[kMost];
 #pragma unroll
-  for (int c = 0; c < kLdsSegs; ++c) {
+  for (int c = 0; c < kMost; ++c) {
     mx[c] = -INFINITY;  // marks an absent or empty segment (nothing was written for it)
     lx[c] = 0.f;
     vx[c] = make_float2(0.f, 0.f);
@@ -219,10 +221,10 @@ __device__ __forceinline__ uint32_t merge_short(F o_ptr, G ml_ptr, int n_seg, in
   }
   float M = -INFINITY;
 #pragma unroll
-  for (int c = 0; c < kLdsSegs; ++c) M = fmaxf(M, mx[c]);
+  for (int c = 0; c < kMost; ++c) M = fmaxf(M, mx[c]);
   float o0 = 0.f, o1 = 0.f, den = 0.f;
 #pragma unroll
-  for (int c = 0; c < kLdsSegs; ++c) {
+  for (int c = 0; c < kMost; ++c) {
     if (mx[c] != -INFINITY) {  // a segment with keys has a finite maximum
       const float w = __expf(mx[c] - M);
       den = fmaf(w, lx[c], den);
@@ -286,10 +288,14 @@ __global__ __launch_bounds__(256, KV8 ? 3 : 2) void attn_decode_bf16_kernel(cons
     const AttnShared* sh = shared + (blockIdx.y - n_rows);
     n_members = sh->n_rows;
     shared_segs = sh->n_segs;
-    is_pack = shared_segs == 0;
-    if (is_pack && (blockIdx.z > 0 || n_members == 0)) return;  // block-uniform
-    r = __builtin_amdgcn_readfirstlane(sh->rows[is_pack ? uw : 0]);
-    pack_seg = __builtin_amdgcn_readfirstlane(sh->rows[kAttnPackSegs + uw]);
+    if constexpr (APPEND) {  // only decode steps have packs
+      is_pack = shared_segs == 0;
+      if (is_pack && (blockIdx.z > 0 || n_members == 0)) return;  // block-uniform
+      r = __builtin_amdgcn_readfirstlane(sh->rows[is_pack ? uw : 0]);
+      pack_seg = __builtin_amdgcn_readfirstlane(sh->rows[kAttnPackSegs + uw]);
+    } else {
+      r = sh->rows[0];
+    }
 #pragma unroll
     for (int c = 0; c < 2; ++c) {
       const int mj = (j + 16 * c) / group;
@@ -344,13 +350,18 @@ __global__ __launch_bounds__(256, KV8 ? 3 : 2) void attn_decode_bf16_kernel(cons
   // pages of its segment.
   const int page0 = is_pack ? uw * kPackPages - 2 * it_begin : 0;
   const int32_t* const bt = block_table + (size_t)rm.seq * max_blocks;
-  // The keys and values of the wave's first step are requested before the queries are formed: their pages are looked up
+  // APPEND: the keys and values of the wave's first step are requested before the queries are formed: their pages are looked up
   // directly, and they arrive while the queries are summed, normalised and rotated (a wave without steps asks for what
   // its neighbour asks for).  The list's first 256 entries are requested before them and stored behind them, so that
   // nothing in between waits for the keys; for the same reason the barriers up to the first step order LDS alone.
-  const int first_a = __builtin_amdgcn_readfirstlane(bt[min(2 * it_begin, n_blk - 1)]);
-  const int first_b = __builtin_amdgcn_readfirstlane(bt[min(2 * it_begin + 1, n_blk - 1)]);
-  const int page_early = bt[min(is_pack ? 2 * it_begin + lane : (int)threadIdx.x, n_blk - 1)];
+  // Finished queries are one load away, and keys asked for ahead of them only make them wait (1024 rows of up to 1024 keys
+  // 54 -> 52 us without).
+  int first_a = 0, first_b = 0, page_early = 0;
+  if constexpr (APPEND) {
+    first_a = __builtin_amdgcn_readfirstlane(bt[min(2 * it_begin, n_blk - 1)]);
+    first_b = __builtin_amdgcn_readfirstlane(bt[min(2 * it_begin + 1, n_blk - 1)]);
+    page_early = bt[min(is_pack ? 2 * it_begin + lane : (int)threadIdx.x, n_blk - 1)];
+  }
   auto put_pages = [&]() __attribute__((always_inline)) {
     if (is_pack) {
       if (lane < kPackPages) pages[uw * kPackPages + lane] = page_early;
@@ -366,11 +377,8 @@ __global__ __launch_bounds__(256, KV8 ? 3 : 2) void attn_decode_bf16_kernel(cons
   };
   typedef typename std::conditional<KV8, PagePair8, PagePair>::type Buf;  // registers of a step as loaded
   Buf pa;
-  if (!APPEND) {
-    load_pair(pa, kb, first_a, first_b, n_kv, lane, false);
-    __builtin_amdgcn_sched_barrier(0);
-    put_pages();
-  }
+  if constexpr (!APPEND)
+    for (int i = threadIdx.x; i <= n_blk; i += 256) pages[i] = bt[min(i, n_blk - 1)];
 
   // ---- APPEND: queries of this block's columns into LDS, the row's new key and value for the appending wave ----
   bool appends = false;  // wave-uniform: this wave owns the row's last step and with it the new key and value
@@ -810,7 +818,7 @@ __global__ __launch_bounds__(256, KV8 ? 3 : 2) void attn_decode_bf16_kernel(cons
     constexpr bool kRow = decltype(ng)::value == 1;  // only a row block appends
     if (it_begin < it_end) {
       Buf pb;
-      if constexpr (!kRow) fetch(pa, it_begin);  // once more, from the caches: there are no registers to hold it from above
+      if constexpr (!APPEND || !kRow) fetch(pa, it_begin);  // a wide set: once more, from the caches, for want of registers
       int it = it_begin;
       for (; it + 1 < it_end; it += 2) {
         fetch(pb, it + 1);
@@ -858,7 +866,7 @@ __global__ __launch_bounds__(256, KV8 ? 3 : 2) void attn_decode_bf16_kernel(cons
     for (int c = wave; c < n_cols; c += 4) {
       const int head = hk * group + c % group;
       const float* p = lds_part + (size_t)c * n_seg * kPartStride;
-      const uint32_t o2 = merge_short([&](int e) { return p + (size_t)e * kPartStride; },
+      const uint32_t o2 = merge_short<4>([&](int e) { return p + (size_t)e * kPartStride; },
                                       [&](int e) { return p + (size_t)e * kPartStride + kD; }, n_seg, n_it, lane);
       *(uint32_t*)(o_out + frag_offset(sh->rows[c / group], head * kD + 2 * lane, (n_q * kD) >> 6)) = o2;
     }
@@ -874,7 +882,7 @@ __global__ __launch_bounds__(256, KV8 ? 3 : 2) void attn_decode_bf16_kernel(cons
   for (int hh = wave; hh < group; hh += 4) {
     const int head = hk * group + hh;
     const float* p = lds_part + (size_t)hh * n_seg * kPartStride;
-    const uint32_t o2 = merge_short([&](int c) { return p + (size_t)c * kPartStride; },
+    const uint32_t o2 = merge_short<kLdsSegs>([&](int c) { return p + (size_t)c * kPartStride; },
                                     [&](int c) { return p + (size_t)c * kPartStride + kD; }, n_seg, n_it, lane);
     *(uint32_t*)(o_out + frag_offset(r, head * kD + 2 * lane, (n_q * kD) >> 6)) = o2;
   }
@@ -897,7 +905,7 @@ __global__ __launch_bounds__(256) void attn_merge_bf16_kernel(const float* __res
   if (n_seg <= kLdsSegs) {
     if (!skip_segs || skip_segs[r] == 0) return;  // finished by its own block
     if (n_seg <= 4 && skip_segs[r] == n_seg) return;  // ... or by that of a set that covers all its segments
-    const uint32_t o2 = merge_short([&](int c) { return p + part_o(max_segs, c); }, [&](int c) { return p + part_ml(max_segs, c); },
+    const uint32_t o2 = merge_short<kLdsSegs>([&](int c) { return p + part_o(max_segs, c); }, [&](int c) { return p + part_ml(max_segs, c); },
                                     n_seg, (ctx + 31) >> 5, lane);
     *(uint32_t*)(o_out + frag_offset(r, head * kD + 2 * lane, (n_q * kD) >> 6)) = o2;
     return;
