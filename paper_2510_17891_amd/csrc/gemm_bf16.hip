@@ -126,8 +126,8 @@ __device__ __forceinline__ void store_block(const float (&sum)[2][16], int m, in
           *(float4*)(se.logits_out + (size_t)m * N + n0) =
               make_float4(sum[nb][4 * q], sum[nb][4 * q + 1], sum[nb][4 * q + 2], sum[nb][4 * q + 3]);
       }
-    best = better(best, shfl_xor_best(best, 32));  // the other half of this row's 64 entries
-    lse_merge(lm, ls, lane_xor(lm, 32), lane_xor(ls, 32));
+    best = best_of_lanes(best, 32);  // the other half of this row's 64 entries
+    lse_merge_lanes(lm, ls, 32);
     if (hb == 0) {
       float* p = se.part + ((size_t)m * (N >> 6) + tile) * kSamplePartFloats;
       *(float4*)p = make_float4(best.y, __int_as_float(best.idx), best.z, 0.f);

@@ -45,8 +45,8 @@ __global__ __launch_bounds__(256) void sample_stage1_kernel(const float* __restr
     }
   }
   each_mask([&](int o) __attribute__((always_inline)) {
-    best = better(best, shfl_xor_best(best, o));
-    lse_merge(m, s, lane_xor(m, o), lane_xor(s, o));
+    best = best_of_lanes(best, o);
+    lse_merge_lanes(m, s, o);
   });
   const int wave = threadIdx.x >> 6;
   if ((threadIdx.x & 63) == 0) { sh_y[wave] = best.y; sh_i[wave] = best.idx; sh_z[wave] = best.z; sh_m[wave] = m; sh_s[wave] = s; }
@@ -98,8 +98,8 @@ __global__ __launch_bounds__(1024) void sample_row_kernel(const float* __restric
     }
   }
   const auto merge = [&](int o) __attribute__((always_inline)) {
-    best = better(best, shfl_xor_best(best, o));
-    lse_merge(m, s, lane_xor(m, o), lane_xor(s, o));
+    best = best_of_lanes(best, o);
+    lse_merge_lanes(m, s, o);
   };
   each_mask(merge);
   if (lane == 0) { sh_y[wave] = best.y; sh_i[wave] = best.idx; sh_z[wave] = best.z; sh_m[wave] = m; sh_s[wave] = s; }
@@ -140,8 +140,8 @@ __global__ __launch_bounds__(1024) void sample_stage2_kernel(const float* __rest
     lse_merge(m, s, b.x, b.y);
   }
   each_mask([&](int o) __attribute__((always_inline)) {
-    best = better(best, shfl_xor_best(best, o));
-    lse_merge(m, s, lane_xor(m, o), lane_xor(s, o));
+    best = best_of_lanes(best, o);
+    lse_merge_lanes(m, s, o);
   });
   if (lane == 0) { sh_y[wave] = best.y; sh_i[wave] = best.idx; sh_z[wave] = best.z; sh_m[wave] = m; sh_s[wave] = s; }
   __syncthreads();
@@ -569,7 +569,7 @@ __device__ __forceinline__ Draw empty_draw() { return Draw{Best{-INFINITY, -1, 0
 template <int kThreads>
 __device__ __forceinline__ Draw block_draw(Draw d, Draw (&sh)[kThreads / 64]) {
   each_mask([&](int o) __attribute__((always_inline)) {
-    d.best = better(d.best, shfl_xor_best(d.best, o));
+    d.best = best_of_lanes(d.best, o);
     d.sum = Draw::plus(d.sum, lane_xor(d.sum, o));
   });
   if ((threadIdx.x & 63) == 0) sh[threadIdx.x >> 6] = d;

