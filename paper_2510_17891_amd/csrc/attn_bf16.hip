@@ -351,8 +351,8 @@ __global__ __launch_bounds__(256, KV8 ? 3 : 2) void attn_decode_bf16_kernel(cons
   const int page0 = is_pack ? uw * kPackPages - 2 * it_begin : 0;
   const int32_t* const bt = block_table + (size_t)rm.seq * max_blocks;
   // APPEND: the keys and values of the wave's first step are requested before the queries are formed: their pages are looked up
-  // directly, and they arrive while the queries are summed, normalised and rotated (a wave without steps asks for what
-  // its neighbour asks for).  The list's first 256 entries are requested before them and stored behind them, so that
+  // directly, and they arrive while the queries are summed, normalised and rotated (a wave without steps asks for
+  // nothing: 128 rows of 40 keys 21.4 us when it asked for what its neighbour asks for, 20.1 now).  The list's first 256 entries are requested before them and stored behind them, so that
   // nothing in between waits for the keys; for the same reason the barriers up to the first step order LDS alone.
   // Finished queries are one load away, and keys asked for ahead of them only make them wait (1024 rows of up to 1024 keys
   // 54 -> 52 us without).
@@ -451,7 +451,7 @@ __global__ __launch_bounds__(256, KV8 ? 3 : 2) void attn_decode_bf16_kernel(cons
       }
     }
     __builtin_amdgcn_sched_barrier(0);
-    load_pair(pa, kb, first_a, first_b, n_kv, lane, false);
+    load_pair(pa, kb, first_a, first_b, n_kv, lane, it_begin >= it_end);
     __builtin_amdgcn_sched_barrier(0);
     // Everything loaded above is first touched below this line: the empty statements keep the compiler from moving
     // the arithmetic (and with it the waits) up between the loads.
