@@ -104,8 +104,8 @@ void compute_layout(const rl_model_config& c, Layout* L) {
   L->max_segs = attn_bf16_max_segments((int)c.max_ctx);
   L->n_tiles = (int)((V + kSampleTile - 1) / kSampleTile);
   L->slot_upd = align_up(R * sizeof(RowMeta));
-  L->slot_tok = L->slot_upd + align_up(R * 3 * sizeof(int32_t));
-  L->slot_skip = L->slot_tok + align_up(R * sizeof(int32_t));
+  L->slot_tok = L->slot_upd + align_up(R * 2 * sizeof(int32_t));  // pairs of a row
+  L->slot_skip = L->slot_tok + align_up(R * sizeof(int32_t));  // tokens: read from the host side, by the first kernel alone
   L->slot_sets = L->slot_skip + align_up(R * sizeof(int32_t));
   L->slot_tail = L->slot_sets + align_up(R * sizeof(AttnShared));  // window sets: up to one per row
   L->slot_head = L->slot_tail + align_up(R * sizeof(RowMeta));
@@ -428,7 +428,7 @@ rl_status admit_decode(rl_model* m, int32_t n, const int32_t* seq_ids) {
     need += T.pages_missing(s, T.len(s) + 1);
   }
   if (need > T.free_pages()) return fail(RL_ERR_KV_FULL, "need %lld pages, %lld free", (long long)need, (long long)T.free_pages());
-  for (int i = 0; i < n; ++i) T.reserve(seq_ids[i], T.len(seq_ids[i]) + 1, nullptr);
+  for (int i = 0; i < n; ++i) T.reserve(seq_ids[i], T.len(seq_ids[i]) + 1);
   return RL_OK;
 }
 
@@ -939,7 +939,7 @@ static rl_status fork_seqs(rl_model* m, hipStream_t st, const std::vector<Fork>&
     T.activate(f.dst);
     T.share_prefix(f.dst, f.src, full);
     const bool partial = f.len % SeqTable::kBlock != 0;
-    if (partial) T.reserve(f.dst, f.len, nullptr);
+    if (partial) T.reserve(f.dst, f.len);
     if (f.len == 0) continue;
     batch.f[batch.n++] = ForkBatch::One{f.src, f.dst, full, partial ? T.pages(f.dst)[full] : -1};
     if (batch.n == kForkBatch) flush();
@@ -985,7 +985,7 @@ static rl_status prefill_impl(rl_model* m, hipStream_t st, int32_t n_prompts, in
   for (int i = 0; i < n_prompts; ++i) {
     const int32_t s = seq_ids[i * group];
     T.activate(s);
-    T.reserve(s, prompt_lens[i], nullptr);
+    T.reserve(s, prompt_lens[i]);
   }
 
   // rows in (prompt, position) order, cut into chunks of R
@@ -1150,7 +1150,7 @@ rl_status rl_score(rl_model* m, void* stream, int32_t n, const int32_t* seq_ids,
   rl_status result = RL_OK;
   for (int i = 0; i < n; ++i) {
     T.activate(seq_ids[i]);
-    T.reserve(seq_ids[i], lens[i], nullptr);
+    T.reserve(seq_ids[i], lens[i]);
   }
   float* x = m->wsp<float>(m->lay.x);
   int32_t* tmp_tok = m->wsp<int32_t>(m->lay.tmp_tok);
@@ -1207,7 +1207,7 @@ static rl_status append_kv(rl_model* m, hipStream_t st, int32_t seq_id, int32_t 
   SeqTable& T = *m->table;
   const int32_t len = T.len(seq_id);
   const size_t have = T.pages(seq_id).size();
-  T.reserve(seq_id, len + n_tokens, nullptr);
+  T.reserve(seq_id, len + n_tokens);
   int32_t* bt_row = m->wsp<int32_t>(m->lay.block_table) + (size_t)seq_id * m->geo.max_blocks;
   if (n_tokens > 0) {
     const size_t now = T.pages(seq_id).size();

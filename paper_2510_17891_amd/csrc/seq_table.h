@@ -15,10 +15,6 @@
 
 namespace rl {
 
-struct PageGrant {
-  int32_t seq, block, page;
-};
-
 class SeqTable {
  public:
   static constexpr int kBlock = 16;
@@ -63,12 +59,11 @@ class SeqTable {
   }
 
   // Grow the page list of `s` to cover `tokens` tokens; the caller has checked free_pages().
-  void reserve(int32_t s, int tokens, std::vector<PageGrant>* grants) {
+  void reserve(int32_t s, int tokens) {
     int need = blocks_for(tokens);
     while ((int)pages_[s].size() < need) {
       const int32_t p = take_page(pages_[s].empty() ? -1 : pages_[s].back());
       ref_[p] = 1;
-      if (grants) grants->push_back(PageGrant{s, (int32_t)pages_[s].size(), p});
       pages_[s].push_back(p);
     }
   }

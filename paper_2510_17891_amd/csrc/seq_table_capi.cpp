@@ -21,17 +21,16 @@ void st_share_prefix(void* t, int dst, int src, int n_blocks) { ((rl::SeqTable*)
 int st_refcount(void* t, int page) { return ((rl::SeqTable*)t)->refcount(page); }
 int st_n_seq_pages(void* t, int s) { return (int)((rl::SeqTable*)t)->pages(s).size(); }
 int st_seq_page(void* t, int s, int i) { return ((rl::SeqTable*)t)->pages(s)[i]; }
-// returns the number of grants written (seq, block, page triples)
-int st_reserve(void* t, int s, int tokens, int* grants_out, int max_grants) {
-  std::vector<rl::PageGrant> g;
-  ((rl::SeqTable*)t)->reserve(s, tokens, &g);
-  int n = 0;
-  for (auto& x : g) {
-    if (n >= max_grants) break;
-    grants_out[3 * n] = x.seq; grants_out[3 * n + 1] = x.block; grants_out[3 * n + 2] = x.page;
-    ++n;
+// returns the number of pages added; what fits of them as (seq, block, page) triples
+int st_reserve(void* t, int s, int tokens, int* added_out, int max_added) {
+  auto* T = (rl::SeqTable*)t;
+  const int before = (int)T->pages(s).size();
+  T->reserve(s, tokens);
+  const std::vector<int32_t>& pages = T->pages(s);
+  for (int n = 0; n < max_added && before + n < (int)pages.size(); ++n) {
+    added_out[3 * n] = s; added_out[3 * n + 1] = before + n; added_out[3 * n + 2] = pages[before + n];
   }
-  return (int)g.size();
+  return (int)pages.size() - before;
 }
 
 long long st_prefix_id(void* t, int s) { return ((rl::SeqTable*)t)->prefix_id(s); }
