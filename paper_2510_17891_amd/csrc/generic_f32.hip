@@ -171,21 +171,25 @@ struct F32Append {
 };
 
 // One block of four waves per (row, q head), keys in tiles of 256: one key per thread for the scores; for the weighted
-// sum a thread owns VEC dims and every (256 / (d / VEC))-th key; online softmax across tiles.  d <= VEC * ND, d % VEC == 0.
+// sum a thread owns VEC dims and every (256 / (d / VEC))-th key; online softmax across tiles.  d <= 128, d % VEC == 0.
 // APPEND (one row per sequence): the block forms its query and the row's new key and value from the QKV projection, uses
 // the latter two from LDS, and the first head of the group writes them to the row's page.
-// What bounds it is the chain of round trips, not the bytes: a thread's key and its first kFirst values are requested
-// together, for the first tile before the query is formed (7.5 -> 6.8 us at 4 rows of 64 to 96 keys; 64 rows of 900 keys of
-// 62 dims, two layers, 364 -> 323; keys beyond the context repeat the last one and have no
-// weight, dims beyond d repeat the last ones and are not used), and there is one copy of everything, because a
-// block runs this code once, from a cold instruction cache.
+// What bounds it is the chain of round trips in small batches and the keys' way through the caches in large ones.  So the
+// pages are looked up and a thread's first kFirst values requested before the scores (for the first tile the pages, and the
+// values, before the query is formed); a key comes in pieces of ND loads in flight, which leaves the registers for three and
+// more blocks per compute unit; and everything that may be in a page is loaded from there, the new key and value replacing
+// it in registers, because a pointer that may lead to LDS as well as to memory makes every load wait for both.  Kernel
+// times (us) with such pointers -> with whole keys of up to 128 dims requested ahead of the query -> now: 4 rows of 70 keys of
+// 64 dims 7.6 -> 7.0 -> 6.8, of 250 12.1 -> 11.8 -> 9.6, of 1500 57.9 -> 47.8 -> 37.0; 4 rows of 250 keys of 128 dims 17.8 -> 19.0 -> 14.1,
+// of 126 dims 22.9 -> 28.1 -> 15.0; 64 rows of 600 keys of 64 dims 66 -> 69 -> 59, of 128 117 -> 131 -> 106, of 62 59 -> 53 -> 36.
+// Finished rows (scoring, prefill), whose values are not requested ahead: 64 rows of 600 keys of 128 dims 31 -> 50 -> 30, of 64 18 -> 22 -> 18.
 template <bool APPEND, int VEC, int ND>
-__global__ __launch_bounds__(256, 2) void attn_f32_kernel(const float* __restrict__ q, const RowMeta* __restrict__ rows,
+__global__ __launch_bounds__(256) void attn_f32_kernel(const float* __restrict__ q, const RowMeta* __restrict__ rows,
                                                        const int32_t* __restrict__ block_table, int max_blocks,
                                                        float* k_pool, float* v_pool, float* __restrict__ o_out, int n_q,
                                                        int n_kv, int d, float scale, F32Append ap) {
   typedef float vec_t __attribute__((ext_vector_type(VEC)));
-  constexpr int kFirst = 8;
+  constexpr int kFirst = 4;
   __shared__ __align__(16) float qs[128], kn[128], vn[128], ps[256], part[256 * VEC];
   __shared__ float red[8];
   const int h = blockIdx.x, r = blockIdx.y, tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
@@ -200,12 +204,16 @@ __global__ __launch_bounds__(256, 2) void attn_f32_kernel(const float* __restric
   vec_t acc = 0.f;
   float m_run = -INFINITY, l_run = 0.f;
   for (int kb = 0; kb < ctx; kb += 256) {
-    const int key = min(kb + tid, ctx - 1), k_page = bt[key >> 4];
+    const int key = min(kb + tid, ctx - 1);  // keys beyond the context repeat the last one and have no weight
+    const float* const kp = row_of(k_pool, key, bt[key >> 4]);
+    const bool has_keys = kb + 64 * wave < ctx;  // wave-uniform
     int v_key[kFirst], v_page[kFirst];
+    if constexpr (APPEND) {
 #pragma unroll
-    for (int i = 0; i < kFirst; ++i) {
-      v_key[i] = min(kb + grp + i * groups, ctx - 1);
-      v_page[i] = bt[v_key[i] >> 4];
+      for (int i = 0; i < kFirst; ++i) {
+        v_key[i] = min(kb + grp + i * groups, ctx - 1);
+        v_page[i] = bt[v_key[i] >> 4];
+      }
     }
     HeadPair hp;
     const bool forms = APPEND && kb == 0 && wave < 3;  // query, new key, new value: one wave each
@@ -216,13 +224,11 @@ __global__ __launch_bounds__(256, 2) void attn_f32_kernel(const float* __restric
       hp = head_pair_load<false>(ap.qkv + ((size_t)r * (n_q + 2 * n_kv) + head) * d, 1, 0, d, lane, wave < 2,
                                  ap.rope + (size_t)rm.pos * half, norm ? (wave == 0 ? ap.q_gain : ap.k_gain) : nullptr);
     }
-    vec_t kr[ND], vr[kFirst];
-    {
-      const float* kp = row_of(k_pool, key, k_page);
+    vec_t vr[kFirst];
+    if constexpr (APPEND) {
 #pragma unroll
-      for (int i = 0; i < ND; ++i) kr[i] = *(const vec_t*)(kp + min(i, nd - 1) * VEC);
-#pragma unroll
-      for (int i = 0; i < kFirst; ++i) vr[i] = *(const vec_t*)(row_of(v_pool, v_key[i], v_page[i]) + dim);
+      for (int i = 0; i < kFirst; ++i)
+        if (kb + i * groups < ctx) vr[i] = *(const vec_t*)(row_of(v_pool, v_key[i], v_page[i]) + dim);
     }
     if (kb == 0) {
       if (forms) {
@@ -242,14 +248,35 @@ __global__ __launch_bounds__(256, 2) void attn_f32_kernel(const float* __restric
         for (int i = tid; i < d; i += 256) qs[i] = q[((size_t)r * n_q + h) * d + i];
       __syncthreads();
     }
-    if (APPEND && key == rm.pos) {  // the new key is not in its page yet
-#pragma unroll
-      for (int i = 0; i < ND; ++i) kr[i] = *(const vec_t*)(kn + min(i, nd - 1) * VEC);
-    }
     vec_t dot = 0.f;
+    if constexpr (!APPEND) {
+      if (kb + tid < ctx) {
+#pragma unroll 8
+        for (int i = 0; i < d; i += VEC) dot += *(const vec_t*)(qs + i) * *(const vec_t*)(kp + i);
+      }
+    } else if (has_keys) {
+      vec_t kr[ND];
+      const auto load = [&](int first, int last) __attribute__((always_inline)) {  // pieces beyond `last` repeat it
 #pragma unroll
-    for (int i = 0; i < ND; ++i)
-      if (i < nd) dot += *(const vec_t*)(qs + i * VEC) * kr[i];
+        for (int i = 0; i < ND; ++i) kr[i] = *(const vec_t*)(kp + min(first + i, last) * VEC);
+        if (key == rm.pos) {  // the new key is not in its page yet
+#pragma unroll
+          for (int i = 0; i < ND; ++i) kr[i] = *(const vec_t*)(kn + min(first + i, last) * VEC);
+        }
+      };
+      int first = 0;
+      for (; first + ND <= nd; first += ND) {
+        load(first, first + ND - 1);
+#pragma unroll
+        for (int i = 0; i < ND; ++i) dot += *(const vec_t*)(qs + (first + i) * VEC) * kr[i];
+      }
+      if (first < nd) {
+        load(first, nd - 1);
+#pragma unroll
+        for (int i = 0; i < ND; ++i)
+          if (first + i < nd) dot += *(const vec_t*)(qs + (first + i) * VEC) * kr[i];
+      }
+    }
     float sc = dot[0];
 #pragma unroll
     for (int e = 1; e < VEC; ++e) sc += dot[e];
@@ -269,15 +296,19 @@ __global__ __launch_bounds__(256, 2) void attn_f32_kernel(const float* __restric
     acc *= alpha;
     if (grp < groups) {
       const int nk = min(256, ctx - kb);
+      if constexpr (APPEND) {
 #pragma unroll
-      for (int i = 0; i < kFirst; ++i) {
-        const int t = grp + i * groups;
-        if (t < nk) acc += ps[t] * (APPEND && kb + t == rm.pos ? *(const vec_t*)(vn + dim) : vr[i]);
+        for (int i = 0; i < kFirst; ++i) {
+          const int t = grp + i * groups;
+          if (t < nk) acc += ps[t] * (kb + t == rm.pos ? *(const vec_t*)(vn + dim) : vr[i]);
+        }
       }
 #pragma unroll 4
-      for (int t = grp + kFirst * groups; t < nk; t += groups) {
+      for (int t = grp + (APPEND ? kFirst * groups : 0); t < nk; t += groups) {
         const int kt = kb + t;
-        acc += ps[t] * *(const vec_t*)((APPEND && kt == rm.pos ? vn : row_of(v_pool, kt, bt[kt >> 4])) + dim);
+        vec_t v = *(const vec_t*)(row_of(v_pool, kt, bt[kt >> 4]) + dim);
+        if (APPEND && kt == rm.pos) v = *(const vec_t*)(vn + dim);
+        acc += ps[t] * v;
       }
     }
     __syncthreads();
@@ -342,11 +373,9 @@ void launch_attn_f32(hipStream_t s, const Geometry& g, const float* q, const Row
       attn_f32_kernel<false, VEC, ND><<<grid, 256, 0, s>>>(q, rows, block_table, g.max_blocks, (float*)k_pool_layer, \
                                                            (float*)v_pool_layer, o_out, g.n_q, g.n_kv, g.head_dim, scale, ap); \
   } while (0)
-  // the key registers of a thread: 64 floats for heads of up to 64 dims, 128 beyond
-  if (g.head_dim % 4 == 0 && g.head_dim <= 64) RL_ATTN_F32(4, 16);
-  else if (g.head_dim % 4 == 0) RL_ATTN_F32(4, 32);
-  else if (g.head_dim <= 64) RL_ATTN_F32(2, 32);  // an even head_dim: pairs keep the loads aligned
-  else RL_ATTN_F32(2, 64);
+  if (g.head_dim % 4 == 0 && g.head_dim <= 16) RL_ATTN_F32(4, 4);
+  else if (g.head_dim % 4 == 0) RL_ATTN_F32(4, 8);  // with sixteen loads in flight heads of 96 and 128 dims lose up to a fifth
+  else RL_ATTN_F32(2, 16);  // an even head_dim: pairs keep the loads aligned
 #undef RL_ATTN_F32
 }
 

@@ -1907,7 +1907,9 @@ def test_truncated_logprobs_have_the_same_bits_in_every_call_and_batch(amd):
 @pytest.mark.parametrize("over", [
     dict(head_dim=126), dict(head_dim=20, n_q=6, n_kv=2, hidden=520, ffn=72, qk_norm=0), dict(head_dim=128),
     # an odd number of heads and head_dim % 4 == 2: the O projection's rows are no multiple of four elements
-    dict(head_dim=126, n_q=3, n_kv=1), dict(head_dim=6, n_q=1, n_kv=1), dict(head_dim=18, n_q=5, n_kv=5, qk_norm=0)])
+    dict(head_dim=126, n_q=3, n_kv=1), dict(head_dim=6, n_q=1, n_kv=1), dict(head_dim=18, n_q=5, n_kv=5, qk_norm=0),
+    # pieces of a key that decode attention has in flight: less than one, one, one and a single load, several
+    dict(head_dim=12), dict(head_dim=16, n_q=8), dict(head_dim=32), dict(head_dim=34), dict(head_dim=36), dict(head_dim=96)])
 def test_f32_steps_for_other_head_dims_and_batch_sizes(amd, over):
     """The fp32 kernels at head dims whose rows are 8- or 16-byte aligned, widths that are no multiple of a wave's 256
     elements or of four, contexts beyond one tile of 256 keys, and 1, 4, 8 or more rows per launch: logits match the
