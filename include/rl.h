@@ -23,6 +23,10 @@
  *   - `stream` is a hipStream_t passed as void*.  Calls enqueue work on it and
  *     return; outputs are valid once the stream has been synchronised.  Host
  *     arrays passed to a call may be reused as soon as the call returns.
+ *   - Calls that take a model (or its decode graph) share the model's workspace, KV pool and pinned metadata, so they
+ *     have to be ordered one after another: made by one thread at a time and enqueued on one stream, or on several
+ *     streams of which each waits (hipStreamWaitEvent) for the call before.  Nothing of a call's is safe to reuse
+ *     from another stream before that, the library's own metadata included.
  *   - A sequence is named by a caller-chosen id in [0, max_seqs).  The id is
  *     also the stream id of the sampler's random numbers.  Group member j of
  *     prompt i is simply a distinct id (e.g. i*G + j).
@@ -278,7 +282,7 @@ rl_status rl_sample_logits(rl_model* m, void* stream, int32_t n, const float* lo
  *   forced  device[n] or NULL;  out_tokens device[n] int32;  out_logprobs device[n] fp32
  * Limits: n <= 256 and n * ceil(vocab / 2048) <= 20480 (a 151 936-entry vocabulary at 256 rows needs 19 200);
  * beyond them RL_ERR_INVALID_ARG.  top_k / top_p cuts are not available here (RL_ERR_UNSUPPORTED): they need
- * 164 KB of histograms per row.  All calls on one GPU share that GPU's array: calls that overlap on one GPU
+ * 85 KB of histograms and lists per row.  All calls on one GPU share that GPU's array: calls that overlap on one GPU
  * (different streams or threads) race; calls on one stream are ordered.  Nothing in the array has to be cleared
  * between calls.
  */
@@ -394,8 +398,9 @@ rl_status rl_debug_shuffle_free_pages(rl_model* m, uint64_t seed);
  */
 rl_status rl_debug_share_attention(rl_model* m, int32_t on);
 /* on = 2: as on = 1, and the sets are as large as the kernel allows (bf16 pages: two 16-column operands side by
- * side, i.e. up to 32 / (query heads per kv head) rows) in every call; on = 3: a single operand in every call.
- * By default the size of the call decides.  No bit of any result depends on the choice. */
+ * side, i.e. up to 32 / (query heads per kv head) rows) and the one to three segments that a row's sets leave are
+ * packed four to a block in every call; on = 3: a single operand and no packs in any call.  By default the size of
+ * the call decides both.  No bit of any result depends on the choice. */
 
 /*
  * Test aid: switch off (on = 0) or on again (the default) the fused form of a bf16 decode step in which the
@@ -421,9 +426,10 @@ rl_status rl_debug_attention_split(rl_model* m, int32_t segs_per_block);
  */
 rl_status rl_profile_enable(rl_model* m, int32_t on);
 /* Host microseconds that rl_decode_step spent since the last read (always collected): admission checks (ids, pages),
- * building and uploading the rows / page grants / shared-attention plan, enqueueing the kernels, and -- apart from
- * those -- waiting for a metadata slot that the device has not consumed yet (the device is then 62 calls behind the
- * host; calls of other entry points that take a slot add to this figure too); and the number of calls. */
+ * building the rows and the shared-attention plan, enqueueing the kernels, and -- apart from those -- waiting for a
+ * metadata slot that the device has not consumed yet (calls of other entry points that take a slot add to this figure
+ * too); and the number of calls.  There are 62 slots, and one event covers twelve calls: the host waits when the group
+ * of calls that last used the slot, 51 to 62 calls back, has not finished as a whole. */
 rl_status rl_profile_host_read(rl_model* m, double* admit_us, double* meta_us, double* launch_us, double* wait_us,
                                int64_t* calls);
 rl_status rl_profile_read(rl_model* m, int32_t n_max, const char** names_out, double* ms_out,

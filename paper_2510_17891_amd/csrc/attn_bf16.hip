@@ -39,8 +39,9 @@
 // one wave per segment: at 1024 rows the merge launch (20 us) and 68 MB of partials written and read back are gone.
 //
 // What the rows of sets have left behind the shared segments is often one segment, i.e. work for one wave.  In large
-// launches these segments are packed four to a block, one per wave (plan_packs): a layer of 128 rows with 1024 of 1100
-// keys shared 182 -> 167 us, of 512 rows 462 -> 443; with two or three segments left no faster and no slower.
+// launches these segments are packed four to a block, one per wave (plan_packs).  With that and what follows, the launch over
+// 128 rows with 1024 of 1100 keys shared takes 34 us instead of 48, over 512 rows 132 instead of 151; with two or three
+// segments left packs are no faster and no slower.
 // A block of a short context spends as long on its way to the first step as on its steps.  So the first step's keys are
 // requested before the queries are formed, the queries lie in LDS with a stride that spreads 16 columns over the banks, one
 // split is not loaded four times over, segment bounds take no divisions, and a step exists in three copies instead of five
@@ -596,8 +597,8 @@ __global__ __launch_bounds__(256, KV8 ? 3 : 2) void attn_decode_bf16_kernel(cons
   int boundary = set_merges ? -1 : seg < seg_end ? seg_begin(seg + 1) : it_end;
 
   // One step = 32 keys (two pages): scores, online softmax, P*V; at a segment end the partial is written.  In small batches
-  // a wave's chain of steps is what the launch lasts, and a step is bound by its own instructions (about 1.4 us; fetching
-  // the keys ahead into L2 changed nothing).  One-instruction bf16 conversions, masks in the last step only and no
+  // a wave's chain of steps is what the launch lasts: about 1.05 us each, 0.7 with the pages in a cache, since a compute unit
+  // draws some 63 GB/s from memory however many loads are in flight.  One-instruction bf16 conversions, masks in the last step only and no
   // rescaling by one, all three together: 19.2 -> 17.8 us at one row of 1000 keys, 17.0 -> 16.6 at 32 rows, fp8 pages
   // 695 -> 685 at 256 rows -- of a layer or a step no more than its runs differ by.
   // NG = 2: the same for both column groups of a wide set, from the same key and value registers.

@@ -181,9 +181,9 @@ __global__ __launch_bounds__(1024) void sample_stage2_kernel(const float* __rest
 // What bounds it: the passes' arithmetic per token (order keys, weights, LDS additions), then the finishing blocks, one per
 // row.  A radix selection over the digits of the key took five passes, each with its own scan, and a draw over every
 // entry.  Rows of 151936 entries, that selection -> these passes: 0.6 / 0.95 at 128 rows 217 -> 57 us, at one row 65 -> 26;
-// top-k 50 198 -> 52 and 56 -> 31, also with masked tokens or logits rounded to 16 bits; a top-k cut among masked tokens
-// 323 -> 97 and 58 -> 41; equal logits 360 -> 78 and 63 -> 26 (the cut follows from their number).  Slower at few rows is a
-// crowd 30000 times narrower than the distance of an outlier above it (top-k: 197 -> 140 at 128 rows, 56 -> 76 at one):
+// top-k 50 198 -> 52 and 56 -> 28, also with masked tokens or logits rounded to 16 bits; a top-k cut among masked tokens
+// 323 -> 87 and 58 -> 38; equal logits 360 -> 70 and 63 -> 23 (the cut follows from their number).  Slower at few rows is a
+// crowd 30000 times narrower than the distance of an outlier above it (top-k: 197 -> 132 at 128 rows, 56 -> 76 at one):
 // steps that follow such a crowd cost plain rows 5 % at 256 rows.
 // ------------------------------------------------------------------------------------------------
 constexpr int kCutBins = 1024;
@@ -521,7 +521,7 @@ __global__ __launch_bounds__(kCutThreads) void cut_hist_kernel(const float* __re
     });
   };
   // The scan is bound by its instructions (45 per token): the usual row does without the branch for weights beyond one and
-  // without a cut before this one, 20.4 -> 18 us at 128 rows.  Largest scores below 2^20 are off by less than a sixteenth
+  // without a cut before this one, 20.4 -> 18 us at 128 rows (16.3 in the present slices).  Largest scores below 2^20 are off by less than a sixteenth
   // when rounded: no score exceeds them by more.
   if (!kMass || (fabsf(cb.s_max) <= 0x1p20f && !use_k)) scan(std::true_type{}, std::true_type{});  // block-uniform
   else scan(std::false_type{}, std::false_type{});
@@ -672,7 +672,8 @@ __global__ __launch_bounds__(kCutThreads) void cut_gather_kernel(const float* __
     // A wave takes every eighth unit, and of those only the ones whose largest logit is in the cut's bin or before it (the
     // bin is a monotone function of the logit): where some dozens of tokens are kept, most of the row is not read again.
     // The code for a token exists once: sixteen copies of it, drawing included, were fetched past cold by every block.
-    // 128 rows of 151936 entries, 0.6 / 0.95 (100 kept): this kernel 25.9 -> 14.9 us; 1.0 / 0.95 (14000 kept) all 113 -> 84.
+    // 128 rows of 151936 entries, 0.6 / 0.95 (100 kept): this kernel 25.9 -> 14.9 us (14.1 in the present slices); 1.0 / 0.95
+    // (14000 kept) all 113 -> 84.
     const bool read_all = sl.unit0 < 0 || sl.units <= 4 * (kCutThreads / 64);  // all at once is faster than asking first
     for (int u0 = wave; u0 < sl.units; u0 += 64 * (kCutThreads / 64)) {
       const int u = u0 + lane * (kCutThreads / 64);

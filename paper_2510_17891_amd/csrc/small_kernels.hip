@@ -17,7 +17,7 @@ namespace rl {
 // copy of the caller's rows and the norm are a chain in which every link costs a launch and at least one round trip to
 // memory.  Here a few leading blocks read the slot while the others work on their rows.  Together with the last copy (the
 // sums behind the last layer go straight to the caller's buffer) and one event per twelve calls instead of per call: one
-// layer on one row 109.9 -> 99.5 us, on 64 rows 205.0 -> 194.0, on 512 rows 492 -> 463.
+// layer on one row 109.9 -> 99.5 us, on 64 rows 205.0 -> 194.0.
 // ------------------------------------------------------------------------------------------------
 __host__ __device__ inline int slot_units(const SlotUpload& u) {
   int n = u.n_rows;
@@ -79,7 +79,8 @@ __global__ __launch_bounds__(256) void entry_rows_kernel(RowSource in, SlotUploa
 // 1 and 2 are the first kernel of a call: x is always written, and leading blocks move the metadata slot.
 // xo may be xi.  gain: H bf16 gains; without a norm (has_gain = 0) any readable H-element array.
 // R: rows per block.  A block of 1024 threads spends its time on one round trip and a barrier, and two blocks fill a compute
-// unit: beyond 512 rows, two rows per block keep it at one round of blocks (1024 rows 11.3 -> 8.3 us, from the table 18.3 -> 13.0).  A row's bits do not
+// unit: beyond 512 rows, two rows per block keep it at one round of blocks (1024 rows 11.3 -> 8.3 us, from the table 18.3 -> 13.0;
+// 513 rows 7.2 -> 6.0 and 11.8 -> 9.9; 512 rows 11.2 -> 10.7 with four split sums to add, and 9.9 -> 10.0).  A row's bits do not
 // depend on R.
 template <int SRC, int R>
 __global__ __launch_bounds__(1024) void residual_norm_kernel(const float* xi, float* xo, const float* __restrict__ part,

@@ -1434,7 +1434,7 @@ def test_decode_graph_steps_equal_eager_steps(amd, kv_fp8, G, wide):
     bit, on every one of 40 steps (compared after each launch, with eager work and synchronisations in between).  The
     batch holds two groups of four samples (shared prompt pages: set blocks in the attention launch) and a single
     sequence whose context crosses 1024 tokens on the way, which changes a launch shape and forces a new capture; page
-    grants arrive every 16 steps through the device-counted table update.  An eager step in the middle of the graph
+    new pages enter the block table every 16 steps, in the first kernel of a step.  An eager step in the middle of the graph
     steps keeps both instances in agreement too.  In the third case the groups have eight samples and the graph
     instance uses the wide sets (two operands) while the eager one keeps sets of four."""
     shape = dict(ri.SHAPES["layer8b"], n_layers=2, hidden=512, n_q=8, n_kv=2, ffn=768, vocab=8192)
