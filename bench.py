@@ -392,7 +392,7 @@ def run_wave(args):
 
 def run_tiny(args):
     """The tiny fp32 workload end to end (4 prompts x 64 tokens, 32 greedy tokens each) and the oracle's wall time for
-    the same run.  A launch-bound case by nature: 2 layers of 256-wide matrices, about 40 small kernels per step."""
+    the same run.  A launch-bound case by nature: 2 layers of 256-wide matrices, 13 small kernels per step."""
     import numpy as np
     import torch
     import rollout_inputs as ri
@@ -425,7 +425,7 @@ def run_tiny(args):
            "n_gpus": 1, "steps": 32 * reps, "warmup": 32, "ms_per_step": gpu_s / 32 * 1e3, "higher_is_better": True,
            "dtype": "f32", "data": "synthetic",
            "config": {"workload": "tiny_2L_fp32_4x64_prompt_32_greedy", "note": "launch-bound: prefill of 256 rows in "
-                      "chunks of 64 plus 31 decode steps of about 40 small kernels each; the rate says nothing about HBM"},
+                      "chunks of 64 plus 31 decode steps of 13 small kernels each; the rate says nothing about HBM"},
            "whole_run_ms": gpu_s * 1e3}
     if not args.no_cpu_baseline:
         from oracle import oracle as orc
@@ -579,7 +579,7 @@ def run_sched(args):
            "value": res["256_rows"]["admit_us_per_call"] + res["256_rows"]["meta_us_per_call"], "higher_is_better": False,
            "n_gpus": 1, "steps": args.steps, "data": "synthetic",
            "config": {"workload": "layer8b_1L_vocab4096_groups_of_8_prompt64", "note": "wall_us_per_step includes the "
-                      "prefills of the run (one per group); wait_for_device is the time the host, 62 calls ahead, "
+                      "prefills of the run (one per group); wait_for_device is the time the host, up to 62 calls ahead, "
                       "stood still for the GPU; the scheduler's own share is admit + meta"}, "rows": res}
     print(json.dumps(out))
 
