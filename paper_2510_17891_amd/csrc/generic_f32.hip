@@ -46,7 +46,7 @@ __device__ __forceinline__ float wave_sums(const float (&v)[R], int lane) {
 // every 64 VEC.  K % VEC == 0.  VEC is 4 except for the O projection of an odd number of heads whose head_dim is no
 // multiple of four: there K is only even, rows begin on 8-byte boundaries, and a group of four would reach into the next row.
 // kEpiSwiGLU: W has 2N rows (gate then up); out[m][n] = silu(gate)*up.  kEpiResidual: out[m][n] += product.
-// gain (may be null): the rows are RMS-normalised first, x * rsqrt(mean(x^2) + eps) * gain; every wave forms the row's
+// gain (may be null, not used with kEpiResidual): the rows are RMS-normalised first, x * rsqrt(mean(x^2) + eps) * gain; every wave forms the row's
 // mean square from the elements it holds anyway.  A row's result depends neither on R and C nor on the rows beside it.
 template <int EPI, int R, int C, int VEC>
 __global__ __launch_bounds__(256) void gemm_f32_kernel(const float* __restrict__ X, const float* __restrict__ W,

@@ -182,7 +182,7 @@ bool gemm_bf16_adds_residual(int M, int N, int K);
 void launch_gemm_bf16(hipStream_t s, const void* X, const void* W, void* out, int M, int N, int K, int epi,
                       bool allow_split = true, const SampleEpilogue* se = nullptr);
 // fp32 GEMM on vector ALUs, row-major everything, K even; kEpiPartial writes [M][N] (one split), kEpiResidual adds to
-// it.  gain (may be null): K gains; the rows of X are RMS-normalised with them first.
+// it.  gain (may be null; not used with kEpiResidual): K gains; the rows of X are RMS-normalised with them first.
 void launch_gemm_f32(hipStream_t s, const float* X, const float* W, float* out, int M, int N, int K, int epi,
                      const float* gain = nullptr, float eps = 0.f);
 

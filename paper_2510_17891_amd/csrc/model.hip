@@ -61,7 +61,8 @@ size_t align_up(size_t v, size_t a = 256) { return (v + a - 1) / a * a; }
 
 struct Layout {
   size_t block_table, rope, ring, x, x_last, q_last, h, part, q, attn_part, o, a, logits, samp_part, forced_z, tmp_tok, tmp_lp, cuts, last_tok, total;
-  size_t slot_bytes, slot_upd, slot_tok, slot_skip, slot_sets, slot_tail, slot_head;
+  size_t slot_bytes, slot_upd, slot_skip, slot_sets, slot_tail, slot_head;
+  size_t host_slot_bytes, slot_tok;  // the host side of a slot also holds tokens, which the first kernel reads there
   int max_segs, n_tiles;
 };
 
@@ -104,12 +105,13 @@ void compute_layout(const rl_model_config& c, Layout* L) {
   L->max_segs = attn_bf16_max_segments((int)c.max_ctx);
   L->n_tiles = (int)((V + kSampleTile - 1) / kSampleTile);
   L->slot_upd = align_up(R * sizeof(RowMeta));
-  L->slot_tok = L->slot_upd + align_up(R * 2 * sizeof(int32_t));  // pairs of a row
-  L->slot_skip = L->slot_tok + align_up(R * sizeof(int32_t));  // tokens: read from the host side, by the first kernel alone
+  L->slot_skip = L->slot_upd + align_up(R * 2 * sizeof(int32_t));  // upd: two integers per row
   L->slot_sets = L->slot_skip + align_up(R * sizeof(int32_t));
   L->slot_tail = L->slot_sets + align_up(R * sizeof(AttnShared));  // window sets: up to one per row
   L->slot_head = L->slot_tail + align_up(R * sizeof(RowMeta));
   L->slot_bytes = L->slot_head + align_up(R * sizeof(RowMeta));
+  L->slot_tok = L->slot_bytes;
+  L->host_slot_bytes = L->slot_tok + align_up(R * sizeof(int32_t));
   L->block_table = take((size_t)c.max_seqs * (c.max_ctx / 16) * 4);
   L->rope = take((size_t)c.max_ctx * (d / 2) * sizeof(float2));
   L->ring = take(kRing * L->slot_bytes);
@@ -571,7 +573,7 @@ struct DecodeMeta {
 rl_status prepare_decode_meta(rl_model* m, int32_t n, const int32_t* seq_ids, DecodeMeta* dm) {
   rl_status rs = ring_acquire(m, &dm->slot);
   if (rs != RL_OK) return rs;
-  dm->hs = m->host_ring + (size_t)dm->slot * m->lay.slot_bytes;
+  dm->hs = m->host_ring + (size_t)dm->slot * m->lay.host_slot_bytes;
   char* ds = m->ws + m->lay.ring + (size_t)dm->slot * m->lay.slot_bytes;
   dm->up = build_decode_meta(m, n, seq_ids, dm->hs, ds, &dm->max_ctx, &dm->sa);
   dm->rows_dev = (const RowMeta*)ds;
@@ -677,7 +679,7 @@ rl_status rl_init_model(const rl_model_config* c, const rl_weights* w, rl_model*
     return r;
   };
   hipError_t e;
-  if ((e = hipHostMalloc((void**)&m->host_ring, kRing * L.slot_bytes, hipHostMallocDefault)) != hipSuccess) return bail(e, "hipHostMalloc");
+  if ((e = hipHostMalloc((void**)&m->host_ring, kRing * L.host_slot_bytes, hipHostMallocDefault)) != hipSuccess) return bail(e, "hipHostMalloc");
   for (int i = 0; i < kEpochs; ++i)
     if ((e = hipEventCreateWithFlags(&m->epoch_ev[i], hipEventDisableTiming)) != hipSuccess) return bail(e, "hipEventCreate");
   // Stale slots of recycled pages are multiplied by zero weights, so the pool must never hold NaN/Inf patterns.
@@ -1001,7 +1003,7 @@ static rl_status prefill_impl(rl_model* m, hipStream_t st, int32_t n_prompts, in
     int slot;
     rl_status rs = ring_acquire(m, &slot);
     if (rs != RL_OK) return rs;
-    char* hs = m->host_ring + (size_t)slot * m->lay.slot_bytes;
+    char* hs = m->host_ring + (size_t)slot * m->lay.host_slot_bytes;
     char* ds = m->ws + m->lay.ring + (size_t)slot * m->lay.slot_bytes;
     RowMeta* hr = (RowMeta*)hs;
     int32_t* ht = (int32_t*)(hs + m->lay.slot_tok);
@@ -1166,7 +1168,7 @@ rl_status rl_score(rl_model* m, void* stream, int32_t n, const int32_t* seq_ids,
     int slot;
     result = ring_acquire(m, &slot);
     if (result != RL_OK) break;
-    char* hs = m->host_ring + (size_t)slot * m->lay.slot_bytes;
+    char* hs = m->host_ring + (size_t)slot * m->lay.host_slot_bytes;
     char* ds = m->ws + m->lay.ring + (size_t)slot * m->lay.slot_bytes;
     RowMeta* hr = (RowMeta*)hs;
     int32_t* ht = (int32_t*)(hs + m->lay.slot_tok);
@@ -1264,7 +1266,7 @@ rl_status rl_sample_logits(rl_model* m, void* stream, int32_t n, const float* lo
   int slot;
   rl_status rs = ring_acquire(m, &slot);
   if (rs != RL_OK) return rs;
-  char* hs = m->host_ring + (size_t)slot * m->lay.slot_bytes;
+  char* hs = m->host_ring + (size_t)slot * m->lay.host_slot_bytes;
   char* ds = m->ws + m->lay.ring + (size_t)slot * m->lay.slot_bytes;
   RowMeta* hr = (RowMeta*)hs;
   for (int i = 0; i < n; ++i) { hr[i].seq = seq_ids[i]; hr[i].pos = positions[i]; hr[i].page = 0; hr[i].pad = 0; }
