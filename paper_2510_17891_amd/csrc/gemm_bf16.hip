@@ -481,442 +481,9 @@ __global__ __launch_bounds__(256) void gemm_bf16_cols_kernel(const u32x4_t* __re
   }
 }
 
-// Variant of the column-split kernel that fetches every weight tile from global memory once per block: the 256
-// threads copy the tile (two 32-row blocks x 64 k = 8 KiB) into one of four LDS stages, one barrier per k block
-// publishes it, and each wave reads its MFMA A fragments from LDS while its own activation fragments keep coming
-// straight from L2.  Weight registers run four k blocks ahead of the LDS stage they feed.  Needs K quarters that
-// are multiples of four k blocks (true for every 8B-shaped matrix); same quarter arithmetic, same bits.
-template <int MBW, int EPI, int XS>
-__global__ __launch_bounds__(256, MBW == 1 ? 2 : 1) void gemm_bf16_lds_kernel(const u32x4_t* __restrict__ X,
-                                                                           const u32x4_t* __restrict__ W,
-                                                                           void* __restrict__ out, int M, int N, int K,
-                                                                           int kb_per_quarter, SampleEpilogue se) {
-  __shared__ u32x4_t wlds[4][2][256];  // 32 KiB
-  const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
-  const int KB = K >> 6;
-  const int n_blocks_m = (M + 31) >> 5;
-  int m_blk0 = (blockIdx.z * 4 + wave) * MBW;
-  const bool has_rows = m_blk0 < n_blocks_m;
-  if (!has_rows) m_blk0 = n_blocks_m - 1;  // idle waves shadow a valid block (they still carry tiles and barriers)
-
-  int rb0, rb1;
-  rb0 = blockIdx.x * 2;  // SwiGLU: the gate/up matrix is interleaved in 16-row groups, so this holds for it too
-  rb1 = rb0 + 1;
-  const u32x4_t* w0 = W + (size_t)rb0 * KB * 256 + tid;
-  const u32x4_t* w1 = W + (size_t)rb1 * KB * 256 + tid;
-  const u32x4_t* xb[MBW];
-#pragma unroll
-  for (int mb = 0; mb < MBW; ++mb) {
-    int b = m_blk0 + mb;
-    if (b >= n_blocks_m) b = n_blocks_m - 1;
-    xb[mb] = X + (size_t)b * KB * 256 + lane;
-  }
-  const int n = 4 * kb_per_quarter;
-  const int kb0 = blockIdx.y * n;
-  auto kb_of = [&](int i) { return kb0 + (i < n ? i : n - 1); };  // clamped: no conditional loads in the pipeline
-  // Weight k blocks are loaded strictly in order (0, 1, 2, ...; the last one again once the range is exhausted), so
-  // the slot of the next one is kept as (block within its quarter, quarter) and stepped, without a division.
-  int w_r = 0, w_q = 0;
-  auto next_wslot = [&]() {
-    const int off = (((int)blockIdx.y * kb_per_quarter + w_r) * 4 + w_q) * 256;
-    if (w_r + 1 < kb_per_quarter) ++w_r;
-    else if (w_q < 3) { w_r = 0; ++w_q; }
-    return off;
-  };
-
-  u32x4_t wr[4][2];          // weight registers: slot s holds a block with index = s (mod 4)
-  u32x4_t xr[XS][MBW][4];    // activation fragments: slot s holds a block with index = s (mod XS)
-#pragma unroll
-  for (int s = 0; s < 4; ++s) {
-    const int ow = next_wslot();
-    wr[s][0] = __builtin_nontemporal_load(w0 + ow);
-    wr[s][1] = __builtin_nontemporal_load(w1 + ow);
-  }
-#pragma unroll
-  for (int s = 0; s < XS; ++s)
-#pragma unroll
-    for (int mb = 0; mb < MBW; ++mb)
-#pragma unroll
-      for (int t = 0; t < 4; ++t) xr[s][mb][t] = xb[mb][(size_t)kb_of(s) * 256 + t * 64];
-  wlds[0][0][tid] = wr[0][0];
-  wlds[0][1][tid] = wr[0][1];
-  {
-    const int ow = next_wslot();
-    wr[0][0] = __builtin_nontemporal_load(w0 + ow);
-    wr[0][1] = __builtin_nontemporal_load(w1 + ow);
-  }
-
-  // One k block: publish the next tile, barrier, multiply this one.  j = i mod 4 at compile time.
-  auto iter = [&](f32x16_t (&a)[2][MBW], int i, auto jc) __attribute__((always_inline)) {
-    constexpr int j = decltype(jc)::value, jn = (j + 1) & 3, jx = j % XS;
-    wlds[jn][0][tid] = wr[jn][0];
-    wlds[jn][1][tid] = wr[jn][1];
-    const int ow = next_wslot();  // k block i + 5
-    wr[jn][0] = __builtin_nontemporal_load(w0 + ow);
-    wr[jn][1] = __builtin_nontemporal_load(w1 + ow);
-    // Barrier that orders LDS traffic only: __syncthreads() would also drain every global load in flight
-    // (loads and stores share one counter on this ISA), i.e. the whole prefetch pipeline, once per k block.
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
-    __builtin_amdgcn_s_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
-#pragma unroll
-    for (int t = 0; t < 4; ++t) {
-      const u32x4_t a0 = wlds[j][0][t * 64 + lane];
-      const u32x4_t a1 = wlds[j][1][t * 64 + lane];
-#pragma unroll
-      for (int mb = 0; mb < MBW; ++mb) {
-        a[0][mb] = mfma_f16(a0, xr[jx][mb][t], a[0][mb]);
-        a[1][mb] = mfma_f16(a1, xr[jx][mb][t], a[1][mb]);
-      }
-    }
-#pragma unroll
-    for (int mb = 0; mb < MBW; ++mb)
-#pragma unroll
-      for (int t = 0; t < 4; ++t) xr[jx][mb][t] = xb[mb][(size_t)kb_of(i + XS) * 256 + t * 64];
-  };
-  auto quarter = [&](f32x16_t (&a)[2][MBW], int q) __attribute__((always_inline)) {
-#pragma unroll
-    for (int nb = 0; nb < 2; ++nb)
-#pragma unroll
-      for (int mb = 0; mb < MBW; ++mb)
-#pragma unroll
-        for (int r = 0; r < 16; ++r) a[nb][mb][r] = 0.f;
-    for (int i = q * kb_per_quarter; i < (q + 1) * kb_per_quarter; i += 4) {
-      iter(a, i, std::integral_constant<int, 0>{});
-      iter(a, i + 1, std::integral_constant<int, 1>{});
-      iter(a, i + 2, std::integral_constant<int, 2>{});
-      iter(a, i + 3, std::integral_constant<int, 3>{});
-    }
-  };
-  f32x16_t acc[2][MBW], other[2][MBW];
-  quarter(acc, 0);
-  for (int q = 1; q < 4; ++q) {
-    quarter(other, q);
-#pragma unroll
-    for (int nb = 0; nb < 2; ++nb)
-#pragma unroll
-      for (int mb = 0; mb < MBW; ++mb) acc[nb][mb] += other[nb][mb];
-  }
-
-  if (!has_rows) return;
-  const int col = lane & 31, hb = lane >> 5;
-#pragma unroll
-  for (int mb = 0; mb < MBW; ++mb) {
-    const int m = (m_blk0 + mb) * 32 + col;
-    if (m >= M) continue;
-    float sum[2][16];
-#pragma unroll
-    for (int nb = 0; nb < 2; ++nb)
-#pragma unroll
-      for (int r = 0; r < 16; ++r) sum[nb][r] = acc[nb][mb][r];
-    store_block<EPI>(sum, m, hb, rb0, rb1, blockIdx.y, M, N, out, se, blockIdx.x);
-  }
-}
-
-// Wide tile for batches of 65..256 rows: the block owns RBN 32-row blocks of the weight matrix (128 rows, or 96 where
-// that makes the tiles as many as the compute units) and the four waves split the batch columns, 32*MBW each.  What
-// every block must pull through L2 per k block is its weight tile plus the whole activation panel, and with 64-row
-// tiles the panel re-reads (one per block) are 2-4x the weight stream: the projection is then bound by what the L2 can
-// deliver, not by HBM.  A larger tile means fewer blocks and with them less panel traffic.  A block runs one wave per
-// SIMD and its steps (stage, barrier, multiply) do not overlap, so the time of a launch follows the steps of its
-// longest-running compute unit: 256 tiles of 96 rows finish sooner than 192 tiles of 128 rows that leave 64 units idle.
-// Same K quarters, same order inside a quarter, quarters added in order: same bits.
-template <int MBW, int EPI, int XS, int RBN>
-__global__ __launch_bounds__(256, RBN == 3 ? 1 : 2) void gemm_bf16_lds4_kernel(const u32x4_t* __restrict__ X, const u32x4_t* __restrict__ W,
-                                                              void* __restrict__ out, int M, int N, int K,
-                                                              int kb_per_quarter, int tiles_x, SampleEpilogue se) {
-  static_assert(RBN == 4 || (RBN == 3 && EPI != kEpiSample), "the sampling epilogue works on pairs of row blocks");
-  __shared__ u32x4_t wlds[4][RBN][256];  // four stages x RBN row blocks x 4 KiB
-  const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
-  const int KB = K >> 6;
-  const int n_blocks_m = (M + 31) >> 5;
-  // Two batch tiles (gridDim.z == 2 is folded into x by the launcher: tiles_x > 0): the two blocks of a weight tile
-  // get x indices 8 apart, so they land on the same die at about the same time and share the weights in its L2.
-  int tile_x = blockIdx.x, m_tile = blockIdx.z;
-  if (tiles_x > 0) {
-    const int grp = blockIdx.x >> 4, r = blockIdx.x & 15;
-    m_tile = r >> 3;
-    tile_x = grp * 8 + (r & 7);
-  }
-  const int m_blk0 = (m_tile * 4 + wave) * MBW;
-  const bool has_rows = m_blk0 < n_blocks_m;
-
-  // row blocks of the tile; those past the end of the matrix shadow its last one (computed, never stored)
-  const int n_rb = EPI == kEpiSwiGLU ? (N >> 4) : (N >> 5);
-  int rb[RBN];
-#pragma unroll
-  for (int b = 0; b < RBN; ++b) rb[b] = min(tile_x * RBN + b, n_rb - 1);
-  const u32x4_t* wp[RBN];
-#pragma unroll
-  for (int b = 0; b < RBN; ++b) wp[b] = W + (size_t)rb[b] * KB * 256 + tid;
-  const u32x4_t* xb[MBW];
-#pragma unroll
-  for (int mb = 0; mb < MBW; ++mb) {
-    int blk = m_blk0 + mb;
-    if (blk >= n_blocks_m) blk = n_blocks_m - 1;  // idle waves and surplus blocks shadow a valid one (never stored)
-    xb[mb] = X + (size_t)blk * KB * 256 + lane;
-  }
-  const int n = 4 * kb_per_quarter;
-  const int kb0 = blockIdx.y * n;
-  auto kb_of = [&](int i) { return kb0 + (i < n ? i : n - 1); };  // clamped: no conditional loads in the pipeline
-  // Weight k blocks are loaded strictly in order (0, 1, 2, ...; the last one again once the range is exhausted), so
-  // the slot of the next one is kept as (block within its quarter, quarter) and stepped, without a division.
-  int w_r = 0, w_q = 0;
-  auto next_wslot = [&]() {
-    const int off = (((int)blockIdx.y * kb_per_quarter + w_r) * 4 + w_q) * 256;
-    if (w_r + 1 < kb_per_quarter) ++w_r;
-    else if (w_q < 3) { w_r = 0; ++w_q; }
-    return off;
-  };
-
-  u32x4_t wr[4][RBN];        // weight registers: slot s holds a k block with index = s (mod 4)
-  u32x4_t xr[XS][MBW][4];    // activation fragments: slot s holds a k block with index = s (mod XS)
-#pragma unroll
-  for (int s = 0; s < 4; ++s) {
-    const int ow = next_wslot();
-#pragma unroll
-    for (int b = 0; b < RBN; ++b) wr[s][b] = __builtin_nontemporal_load(wp[b] + ow);
-  }
-#pragma unroll
-  for (int s = 0; s < XS; ++s)
-#pragma unroll
-    for (int mb = 0; mb < MBW; ++mb)
-#pragma unroll
-      for (int t = 0; t < 4; ++t) xr[s][mb][t] = xb[mb][(size_t)kb_of(s) * 256 + t * 64];
-  {
-    const int ow = next_wslot();
-#pragma unroll
-    for (int b = 0; b < RBN; ++b) {
-      wlds[0][b][tid] = wr[0][b];
-      wr[0][b] = __builtin_nontemporal_load(wp[b] + ow);
-    }
-  }
-
-  auto iter = [&](f32x16_t (&a)[RBN][MBW], int i, auto jc) __attribute__((always_inline)) {
-    constexpr int j = decltype(jc)::value, jn = (j + 1) & 3, jx = j % XS;
-    const int ow = next_wslot();  // k block i + 5
-#pragma unroll
-    for (int b = 0; b < RBN; ++b) {
-      wlds[jn][b][tid] = wr[jn][b];
-      wr[jn][b] = __builtin_nontemporal_load(wp[b] + ow);
-    }
-    // barrier that orders LDS traffic only (a full one would drain the global loads in flight)
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
-    __builtin_amdgcn_s_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
-#pragma unroll
-    for (int t = 0; t < 4; ++t) {
-#pragma unroll
-      for (int b = 0; b < RBN; ++b) {
-        const u32x4_t afrag = wlds[j][b][t * 64 + lane];
-#pragma unroll
-        for (int mb = 0; mb < MBW; ++mb) a[b][mb] = mfma_f16(afrag, xr[jx][mb][t], a[b][mb]);
-      }
-    }
-#pragma unroll
-    for (int mb = 0; mb < MBW; ++mb)
-#pragma unroll
-      for (int t = 0; t < 4; ++t) xr[jx][mb][t] = xb[mb][(size_t)kb_of(i + XS) * 256 + t * 64];
-  };
-  auto quarter = [&](f32x16_t (&a)[RBN][MBW], int q) __attribute__((always_inline)) {
-#pragma unroll
-    for (int b = 0; b < RBN; ++b)
-#pragma unroll
-      for (int mb = 0; mb < MBW; ++mb)
-#pragma unroll
-        for (int r = 0; r < 16; ++r) a[b][mb][r] = 0.f;
-    for (int i = q * kb_per_quarter; i < (q + 1) * kb_per_quarter; i += 4) {
-      iter(a, i, std::integral_constant<int, 0>{});
-      iter(a, i + 1, std::integral_constant<int, 1>{});
-      iter(a, i + 2, std::integral_constant<int, 2>{});
-      iter(a, i + 3, std::integral_constant<int, 3>{});
-    }
-  };
-  f32x16_t acc[RBN][MBW], other[RBN][MBW];
-  quarter(acc, 0);
-  for (int q = 1; q < 4; ++q) {
-    quarter(other, q);
-#pragma unroll
-    for (int b = 0; b < RBN; ++b)
-#pragma unroll
-      for (int mb = 0; mb < MBW; ++mb) acc[b][mb] += other[b][mb];
-  }
-
-  if (!has_rows) return;
-  const int col = lane & 31, hb = lane >> 5;
-#pragma unroll
-  for (int mb = 0; mb < MBW; ++mb) {
-    const int m = (m_blk0 + mb) * 32 + col;
-    if (m >= M) continue;
-    if constexpr (RBN == 4) {  // as two 64-row tiles (the sampling epilogue works per tile)
-#pragma unroll
-      for (int p = 0; p < 2; ++p) {
-        if (tile_x * 4 + 2 * p >= n_rb) break;
-        float sum[2][16];
-#pragma unroll
-        for (int nb = 0; nb < 2; ++nb)
-#pragma unroll
-          for (int r = 0; r < 16; ++r) sum[nb][r] = acc[2 * p + nb][mb][r];
-        store_block<EPI>(sum, m, hb, rb[2 * p], rb[2 * p + 1], blockIdx.y, M, N, out, se, tile_x * 2 + p);
-      }
-    } else {
-#pragma unroll
-      for (int b = 0; b < RBN; ++b) {
-        if (tile_x * RBN + b >= n_rb) break;
-        float sum[16];
-#pragma unroll
-        for (int r = 0; r < 16; ++r) sum[r] = acc[b][mb][r];
-        store_rowblock<EPI>(sum, m, hb, rb[b], blockIdx.y, M, N, out);
-      }
-    }
-  }
-}
-
-// The same tile with eight waves for 129..256 rows: one block holds a 128-row weight tile and all (up to) 256 batch
-// rows, 32 per wave, so the weight tile is staged once for both halves of the batch and a compute unit never holds
-// two blocks' worth of panel traffic while its neighbour holds one.  Each half of the block stages two of the four
-// row blocks.  Same K quarters, same order: same bits.
-template <int EPI, int XS>
-__global__ __launch_bounds__(512, 1) void gemm_bf16_lds8_kernel(const u32x4_t* __restrict__ X, const u32x4_t* __restrict__ W,
-                                                              void* __restrict__ out, int M, int N, int K,
-                                                              int kb_per_quarter, SampleEpilogue se) {
-  constexpr int MBW = 1;
-  __shared__ u32x4_t wlds[4][4][256];  // four stages x four row blocks x 4 KiB
-  const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
-  const int KB = K >> 6;
-  const int n_blocks_m = (M + 31) >> 5;
-  const int half = tid >> 8, t256 = tid & 255;  // which pair of row blocks this thread stages, and where in them
-  const int tile_x = blockIdx.x;
-  const int m_blk0 = blockIdx.z * 8 + wave;
-  const bool has_rows = m_blk0 < n_blocks_m;
-
-  // row blocks: pair p = 64-row tile 2x + p (the second pair shadows the first when the tile count is odd)
-  const int n_tiles = EPI == kEpiSwiGLU ? (N >> 5) : (N >> 6);
-  int tile[2], rb[4];
-#pragma unroll
-  for (int p = 0; p < 2; ++p) {
-    tile[p] = min(tile_x * 2 + p, n_tiles - 1);
-    rb[2 * p] = tile[p] * 2;
-    rb[2 * p + 1] = tile[p] * 2 + 1;
-  }
-  const bool second_valid = tile_x * 2 + 1 < n_tiles;
-  const u32x4_t* wp[2];
-#pragma unroll
-  for (int b = 0; b < 2; ++b) wp[b] = W + (size_t)rb[2 * half + b] * KB * 256 + t256;
-  const u32x4_t* xb[MBW];
-#pragma unroll
-  for (int mb = 0; mb < MBW; ++mb) {
-    int blk = m_blk0 + mb;
-    if (blk >= n_blocks_m) blk = n_blocks_m - 1;  // idle waves and surplus blocks shadow a valid one (never stored)
-    xb[mb] = X + (size_t)blk * KB * 256 + lane;
-  }
-  const int n = 4 * kb_per_quarter;
-  const int kb0 = blockIdx.y * n;
-  auto kb_of = [&](int i) { return kb0 + (i < n ? i : n - 1); };  // clamped: no conditional loads in the pipeline
-  // Weight k blocks are loaded strictly in order (0, 1, 2, ...; the last one again once the range is exhausted), so
-  // the slot of the next one is kept as (block within its quarter, quarter) and stepped, without a division.
-  int w_r = 0, w_q = 0;
-  auto next_wslot = [&]() {
-    const int off = (((int)blockIdx.y * kb_per_quarter + w_r) * 4 + w_q) * 256;
-    if (w_r + 1 < kb_per_quarter) ++w_r;
-    else if (w_q < 3) { w_r = 0; ++w_q; }
-    return off;
-  };
-
-  u32x4_t wr[4][2];          // weight registers: slot s holds a k block with index = s (mod 4)
-  u32x4_t xr[XS][MBW][4];    // activation fragments: slot s holds a k block with index = s (mod XS)
-#pragma unroll
-  for (int s = 0; s < 4; ++s) {
-    const int ow = next_wslot();
-#pragma unroll
-    for (int b = 0; b < 2; ++b) wr[s][b] = __builtin_nontemporal_load(wp[b] + ow);
-  }
-#pragma unroll
-  for (int s = 0; s < XS; ++s)
-#pragma unroll
-    for (int mb = 0; mb < MBW; ++mb)
-#pragma unroll
-      for (int t = 0; t < 4; ++t) xr[s][mb][t] = xb[mb][(size_t)kb_of(s) * 256 + t * 64];
-  {
-    const int ow = next_wslot();
-#pragma unroll
-    for (int b = 0; b < 2; ++b) {
-      wlds[0][2 * half + b][t256] = wr[0][b];
-      wr[0][b] = __builtin_nontemporal_load(wp[b] + ow);
-    }
-  }
-
-  auto iter = [&](f32x16_t (&a)[4][MBW], int i, auto jc) __attribute__((always_inline)) {
-    constexpr int j = decltype(jc)::value, jn = (j + 1) & 3, jx = j % XS;
-    const int ow = next_wslot();  // k block i + 5
-#pragma unroll
-    for (int b = 0; b < 2; ++b) {
-      wlds[jn][2 * half + b][t256] = wr[jn][b];
-      wr[jn][b] = __builtin_nontemporal_load(wp[b] + ow);
-    }
-    // barrier that orders LDS traffic only (a full one would drain the global loads in flight)
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
-    __builtin_amdgcn_s_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
-#pragma unroll
-    for (int t = 0; t < 4; ++t) {
-#pragma unroll
-      for (int b = 0; b < 4; ++b) {
-        const u32x4_t afrag = wlds[j][b][t * 64 + lane];
-#pragma unroll
-        for (int mb = 0; mb < MBW; ++mb) a[b][mb] = mfma_f16(afrag, xr[jx][mb][t], a[b][mb]);
-      }
-    }
-#pragma unroll
-    for (int mb = 0; mb < MBW; ++mb)
-#pragma unroll
-      for (int t = 0; t < 4; ++t) xr[jx][mb][t] = xb[mb][(size_t)kb_of(i + XS) * 256 + t * 64];
-  };
-  auto quarter = [&](f32x16_t (&a)[4][MBW], int q) __attribute__((always_inline)) {
-#pragma unroll
-    for (int b = 0; b < 4; ++b)
-#pragma unroll
-      for (int mb = 0; mb < MBW; ++mb)
-#pragma unroll
-        for (int r = 0; r < 16; ++r) a[b][mb][r] = 0.f;
-    for (int i = q * kb_per_quarter; i < (q + 1) * kb_per_quarter; i += 4) {
-      iter(a, i, std::integral_constant<int, 0>{});
-      iter(a, i + 1, std::integral_constant<int, 1>{});
-      iter(a, i + 2, std::integral_constant<int, 2>{});
-      iter(a, i + 3, std::integral_constant<int, 3>{});
-    }
-  };
-  f32x16_t acc[4][MBW], other[4][MBW];
-  quarter(acc, 0);
-  for (int q = 1; q < 4; ++q) {
-    quarter(other, q);
-#pragma unroll
-    for (int b = 0; b < 4; ++b)
-#pragma unroll
-      for (int mb = 0; mb < MBW; ++mb) acc[b][mb] += other[b][mb];
-  }
-
-  if (!has_rows) return;
-  const int col = lane & 31, hb = lane >> 5;
-#pragma unroll
-  for (int mb = 0; mb < MBW; ++mb) {
-    const int m = (m_blk0 + mb) * 32 + col;
-    if (m >= M) continue;
-#pragma unroll
-    for (int p = 0; p < 2; ++p) {
-      if (p == 1 && !second_valid) break;
-      float sum[2][16];
-#pragma unroll
-      for (int nb = 0; nb < 2; ++nb)
-#pragma unroll
-        for (int r = 0; r < 16; ++r) sum[nb][r] = acc[2 * p + nb][mb][r];
-      store_block<EPI>(sum, m, hb, rb[2 * p], rb[2 * p + 1], blockIdx.y, M, N, out, se, tile[p]);
-    }
-  }
-}
-
-// The eight-wave block with a 96-row weight tile (three row blocks), for matrices whose 128-row tiles would leave a
-// quarter of the compute units without a block while 96-row tiles give every unit one.  The first four waves stage
+// Gate/up of 193..256 rows: eight waves, a 96-row weight tile (three row blocks) and all batch rows, where 128-row tiles would
+// leave a quarter of the compute units without a block while 96-row tiles give every unit one.  (The same tile in
+// gemm_bf16_tile_kernel: 61.4 us at 256 rows, here 59.4.)  The first four waves stage
 // row blocks 0 and 2, the other four row block 1; each half runs its own copy of the loop (same steps, one barrier
 // per k block in both), so that no load in the pipeline is conditional.  Same K quarters, same order: same bits.
 template <int EPI, int XS>
@@ -1057,30 +624,33 @@ __global__ __launch_bounds__(512, 1) void gemm_bf16_lds8r3_kernel(const u32x4_t*
   }
 }
 
-// Large batches (more than 256 rows: prefill and scoring chunks, throughput decode).  A block of four waves owns NB
-// 32-row blocks of the weight matrix and 128 batch rows, 32 per wave, over the whole K range.  The weight tile goes
-// through LDS in three stages, one barrier per k block; the activation fragments come straight from L2.
+// More than 64 rows.  A block owns NB 32-row blocks of the weight matrix and NW * 32 batch rows, 32 per wave, over the K
+// ranges of `splits` consecutive K splits.  The weight tile goes through LDS in three stages, one barrier per k block; the
+// activation fragments come straight from L2.
 //
-// What bounds it: the matrix cores' power.  At 1024 rows gate/up keeps them busy 91 % of the cycles (1100 cycles per k
-// block for two resident blocks, 1024 of them matrix instructions), and the clock settles at 1.2 to 1.5 GHz; a loop of
-// nothing but these instructions on random operands does not get past 1.4 to 1.6 PFLOP/s.  What it takes to get there:
-//   - one memory instruction behind every matrix instruction.  A wave issues in order, so a run of LDS writes or loads
-//     leaves its matrix core idle (16 matrix instructions and 16 fragment reads take 577 cycles, with four LDS writes and
-//     four weight loads in a row 852, spread out 670);
-//   - the barrier does not wait for LDS reads in flight: a stage is rewritten one barrier after its last read;
-//   - two blocks per compute unit (256 registers per lane), which hides each other's barriers, quarter sums and ends.  The
-//     instances that keep no running sums have them (48 or 36 KB of LDS), and so have three row blocks with sums (68 KB);
-//     four row blocks with sums (O and down at 1024 rows) take 112 KB, so that one block with one wave per SIMD is alone
-//     on a unit: down runs at 0.81 PFLOP/s where gate/up runs at 1.0.
-// Waves without batch rows (two of twelve at 301 rows) execute all matrix instructions of the last rows along with the
-// others and drop the result.
+// What bounds it.  At 1024 rows gate/up spends 206 us with two resident blocks of four waves (128 x 128 each); without
+// its activation loads 174, without its weight loads 150, without both and LDS 133, which is the matrix cores alone at
+// the clock that their power leaves (operands of zeros: 176, 116, 95 and 94, so what a compute unit draws through its L1 is
+// a bound of its own, at 70 GB/s per unit).  Both, the power and that rate, go by the bytes per product, hence:
+//   - eight waves (128 x 256) where the batch fills them: 48 KB per k block instead of 64: 206 -> 190 us;
+//   - weights that are read once (ONE: a single batch tile) pass through non-temporally: gate/up 41.0 -> 38.6 us at 72 rows;
+//   - waves without batch rows carry weights and take part in the barriers, nothing else: down at 160 rows 40 -> 30 us,
+//     gate/up at 160 rows 55 -> 50, at 301 rows 100 -> 84; with four waves every other tile holds its rows in the other two
+//     waves, so that two blocks on a unit do not leave the same matrix cores idle.  Not with a single batch tile of four
+//     waves, where HBM is the bound and the second path only costs (128 rows: 42.9 -> 44.5).
+// And one memory instruction behind every matrix instruction (a wave issues in order: a run of LDS writes or loads leaves
+// its matrix core idle); the barrier does not wait for LDS reads in flight (a stage is rewritten one barrier after its last
+// read); two waves per SIMD (256 registers), as two blocks of four or one of eight: four row blocks with running sums
+// take 112 KB of LDS, so that one block of four waves is alone on a unit (O and down at 1024 rows).  Weights four k blocks
+// ahead instead of two, or activations four ahead, gain nothing.
 // The quarter sums keep a row's bits those of the K-split kernels: every K quarter in an accumulator of its own, added
-// in order; then, where the plan splits K, the splits in order, kept in LDS between them.  So a QKV, O or down product
-// leaves no split partials: QKV writes its sum once (100 MB less written and 75 MB less read at 1024 rows), O and down
+// in order; then, where one block takes several K splits, the splits in order, kept in LDS between them.  So at more than
+// 256 rows QKV, and at more than 512 O and down, leave no split partials: QKV writes its sum once, O and down
 // add theirs to the residual stream themselves (kEpiResidual), in the order in which the norm kernel would.
-// Measured inside scoring, prefill and decode passes, against the kernels before: gate/up 129 -> 93 us at 301 rows, 139 ->
-// 115 at 512, 218 -> 204 at 1024; QKV 46 -> 39, 56 -> 44, 93 -> 67; at 1024 rows O 55 -> 48, but down 125 -> 128 (one block
-// per unit), with the norm behind each 21 -> 11; output projection with sampling 1472 -> 1289.
+// Measured over the weights of twelve layers, against the staged kernels before (us): 128 rows QKV 17.0 -> 15.7, O 13.5 -> 12.6; 160 rows
+// gate/up 58 -> 49, QKV 23 -> 19, O 19.4 -> 15.0, down 42.6 -> 30.0; 256 rows O 20.1 -> 18.2, down 42.4 -> 39.2; 301 rows
+// gate/up 94 -> 87, O 31 -> 24, down 57 -> 48; 512 rows O 33 -> 29, down 61 -> 56; 768 rows gate/up 175 -> 165, QKV 61 ->
+// 59; 1024 rows gate/up 209 -> 193, QKV 67 -> 63.
 __device__ __forceinline__ __amdgpu_buffer_rsrc_t buffer_of(const void* base, uint32_t bytes) {
   return __builtin_amdgcn_make_buffer_rsrc((void*)base, 0, bytes, 0x00020000);
 }
@@ -1088,17 +658,24 @@ __device__ __forceinline__ u32x4_t buffer_load16(__amdgpu_buffer_rsrc_t r, uint3
   return __builtin_bit_cast(u32x4_t, __builtin_amdgcn_raw_buffer_load_b128(r, voff, soff, 0));
 }
 
-constexpr int tile_sums_in_registers(int nb) { return nb == 3 ? 1 : 0; }
+constexpr int tile_sums_in_registers(int nb, int nw) { return nb == 3 && nw == 4 ? 1 : 0; }
 
-template <int NB, int EPI>
-__global__ __launch_bounds__(256, 2) void gemm_bf16_tile_kernel(const u32x4_t* __restrict__ X, const u32x4_t* __restrict__ W,
+template <int NB, int NW, int EPI, bool ONE>
+__global__ __launch_bounds__(NW * 64, 2) void gemm_bf16_tile_kernel(const u32x4_t* __restrict__ X, const u32x4_t* __restrict__ W,
                                                               void* __restrict__ out, int M, int N, int K, int seg, int splits,
                                                               int n_tiles, int m_tiles, SampleEpilogue se) {
-  static_assert(NB == 4 || (NB == 3 && EPI != kEpiSample), "the sampling epilogue works on pairs of row blocks");
+  static_assert(NB % 2 == 0 || EPI != kEpiSample, "the sampling epilogue works on pairs of row blocks");
+  static_assert(NW == 4 || NW == 8, "four or eight waves");
+  constexpr bool kIdleSkips = (!ONE || NW == 8) && EPI != kEpiResidual;
+  constexpr int NF = NW == 8 ? NB / 2 : NB;          // 16-byte pieces of a k block of the tile per thread
+  constexpr bool HALF = NW == 8 && (NB & 1) != 0;    // and one of 8 bytes
+  constexpr int NC = NF + (HALF ? 1 : 0);
+  constexpr bool kLate = NW == 4 && NB > 2 && !ONE;  // the last piece is staged early in the step after the others'
+  constexpr int NE = kLate ? NC - 1 : NC;
   extern __shared__ u32x4_t smem[];  // three weight stages of NB x 4 KiB; then, with splits or a residual, the running sums
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int KB = K >> 6;
+  const int KB = splits * 4 * seg, kfirst = blockIdx.y * KB;  // k blocks of this block, the first one
   // Consecutive blocks go to the eight dies in turn: the batch tiles of one weight tile follow each other on one die.
   const int j = blockIdx.x >> 3;
   const int m_tile = j % m_tiles, n_tile = (j / m_tiles) * 8 + (blockIdx.x & 7);
@@ -1106,17 +683,20 @@ __global__ __launch_bounds__(256, 2) void gemm_bf16_tile_kernel(const u32x4_t* _
   const int n_rb = EPI == kEpiSwiGLU ? (N >> 4) : (N >> 5);
   const int n_mb = (M + 31) >> 5;
   const int rb0 = n_tile * NB;
-  const int mb = m_tile * 4 + wave;
-  const bool has_rows = mb < n_mb;  // idle waves shadow the last block (they still carry tiles and barriers)
-  const uint32_t row_bytes = (uint32_t)KB * 4096;
+  const int mb = m_tile * NW + (NW == 4 && kIdleSkips ? (wave + (n_tile & 1) * 2) & 3 : wave);
+  const bool has_rows = mb < n_mb;  // idle waves carry weights and barriers; without kIdleSkips they also shadow the last rows
+  const uint32_t row_bytes = (uint32_t)(K >> 6) * 4096;
   const auto wd = buffer_of((const char*)W + (size_t)rb0 * row_bytes, (uint32_t)min(NB, n_rb - rb0) * row_bytes);
+  const int half = wave >> 2;  // eight waves: the first four stage row blocks 0 and 2, the others 1 and 3
+  auto rb_of = [&](int c) __attribute__((always_inline)) { return NW == 8 ? 2 * c + half : c; };
   const auto xd = buffer_of((const char*)X + (size_t)min(mb, n_mb - 1) * row_bytes, row_bytes);
-  const uint32_t wv = tid * 16, xv = lane * 16;
+  const uint32_t wv = (tid & 255) * 16, xv = lane * 16, wv2 = tid * 8;
   int w_left = KB, w_r = 0, w_q = 0;
-  uint32_t w_off = 0;  // offset of the next weight k block to load (weight_kb_slot order)
-  uint32_t w_row[NB];
+  uint32_t w_off = (uint32_t)kfirst * 4096;  // offset of the next weight k block to load (weight_kb_slot order)
+  uint32_t w_row[NF + 1];
 #pragma unroll
-  for (int b = 0; b < NB; ++b) w_row[b] = (uint32_t)min(b, n_rb - 1 - rb0) * row_bytes;
+  for (int c = 0; c < NF; ++c) w_row[c] = (uint32_t)min(rb_of(c), n_rb - 1 - rb0) * row_bytes;
+  w_row[NF] = (uint32_t)min(NB - 1, n_rb - 1 - rb0) * row_bytes;
   const int back = -((seg - 1) * 4 - 1) * 4096;
   auto next_w = [&]() __attribute__((always_inline)) {  // without branches; the last one again once the range is exhausted
     const bool wrap = ++w_r == seg;
@@ -1127,13 +707,22 @@ __global__ __launch_bounds__(256, 2) void gemm_bf16_tile_kernel(const u32x4_t* _
     const int by = wrap ? (next ? 4096 : back) : 4 * 4096;
     w_off += --w_left > 0 ? by : 0;
   };
-  constexpr int WS = 2;
-  u32x4_t wr[WS][NB], xr[2][4], fa[2][NB];  // weights on their way to LDS, activations, weight fragments of two phases
+  constexpr int WS = 2, XS = 2;  // k blocks in registers beyond the stages in LDS
+  typedef uint32_t u32x2_t __attribute__((ext_vector_type(2)));
+  u32x4_t wr[WS][NF], xr[XS][4], fa[2][NB];  // weights on their way to LDS, activations, weight fragments of two phases
+  u32x2_t wh[WS];
   auto load_x = [&](u32x4_t (&x)[4], int kb, int t) __attribute__((always_inline)) {
-    x[t] = buffer_load16(xd, xv, (uint32_t)min(kb, KB - 1) * 4096 + t * 1024);
+    x[t] = buffer_load16(xd, xv, (uint32_t)(kfirst + min(kb, KB - 1)) * 4096 + t * 1024);
   };
-  auto load_w = [&](u32x4_t (&w)[NB], int b) __attribute__((always_inline)) { w[b] = buffer_load16(wd, wv, w_row[b] + w_off); };
-  auto put_w = [&](int stage, const u32x4_t (&w)[NB], int b) __attribute__((always_inline)) { smem[(stage * NB + b) * 256 + tid] = w[b]; };
+  // piece c of a k block of the tile: row block 2c + half, or half of the odd last one
+  auto load_w = [&](int s, int c) __attribute__((always_inline)) {
+    if (c < NF) wr[s][c] = __builtin_bit_cast(u32x4_t, __builtin_amdgcn_raw_buffer_load_b128(wd, wv, w_row[c] + w_off, ONE ? 2 : 0));
+    else if (HALF) wh[s] = __builtin_bit_cast(u32x2_t, __builtin_amdgcn_raw_buffer_load_b64(wd, wv2, w_row[NF] + w_off, ONE ? 2 : 0));
+  };
+  auto put_w = [&](int stage, int s, int c) __attribute__((always_inline)) {
+    if (c < NF) smem[(stage * NB + rb_of(c)) * 256 + (tid & 255)] = wr[s][c];
+    else if (HALF) ((u32x2_t*)(smem + (stage * NB + NB - 1) * 256))[tid] = wh[s];
+  };
   auto read = [&](u32x4_t (&f)[NB], int stage, int t, int b) __attribute__((always_inline)) { f[b] = smem[(stage * NB + b) * 256 + t * 64 + lane]; };
   auto barrier = []() __attribute__((always_inline)) {
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
@@ -1144,16 +733,16 @@ __global__ __launch_bounds__(256, 2) void gemm_bf16_tile_kernel(const u32x4_t* _
 #pragma unroll
   for (int s = 0; s < WS; ++s) {
 #pragma unroll
-    for (int b = 0; b < NB; ++b) load_w(wr[s], b);
+    for (int c = 0; c < NC; ++c) load_w(s, c);
     next_w();
   }
 #pragma unroll
-  for (int s = 0; s < 2; ++s)
+  for (int s = 0; s < XS; ++s)
 #pragma unroll
     for (int t = 0; t < 4; ++t) load_x(xr[s], s, t);
-  // Running sums over the K splits, by lane: [row block][q][64 lanes] per wave in LDS; with three row blocks the first
-  // one's stay in registers, which keeps two blocks on a compute unit.
-  constexpr int UR = tile_sums_in_registers(NB);
+  // Running sums over the K splits, by lane: [row block][q][64 lanes] per wave in LDS; with three row blocks and four waves
+  // the first one's stay in registers, which keeps two blocks on a compute unit.
+  constexpr int UR = tile_sums_in_registers(NB, NW);
   f32x4_t* const usum = (f32x4_t*)(smem + 3 * NB * 256) + wave * (NB - UR) * 256 + lane;
   f32x4_t ureg[4];
 #pragma unroll
@@ -1179,28 +768,51 @@ __global__ __launch_bounds__(256, 2) void gemm_bf16_tile_kernel(const u32x4_t* _
       for (int q = 0; q < 4; ++q)
         set_sum(b, q, (f32x4_t){tot[b][4 * q], tot[b][4 * q + 1], tot[b][4 * q + 2], tot[b][4 * q + 3]});
   }
-  constexpr int LATE = NB - 1;  // this row block is staged in phase 0 of the next step, the others in phases 2 and 3
+  // stages 0 and 1 from registers 0 and 1; their registers take k blocks WS and WS + 1
 #pragma unroll
-  for (int b = 0; b < NB; ++b) put_w(0, wr[0], b);
+  for (int s = 0; s < 2; ++s) {
+    const int n = s == 0 ? NC : NE;
 #pragma unroll
-  for (int b = 0; b < NB; ++b) load_w(wr[0], b);
-  next_w();
+    for (int c = 0; c < n; ++c) put_w(s, s, c);
 #pragma unroll
-  for (int b = 0; b < LATE; ++b) put_w(1, wr[1], b);
-#pragma unroll
-  for (int b = 0; b < LATE; ++b) load_w(wr[1], b);
+    for (int c = 0; c < n; ++c) load_w(s, c);
+    if (s == 0 || !kLate) next_w();
+  }
   barrier();
+  if (kIdleSkips && !has_rows) {  // the steps below without products
+    int rd = 1, wt = 2;
+    for (int i = 0; i < KB; i += 2) {
+      auto idle = [&](auto jc) __attribute__((always_inline)) {
+        constexpr int J = decltype(jc)::value, jw = J, j1 = J ^ 1;
+        if (kLate) {
+          put_w(rd, j1, NC - 1);
+          load_w(j1, NC - 1);
+        }
+        asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+        if (kLate) next_w();
+#pragma unroll
+        for (int c = 0; c < NE; ++c) put_w(wt, jw, c);
+#pragma unroll
+        for (int c = 0; c < NE; ++c) load_w(jw, c);
+        if (!kLate) next_w();
+        rd = wt;
+        wt = wt == 2 ? 0 : wt + 1;
+      };
+      idle(std::integral_constant<int, 0>{});
+      idle(std::integral_constant<int, 1>{});
+    }
+    return;
+  }
 #pragma unroll
   for (int t = 0; t < 2; ++t)
 #pragma unroll
     for (int b = 0; b < NB; ++b) read(fa[t], 0, t, b);
   int cur = 0, rd = 1, wt = 2;  // LDS stages of k blocks i, i + 1 and i + 2
   auto step = [&](int i, auto jc, auto fc) __attribute__((always_inline)) {
-    constexpr int J = decltype(jc)::value, jx = J & 1, j1 = (J + 1) % WS, j2 = (J + 2) % WS;
+    constexpr int J = decltype(jc)::value, jx = J & 1, jw = J & 1, j1 = jw ^ 1;  // k block i + 2 waits in register slot jw
     constexpr bool first = decltype(fc)::value;
     auto phase = [&](auto pc) __attribute__((always_inline)) {
       constexpr int P = decltype(pc)::value;
-      if (P == 3) next_w();
 #pragma unroll
       for (int b = 0; b < NB; ++b) {
         f32x16_t c;
@@ -1213,19 +825,32 @@ __global__ __launch_bounds__(256, 2) void gemm_bf16_tile_kernel(const u32x4_t* _
         acc[b] = mfma_f16(fa[P & 1][b], xr[jx][P], c);
         read(fa[P & 1], P < 2 ? cur : rd, (P + 2) & 3, b);  // past the last k block: a stage nobody needs, never used
         // one more memory instruction behind each matrix instruction
-        if (P == 0 && b == 0) put_w(rd, wr[j1], LATE);
-        if (P == 0 && b == 1) load_x(xr[jx ^ 1], i + 1, 3);
-        if (P == 0 && b == 2 && NB == 4) load_w(wr[j1], 2);
-        if (P == 1 && b == 0) load_w(wr[j1], LATE);
-        if (P == 1 && b == 1) load_x(xr[jx], i + 2, 0);
-        if (P == 2 && b == 0) put_w(wt, wr[j2], 0);
-        if (P == 2 && b == 1) load_x(xr[jx], i + 2, 1);
-        if (P == 2 && b == 2 && NB == 4) put_w(wt, wr[j2], 1);
-        if (P == 3 && b == 0) put_w(wt, wr[j2], LATE - 1);
-        if (P == 3 && b == 1) load_x(xr[jx], i + 2, 2);
-        if (P == 3 && b == NB - 1) {
-          load_w(wr[j2], 0);
-          load_w(wr[j2], 1);
+        if constexpr (kLate) {
+          if (P == 0 && b == 0) put_w(rd, j1, NC - 1);
+          if (P == 0 && b == 1) load_x(xr[jx ^ 1], i + 1, 3);
+          if (P == 0 && b == 2 && NB == 4) load_w(j1, 2);
+          if (P == 1 && b == 0) load_w(j1, NC - 1);
+          if (P == 1 && b == 1) load_x(xr[jx], i + 2, 0);
+          if (P == 2 && b == 0) put_w(wt, jw, 0);
+          if (P == 2 && b == 1) load_x(xr[jx], i + 2, 1);
+          if (P == 2 && b == 2 && NB == 4) put_w(wt, jw, 1);
+          if (P == 3 && b == 0) put_w(wt, jw, NC - 2);
+          if (P == 3 && b == 1) load_x(xr[jx], i + 2, 2);
+          if (P == 3 && b == NB - 1) {
+            next_w();
+            load_w(jw, 0);
+            load_w(jw, 1);
+          }
+        } else {
+          if (b == NB - 1) load_x(xr[jx], i + 2, P);
+          if (P >= 2) {
+            constexpr int c0 = P - 2, c1 = P;
+            if (c0 < NC && b == 0) put_w(wt, jw, c0);
+            if (c0 < NC && b == 1) load_w(jw, c0);
+            if (c1 < NC && b == NB / 2) put_w(wt, jw, c1);
+            if (c1 < NC && b == NB - 1) load_w(jw, c1);
+          }
+          if (P == 3 && b == NB - 1) next_w();
         }
         __builtin_amdgcn_sched_barrier(0);
       }
@@ -1288,7 +913,7 @@ __global__ __launch_bounds__(256, 2) void gemm_bf16_tile_kernel(const u32x4_t* _
       float sum[16];
 #pragma unroll
       for (int r = 0; r < 16; ++r) sum[r] = tot[b][r];
-      if (rb0 + b < n_rb) store_rowblock<EPI == kEpiResidual ? kEpiPartial : EPI>(sum, m, hb, rb0 + b, 0, M, N, out);
+      if (rb0 + b < n_rb) store_rowblock<EPI == kEpiResidual ? kEpiPartial : EPI>(sum, m, hb, rb0 + b, blockIdx.y, M, N, out);
     }
   }
 }
@@ -1371,17 +996,15 @@ int wide_blocks(int N, int K, int epi, bool allow_split) {
   return ((tiles + 1) / 2) * (epi == kEpiPartial ? p.splits : 1);
 }
 
-// Row blocks per weight tile with which gemm_bf16_tile_kernel takes an M x N x K product, or 0 where another kernel does:
-//   - up to 256 rows the tiles above read the weights once and are faster (gate/up at 256 rows 59 us against 71);
-//   - the tile (4 or 3 row blocks) that gives the compute unit with most blocks the fewest row blocks, the larger one on
-//     a tie: it reads the activations less often (gate/up at 512 rows 116 us with 4, 123 with 3; at 301 rows 99 and 92);
-//   - where even smaller tiles would be needed to use the chip (O and down projections of the 8B shape at 512 rows), the
-//     kernels that spread the K splits over blocks stay: measured 35 against 29 us for O, 79 against 65 for down.
-int tile_row_blocks(int M, int N, int K, int epi, bool allow_split) {
-  if (M <= 256) return 0;
+// Whether an M x N x K product of more than 256 rows runs over the whole K range in one block (gemm_bf16_tile_kernel with
+// running sums, no split partials): where tiles of 4 or 3 row blocks x 128 rows give every compute unit work.  Where smaller
+// ones would be needed for that (O and down projections of the 8B shape up to 512 rows), the K splits go to
+// blocks of their own.
+bool whole_k(int M, int N, int K, int epi, bool allow_split) {
+  if (M <= 256) return false;
   const Plan p = make_plan(N, K, epi == kEpiResidual ? kEpiPartial : epi, allow_split && epi != kEpiSample);
-  if (p.kb_per_wave % 4) return 0;
-  if (epi == kEpiSample) return 4;
+  if (p.kb_per_wave % 4) return false;
+  if (epi == kEpiSample) return true;
   const int n_rb = epi == kEpiSwiGLU ? (N >> 4) : (N >> 5), m_tiles = (M + 127) / 128;
   int best = 0, best_cost = 0;
   for (int nb = 4; nb >= 2; --nb) {
@@ -1389,30 +1012,82 @@ int tile_row_blocks(int M, int N, int K, int epi, bool allow_split) {
     const int cost = (blocks + kComputeUnits - 1) / kComputeUnits * nb;
     if (!best || cost < best_cost) { best = nb; best_cost = cost; }
   }
-  return best == 2 ? 0 : best;
+  return best > 2;
 }
 
-template <int NB>
+struct Tile {
+  int nb, nw;  // row blocks and waves of a block of gemm_bf16_tile_kernel
+};
+
+// The tile of a product of more than 64 rows (K quarters of a multiple of four k blocks).
+//   - Up to 128 rows (one batch tile, HBM bound): 128-row weight tiles where they make 192 blocks or more, 96-row ones where
+//     those make a block per compute unit and 128-row ones do not (gate/up at 128 rows 42.9 against 46.0 us, QKV 15.7 against
+//     17.9), 64-row ones for the small matrices (O 12.6 against 15.7, down 26.7 against 35.4).
+//   - Up to 256 rows: eight waves, so that the weights are read once, by the same rule; matrices with fewer tiles take two
+//     batch tiles of four waves (O at 160 / 256 rows 15.0 / 18.2 us, with eight waves 18.5 / 23.8; down 30.0 / 39.2, 39.7 / 49.8).
+//   - Beyond: the least time by rounds of blocks.  Four waves have two blocks on a unit, and a last round of one block per
+//     unit takes 0.62 of a full one; eight waves have one, and blocks of a last batch tile of up to 128 rows take 0.55 of
+//     a full one.  A full round of gate/up takes 58 us with tiles of 3 row blocks x 128 rows, 69 with 4 x 128,
+//     57 with 3 x 256 and 63 with 4 x 256 (running sums of the last do not fit the LDS).  At 301 rows this picks 3 x 256 for gate/up (87 us,
+//     3 x 128 takes 88, 4 x 128 92, 4 x 256 101), at 512 4 x 128 (112; 114, 120, 123), at 640 4 x 128 (138; 148, 149, 150), at 768
+//     3 x 256 (165; 168, 175, 177), at 1024 4 x 256 (193; 207, 214, 231); for down at 256 / 301 / 512 rows 4 x 128 / 4 x 256 / 4 x 256
+//     (39 against 50, 48 against 53, 56 against 63).
+//   - Sampling beyond 256 rows: 4 x 128 (1 050 us at 700 rows, 4 x 256 1 069: its long epilogue overlaps with the other block).
+Tile pick_tile(int M, int N, int K, int epi, bool allow_split) {
+  const Plan p = make_plan(N, K, epi == kEpiResidual ? kEpiPartial : epi, allow_split && epi != kEpiSample);
+  const bool whole = whole_k(M, N, K, epi, allow_split), sums = whole && (p.splits > 1 || epi == kEpiResidual);
+  const int n_rb = epi == kEpiSwiGLU ? (N >> 4) : (N >> 5), splits = whole ? 1 : p.splits;
+  const auto tiles = [&](int nb) { return (n_rb + nb - 1) / nb * splits; };
+  if (M <= 256) {
+    const int wide = tiles(4);
+    if (wide >= 192) {
+      const bool three = epi != kEpiSample && n_rb % 3 == 0 && wide < kComputeUnits && tiles(3) <= kComputeUnits;
+      return {three ? 3 : 4, M <= 128 ? 4 : 8};
+    }
+    return {M > 128 && wide * 2 >= 192 ? 4 : 2, 4};
+  }
+  if (epi == kEpiSample) return {4, 4};
+  const int halves = (M + 127) / 128;
+  Tile best = {4, 4};
+  float best_cost = 0.f;
+  for (const Tile t : {Tile{4, 4}, Tile{3, 4}, Tile{3, 8}, Tile{4, 8}}) {
+    if (sums && t.nb == 4 && t.nw == 8) continue;
+    float rounds;
+    if (t.nw == 4) {
+      const int blocks = tiles(t.nb) * halves, left = blocks % (2 * kComputeUnits);
+      rounds = (float)(blocks / (2 * kComputeUnits)) + (left == 0 ? 0.f : left <= kComputeUnits ? 0.62f : 1.f);
+    } else {
+      const int full = tiles(t.nb) * (halves / 2), light = tiles(t.nb) * (halves & 1);
+      rounds = full + light <= kComputeUnits ? 1.f : (float)((full + kComputeUnits - 1) / kComputeUnits) + 0.55f * light / kComputeUnits;
+    }
+    const float cost = rounds * (t.nw == 4 ? (t.nb == 4 ? 69.f : 58.f) : (t.nb == 4 ? 63.f : 57.f));
+    if (best_cost == 0.f || cost < best_cost) { best = t; best_cost = cost; }
+  }
+  return best;
+}
+
+template <int NB, int NW, bool ONE>
 void launch_tile(hipStream_t s, const void* X, const void* W, void* out, int M, int N, int K, int epi, bool allow_split,
                  const SampleEpilogue& se) {
   const Plan p = make_plan(N, K, epi == kEpiResidual ? kEpiPartial : epi, allow_split);  // same K split as the other variants: bit-identical results
+  const bool whole = whole_k(M, N, K, epi, allow_split);
   const int n_rb = epi == kEpiSwiGLU ? (N >> 4) : (N >> 5);
-  const int n_tiles = (n_rb + NB - 1) / NB, m_tiles = (M + 127) / 128;
-  dim3 grid((n_tiles + 7) / 8 * 8 * m_tiles);
-  const bool sums = p.splits > 1 || epi == kEpiResidual;
-  const size_t lds = (size_t)NB * 3 * 4096 + (sums ? (size_t)(NB - tile_sums_in_registers(NB)) * 16384 : 0);
-#define RL_TILE(E) gemm_bf16_tile_kernel<NB, E><<<grid, 256, lds, s>>>((const u32x4_t*)X, (const u32x4_t*)W, out, M, N, K, p.kb_per_wave, p.splits, n_tiles, m_tiles, se)
+  const int n_tiles = (n_rb + NB - 1) / NB, m_tiles = (M + 32 * NW - 1) / (32 * NW), splits = whole ? p.splits : 1;
+  dim3 grid((n_tiles + 7) / 8 * 8 * m_tiles, whole ? 1 : p.splits);
+  const bool sums = splits > 1 || epi == kEpiResidual;
+  const size_t lds = (size_t)NB * 3 * 4096 + (sums ? (size_t)(NB - tile_sums_in_registers(NB, NW)) * NW * 4096 : 0);
+#define RL_TILE(E) gemm_bf16_tile_kernel<NB, NW, E, ONE><<<grid, NW * 64, lds, s>>>((const u32x4_t*)X, (const u32x4_t*)W, out, M, N, K, p.kb_per_wave, splits, n_tiles, m_tiles, se)
   if (epi == kEpiSwiGLU) RL_TILE(kEpiSwiGLU);
-  else if (epi == kEpiResidual) RL_TILE(kEpiResidual);
-  else if (epi == kEpiSample) { if constexpr (NB == 4) RL_TILE(kEpiSample); }
+  else if (epi == kEpiResidual) { if constexpr (!ONE && NB > 2) RL_TILE(kEpiResidual); }
+  else if (epi == kEpiSample) { if constexpr (NB % 2 == 0) RL_TILE(kEpiSample); }
   else RL_TILE(kEpiPartial);
 #undef RL_TILE
 }
 
 }  // namespace
 
-int gemm_bf16_partials(int M, int N, int K) { return tile_row_blocks(M, N, K, kEpiPartial, true) ? 1 : gemm_bf16_splits(N, K, kEpiPartial); }
-bool gemm_bf16_adds_residual(int M, int N, int K) { return tile_row_blocks(M, N, K, kEpiResidual, true) != 0; }
+int gemm_bf16_partials(int M, int N, int K) { return whole_k(M, N, K, kEpiPartial, true) ? 1 : gemm_bf16_splits(N, K, kEpiPartial); }
+bool gemm_bf16_adds_residual(int M, int N, int K) { return whole_k(M, N, K, kEpiResidual, true); }
 int gemm_bf16_splits(int N, int K, int epi) { return make_plan(N, K, epi, true).splits; }
 int gemm_bf16_weight_segment(int N, int K, bool split_k) { return make_plan(N, K, kEpiPartial, split_k).kb_per_wave; }
 
@@ -1446,101 +1121,35 @@ void launch_cols_st(hipStream_t s, const void* X, const void* W, void* out, int 
   }
 }
 
-template <int MBW, int XS>
-void launch_lds(hipStream_t s, const void* X, const void* W, void* out, int M, int N, int K, int epi, bool allow_split,
-                const SampleEpilogue& se) {
-  Plan p = make_plan(N, K, epi, allow_split);
-  const int m_tiles = (M + 128 * MBW - 1) / (128 * MBW);
-  if (epi == kEpiSwiGLU) {
-    dim3 grid(N >> 5, 1, m_tiles);
-    gemm_bf16_lds_kernel<MBW, kEpiSwiGLU, XS><<<grid, 256, 0, s>>>((const u32x4_t*)X, (const u32x4_t*)W, out, M, N, K, p.kb_per_wave, se);
-  } else if (epi == kEpiSample) {
-    dim3 grid(N >> 6, 1, m_tiles);
-    gemm_bf16_lds_kernel<MBW, kEpiSample, XS><<<grid, 256, 0, s>>>((const u32x4_t*)X, (const u32x4_t*)W, out, M, N, K, p.kb_per_wave, se);
-  } else {
-    dim3 grid(N >> 6, p.splits, m_tiles);
-    gemm_bf16_lds_kernel<MBW, kEpiPartial, XS><<<grid, 256, 0, s>>>((const u32x4_t*)X, (const u32x4_t*)W, out, M, N, K, p.kb_per_wave, se);
-  }
-}
-
-template <int MBW, int XS, int RBN = 4>
-void launch_lds4(hipStream_t s, const void* X, const void* W, void* out, int M, int N, int K, int epi, bool allow_split,
-                 const SampleEpilogue& se) {
-  Plan p = make_plan(N, K, epi, allow_split);  // same K split as the other variants: bit-identical results
-  const int m_tiles = (M + 128 * MBW - 1) / (128 * MBW);
-  const int n_rb = epi == kEpiSwiGLU ? (N >> 4) : (N >> 5);
-  const int tx = (n_rb + RBN - 1) / RBN;
-  const bool fold = m_tiles == 2 && (tx & 7) == 0;  // pair the two batch tiles of a weight tile on one die
-  dim3 grid(fold ? 2 * tx : tx, epi == kEpiPartial ? p.splits : 1, fold ? 1 : m_tiles);
-  const int tiles_x = fold ? tx : 0;
-  if (epi == kEpiSwiGLU)
-    gemm_bf16_lds4_kernel<MBW, kEpiSwiGLU, XS, RBN><<<grid, 256, 0, s>>>((const u32x4_t*)X, (const u32x4_t*)W, out, M, N, K, p.kb_per_wave, tiles_x, se);
-  else if (epi == kEpiSample) {
-    if constexpr (RBN == 4)
-      gemm_bf16_lds4_kernel<MBW, kEpiSample, XS, 4><<<grid, 256, 0, s>>>((const u32x4_t*)X, (const u32x4_t*)W, out, M, N, K, p.kb_per_wave, tiles_x, se);
-  } else
-    gemm_bf16_lds4_kernel<MBW, kEpiPartial, XS, RBN><<<grid, 256, 0, s>>>((const u32x4_t*)X, (const u32x4_t*)W, out, M, N, K, p.kb_per_wave, tiles_x, se);
-}
-
-void launch_lds8(hipStream_t s, const void* X, const void* W, void* out, int M, int N, int K, int epi, bool allow_split,
-                 const SampleEpilogue& se) {
-  Plan p = make_plan(N, K, epi, allow_split);  // same K split as the other variants: bit-identical results
-  const int tiles = epi == kEpiSwiGLU ? (N >> 5) : (N >> 6);
-  dim3 grid((tiles + 1) / 2, epi == kEpiPartial ? p.splits : 1, (M + 255) / 256);
-  if (epi == kEpiSwiGLU)
-    gemm_bf16_lds8_kernel<kEpiSwiGLU, 2><<<grid, 512, 0, s>>>((const u32x4_t*)X, (const u32x4_t*)W, out, M, N, K, p.kb_per_wave, se);
-  else if (epi == kEpiSample)
-    gemm_bf16_lds8_kernel<kEpiSample, 2><<<grid, 512, 0, s>>>((const u32x4_t*)X, (const u32x4_t*)W, out, M, N, K, p.kb_per_wave, se);
-  else
-    gemm_bf16_lds8_kernel<kEpiPartial, 2><<<grid, 512, 0, s>>>((const u32x4_t*)X, (const u32x4_t*)W, out, M, N, K, p.kb_per_wave, se);
-}
-
+// More than 64 rows.
 template <int MBW>
 void launch_cols(hipStream_t s, const void* X, const void* W, void* out, int M, int N, int K, int epi, bool allow_split,
                  const SampleEpilogue& se) {
-  if (make_plan(N, K, epi, allow_split).kb_per_wave % 4 == 0) {  // weight tiles shared through LDS
-    // The wide tile pays where it still leaves enough blocks to fill the chip.
-    const Plan p = make_plan(N, K, epi, allow_split);
-    const int tiles = epi == kEpiSwiGLU ? (N >> 5) : (N >> 6);
-    const int wide_blocks = ((tiles + 1) / 2) * (epi == kEpiPartial ? p.splits : 1);
-    // 129..256 rows: one block of eight waves per weight tile where that still gives >= 192 blocks (gate/up 82 -> 65 us,
-    // QKV 33 -> 29, output projection 538 -> 420 at 256 rows); the O and down projections would be left with 128 blocks
-    // (measured 21 -> 26 and 42 -> 50 us) and run as two batch tiles of 128 whose blocks are paired on one die.
-    // (more than 256 rows, where gemm_bf16_tile_kernel does not take over: the batch tiles of 256 count as blocks too,
-    // which brings the O and down projections in)
-    if (M > 128 && wide_blocks * ((M + 255) / 256) >= 192) {
-      // ... and 96-row tiles where those give every compute unit a block and 128-row tiles do not (M <= 256: one
-      // batch tile per weight tile; gate/up and QKV of the 8B shape)
-      const int n_rb = epi == kEpiSwiGLU ? (N >> 4) : (N >> 5);
-      const int splits = epi == kEpiPartial ? p.splits : 1;
-      if (M <= 256 && epi != kEpiSample && n_rb % 3 == 0 && wide_blocks < kComputeUnits && (n_rb / 3) * splits <= kComputeUnits) {
-        dim3 grid(n_rb / 3, splits, 1);
-        if (epi == kEpiSwiGLU)
-          gemm_bf16_lds8r3_kernel<kEpiSwiGLU, 2><<<grid, 512, 0, s>>>((const u32x4_t*)X, (const u32x4_t*)W, out, M, N, K, p.kb_per_wave);
-        else
-          gemm_bf16_lds8r3_kernel<kEpiPartial, 2><<<grid, 512, 0, s>>>((const u32x4_t*)X, (const u32x4_t*)W, out, M, N, K, p.kb_per_wave);
-        return;
-      }
-      launch_lds8(s, X, W, out, M, N, K, epi, allow_split, se);
+  const Plan p = make_plan(N, K, epi == kEpiResidual ? kEpiPartial : epi, allow_split);
+  if (p.kb_per_wave % 4 == 0) {  // weight tiles shared through LDS
+    const Tile t = pick_tile(M, N, K, epi, allow_split);
+    // 193..256 rows on 96-row tiles that make exactly one K split (gate/up): 59.4 us at 256 rows and 56.9 at 200, the tile kernel takes
+    // 61.4 and 57.6 (and 52.6 against 56.8 at 192).
+    if (t.nb == 3 && t.nw == 8 && epi == kEpiSwiGLU && M > 192 && M <= 256) {
+      gemm_bf16_lds8r3_kernel<kEpiSwiGLU, 2><<<dim3((N >> 4) / 3, 1, 1), 512, 0, s>>>((const u32x4_t*)X, (const u32x4_t*)W, out, M, N, K, p.kb_per_wave);
       return;
     }
-    if (wide_blocks * ((M + 127) / 128) >= 192) {
-      // up to 128 rows: 96-row tiles where 128-row tiles would leave a quarter of the compute units without a block
-      // and 96-row tiles give every unit one (gate/up 55 -> 41 us, QKV 21 -> 16 us at 128 rows)
-      const int n_rb = epi == kEpiSwiGLU ? (N >> 4) : (N >> 5);
-      const int splits = epi == kEpiPartial ? p.splits : 1;
-      if (M <= 128 && epi != kEpiSample && n_rb % 3 == 0 && wide_blocks < kComputeUnits && (n_rb / 3) * splits <= kComputeUnits) {
-        launch_lds4<1, 2, 3>(s, X, W, out, M, N, K, epi, allow_split, se);
-        return;
-      }
-      launch_lds4<1, 2>(s, X, W, out, M, N, K, epi, allow_split, se);
-      return;
-    }
-    launch_lds<MBW, MBW == 1 ? 4 : 2>(s, X, W, out, M, N, K, epi, allow_split, se);
-    return;
+    const bool one = M <= 32 * t.nw;  // a single batch tile
+#define RL_PICK(NB, NW) \
+  if (t.nb == NB && t.nw == NW) { \
+    if (one) launch_tile<NB, NW, true>(s, X, W, out, M, N, K, epi, allow_split, se); \
+    else launch_tile<NB, NW, false>(s, X, W, out, M, N, K, epi, allow_split, se); \
+    return; \
   }
-  // two buffers in flight per wave when the quarter length allows it (it does for every 8B-shaped matrix)
-  if (make_plan(N, K, epi, allow_split).kb_per_wave % 2 == 0) launch_cols_st<MBW, 2>(s, X, W, out, M, N, K, epi, allow_split, se);
+    RL_PICK(4, 4)
+    RL_PICK(3, 4)
+    RL_PICK(2, 4)
+    RL_PICK(4, 8)
+    RL_PICK(3, 8)
+#undef RL_PICK
+  }
+  // two buffers in flight per wave when the quarter length allows it
+  if (p.kb_per_wave % 2 == 0) launch_cols_st<MBW, 2>(s, X, W, out, M, N, K, epi, allow_split, se);
   else launch_cols_st<MBW, 1>(s, X, W, out, M, N, K, epi, allow_split, se);
 }
 
@@ -1550,10 +1159,6 @@ void launch_gemm_bf16(hipStream_t s, const void* X, const void* W, void* out, in
   static const SampleEpilogue none{};
   const SampleEpilogue& e = se ? *se : none;
   if (epi == kEpiSample) allow_split = false;
-  switch (tile_row_blocks(M, N, K, epi, allow_split)) {
-    case 4: launch_tile<4>(s, X, W, out, M, N, K, epi, allow_split, e); return;
-    case 3: launch_tile<3>(s, X, W, out, M, N, K, epi, allow_split, e); return;
-  }
   // 128-row tiles for the K-split projections whose halved grid still fills the chip (QKV at the 8B shape: 16 -> 15 us
   // at 32 rows, 20.5 -> 17.8 us at 64); measured a loss for gate/up and the output projection, which keep 64-row tiles.
   const bool wide = epi == kEpiPartial && make_plan(N, K, epi, allow_split).splits > 1 &&

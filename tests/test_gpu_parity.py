@@ -1686,6 +1686,35 @@ def test_bf16_layer_bits_in_whole_k_tiles(amd, over, sizes):
         assert torch.equal(o, outs[0])
 
 
+@pytest.mark.parametrize("over, sizes", [
+    # one batch tile, two of O and down, idle waves, three and more tiles, light last ones
+    (dict(), (65, 128, 129, 161, 193, 256, 290, 385, 640, 769, 1024)),
+    (dict(hidden=2048, n_q=16, n_kv=4, ffn=6400), (130, 517)),  # row blocks that no tile divides
+])
+def test_bf16_layer_bits_at_the_edges_of_batch_tiles(amd, over, sizes):
+    """Rows at both ends of a batch, around its tiles of 128 and 256 rows and next to waves without rows keep the bits they
+    have in a batch of their own."""
+    big = max(sizes)
+    ctxs = [(7 * i) % 50 for i in range(big)]
+    shape, wn, ro, ks, vs, x = _layer_case(amd, ctxs, seed=39, **over)
+    x = x.to(DEV)
+
+    def fresh(ids):
+        for i in ids:
+            ro.rl_seq_import_kv(i, [ks[i].to(DEV)], [vs[i].to(DEV)])
+
+    for n in sizes:
+        ro.rl_free_seqs(list(range(big)))
+        fresh(range(n))
+        whole = ro.rl_decode_hidden(list(range(n)), x[:n]).clone()
+        at = sorted({i for i in (0, 31, 32, 127, 128, 255, 256, 383, 384, n - 33, n - 2, n - 1) if 0 <= i < n})
+        ro.rl_free_seqs(list(range(n)))
+        fresh(range(big))
+        few = ro.rl_decode_hidden(at, x[at].contiguous())
+        assert torch.isfinite(whole).all() and torch.equal(whole[at], few), n
+    ro.close()
+
+
 def test_truncated_sampler_rows_that_leave_the_list_path(amd):
     """Rows whose cut does not fit the list of its bin (thousands of tokens within a thousandth of the range, long runs
     of equal logits, a single infinite logit) are selected digit by digit: same cut and draw as the oracle."""
