@@ -394,7 +394,8 @@ rl_status rl_debug_shuffle_free_pages(rl_model* m, uint64_t seed);
  * Test aid: switch off (on = 0) or on again (the default) the decode-step treatment of the samples of one
  * prompt (Section 2.3): sequences made by rl_prefill_groups hold the prompt's full pages in common, and rows
  * of such sequences that stand at the same position have the attention over those pages computed once per set
- * of rows instead of once per row.  Results of every other call must not change by a single bit.
+ * of rows instead of once per row, in steps whose size and contexts make that the faster way (on = 2, 3: in every step, in
+ * sets as wide as they get, or narrow ones).  Results of every other call must not change by a single bit.
  */
 rl_status rl_debug_share_attention(rl_model* m, int32_t on);
 /* on = 2: as on = 1, and the sets are as large as the kernel allows (bf16 pages: two 16-column operands side by

@@ -47,6 +47,18 @@ inline int attn_rows_per_set(int group, bool kv_fp8, int n_rows, int n_kv) {
   return std::min(kAttnSetRows, 32 / group);
 }
 
+// The longest context up to which the rows of a decode step do better each on its own (0: sharing always pays).  Sets make a merge launch
+// necessary (4.8 us) that rows of at most 4096 keys do without, and what they save is steps of a wave: a quarter of a
+// row's steps against those of a segment.  Up to a (row, kv head) pair per compute unit a step takes 1.05 us: 32 rows of 8 kv heads, attention
+// and merge, shared / each on its own: 600 keys 18.3 / 13.0 us, 1025 20.5 / 16.8, 1500 22.5 / 20.5, 1700 23.4 / 21.8, 1900 24.9 / 22.8,
+// 2040 23.6 / 24.4; 8 rows: 1025 16.9 / 15.4, 1500 18.7 / 18.0, 1700 19.6 / 19.5, 2040 18.6 / 21.6.  With more pairs the blocks of a unit share what it draws from memory:
+// 48 rows: 300 keys 16.8 / 13.7, 1025 23.9 / 24.0, 1300 25.0 / 28.2; 64 rows: 600 24.8 / 18.2, 1025 27.5 / 25.5, 1200 27.6 / 28.2; 96
+// rows: 600 30.5 / 27.5, 1025 38.9 / 37.6.  From 1024 pairs on (wide sets, packs): 128 rows of 300 keys 25.7 / 26.1, 600 30.9 / 35.1.
+inline int attn_alone_up_to(int n_rows, int n_kv) {
+  const int pairs = n_rows * n_kv;
+  return pairs <= 256 ? 1700 : pairs < 1024 ? 1024 : 0;
+}
+
 // Leading segments of a context of ctx keys that end inside the first shared_keys keys.
 inline int attn_shared_segments(int ctx, int shared_keys) {
   const int n_it = (ctx + 31) >> 5, n_seg = attn_num_segments(ctx);

@@ -176,7 +176,7 @@ struct rl_model {
   float* capture = nullptr;
   bool graph_alive = false;     // a decode graph owns the last two metadata slots
   int attn_segs_per_block = 4;  // segments per attention block of contexts beyond 4096 keys (one per wave)
-  int share_attention = 1;  // compute segments inside shared prompt pages once per set of rows (0: off, 2 / 3: wide sets always / never)
+  int share_attention = 1;  // compute segments inside shared prompt pages once per set of rows where that pays (0: never, 2 / 3: always, in wide / narrow sets)
   bool attention_appends = true;  // decode steps: the attention kernel forms q and appends k, v itself
   // profiling
   bool prof_on = false;
@@ -539,7 +539,8 @@ SlotUpload build_decode_meta(rl_model* m, int32_t n, const int32_t* seq_ids, cha
   }
   // rows of sequences that hold prompt pages in common and stand at the same position share those segments
   AttnPlan plan;
-  if (m->geo.dtype == kBF16 && m->share_attention) {
+  // (the test switch's wide and narrow sets: in every call)
+  if (m->geo.dtype == kBF16 && m->share_attention && (m->share_attention > 1 || max_ctx > attn_alone_up_to(n, m->geo.n_kv))) {
     std::vector<int64_t> fam(n);
     std::vector<int32_t> fam_blocks(n), pos(n);
     bool any = false;

@@ -1264,6 +1264,33 @@ def test_shared_attention_set_widths_agree_for_other_head_groupings(amd, n_q, n_
 
 
 @pytest.mark.parametrize("kv_fp8", [False, True])
+def test_steps_on_both_sides_of_the_line_where_sharing_pays(amd, kv_fp8):
+    """Small decode steps leave every row to itself up to 1700 keys and share beyond: over the line, the steps have the bits of
+    an instance that never shares and of one that always does, in the narrow sets."""
+    shape = dict(ri.SHAPES["layer8b"], n_layers=2, hidden=512, n_q=8, n_kv=2, ffn=768, vocab=8192)
+    w, _ = make_both(shape, 68, std=0.05)
+    wd = to_device(w)
+    seed, G = 12, 5
+    prompts = [ri.tokens((n,), shape["vocab"], 68, 975 + n).tolist() for n in (1693, 40)]
+    ids = list(range(2 * G))
+    every = [amd.Rollout(shape, wd, max_seqs=16, max_ctx=1760, max_rows=64, kv_pages=160, kv_fp8=kv_fp8) for _ in range(3)]
+    for r, mode in zip(every, (1, 0, 3)):
+        r.rl_debug_share_attention(mode)
+        r.rl_prefill_groups(ids, G, prompts, 1.0, seed)
+    V = shape["vocab"]
+    tok = torch.tensor(ri.tokens((len(ids),), V, 68, 990).tolist(), dtype=torch.int32, device=DEV)
+    for step in range(16):
+        zs = [torch.empty(len(ids), V, device=DEV) for _ in every]
+        outs = [r.rl_decode_step(ids, tok, 1.0, seed, debug_logits=z) for r, z in zip(every, zs)]
+        torch.cuda.synchronize()
+        for z, (t_, l_) in zip(zs[1:], outs[1:]):
+            assert torch.equal(zs[0], z) and torch.equal(outs[0][0], t_) and torch.equal(outs[0][1], l_), step
+        tok = outs[0][0].clone()
+    for r in every:
+        r.close()
+
+
+@pytest.mark.parametrize("kv_fp8", [False, True])
 def test_packed_segments_behind_shared_prompts_keep_their_bits(amd, kv_fp8):
     """Three samples each of prompts of one to nine shared segments (odd numbers of left-over segments; one beyond 4096 keys,
     one with rows of their own beside the packs) and one sequence alone, over a change of the segments left and of the page:
