@@ -48,15 +48,21 @@ inline int attn_rows_per_set(int group, bool kv_fp8, int n_rows, int n_kv) {
 }
 
 // The longest context up to which the rows of a decode step do better each on its own (0: sharing always pays).  Sets make a merge launch
-// necessary (4.8 us) that rows of at most 4096 keys do without, and what they save is steps of a wave: a quarter of a
-// row's steps against those of a segment.  Up to a (row, kv head) pair per compute unit a step takes 1.05 us: 32 rows of 8 kv heads, attention
-// and merge, shared / each on its own: 600 keys 18.3 / 13.0 us, 1025 20.5 / 16.8, 1500 22.5 / 20.5, 1700 23.4 / 21.8, 1900 24.9 / 22.8,
-// 2040 23.6 / 24.4; 8 rows: 1025 16.9 / 15.4, 1500 18.7 / 18.0, 1700 19.6 / 19.5, 2040 18.6 / 21.6.  With more pairs the blocks of a unit share what it draws from memory:
-// 48 rows: 300 keys 16.8 / 13.7, 1025 23.9 / 24.0, 1300 25.0 / 28.2; 64 rows: 600 24.8 / 18.2, 1025 27.5 / 25.5, 1200 27.6 / 28.2; 96
-// rows: 600 30.5 / 27.5, 1025 38.9 / 37.6.  From 1024 pairs on (wide sets, packs): 128 rows of 300 keys 25.7 / 26.1, 600 30.9 / 35.1.
+// necessary (4.8 us) that rows of at most 4096 keys do without.  What they save: a row alone takes its segments in one block, a quarter of the
+// steps per wave, where the two set blocks of five to eight segments (more than 1024 keys) take half of that; and bytes, as soon as several
+// blocks of a compute unit share what it draws from memory.  One layer, us, shared / each on its own (8 kv heads, groups of 8 samples):
+//   8 rows: 1200 keys 97.1 / 97.9, 1600 98.6 / 100.5, attention and merge alone at 600 15.8 / 12.4, at 1000 18.6 / 14.9
+//   16 rows: 1200 98.6 / 99.2;  32 rows: 1200 104.0 / 102.1, 1400 105.2 / 103.8, 1600 106.3 / 105.4, 36 layers of 1025 3891 / 3797
+//   48 rows: 600 120.0 / 119.5, 1000 124.6 / 125.3;  64 rows: 600 127.9 / 122.9, 800 129.5 / 125.9, 1000 130.2 / 129.4
+//   80 rows: 300 135.0 / 130.5, 700 142.6 / 138.3, 900 142.2 / 142.8;  104 rows: 500 152.5 / 151.9, 700 154.6 / 158.3
+//   120 rows: 300 153.9 / 151.1, 500 157.8 / 156.8, 700 159.7 / 162.0
+// From 1024 pairs on (wide sets, packs), attention and merge: 128 rows of 300 keys 25.7 / 26.1, 600 30.9 / 35.1.
 inline int attn_alone_up_to(int n_rows, int n_kv) {
   const int pairs = n_rows * n_kv;
-  return pairs <= 256 ? 1700 : pairs < 1024 ? 1024 : 0;
+  if (pairs <= 128) return 1024;
+  if (pairs <= 256) return 1500;
+  if (pairs <= 512) return 900;
+  return pairs <= 704 ? 768 : pairs < 1024 ? 512 : 0;
 }
 
 // Leading segments of a context of ctx keys that end inside the first shared_keys keys.
