@@ -37,7 +37,7 @@ TRAFFIC_RATIO = {
     ("wave", "attn_decode"): (1.045, "attn_bf16.hip", "ce330bccad2cbe27"),
     ("layer", "attn_decode"): (1.045, "attn_bf16.hip", "ce330bccad2cbe27"),
     ("full", "attn_decode"): (1.040, "attn_bf16.hip", "ce330bccad2cbe27"),
-    ("full", "gemm_gate_up_swiglu"): (1.010, "gemm_bf16.hip", "cc11ad038a976f7b"),
+    ("full", "gemm_gate_up_swiglu"): (1.010, "gemm_bf16.hip", "7c0f19125f9ae035"),
 }
 
 

@@ -268,6 +268,149 @@ __global__ __launch_bounds__(256) void gemm_bf16_mixed_kernel(const u32x4_t* __r
   }
 }
 
+// Gate/up of one or two rows, with the residual sums and the RMSNorm before it.  A norm launch of its own takes 4 us, and the
+// weights that follow wait for it.  Here every block forms the normalised rows itself: x and the split sums of the O projection are
+// requested first, the weights of ST k blocks per wave right behind them, and while those travel the rows are summed, normalised and left in
+// LDS as f16, from which the products take them.  No block waits for another (flags between blocks, written through:
+// no faster than the two launches; with fences at device scope 14 us slower).  x is not changed: the split sums stay pending
+// beside those of the down projection, for the next norm to add in the same order.
+// Norm, gate/up and down over the weights of six layers, us: one row 54.0 -> 49.9, two rows 54.1 -> 51.9 (every block reads 80 KB per row
+// from L2: more rows would pay more than the launch).  Arithmetic of residual_norm_kernel and of the K-split kernels: same bits.
+// grid: x = n_big tiles of two row blocks, then n_small of one (see gemm_bf16_mixed_kernel).
+struct RowNorm {
+  const float* x;
+  const float* part;  // S <= kRowNormMaxS split sums, `stride` floats apart
+  size_t stride;
+  const uint16_t* gain;
+  float eps;
+  int S;
+};
+constexpr int kRowNormMaxS = 4, kRowNormPass = 1024, kRowNormMaxPass = 4;  // a pass: four elements per thread
+
+template <int R, int ST, int RB>
+__device__ __forceinline__ void row_tile(const RowNorm& rn, const u32x4_t* __restrict__ W, void* __restrict__ out, int M, int N,
+                                        int K, int rb_first, float (&red)[4][16][64], u32x4_t* xs) {
+  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+  const int KB = K >> 6, n = KB >> 2, passes = K / kRowNormPass;
+  const u32x4_t* wr[RB];
+#pragma unroll
+  for (int nb = 0; nb < RB; ++nb) wr[nb] = W + (size_t)(rb_first + nb) * KB * 256 + wave * 256 + lane;  // slot 4 b + wave: k block b of this wave's quarter
+  u32x4_t f[ST][RB][4];
+  auto load = [&](int s, int b) __attribute__((always_inline)) {
+#pragma unroll
+    for (int t = 0; t < 4; ++t)
+#pragma unroll
+      for (int nb = 0; nb < RB; ++nb) f[s][nb][t] = __builtin_nontemporal_load(wr[nb] + b * 1024 + t * 64);
+  };
+  auto barrier = []() __attribute__((always_inline)) {  // orders LDS alone: the weights stay in flight
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+    __builtin_amdgcn_s_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+  };
+  float4 v[R][kRowNormMaxPass], p[R][kRowNormMaxS][kRowNormMaxPass];
+  uint2 graw[kRowNormMaxPass];
+#pragma unroll
+  for (int q = 0; q < kRowNormMaxPass; ++q) {
+    const int i0 = min(q, passes - 1) * kRowNormPass + threadIdx.x * 4;  // surplus passes repeat the last one and are dropped
+    graw[q] = *(const uint2*)(rn.gain + i0);
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+      const size_t at = (size_t)min(r, M - 1) * K + i0;
+      v[r][q] = *(const float4*)(rn.x + at);
+#pragma unroll
+      for (int sp = 0; sp < kRowNormMaxS; ++sp) p[r][sp][q] = *(const float4*)(rn.part + min(sp, rn.S - 1) * rn.stride + at);
+    }
+  }
+  __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+  for (int s = 0; s < ST; ++s) load(s, s);
+  __builtin_amdgcn_sched_barrier(0);
+  float* const ss = &red[0][0][0];
+#pragma unroll
+  for (int r = 0; r < R; ++r)
+#pragma unroll
+    for (int q = 0; q < kRowNormMaxPass; ++q) {
+      float4 a = v[r][q];
+#pragma unroll
+      for (int sp = 0; sp < kRowNormMaxS; ++sp)
+        if (sp < rn.S) {
+          const float4 b = p[r][sp][q];
+          a.x += b.x; a.y += b.y; a.z += b.z; a.w += b.w;
+        }
+      v[r][q] = a;
+      const float sum = wave_sum((a.x * a.x + a.y * a.y) + (a.z * a.z + a.w * a.w));
+      if (lane == 0) ss[(r * kRowNormMaxPass + q) * 4 + wave] = sum;
+    }
+  barrier();
+#pragma unroll
+  for (int r = 0; r < R; ++r) {
+    float sum = 0.f;
+    for (int w = 0; w < 4 * passes; ++w) sum += ss[r * kRowNormMaxPass * 4 + w];
+    const float inv = 1.0f / sqrtf(sum / (float)K + rn.eps);
+#pragma unroll
+    for (int q = 0; q < kRowNormMaxPass; ++q) {
+      if (q >= passes) break;
+      const float4 a = v[r][q];
+      const float4 g = make_float4(bf2f(graw[q].x & 0xffffu), bf2f(graw[q].x >> 16), bf2f(graw[q].y & 0xffffu), bf2f(graw[q].y >> 16));
+      ((uint2*)xs)[r * (K >> 2) + q * (kRowNormPass / 4) + threadIdx.x] =
+          make_uint2(pack2h(a.x * inv * g.x, a.y * inv * g.y), pack2h(a.z * inv * g.z, a.w * inv * g.w));
+    }
+  }
+  barrier();
+  f32x16_t acc[RB];
+#pragma unroll
+  for (int nb = 0; nb < RB; ++nb)
+#pragma unroll
+    for (int r = 0; r < 16; ++r) acc[nb][r] = 0.f;
+  const int col = lane & 31, hb = lane >> 5;
+  const u32x4_t* const xl = xs + (size_t)min(col, R - 1) * (K >> 3) + wave * n * 8 + hb * 4;  // surplus columns repeat the last row, never stored
+  auto multiply = [&](int s, int b) __attribute__((always_inline)) {
+#pragma unroll
+    for (int t = 0; t < 4; ++t) {
+      const u32x4_t x = xl[b * 8 + t];
+#pragma unroll
+      for (int nb = 0; nb < RB; ++nb) acc[nb] = mfma_f16(f[s][nb][t], x, acc[nb]);
+    }
+  };
+  int b = 0;
+  for (; b + ST < n; b += ST) {  // n is a multiple of ST
+#pragma unroll
+    for (int s = 0; s < ST; ++s) {
+      multiply(s, b + s);
+      __builtin_amdgcn_sched_barrier(0);
+      load(s, b + s + ST);
+      __builtin_amdgcn_sched_barrier(0);
+    }
+  }
+#pragma unroll
+  for (int s = 0; s < ST; ++s) multiply(s, b + s);
+  float sum[RB][16];
+#pragma unroll
+  for (int nb = 0; nb < RB; ++nb) {
+    __syncthreads();
+#pragma unroll
+    for (int r = 0; r < 16; ++r) red[wave][r][lane] = acc[nb][r];
+    __syncthreads();
+    if (wave == 0) {
+#pragma unroll
+      for (int r = 0; r < 16; ++r) sum[nb][r] = ((red[0][r][lane] + red[1][r][lane]) + red[2][r][lane]) + red[3][r][lane];
+    }
+  }
+  if (wave != 0 || col >= M) return;
+#pragma unroll
+  for (int nb = 0; nb < RB; ++nb) store_rowblock<kEpiSwiGLU>(sum[nb], col, hb, rb_first + nb, 0, M, N, out);
+}
+
+template <int R, int ST>
+__global__ __launch_bounds__(256, 2) void norm_gate_up_kernel(RowNorm rn, const u32x4_t* __restrict__ W, void* __restrict__ out, int M,
+                                                             int N, int K, int n_big) {
+  __shared__ float red[4][16][64];
+  __shared__ u32x4_t xs[R * kRowNormPass * kRowNormMaxPass / 8];
+  const int id = blockIdx.x;  // block-uniform
+  if (id < n_big) row_tile<R, ST, 2>(rn, W, out, M, N, K, id * 2, red, xs);
+  else row_tile<R, ST, 1>(rn, W, out, M, N, K, n_big + id, red, xs);
+}
+
 // The K-split kernel with a 128-row weight tile (two 64-row pairs, four 32-row blocks per wave).  Every block reads
 // the whole activation panel once, so halving the number of blocks halves that traffic; from about 48 rows on the
 // panel reads of the 64-row tiling are as large as the weight stream itself and the launch is bound by what L2
@@ -1090,6 +1233,19 @@ int gemm_bf16_partials(int M, int N, int K) { return whole_k(M, N, K, kEpiPartia
 bool gemm_bf16_adds_residual(int M, int N, int K) { return whole_k(M, N, K, kEpiResidual, true); }
 int gemm_bf16_splits(int N, int K, int epi) { return make_plan(N, K, epi, true).splits; }
 int gemm_bf16_weight_segment(int N, int K, bool split_k) { return make_plan(N, K, kEpiPartial, split_k).kb_per_wave; }
+
+// Whole k blocks per wave and pass: hidden a multiple of 1024; the K quarters hold at least the four k blocks of the ring.
+bool norm_gate_up_takes(int M, int H, int S) { return M <= 2 && H % kRowNormPass == 0 && H <= kRowNormPass * kRowNormMaxPass && S >= 1 && S <= kRowNormMaxS; }
+
+void launch_norm_gate_up(hipStream_t s, const float* x, const float* part, int S, const void* gain, float eps, const void* W, void* out,
+                         int M, int F, int H) {
+  const RowNorm rn = {x, part, (size_t)M * H, (const uint16_t*)gain, eps, S};
+  const int tiles = F >> 4;  // row blocks of the interleaved matrix
+  const bool mixed = mixed_fits(F, H, kEpiSwiGLU, true);
+  const int n_big = mixed ? tiles / 3 : tiles / 2, blocks = mixed ? 2 * n_big : n_big;
+  if (M == 1) norm_gate_up_kernel<1, 4><<<blocks, 256, 0, s>>>(rn, (const u32x4_t*)W, out, M, F, H, n_big);
+  else norm_gate_up_kernel<2, 2><<<blocks, 256, 0, s>>>(rn, (const u32x4_t*)W, out, M, F, H, n_big);
+}
 
 template <int MB>
 void launch_st(hipStream_t s, const void* X, const void* W, void* out, int M, int N, int K, int epi, bool allow_split,

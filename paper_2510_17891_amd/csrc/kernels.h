@@ -174,6 +174,10 @@ int gemm_bf16_splits(int N, int K, int epi);
 int gemm_bf16_partials(int M, int N, int K);
 // Whether a product of M rows can be added to the residual stream by the projection itself (kEpiResidual).
 bool gemm_bf16_adds_residual(int M, int N, int K);
+// Gate/up with the residual sums and the norm before it, for a row or two: x + S split sums [S][M][H], normalised, times W, SwiGLU; x stays as it is.
+bool norm_gate_up_takes(int M, int H, int S);
+void launch_norm_gate_up(hipStream_t s, const float* x, const float* part, int S, const void* gain, float eps, const void* W, void* out,
+                         int M, int F, int H);
 // MFMA GEMM of the bf16 models: X f16 fragment-major [M x K], W bf16 fragment-major [N x K] (2N rows for SwiGLU: gate
 // and up rows interleaved in groups of 16).
 // kEpiPartial: out = fp32 [gemm_bf16_partials(M, N, K)][M][N];  kEpiResidual (only where gemm_bf16_adds_residual): out =

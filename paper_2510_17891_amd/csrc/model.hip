@@ -250,8 +250,11 @@ rl_status slot_in_use(rl_model* m, hipStream_t st, int slot) {
 }
 
 // Run all decoder layers on the M rows whose residual stream sits in ws.x.  Leaves the last down-projection's
-// split partials pending; returns their count (0 where the projection added them itself) so that the caller's final
-// residual_norm adds them.
+// split partials pending and returns them, so that the caller's final residual_norm adds them.
+struct Pending {  // n split sums of M rows that are still to be added to the residual stream, in order
+  const float* part = nullptr;
+  int n = 0;
+};
 struct SharedAttn {  // device pointers into the metadata slot of the call (empty: every row on its own)
   const int32_t* skip = nullptr;
   const AttnShared* sets = nullptr;
@@ -267,8 +270,8 @@ void copy_capture(hipStream_t st, float* cap, const float* x, int M, int H) {
 
 // One layer from the attention on, for M rows with residual stream x.  ap: a decode step, whose attention takes over the
 // rotation and the KV append (a row's block is then the only reader of the key it writes); otherwise the queries are in
-// q.  Returns the down projection's split partials that are left to add to x (0 where it added them itself).
-int finish_layer(rl_model* m, hipStream_t st, int l, int M, const RowMeta* rows, int max_ctx_in_batch, const SharedAttn& sa,
+// q.  Returns the split partials that are left to add to x (none where the projections added them themselves).
+Pending finish_layer(rl_model* m, hipStream_t st, int l, int M, const RowMeta* rows, int max_ctx_in_batch, const SharedAttn& sa,
                  const float* q, const AttnAppend* ap, float* x) {
   const Geometry& g = m->geo;
   const bool bf = g.dtype == kBF16;
@@ -292,10 +295,23 @@ int finish_layer(rl_model* m, hipStream_t st, int l, int M, const RowMeta* rows,
     Timer t(m, st, K_ATTN);
     launch_attn_f32(st, g, q, rows, bt, m->k_pool(l), m->v_pool(l), (float*)o, M, ap);
   }
+  // A row or two: gate/up does the norm before it, and leaves the O projection's split sums pending with those of the down projection behind them;
+  // the attention's partials make room for both (a model of one row has no other buffer that long).
+  const int s_up = bf ? gemm_bf16_partials(M, H, nqd) : 0, s_down = bf ? gemm_bf16_partials(M, H, F) : 0;
+  if (bf && norm_gate_up_takes(M, H, s_up) && !gemm_bf16_adds_residual(M, H, nqd) && !gemm_bf16_adds_residual(M, H, F) &&
+      (size_t)(s_up + s_down) * M * H <= (size_t)m->cfg.max_rows * g.n_q * m->lay.max_segs * (g.head_dim + 2)) {
+    { Timer t(m, st, K_OPROJ);
+      launch_gemm_bf16(st, o, m->wo[l], apart, M, H, nqd, kEpiPartial); }
+    { Timer t(m, st, K_GATEUP);
+      launch_norm_gate_up(st, x, apart, s_up, m->mlp_norm[l], g.rms_eps, m->w_gate_up[l], a, M, F, H); }
+    Timer t(m, st, K_DOWN);
+    launch_gemm_bf16(st, a, m->w_down[l], apart + (size_t)s_up * M * H, M, H, F, kEpiPartial);
+    return {apart, s_up + s_down};
+  }
   int s_o = 1;
   { Timer t(m, st, K_OPROJ);
     if (bf && gemm_bf16_adds_residual(M, H, nqd)) { launch_gemm_bf16(st, o, m->wo[l], x, M, H, nqd, kEpiResidual); s_o = 0; }
-    else if (bf) { launch_gemm_bf16(st, o, m->wo[l], part, M, H, nqd, kEpiPartial); s_o = gemm_bf16_partials(M, H, nqd); }
+    else if (bf) { launch_gemm_bf16(st, o, m->wo[l], part, M, H, nqd, kEpiPartial); s_o = s_up; }
     else { launch_gemm_f32(st, (const float*)o, (const float*)m->wo[l], x, M, H, nqd, kEpiResidual); s_o = 0; } }
   if (bf) {
     Timer t(m, st, K_NORM);
@@ -305,10 +321,10 @@ int finish_layer(rl_model* m, hipStream_t st, int l, int M, const RowMeta* rows,
     if (bf) launch_gemm_bf16(st, h, m->w_gate_up[l], a, M, F, H, kEpiSwiGLU);
     else launch_gemm_f32(st, x, (const float*)m->w_gate_up[l], (float*)a, M, F, H, kEpiSwiGLU, (const float*)m->mlp_norm[l], g.rms_eps); }
   Timer t(m, st, K_DOWN);
-  if (bf && gemm_bf16_adds_residual(M, H, F)) { launch_gemm_bf16(st, a, m->w_down[l], x, M, H, F, kEpiResidual); return 0; }
-  if (bf) { launch_gemm_bf16(st, a, m->w_down[l], part, M, H, F, kEpiPartial); return gemm_bf16_partials(M, H, F); }
+  if (bf && gemm_bf16_adds_residual(M, H, F)) { launch_gemm_bf16(st, a, m->w_down[l], x, M, H, F, kEpiResidual); return {}; }
+  if (bf) { launch_gemm_bf16(st, a, m->w_down[l], part, M, H, F, kEpiPartial); return {part, s_down}; }
   launch_gemm_f32(st, (const float*)a, (const float*)m->w_down[l], x, M, H, F, kEpiResidual);
-  return 0;
+  return {};
 }
 
 // Rows of a prefill chunk that end a prompt: device pairs (row of the chunk, prompt).
@@ -324,7 +340,7 @@ struct PromptEnds {
 // q_last, by prompt) for one pass over the prompts of all chunks, and the layer ends there unless its boundary is captured.
 // It saves most of one layer: of four, 4 prompts of 1024 tokens 9.4 -> 7.8 ms and one of 301 1.88 -> 1.72 (with the copies per
 // sequence gone); of thirty-six 79.1 -> 77.1 and 12.95 -> 12.75.
-int run_layers(rl_model* m, hipStream_t st, int M, const RowMeta* rows, int max_ctx_in_batch,
+Pending run_layers(rl_model* m, hipStream_t st, int M, const RowMeta* rows, int max_ctx_in_batch,
                const SharedAttn& sa = SharedAttn(), bool one_row_per_seq = false, const PromptEnds* ends = nullptr) {
   const Geometry& g = m->geo;
   const bool bf = g.dtype == kBF16;
@@ -334,14 +350,14 @@ int run_layers(rl_model* m, hipStream_t st, int M, const RowMeta* rows, int max_
   float* part = m->wsp<float>(m->lay.part);
   float* q = m->wsp<float>(m->lay.q);
   const float2* rope = m->wsp<float2>(m->lay.rope);
-  int pend = 0;
+  Pending pend;
   for (int l = 0; l < g.n_layers; ++l) {
     float* cap = m->capture ? m->capture + (size_t)l * m->cfg.max_rows * H : nullptr;
     if (!bf) {
       copy_capture(st, cap, x, M, H);
     } else if (l > 0) {
       Timer t(m, st, K_NORM);
-      launch_residual_norm(st, x, x, pend ? part : nullptr, pend, m->attn_norm[l], h, cap, M, H, g.rms_eps);
+      launch_residual_norm(st, x, x, pend.part, pend.n, m->attn_norm[l], h, cap, M, H, g.rms_eps);
     }
     int s_qkv = 1;
     { Timer t(m, st, K_QKV);
@@ -357,7 +373,7 @@ int run_layers(rl_model* m, hipStream_t st, int M, const RowMeta* rows, int max_
     }
     if (ends && l + 1 == g.n_layers) {
       launch_put_aside(st, ends->pairs, ends->n, x, m->wsp<float>(m->lay.x_last), H, q, m->wsp<float>(m->lay.q_last), g.n_q * g.head_dim);
-      if (!m->capture) return 0;
+      if (!m->capture) return {};
     }
     pend = finish_layer(m, st, l, M, rows, max_ctx_in_batch, sa, q, fused ? &ap : nullptr, x);
   }
@@ -366,7 +382,7 @@ int run_layers(rl_model* m, hipStream_t st, int M, const RowMeta* rows, int max_
 
 // Final norm, output projection and sampling for M rows; row r's residual (pending partials added) is row r / group of `xbuf`,
 // which is not the workspace's own x if group > 1.
-void run_head(rl_model* m, hipStream_t st, int M, float* xbuf, int pend, const RowMeta* rows, int pos_offset,
+void run_head(rl_model* m, hipStream_t st, int M, float* xbuf, const Pending& pend, const RowMeta* rows, int pos_offset,
               const int32_t* forced, const rl_sampling* sp, int32_t* out_tokens, float* out_lp, float* debug_logits,
               bool score_only = false, int group = 1) {
   int32_t* last_tok = score_only ? nullptr : m->wsp<int32_t>(m->lay.last_tok);
@@ -378,7 +394,7 @@ void run_head(rl_model* m, hipStream_t st, int M, float* xbuf, int pend, const R
   const bool bf = g.dtype == kBF16;
   if (bf) {
     Timer t(m, st, K_NORM);
-    launch_residual_norm(st, xbuf, group > 1 ? m->wsp<float>(m->lay.x) : xbuf, pend ? part : nullptr, pend, m->final_norm, h, cap, M, g.hidden, g.rms_eps, group);
+    launch_residual_norm(st, xbuf, group > 1 ? m->wsp<float>(m->lay.x) : xbuf, pend.part, pend.n, m->final_norm, h, cap, M, g.hidden, g.rms_eps, group);
   } else {
     if (group > 1) {
       launch_repeat_rows(st, xbuf, m->wsp<float>(m->lay.x), M, g.hidden, group);
@@ -584,7 +600,7 @@ rl_status prepare_decode_meta(rl_model* m, int32_t n, const int32_t* seq_ids, De
 // The kernels of one decode step behind its first: layers and head.
 void decode_enqueue(rl_model* m, hipStream_t st, int n, const RowMeta* rows, int max_ctx_in_batch, const SharedAttn& sa,
                     const int32_t* forced_next, const rl_sampling* sp, int32_t* out_tokens, float* out_logprobs, float* debug_logits) {
-  int pend = run_layers(m, st, n, rows, max_ctx_in_batch, sa, true);
+  const Pending pend = run_layers(m, st, n, rows, max_ctx_in_batch, sa, true);
   run_head(m, st, n, m->wsp<float>(m->lay.x), pend, rows, 1, forced_next, sp, out_tokens, out_logprobs, debug_logits);
 }
 
@@ -909,13 +925,13 @@ rl_status rl_decode_hidden(rl_model* m, void* stream, int32_t n, const int32_t* 
   in.src = hidden_in;
   rs = enter_rows(m, st, dm.slot, in, dm.up, n);
   if (rs != RL_OK) return rs;
-  int pend = run_layers(m, st, n, dm.rows_dev, dm.max_ctx, dm.sa, true);
+  const Pending pend = run_layers(m, st, n, dm.rows_dev, dm.max_ctx, dm.sa, true);
   float* cap = m->capture ? m->capture + (size_t)m->geo.n_layers * m->cfg.max_rows * m->geo.hidden : nullptr;
   // the last sums go straight to the caller's buffer, which may be the one the rows came from
-  const bool direct = pend && (uintptr_t)hidden_out % 16 == 0;
-  if (pend) {
+  const bool direct = pend.n && (uintptr_t)hidden_out % 16 == 0;
+  if (pend.n) {
     Timer t(m, st, K_NORM);
-    launch_residual_norm(st, x, direct ? hidden_out : x, m->wsp<float>(m->lay.part), pend, nullptr, nullptr, cap, n, m->geo.hidden, m->geo.rms_eps);
+    launch_residual_norm(st, x, direct ? hidden_out : x, pend.part, pend.n, nullptr, nullptr, cap, n, m->geo.hidden, m->geo.rms_eps);
   } else {
     copy_capture(st, cap, x, n, m->geo.hidden);
   }
@@ -1043,18 +1059,18 @@ static rl_status prefill_impl(rl_model* m, hipStream_t st, int32_t n_prompts, in
     }
     rs = enter_rows(m, st, slot, table_rows(m, hs, ht), up, M);
     if (rs != RL_OK) return rs;
-    const int pend = run_layers(m, st, M, (const RowMeta*)ds, max_ctx, sa, false, &ends);
+    const Pending pend = run_layers(m, st, M, (const RowMeta*)ds, max_ctx, sa, false, &ends);
     if (m->capture) {  // the boundary behind the last layer
       float* x = m->wsp<float>(m->lay.x);
       float* cap = m->capture + (size_t)m->geo.n_layers * m->cfg.max_rows * H;
-      if (pend) launch_residual_norm(st, x, x, m->wsp<float>(m->lay.part), pend, nullptr, nullptr, cap, M, H, m->geo.rms_eps);
+      if (pend.n) launch_residual_norm(st, x, x, pend.part, pend.n, nullptr, nullptr, cap, M, H, m->geo.rms_eps);
       else copy_capture(st, cap, x, M, H);
     }
   }
 
   // ---- the last rows of all prompts through the rest of the last layer -------------------------------------
   float* x_last = m->wsp<float>(m->lay.x_last);
-  const int pend = finish_layer(m, st, m->geo.n_layers - 1, n_prompts, tail, max_len, SharedAttn(), m->wsp<float>(m->lay.q_last), nullptr, x_last);
+  const Pending pend = finish_layer(m, st, m->geo.n_layers - 1, n_prompts, tail, max_len, SharedAttn(), m->wsp<float>(m->lay.q_last), nullptr, x_last);
 
   // ---- the other members of each group: shared full pages, private copy of the partial page ---------------
   if (group > 1) {
@@ -1193,7 +1209,7 @@ rl_status rl_score(rl_model* m, void* stream, int32_t n, const int32_t* seq_ids,
     if (result != RL_OK) break;
     const RowMeta* rows = (const RowMeta*)ds;
     const int32_t* forced = (const int32_t*)(ds + m->lay.slot_upd);
-    int pend = run_layers(m, st, M, rows, max_ctx, sa);
+    const Pending pend = run_layers(m, st, M, rows, max_ctx, sa);
     run_head(m, st, M, x, pend, rows, 1, forced, &sp, tmp_tok, tmp_lp, nullptr, true);
     launch_scatter_f32(st, tmp_lp, forced + M, out_logprobs, M);
     done += M;

@@ -1742,6 +1742,42 @@ def test_bf16_layer_bits_at_the_edges_of_batch_tiles(amd, over, sizes):
     ro.close()
 
 
+@pytest.mark.parametrize("over, max_rows", [
+    (dict(hidden=1024, n_q=8, n_kv=2, ffn=768), 1), (dict(hidden=2048, n_q=4, n_kv=4, ffn=256), 8),
+    (dict(hidden=3072, n_q=24, n_kv=8, ffn=2304), 8), (dict(hidden=4096, n_q=32, n_kv=8, ffn=12288), 1),  # tiles of one and of two sizes
+    (dict(hidden=4096, n_q=2, n_kv=1, ffn=512), 1),                                                     # room for the split sums or not
+    (dict(hidden=512, n_q=4, n_kv=1, ffn=768), 8),                                                      # a norm launch of its own
+])
+def test_bf16_steps_of_one_and_two_rows_keep_a_rows_bits(amd, over, max_rows):
+    """A row or two: gate/up forms the normalised rows itself and the split sums of two projections wait for the next norm.  Prefill (a
+    prompt's last row alone), decode steps and the captured boundaries have the bits of a model that steps three rows."""
+    shape = dict(ri.SHAPES["layer8b"], n_layers=2, vocab=8192, **over)
+    w, _ = make_both(shape, 69, std=0.05)
+    wd = to_device(w)
+    V, seed = shape["vocab"], 13
+    prompts = [ri.tokens((n,), V, 69, 980 + n).tolist() for n in (21, 34, 5)]
+    fed = [ri.tokens((3,), V, 69, 990 + k).tolist() for k in range(3)]
+    got = {}
+    for n, rows in ((3, 8), (2, max(2, max_rows)), (1, max_rows)):
+        ro = amd.Rollout(shape, wd, max_seqs=3, max_ctx=64, max_rows=rows, kv_pages=12)
+        ids = list(range(n))
+        out = [t.clone() for t in ro.rl_prefill(ids, prompts[:n], 1.0, seed)] if rows > 2 else None
+        if out is None:  # one prompt per call, token by token
+            per = [ro.rl_prefill([i], [prompts[i]], 1.0, seed) for i in ids]
+            out = [torch.cat([p[k] for p in per]) for k in (0, 1)]
+        cap = ro.rl_set_capture(True)
+        for k in range(3):
+            z = torch.empty(n, V, device=DEV)
+            tok, lp = ro.rl_decode_step(ids, torch.tensor(fed[k][:n], dtype=torch.int32, device=DEV), 1.0, seed, debug_logits=z)
+            out += [tok.clone(), lp.clone(), z, cap[:, :n].transpose(0, 1).clone()]
+        torch.cuda.synchronize()
+        ro.close()
+        got[n] = out
+    for n in (1, 2):
+        for a, b in zip(got[n], got[3]):
+            assert torch.equal(a, b[:n]), n
+
+
 def test_truncated_sampler_rows_that_leave_the_list_path(amd):
     """Rows whose cut does not fit the list of its bin (thousands of tokens within a thousandth of the range, long runs
     of equal logits, a single infinite logit) are selected digit by digit: same cut and draw as the oracle."""
