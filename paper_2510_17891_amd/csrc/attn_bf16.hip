@@ -13,13 +13,12 @@
 // The context is cut into segments whose number and bounds depend on the context length alone
 // (4*ceil(ctx/1024) equal runs of 32-key steps), each leaving (max, sum, unnormalised O) per head.  One block of
 // four waves handles up to 16 segments of one (row, kv head), each wave a contiguous quarter; beyond 4096 keys a block
-// takes `spb` segments (a launch parameter, 4 by default: shorter blocks fill the end of a long launch better).
-//   ctx <= 4096: one block per (row, kv head); partials stay in LDS and after a block barrier the four waves
-//                merge the segments of one head each, flat and in index order.
-//   ctx  > 4096: ceil(segments/spb) blocks per (row, kv head), so that long contexts become many short blocks
-//                that the dispatcher can balance; partials go to the workspace and a second small kernel does the
-//                same flat merge.
-// Which path runs is a function of the row's context only, and nothing synchronises across blocks inside a
+// takes `spb` segments (a launch parameter, 4 by default: shorter blocks fill the end of a long launch better), and in small
+// launches that leave compute units idle also below (attn_split).
+//   one block:      partials stay in LDS and after a block barrier the four waves merge the segments of one head each,
+//                   flat and in index order.
+//   several blocks: partials go to the workspace and a second small kernel does the same flat merge.
+// Segments and merge are functions of the row's context only, and nothing synchronises across blocks inside a
 // kernel (a device-scope fence is an L2 write-back on this multi-die part), so the bits of a row's result do not
 // depend on the batch.
 //
@@ -78,6 +77,7 @@ __device__ __forceinline__ size_t part_o(int max_segs, int seg) { return (size_t
 __device__ __forceinline__ size_t part_ml(int max_segs, int seg) { return (size_t)max_segs * kD + 2 * (size_t)seg; }
 constexpr int kQStride = kD + 4;              // floats per column of the queries in LDS: 16 columns read at once hit different banks
 constexpr int kPackPages = 32;                // room for the page list of a wave of a pack
+constexpr int kComputeUnits = 256;
 constexpr int kLdsSegs = 16;                  // contexts up to 4096 keep their segment partials in LDS
 
 constexpr int kPairU4(bool kv8) { return kv8 ? 2 * kPageElems / 16 : 2 * kPageElems / 8; }  // 16-byte units of one (page, kv head): K and V
@@ -175,10 +175,10 @@ __device__ __forceinline__ void widen(PagePair& out, const PagePair8& in) {
       }
 }
 
-// Blocks per (row, kv head): contexts of up to kLdsSegs segments take one block (partials merged in LDS), longer ones
-// one block per spb segments (spb <= kLdsSegs, a launch parameter: smaller blocks balance better at the end of a
-// launch; the partials and their merge do not depend on it).
-__host__ __device__ inline int attn_num_splits(int n_seg, int spb) { return n_seg <= kLdsSegs ? 1 : (n_seg + spb - 1) / spb; }
+// Blocks per (row, kv head): contexts of up to whole_segs (<= kLdsSegs) segments take one block (partials merged in LDS), longer ones
+// one block per spb segments (spb <= kLdsSegs; both are launch parameters: smaller blocks balance better at the end of a
+// launch; the partials and their merge do not depend on them).
+__host__ __device__ inline int attn_num_splits(int n_seg, int whole_segs, int spb) { return n_seg <= whole_segs ? 1 : (n_seg + spb - 1) / spb; }
 
 // attn_seg_begin with the division as a multiplication: exact, since sgm * n_it <= 256 * 2048 and m exceeds 2^32 / n_seg by
 // less than one.
@@ -270,7 +270,7 @@ __global__ __launch_bounds__(256, KV8 ? 3 : 2) void attn_decode_bf16_kernel(cons
                                                                int max_segs, int n_q, int n_kv, float scale,
                                                                uint16_t* __restrict__ o_out, int lds_part_offset,
                                                                int lds_q_offset, int n_rows, const int32_t* __restrict__ skip_segs,
-                                                               const AttnShared* __restrict__ shared, AppendArgs ap, int spb) {
+                                                               const AttnShared* __restrict__ shared, AppendArgs ap, int whole_segs, int spb) {
   extern __shared__ int32_t pages[];  // block-table slice of this row: ceil(ctx/16) entries (+1 pad), then partials
   const int hk = blockIdx.x;
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
@@ -319,7 +319,7 @@ __global__ __launch_bounds__(256, KV8 ? 3 : 2) void attn_decode_bf16_kernel(cons
   const bool own_ctx = is_set && !is_pack;
   const int ctx_col[2] = {own_ctx ? rows[col_row[0]].pos + 1 : ctx, own_ctx ? rows[col_row[1]].pos + 1 : ctx};
   const int n_seg = attn_num_segments(ctx);
-  const bool in_lds = !is_set && skip == 0 && n_seg <= kLdsSegs;  // merged by this block
+  const bool in_lds = !is_set && skip == 0 && n_seg <= whole_segs;  // merged by this block
   // this block's segments [lo, hi)
   int lo, hi;
   if (is_pack) {
@@ -329,8 +329,8 @@ __global__ __launch_bounds__(256, KV8 ? 3 : 2) void attn_decode_bf16_kernel(cons
     lo = blockIdx.z * 4;
     hi = min(lo + 4, shared_segs);
   } else {
-    if ((int)blockIdx.z >= attn_num_splits(n_seg, spb)) return;  // block-uniform
-    const int per = n_seg <= kLdsSegs ? kLdsSegs : spb;
+    if ((int)blockIdx.z >= attn_num_splits(n_seg, whole_segs, spb)) return;  // block-uniform
+    const int per = n_seg <= whole_segs ? kLdsSegs : spb;
     lo = max((int)blockIdx.z * per, skip);
     hi = min((int)blockIdx.z * per + per, n_seg);
   }
@@ -897,15 +897,15 @@ __global__ __launch_bounds__(256, KV8 ? 3 : 2) void attn_decode_bf16_kernel(cons
 // short contexts were finished by the first kernel.
 __global__ __launch_bounds__(256) void attn_merge_bf16_kernel(const float* __restrict__ part, const RowMeta* __restrict__ rows,
                                                              int max_segs, uint16_t* __restrict__ o_out, int n_q,
-                                                             const int32_t* __restrict__ skip_segs) {
+                                                             const int32_t* __restrict__ skip_segs, int whole_segs) {
   const int head = blockIdx.x * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), r = blockIdx.y, lane = threadIdx.x & 63;
   if (head >= n_q) return;
   const int ctx = rows[r].pos + 1;
   const int n_seg = attn_num_segments(ctx);
   const float* p = part + ((size_t)r * n_q + head) * max_segs * kPartStride;
   if (n_seg <= kLdsSegs) {
-    if (!skip_segs || skip_segs[r] == 0) return;  // finished by its own block
-    if (n_seg <= 4 && skip_segs[r] == n_seg) return;  // ... or by that of a set that covers all its segments
+    if (n_seg <= whole_segs && (!skip_segs || skip_segs[r] == 0)) return;  // finished by its own block
+    if (n_seg <= 4 && skip_segs && skip_segs[r] == n_seg) return;  // ... or by that of a set that covers all its segments
     const uint32_t o2 = merge_short<kLdsSegs>([&](int c) { return p + part_o(max_segs, c); }, [&](int c) { return p + part_ml(max_segs, c); },
                                     n_seg, (ctx + 31) >> 5, lane);
     *(uint32_t*)(o_out + frag_offset(r, head * kD + 2 * lane, (n_q * kD) >> 6)) = o2;
@@ -959,6 +959,31 @@ __global__ __launch_bounds__(256) void attn_merge_bf16_kernel(const float* __res
 
 }  // namespace
 
+// Segments up to which a row is finished by one block, and the segments of a block beyond.
+// A compute unit draws 63 GB/s from memory whatever is in flight, so a step of four waves of a block takes 1.05 us, that of a
+// wave alone 0.7: rows that leave compute units idle take blocks of four, two or one segment, as few as still make no more
+// than a block per unit.  That costs the merge launch, 3 us, which from 1025 keys (eight segments: half the steps per wave)
+// always pays, and with four segments of bf16 pages from some 350 keys on.  One layer, us, before / with several blocks:
+//   1 row:  1000 keys 93.2 / 88.3, 1500 97.6 / 89.3, 3900 102.5 / 90.3, 7000 (blocks of four / of one) 96.8 / 92.5
+//   2 rows of 2000 104.1 / 92.0;  4 rows: 1000 98.1 / 93.3, 2000 106.7 / 95.1, fp8 pages 99.7 / 94.1
+//   8 rows: 1000 99.6 / 95.8, 1500 104.0 / 97.9, 3000 118.1 / 105.3
+// The line at 384: 1 row of 150 keys 85.9 / 86.6, 300 87.1 / 87.2, 450 88.3 / 87.9, 600 89.5 / 88.4; 8 rows of 150 91.4 / 92.0,
+// 450 94.4 / 93.6; four segments of fp8 pages, 4 rows of 500 keys, 91.3 / 92.6.
+// (Sets have blocks of their own beside the rows': there the rows' stay as they are.)
+struct AttnSplit {
+  int whole_segs, spb;
+};
+static AttnSplit attn_split(const Geometry& g, int M, int max_ctx, bool sets, int segs_per_block) {
+  AttnSplit r = {kLdsSegs, std::min(std::max(segs_per_block, 1), kLdsSegs)};
+  const int pairs = M * g.n_kv, n_seg = attn_num_segments(max_ctx);
+  if (sets || pairs * (n_seg / 4) > kComputeUnits) return r;
+  const bool ones = pairs * n_seg <= kComputeUnits;
+  r.whole_segs = ones && !g.kv_fp8 && max_ctx > 384 ? 0 : 4;
+  if (ones) r.spb = 1;
+  else if (pairs * (n_seg / 2) <= kComputeUnits) r.spb = std::min(r.spb, 2);
+  return r;
+}
+
 // Segment records to allocate per (row, head): a multiple of 16, which keeps every O row of the workspace on whole
 // cache lines.
 int attn_bf16_max_segments(int max_ctx) { return (attn_num_segments(max_ctx) + 15) & ~15; }
@@ -969,14 +994,15 @@ bool launch_attn_decode_bf16(hipStream_t s, const Geometry& g, const float* q, c
                              const AttnShared* shared, int n_shared, int max_shared_segs, const AttnAppend* append,
                              int segs_per_block, bool window_sets, bool packs, bool all_packed) {
   const int n_seg_max = attn_num_segments(max_ctx_in_batch);
-  const int spb = std::min(std::max(segs_per_block, 1), kLdsSegs);
   int page_ints = ((max_ctx_in_batch + 15) / 16 + 1 + 3) & ~3;  // keeps the partials 16-byte aligned
   if (packs) page_ints = std::max(page_ints, 4 * kPackPages);
   if (n_shared <= 0) { skip_segs = nullptr; n_shared = 0; max_shared_segs = 0; }
   // Window sets hold every row: no row blocks (at 1024 rows 8192 blocks that only find out that they have nothing to do,
   // 70 -> 52 us for up to 1024 keys, the longest contexts first).
   const int row_blocks = n_shared > 0 && (window_sets || all_packed) ? 0 : M;
-  const int z = std::max(row_blocks > 0 ? attn_num_splits(n_seg_max, spb) : 1, (max_shared_segs + 3) / 4);
+  const AttnSplit split = attn_split(g, M, max_ctx_in_batch, n_shared > 0, segs_per_block);
+  const int whole_segs = split.whole_segs, spb = split.spb;
+  const int z = std::max(row_blocks > 0 ? attn_num_splits(n_seg_max, whole_segs, spb) : 1, (max_shared_segs + 3) / 4);
   dim3 grid(g.n_kv, row_blocks + n_shared, z);
   const int segs = n_seg_max > kLdsSegs ? kLdsSegs : n_seg_max;
   int part_floats = (g.n_q / g.n_kv) * segs * kPartStride;  // a multiple of 4
@@ -998,7 +1024,7 @@ bool launch_attn_decode_bf16(hipStream_t s, const Geometry& g, const float* q, c
   attn_decode_bf16_kernel<APP, K8><<<grid, 256, lds, s>>>(q, rows, block_table, g.max_blocks, (const u32x4_t*)k_pool_layer, \
                                                           (const u32x4_t*)v_pool_layer, part, max_segs_alloc, g.n_q, g.n_kv, \
                                                           scale, (uint16_t*)o_out, page_ints, page_ints + part_floats, row_blocks, \
-                                                          skip_segs, shared, ap, spb)
+                                                          skip_segs, shared, ap, whole_segs, spb)
   if (append) {
     if (g.kv_fp8) RL_ATTN_LAUNCH(true, true); else RL_ATTN_LAUNCH(true, false);
   } else {
@@ -1007,13 +1033,14 @@ bool launch_attn_decode_bf16(hipStream_t s, const Geometry& g, const float* q, c
 #undef RL_ATTN_LAUNCH
   // every row of a set over at most four segments is merged by the set's block, every other short row by its own
   if (n_shared > 0 && window_sets && n_seg_max <= 4) return false;
-  return n_seg_max > kLdsSegs || n_shared > 0;
+  return n_seg_max > whole_segs || n_shared > 0;
 }
 
 void launch_attn_merge_bf16(hipStream_t s, const Geometry& g, const RowMeta* rows, float* part, int max_segs_alloc,
-                            void* o_out, int M, const int32_t* skip_segs, int n_shared) {
+                            int max_ctx_in_batch, void* o_out, int M, const int32_t* skip_segs, int n_shared) {
   if (n_shared <= 0) skip_segs = nullptr;
-  attn_merge_bf16_kernel<<<dim3((g.n_q + 3) / 4, M), 256, 0, s>>>(part, rows, max_segs_alloc, (uint16_t*)o_out, g.n_q, skip_segs);
+  attn_merge_bf16_kernel<<<dim3((g.n_q + 3) / 4, M), 256, 0, s>>>(part, rows, max_segs_alloc, (uint16_t*)o_out, g.n_q, skip_segs,
+                                                                  attn_split(g, M, max_ctx_in_batch, n_shared > 0, 1).whole_segs);
 }
 
 }  // namespace rl

@@ -289,7 +289,7 @@ Pending finish_layer(rl_model* m, hipStream_t st, int l, int M, const RowMeta* r
                                       o, M, sa.skip, sa.sets, sa.n_sets, sa.max_segs, ap, m->attn_segs_per_block, sa.window, sa.packs, sa.all_packed); }
     if (merge) {
       Timer t(m, st, K_ATTN_MERGE);
-      launch_attn_merge_bf16(st, g, rows, apart, m->lay.max_segs, o, M, sa.skip, sa.n_sets);
+      launch_attn_merge_bf16(st, g, rows, apart, m->lay.max_segs, max_ctx_in_batch, o, M, sa.skip, sa.n_sets);
     }
   } else {
     Timer t(m, st, K_ATTN);

@@ -1291,6 +1291,38 @@ def test_steps_on_both_sides_of_the_line_where_sharing_pays(amd, kv_fp8):
 
 
 @pytest.mark.parametrize("kv_fp8", [False, True])
+def test_few_rows_over_several_blocks_keep_a_rows_bits(amd, kv_fp8):
+    """Steps that leave compute units idle spread a row's segments over blocks of one, two or four: rows stepped alone, in twos and in
+    threes (contexts around 384, 1024 and 4096 keys, a segment without steps) have the bits of one step over all rows, and so do
+    prompts whose last chunk is one row."""
+    shape = dict(ri.SHAPES["layer8b"], n_layers=2, hidden=512, n_q=16, n_kv=8, ffn=768, vocab=4096)
+    w, _ = make_both(shape, 70, std=0.05)
+    wd = to_device(w)
+    V, seed = shape["vocab"], 14
+    lens = [7000, 2500, 1023, 383, 382, 4095, 385, 5, 1025, 600, 100, 4097, 33, 1022] + [20] * 22
+    prompts = [ri.tokens((n,), V, 70, 1000 + i).tolist() for i, n in enumerate(lens)]
+    fed = [ri.tokens((len(lens),), V, 70, 1100 + k).tolist() for k in range(4)]
+    kw = dict(max_seqs=len(lens), max_ctx=7040, kv_pages=1600, kv_fp8=kv_fp8)
+    few, many = amd.Rollout(shape, wd, max_rows=64, **kw), amd.Rollout(shape, wd, max_rows=1024, **kw)
+    ids = list(range(len(lens)))
+    first = [few.rl_prefill([i], [prompts[i]], 1.0, seed)[1].clone() for i in ids]
+    assert torch.equal(torch.cat(first), many.rl_prefill(ids, prompts, 1.0, seed)[1])
+    groups = [[[i] for i in range(14)], [[0, 1], [5, 2], [3, 4], [6, 7], [8, 9], [10, 11], [12, 13]],
+              [[0, 1, 2], [3, 4, 5], [6, 7, 8], [9, 10, 11], [12, 13]], [list(range(2, 5)), list(range(7, 11)), [0, 1, 5, 6, 11], [12, 13]]]
+    for tok, parts in zip(fed, groups):
+        parts = parts + [ids[14:]]
+        zm = torch.empty(len(ids), V, device=DEV)
+        tm, lm = many.rl_decode_step(ids, torch.tensor(tok, dtype=torch.int32, device=DEV), 1.0, seed, debug_logits=zm)
+        for part in parts:
+            z = torch.empty(len(part), V, device=DEV)
+            t_, l_ = few.rl_decode_step(part, torch.tensor([tok[i] for i in part], dtype=torch.int32, device=DEV), 1.0, seed, debug_logits=z)
+            torch.cuda.synchronize()
+            assert torch.equal(z, zm[part]) and torch.equal(t_, tm[part]) and torch.equal(l_, lm[part]), part
+    few.close()
+    many.close()
+
+
+@pytest.mark.parametrize("kv_fp8", [False, True])
 def test_packed_segments_behind_shared_prompts_keep_their_bits(amd, kv_fp8):
     """Three samples each of prompts of one to nine shared segments (odd numbers of left-over segments; one beyond 4096 keys,
     one with rows of their own beside the packs) and one sequence alone, over a change of the segments left and of the page:
