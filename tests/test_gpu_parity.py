@@ -1265,15 +1265,15 @@ def test_shared_attention_set_widths_agree_for_other_head_groupings(amd, n_q, n_
 
 @pytest.mark.parametrize("kv_fp8", [False, True])
 def test_steps_on_both_sides_of_the_line_where_sharing_pays(amd, kv_fp8):
-    """Small decode steps leave every row to itself up to 1024 keys and share beyond: over the line, the steps have the bits of
+    """Small decode steps leave every row to itself up to a line (10 rows of 8 kv heads: 1792 keys) and share beyond: over it, the steps have the bits of
     an instance that never shares and of one that always does, in the narrow sets."""
-    shape = dict(ri.SHAPES["layer8b"], n_layers=2, hidden=512, n_q=8, n_kv=2, ffn=768, vocab=8192)
+    shape = dict(ri.SHAPES["layer8b"], n_layers=2, hidden=512, n_q=16, n_kv=8, ffn=768, vocab=8192)
     w, _ = make_both(shape, 68, std=0.05)
     wd = to_device(w)
     seed, G = 12, 5
-    prompts = [ri.tokens((n,), shape["vocab"], 68, 975 + n).tolist() for n in (1017, 40)]
+    prompts = [ri.tokens((n,), shape["vocab"], 68, 975 + n).tolist() for n in (1785, 40)]
     ids = list(range(2 * G))
-    every = [amd.Rollout(shape, wd, max_seqs=16, max_ctx=1088, max_rows=64, kv_pages=160, kv_fp8=kv_fp8) for _ in range(3)]
+    every = [amd.Rollout(shape, wd, max_seqs=16, max_ctx=1856, max_rows=64, kv_pages=208, kv_fp8=kv_fp8) for _ in range(3)]
     for r, mode in zip(every, (1, 0, 3)):
         r.rl_debug_share_attention(mode)
         r.rl_prefill_groups(ids, G, prompts, 1.0, seed)
