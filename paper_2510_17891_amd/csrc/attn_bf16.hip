@@ -24,7 +24,7 @@
 //
 // Shared prompt pages (the samples of one prompt, Section 2.3): rows of equal context length whose first pages are
 // the same physical pages form sets of up to 16 / group rows, or 32 / group when the launch is large enough to be
-// bound by memory traffic.  The same launch holds one more kind of block: a "set" block computes up to four of
+// bound by memory traffic.  The same launch holds one more kind of block: a "set" block computes two or up to four of
 // the segments that lie inside the shared pages once for the whole set, the set's (row, head) pairs side by side
 // in the columns of the matrix operand (two operands of 16 columns, fed from the same key and value registers,
 // for the larger sets).  The rows of a set start after those
@@ -270,7 +270,7 @@ __global__ __launch_bounds__(256, KV8 ? 3 : 2) void attn_decode_bf16_kernel(cons
                                                                int max_segs, int n_q, int n_kv, float scale,
                                                                uint16_t* __restrict__ o_out, int lds_part_offset,
                                                                int lds_q_offset, int n_rows, const int32_t* __restrict__ skip_segs,
-                                                               const AttnShared* __restrict__ shared, AppendArgs ap, int whole_segs, int spb) {
+                                                               const AttnShared* __restrict__ shared, AppendArgs ap, int whole_segs, int spb, int set_segs) {
   extern __shared__ int32_t pages[];  // block-table slice of this row: ceil(ctx/16) entries (+1 pad), then partials
   const int hk = blockIdx.x;
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
@@ -326,8 +326,8 @@ __global__ __launch_bounds__(256, KV8 ? 3 : 2) void attn_decode_bf16_kernel(cons
     lo = pack_seg;
     hi = pack_seg + (uw < n_members ? 1 : 0);
   } else if (is_set) {
-    lo = blockIdx.z * 4;
-    hi = min(lo + 4, shared_segs);
+    lo = blockIdx.z * set_segs;
+    hi = min(lo + set_segs, shared_segs);
   } else {
     if ((int)blockIdx.z >= attn_num_splits(n_seg, whole_segs, spb)) return;  // block-uniform
     const int per = n_seg <= whole_segs ? kLdsSegs : spb;
@@ -1002,7 +1002,13 @@ bool launch_attn_decode_bf16(hipStream_t s, const Geometry& g, const float* q, c
   const int row_blocks = n_shared > 0 && (window_sets || all_packed) ? 0 : M;
   const AttnSplit split = attn_split(g, M, max_ctx_in_batch, n_shared > 0, segs_per_block);
   const int whole_segs = split.whole_segs, spb = split.spb;
-  const int z = std::max(row_blocks > 0 ? attn_num_splits(n_seg_max, whole_segs, spb) : 1, (max_shared_segs + 3) / 4);
+  // Set blocks take four segments, or two where those make no more than a block per compute unit (few samples, long prompts):
+  // one layer, us, four / two: 8 rows of 5000 shared keys 106.0 / 103.6, 16 of 2500 103.2 / 101.8, 24 of 1700 107.5 / 102.9,
+  // 32 of 1700 107.0 / 106.6, 32 with 1024 of 1924 shared 124.2 / 122.4.  Four / one: 16 rows with 1500 of 2500 shared 111.9 / 113.0;
+  // fp8 pages, 16 rows of 3000, four / two and less 99.6 / 102.6.
+  const bool pairs_of_segs = n_shared > 0 && !window_sets && !packs && !g.kv_fp8 && n_shared * g.n_kv * ((max_shared_segs + 1) / 2) <= kComputeUnits;
+  const int set_segs = pairs_of_segs ? 2 : 4;
+  const int z = std::max(row_blocks > 0 ? attn_num_splits(n_seg_max, whole_segs, spb) : 1, (max_shared_segs + set_segs - 1) / set_segs);
   dim3 grid(g.n_kv, row_blocks + n_shared, z);
   const int segs = n_seg_max > kLdsSegs ? kLdsSegs : n_seg_max;
   int part_floats = (g.n_q / g.n_kv) * segs * kPartStride;  // a multiple of 4
@@ -1024,7 +1030,7 @@ bool launch_attn_decode_bf16(hipStream_t s, const Geometry& g, const float* q, c
   attn_decode_bf16_kernel<APP, K8><<<grid, 256, lds, s>>>(q, rows, block_table, g.max_blocks, (const u32x4_t*)k_pool_layer, \
                                                           (const u32x4_t*)v_pool_layer, part, max_segs_alloc, g.n_q, g.n_kv, \
                                                           scale, (uint16_t*)o_out, page_ints, page_ints + part_floats, row_blocks, \
-                                                          skip_segs, shared, ap, whole_segs, spb)
+                                                          skip_segs, shared, ap, whole_segs, spb, set_segs)
   if (append) {
     if (g.kv_fp8) RL_ATTN_LAUNCH(true, true); else RL_ATTN_LAUNCH(true, false);
   } else {

@@ -1322,6 +1322,30 @@ def test_few_rows_over_several_blocks_keep_a_rows_bits(amd, kv_fp8):
     many.close()
 
 
+@pytest.mark.parametrize("prompts", [8, 9])
+def test_set_blocks_of_two_and_of_four_segments_keep_a_rows_bits(amd, prompts):
+    """Seven shared segments: the sets of eight prompts make 256 blocks of two segments, those of nine take blocks of four; both
+    give the bits of an instance that never shares."""
+    shape = dict(ri.SHAPES["layer8b"], n_layers=2, hidden=512, n_q=16, n_kv=8, ffn=768, vocab=4096)
+    w, _ = make_both(shape, 71, std=0.05)
+    wd = to_device(w)
+    V, seed, G = shape["vocab"], 15, 4
+    toks = [ri.tokens((1590 + i % 2,), V, 71, 1200 + i).tolist() for i in range(prompts)]
+    ids = list(range(prompts * G))
+    every = [amd.Rollout(shape, wd, max_seqs=len(ids), max_ctx=1632, max_rows=256, kv_pages=1200) for _ in range(2)]
+    every[1].rl_debug_share_attention(0)
+    for r in every:
+        r.rl_prefill_groups(ids, G, toks, 1.0, seed)
+    for step in range(3):
+        fed = torch.tensor(ri.tokens((len(ids),), V, 71, 1300 + step).tolist(), dtype=torch.int32, device=DEV)
+        zs = [torch.empty(len(ids), V, device=DEV) for _ in every]
+        outs = [r.rl_decode_step(ids, fed, 1.0, seed, debug_logits=z) for r, z in zip(every, zs)]
+        torch.cuda.synchronize()
+        assert torch.equal(*zs) and torch.equal(outs[0][0], outs[1][0]) and torch.equal(outs[0][1], outs[1][1]), step
+    for r in every:
+        r.close()
+
+
 @pytest.mark.parametrize("kv_fp8", [False, True])
 def test_packed_segments_behind_shared_prompts_keep_their_bits(amd, kv_fp8):
     """Three samples each of prompts of one to nine shared segments (odd numbers of left-over segments; one beyond 4096 keys,
