@@ -48,20 +48,20 @@ inline int attn_rows_per_set(int group, bool kv_fp8, int n_rows, int n_kv) {
 }
 
 // The longest context up to which the rows of a decode step do better each on its own (0: sharing always pays).  Sets make a merge launch
-// necessary (4.8 us) that rows of at most 4096 keys can do without, and set blocks take four segments, where the blocks of few rows alone
-// take as few as fill the compute units.  What sets save: bytes, as soon as the blocks of a compute unit share what it draws from memory,
+// necessary (4.8 us) that rows of at most 4096 keys can do without, and set blocks take two segments or more, where the blocks of few rows
+// alone take as few as fill the compute units.  What sets save: bytes, as soon as the blocks of a compute unit share what it draws from memory,
 // and blocks, which few rows alone have to share a unit with beyond.  One layer, us, shared / each on its own (8 kv heads, groups of 8):
-//   2 rows: 1500 keys 95.3 / 91.8, 3900 97.4 / 93.6, 7000 99.4 / 95.8;  4 rows: 1500 98.3 / 94.0, 5000 100.9 / 99.7, 7900 108.5 / 106.9
-//   8 rows: 1500 98.4 / 95.1, 3000 99.8 / 98.4, 3900 103.5 / 102.8, 5000 106.1 / 106.3, 7900 112.2 / 115.9, fp8 pages 3900 99.5 / 98.3
-//   16 rows: 1300 99.4 / 97.9, 1750 101.3 / 100.0, 2040 101.8 / 105.3, fp8 pages 1900 99.5 / 99.0
-//   32 rows: 1200 104.0 / 102.1, 1400 105.2 / 103.8, 1600 106.3 / 105.4, 36 layers of 1025 3891 / 3797
+//   2 rows: 3900 keys 94.1 / 93.3, 7000 96.9 / 95.6;  4 rows: 2000 95.2 / 94.0, 3900 97.3 / 97.4, 5000 97.7 / 99.6, 7900 105.4 / 105.0
+//   8 rows: 1500 95.9 / 94.9, 3000 99.1 / 98.3, 3900 101.7 / 101.1, 5000 103.6 / 106.3, fp8 pages 3900 99.5 / 98.3
+//   16 rows: 1300 98.6 / 97.9, 1750 100.1 / 99.9, 2040 101.1 / 105.3, fp8 pages 1900 99.5 / 99.0
+//   32 rows: 1200 104.5 / 102.5, 1450 105.3 / 105.0, 36 layers of 1025 3891 / 3797
 //   48 rows: 600 120.0 / 119.5, 1000 124.6 / 125.3;  64 rows: 600 127.9 / 122.9, 800 129.5 / 125.9, 1000 130.2 / 129.4
 //   80 rows: 300 135.0 / 130.5, 700 142.6 / 138.3, 900 142.2 / 142.8;  104 rows: 500 152.5 / 151.9, 700 154.6 / 158.3
 //   120 rows: 300 153.9 / 151.1, 500 157.8 / 156.8, 700 159.7 / 162.0
 // From 1024 pairs on (wide sets, packs), attention and merge: 128 rows of 300 keys 25.7 / 26.1, 600 30.9 / 35.1.
 inline int attn_alone_up_to(int n_rows, int n_kv) {
   const int pairs = n_rows * n_kv;
-  if (pairs <= 128) return pairs <= 32 ? 8192 : pairs <= 64 ? 4096 : 1792;
+  if (pairs <= 128) return pairs <= 16 ? 8192 : pairs <= 64 ? 4096 : 1792;
   if (pairs <= 256) return 1500;
   if (pairs <= 512) return 900;
   return pairs <= 704 ? 768 : pairs < 1024 ? 512 : 0;
