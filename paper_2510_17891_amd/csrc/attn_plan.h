@@ -29,6 +29,7 @@ RL_HOST_DEVICE inline int attn_seg_begin(int sgm, int n_it, int n_seg) {
 // computed once for the set.  n_segs == 0: a pack of up to four (row, segment) pairs, pair w being rows[w] and
 // rows[kAttnPackSegs + w] (unused pairs repeat the first).
 constexpr int kAttnSetRows = 8, kAttnPackSegs = 4;
+constexpr int kDies = 8;  // blocks go to them in turn, each has an L2 of its own
 struct AttnShared {
   int32_t rows[kAttnSetRows];  // entries beyond n_rows repeat rows[0]
   int32_t n_rows;
@@ -59,7 +60,13 @@ inline int attn_rows_per_set(int group, bool kv_fp8, int n_rows, int n_kv) {
 //   80 rows: 300 135.0 / 130.5, 700 142.6 / 138.3, 900 142.2 / 142.8;  104 rows: 500 152.5 / 151.9, 700 154.6 / 158.3
 //   120 rows: 300 153.9 / 151.1, 500 157.8 / 156.8, 700 159.7 / 162.0
 // From 1024 pairs on (wide sets, packs), attention and merge: 128 rows of 300 keys 25.7 / 26.1, 600 30.9 / 35.1.
-inline int attn_alone_up_to(int n_rows, int n_kv) {
+// Rows alone read a prompt's pages once each, and only the L2 of a die makes that bearable: the kv head is the fastest grid index, so its rows
+// meet on one die where the kv heads are a multiple of the eight dies.  Otherwise every die reads the pages (one layer, us, sets of four samples /
+// alone: 2 kv heads, 128 rows of 1456 keys 127.5 / 135.4, 64 of 896 97.5 / 99.9; 1 kv head, 256 of 1456 152.6 / 158.4).  With 16 kv heads as with
+// 8 (4 rows of 2000 keys 93.1 / 91.0).  One query head per kv head: the larger steps lose (88 rows of 720 keys 112.2 / 117.2, 120 of 464
+// 120.5 / 124.1) and the smaller ones gain nothing (all of them together 1.001).
+inline int attn_alone_up_to(int n_rows, int n_kv, int group) {
+  if (n_kv % kDies != 0 || group == 1) return 0;
   const int pairs = n_rows * n_kv;
   if (pairs <= 128) return pairs <= 16 ? 8192 : pairs <= 64 ? 4096 : 1792;
   if (pairs <= 256) return 1500;

@@ -556,7 +556,7 @@ SlotUpload build_decode_meta(rl_model* m, int32_t n, const int32_t* seq_ids, cha
   // rows of sequences that hold prompt pages in common and stand at the same position share those segments
   AttnPlan plan;
   // (the test switch's wide and narrow sets: in every call)
-  if (m->geo.dtype == kBF16 && m->share_attention && (m->share_attention > 1 || max_ctx > attn_alone_up_to(n, m->geo.n_kv))) {
+  if (m->geo.dtype == kBF16 && m->share_attention && (m->share_attention > 1 || max_ctx > attn_alone_up_to(n, m->geo.n_kv, m->geo.n_q / m->geo.n_kv))) {
     std::vector<int64_t> fam(n);
     std::vector<int32_t> fam_blocks(n), pos(n);
     bool any = false;

@@ -36,8 +36,7 @@ int st_reserve(void* t, int s, int tokens, int* added_out, int max_added) {
 long long st_prefix_id(void* t, int s) { return ((rl::SeqTable*)t)->prefix_id(s); }
 int st_prefix_blocks(void* t, int s) { return ((rl::SeqTable*)t)->prefix_blocks(s); }
 int st_weight_kb_slot(int kb, int seg) { return rl::weight_kb_slot(kb, seg); }
-int st_attn_alone_up_to(int n_rows, int n_kv) { return rl::attn_alone_up_to(n_rows, n_kv); }
-
+int st_attn_alone_up_to(int n_rows, int n_kv, int group) { return rl::attn_alone_up_to(n_rows, n_kv, group); }
 int st_attn_rows_per_set(int group, int kv_fp8, int n_rows, int n_kv) {
   return rl::attn_rows_per_set(group, kv_fp8 != 0, n_rows, n_kv);
 }

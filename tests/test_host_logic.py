@@ -234,8 +234,11 @@ def test_shared_attention_plan(st):
     assert [st.st_attn_rows_per_set(g, 0, 128, 8) for g in (1, 2, 4, 8)] == [8, 8, 8, 4]
     assert [st.st_attn_rows_per_set(g, 1, 128, 8) for g in (1, 2, 4, 8)] == [4, 4, 4, 2]
     assert [st.st_attn_rows_per_set(4, 0, n, 8) for n in (1, 32, 64, 127, 128, 256)] == [4, 4, 4, 4, 8, 8]
-    # rows of small steps and short contexts are better off alone
-    assert [st.st_attn_alone_up_to(n, 8) for n in (1, 2, 3, 8, 9, 16, 17, 32, 33, 64, 65, 88, 89, 127, 128, 512)] == [8192] * 2 + [4096] * 2 + [1792] * 2 + [1500] * 2 + [900] * 2 + [768] * 2 + [512] * 2 + [0] * 2
+    # rows of small steps and short contexts are better off alone, where the rows of a kv head meet on one die
+    assert [st.st_attn_alone_up_to(n, 8, 4) for n in (1, 2, 3, 8, 9, 16, 17, 32, 33, 64, 65, 88, 89, 127, 128, 512)] == [8192] * 2 + [4096] * 2 + [1792] * 2 + [1500] * 2 + [900] * 2 + [768] * 2 + [512] * 2 + [0] * 2
+    for n_kv, group in [(1, 8), (2, 4), (4, 4), (12, 4), (8, 1), (32, 1)]:
+        assert all(st.st_attn_alone_up_to(n, n_kv, group) == 0 for n in (1, 2, 4, 8, 16, 64, 128, 512)), (n_kv, group)
+    assert [st.st_attn_alone_up_to(n, 16, 2) for n in (1, 4, 8, 16)] == [8192, 4096, 1792, 1500]
     # right after the prompt the last shared page may hold the row's own position: never shared
     skip, sets = _plan(st, t, [0, 1], [1088, 1088], 2)
     assert sets and sets[0][1] == covered(1089, 1088) and st.st_attn_seg_begin(sets[0][1], 1089) * 32 <= 1088
