@@ -34,10 +34,10 @@ HBM_PEAK_GBS = 8000.0
 # source file (comments aside) still has the hash it had when the counters were taken; otherwise "traffic" is null.
 TRAFFIC_RATIO = {
     # one layer at the launch shape of the 128-sequence wave (16 groups x 8 samples, 2048 shared + 7168 private tokens)
-    ("wave", "attn_decode"): (1.045, "attn_bf16.hip", "2d1b0dfb9b18c518"),
-    ("layer", "attn_decode"): (1.045, "attn_bf16.hip", "2d1b0dfb9b18c518"),
-    ("full", "attn_decode"): (1.040, "attn_bf16.hip", "2d1b0dfb9b18c518"),
-    ("full", "gemm_gate_up_swiglu"): (1.010, "gemm_bf16.hip", "7c0f19125f9ae035"),
+    ("wave", "attn_decode"): (1.045, "attn_bf16.hip", "d5e6594d27d24d23"),
+    ("layer", "attn_decode"): (1.045, "attn_bf16.hip", "d5e6594d27d24d23"),
+    ("full", "attn_decode"): (1.040, "attn_bf16.hip", "d5e6594d27d24d23"),
+    ("full", "gemm_gate_up_swiglu"): (1.010, "gemm_bf16.hip", "71485521c5ddc7a7"),
 }
 
 

@@ -77,8 +77,6 @@ __device__ __forceinline__ size_t part_o(int max_segs, int seg) { return (size_t
 __device__ __forceinline__ size_t part_ml(int max_segs, int seg) { return (size_t)max_segs * kD + 2 * (size_t)seg; }
 constexpr int kQStride = kD + 4;              // floats per column of the queries in LDS: 16 columns read at once hit different banks
 constexpr int kPackPages = 32;                // room for the page list of a wave of a pack
-constexpr int kComputeUnits = 256;
-constexpr int kLdsSegs = 16;                  // contexts up to 4096 keep their segment partials in LDS
 
 constexpr int kPairU4(bool kv8) { return kv8 ? 2 * kPageElems / 16 : 2 * kPageElems / 8; }  // 16-byte units of one (page, kv head): K and V
 
@@ -959,31 +957,6 @@ __global__ __launch_bounds__(256) void attn_merge_bf16_kernel(const float* __res
 
 }  // namespace
 
-// Segments up to which a row is finished by one block, and the segments of a block beyond.
-// A compute unit draws 63 GB/s from memory whatever is in flight, so a step of four waves of a block takes 1.05 us, that of a
-// wave alone 0.7: rows that leave compute units idle take blocks of four, two or one segment, as few as still make no more
-// than a block per unit.  That costs the merge launch, 3 us, which from 1025 keys (eight segments: half the steps per wave)
-// always pays, and with four segments of bf16 pages from some 350 keys on.  One layer, us, before / with several blocks:
-//   1 row:  1000 keys 93.2 / 88.3, 1500 97.6 / 89.3, 3900 102.5 / 90.3, 7000 (blocks of four / of one) 96.8 / 92.5
-//   2 rows of 2000 104.1 / 92.0;  4 rows: 1000 98.1 / 93.3, 2000 106.7 / 95.1, fp8 pages 99.7 / 94.1
-//   8 rows: 1000 99.6 / 95.8, 1500 104.0 / 97.9, 3000 118.1 / 105.3
-// The line at 384: 1 row of 150 keys 85.9 / 86.6, 300 87.1 / 87.2, 450 88.3 / 87.9, 600 89.5 / 88.4; 8 rows of 150 91.4 / 92.0,
-// 450 94.4 / 93.6; four segments of fp8 pages, 4 rows of 500 keys, 91.3 / 92.6.
-// (Sets have blocks of their own beside the rows': there the rows' stay as they are.)
-struct AttnSplit {
-  int whole_segs, spb;
-};
-static AttnSplit attn_split(const Geometry& g, int M, int max_ctx, bool sets, int segs_per_block) {
-  AttnSplit r = {kLdsSegs, std::min(std::max(segs_per_block, 1), kLdsSegs)};
-  const int pairs = M * g.n_kv, n_seg = attn_num_segments(max_ctx);
-  if (sets || pairs * (n_seg / 4) > kComputeUnits) return r;
-  const bool ones = pairs * n_seg <= kComputeUnits;
-  r.whole_segs = ones && !g.kv_fp8 && max_ctx > 384 ? 0 : 4;
-  if (ones) r.spb = 1;
-  else if (pairs * (n_seg / 2) <= kComputeUnits) r.spb = std::min(r.spb, 2);
-  return r;
-}
-
 // Segment records to allocate per (row, head): a multiple of 16, which keeps every O row of the workspace on whole
 // cache lines.
 int attn_bf16_max_segments(int max_ctx) { return (attn_num_segments(max_ctx) + 15) & ~15; }
@@ -1000,7 +973,7 @@ bool launch_attn_decode_bf16(hipStream_t s, const Geometry& g, const float* q, c
   // Window sets hold every row: no row blocks (at 1024 rows 8192 blocks that only find out that they have nothing to do,
   // 70 -> 52 us for up to 1024 keys, the longest contexts first).
   const int row_blocks = n_shared > 0 && (window_sets || all_packed) ? 0 : M;
-  const AttnSplit split = attn_split(g, M, max_ctx_in_batch, n_shared > 0, segs_per_block);
+  const AttnSplit split = attn_split(M, g.n_kv, g.kv_fp8, max_ctx_in_batch, n_shared > 0, segs_per_block);
   const int whole_segs = split.whole_segs, spb = split.spb;
   // Set blocks take four segments, or two where those make no more than a block per compute unit (few samples, long prompts):
   // one layer, us, four / two: 8 rows of 5000 shared keys 106.0 / 103.6, 16 of 2500 103.2 / 101.8, 24 of 1700 107.5 / 102.9,
@@ -1046,7 +1019,7 @@ void launch_attn_merge_bf16(hipStream_t s, const Geometry& g, const RowMeta* row
                             int max_ctx_in_batch, void* o_out, int M, const int32_t* skip_segs, int n_shared) {
   if (n_shared <= 0) skip_segs = nullptr;
   attn_merge_bf16_kernel<<<dim3((g.n_q + 3) / 4, M), 256, 0, s>>>(part, rows, max_segs_alloc, (uint16_t*)o_out, g.n_q, skip_segs,
-                                                                  attn_split(g, M, max_ctx_in_batch, n_shared > 0, 1).whole_segs);
+                                                                  attn_split(M, g.n_kv, g.kv_fp8, max_ctx_in_batch, n_shared > 0, 1).whole_segs);
 }
 
 }  // namespace rl

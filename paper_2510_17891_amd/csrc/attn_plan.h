@@ -10,6 +10,8 @@
 #include <algorithm>
 #include <vector>
 
+#include "chip.h"
+
 #if defined(__HIPCC__)
 #define RL_HOST_DEVICE __host__ __device__
 #else
@@ -25,11 +27,45 @@ RL_HOST_DEVICE inline int attn_seg_begin(int sgm, int n_it, int n_seg) {
   return (int)(((unsigned)sgm * (unsigned)n_it) / (unsigned)n_seg);
 }
 
+// Segments up to which a row is finished by one block, and the segments of a block beyond.
+// A compute unit draws 63 GB/s from memory whatever is in flight, so a step of four waves of a block takes 1.05 us, that of a
+// wave alone 0.7: rows that leave compute units idle take blocks of four, two or one segment, as few as still make no more
+// than a block per unit.  That costs the merge launch, 3 us, which from 1025 keys (eight segments: half the steps per wave)
+// always pays, and with four segments of bf16 pages from some 350 keys on.  One layer, us, before / with several blocks:
+//   1 row:  1000 keys 93.2 / 88.3, 1500 97.6 / 89.3, 3900 102.5 / 90.3, 7000 (blocks of four / of one) 96.8 / 92.5
+//   2 rows of 2000 104.1 / 92.0;  4 rows: 1000 98.1 / 93.3, 2000 106.7 / 95.1, fp8 pages 99.7 / 94.1
+//   8 rows: 1000 99.6 / 95.8, 1500 104.0 / 97.9, 3000 118.1 / 105.3
+// The line at 384: 1 row of 150 keys 85.9 / 86.6, 300 87.1 / 87.2, 450 88.3 / 87.9, 600 89.5 / 88.4; 8 rows of 150 91.4 / 92.0,
+// 450 94.4 / 93.6; four segments of fp8 pages, 4 rows of 500 keys, 91.3 / 92.6.
+// (Sets have blocks of their own beside the rows': there the rows' stay as they are.)
+constexpr int kLdsSegs = 16;         // contexts up to 4096 can keep their segment partials in LDS
+constexpr int kAttnWholeKeys = 384;  // contexts that one block finishes at least as fast as several
+struct AttnSplit {
+  int whole_segs, spb;
+};
+inline AttnSplit attn_split(int n_rows, int n_kv, bool kv_fp8, int max_ctx, bool sets, int segs_per_block) {
+  AttnSplit r = {kLdsSegs, std::min(std::max(segs_per_block, 1), kLdsSegs)};
+  const int pairs = n_rows * n_kv, n_seg = attn_num_segments(max_ctx);
+  if (sets || pairs * (n_seg / 4) > kComputeUnits) return r;
+  const bool ones = pairs * n_seg <= kComputeUnits;
+  r.whole_segs = ones && !kv_fp8 && max_ctx > kAttnWholeKeys ? 0 : 4;
+  if (ones) r.spb = 1;
+  else if (pairs * (n_seg / 2) <= kComputeUnits) r.spb = std::min(r.spb, 2);
+  return r;
+}
+
+// The context that stands for contexts of max_ctx keys in a captured launch: the end of its 1024 keys, which have the segments of every
+// context in them, or the line between one block and several where that lies between (a batch in lock step meets it once).
+inline int attn_capture_ctx(int n_rows, int n_kv, bool kv_fp8, int max_ctx, bool sets) {
+  const int end = (max_ctx + 1023) / 1024 * 1024;
+  const auto whole = [&](int ctx) { return attn_split(n_rows, n_kv, kv_fp8, ctx, sets, 1).whole_segs; };
+  return whole(max_ctx) == whole(end) ? end : kAttnWholeKeys;
+}
+
 // Rows of equal context length whose leading pages are the same physical pages: their first n_segs segments are
 // computed once for the set.  n_segs == 0: a pack of up to four (row, segment) pairs, pair w being rows[w] and
 // rows[kAttnPackSegs + w] (unused pairs repeat the first).
 constexpr int kAttnSetRows = 8, kAttnPackSegs = 4;
-constexpr int kDies = 8;  // blocks go to them in turn, each has an L2 of its own
 struct AttnShared {
   int32_t rows[kAttnSetRows];  // entries beyond n_rows repeat rows[0]
   int32_t n_rows;

@@ -1109,7 +1109,6 @@ void launch_wide(hipStream_t s, const void* X, const void* W, void* out, int M, 
 
 // Tiles of two sizes (see gemm_bf16_mixed_kernel): used when the matrix has exactly three (row block, K split) units
 // per compute unit.
-constexpr int kComputeUnits = 256;
 bool mixed_fits(int N, int K, int epi, bool allow_split) {
   if (epi == kEpiSample) return false;
   const Plan p = make_plan(N, K, epi, allow_split);

@@ -608,11 +608,12 @@ void decode_enqueue(rl_model* m, hipStream_t st, int n, const RowMeta* rows, int
 
 // A decode step of a fixed batch as a HIP graph.  What changes from step to step is data (rows and the
 // shared-attention plan: one upload from a pinned buffer that the graph's first kernel reads at every launch) except for
-// four launch shapes, which form the key of the captured graph: the 1024-key bracket of the longest context (block
-// count and shared-memory size of the attention launch), the number of row sets, the blocks the sets need, and whether
-// some or all of what the sets leave of their rows is packed.  When
-// the key changes -- once per 1024 steps for a batch in lock step -- the step is captured again.  Two buffers and two
-// graphs alternate, so the host may prepare step k + 1 while step k runs.
+// four launch shapes, which form the key of the captured graph: the context that stands for the longest one (block
+// counts and shared-memory size of the attention launch; attn_capture_ctx), the number of row sets, the blocks the sets need, and
+// whether some or all of what the sets leave of their rows is packed.  When the key changes, the step is captured again.  A batch in
+// lock step does so every 1024 steps, once more at 384 keys if its rows leave compute units idle (attn_split), and, where it
+// holds samples of one prompt, where they begin to share (attn_alone_up_to) and with each four segments more in the
+// prompt's pages.  Two buffers and two graphs alternate, so the host may prepare step k + 1 while step k runs.
 struct rl_decode_graph {
   rl_model* m = nullptr;
   std::vector<int32_t> ids;
@@ -623,7 +624,7 @@ struct rl_decode_graph {
   hipEvent_t ev[2] = {nullptr, nullptr};
   bool ev_used[2] = {false, false};
   hipGraphExec_t exec[2] = {nullptr, nullptr};
-  struct Key { int ctx_bracket, n_sets, set_blocks, packs; } key[2] = {{-1, -1, -1, -1}, {-1, -1, -1, -1}};
+  struct Key { int ctx, n_sets, set_blocks, packs; } key[2] = {{-1, -1, -1, -1}, {-1, -1, -1, -1}};
   int next = 0;
   int64_t captures = 0;
 };
@@ -877,8 +878,8 @@ rl_status rl_decode_graph_step(rl_decode_graph* g, void* stream, int64_t* captur
   int max_ctx = 0;
   SharedAttn sa;
   const SlotUpload up = build_decode_meta(m, n, g->ids.data(), hs, ds, &max_ctx, &sa, true);
-  const rl_decode_graph::Key key = {(max_ctx + 1023) / 1024, sa.n_sets, (sa.max_segs + 3) / 4, sa.packs + sa.all_packed};
-  if (!g->exec[b] || key.ctx_bracket != g->key[b].ctx_bracket || key.n_sets != g->key[b].n_sets ||
+  const rl_decode_graph::Key key = {attn_capture_ctx(n, m->geo.n_kv, m->geo.kv_fp8, max_ctx, sa.n_sets > 0), sa.n_sets, (sa.max_segs + 3) / 4, sa.packs + sa.all_packed};
+  if (!g->exec[b] || key.ctx != g->key[b].ctx || key.n_sets != g->key[b].n_sets ||
       key.set_blocks != g->key[b].set_blocks || key.packs != g->key[b].packs) {
     if (g->exec[b]) { (void)hipGraphExecDestroy(g->exec[b]); g->exec[b] = nullptr; }
     const bool prof = m->prof_on;
@@ -891,7 +892,7 @@ rl_status rl_decode_graph_step(rl_decode_graph* g, void* stream, int64_t* captur
       float* cap = m->geo.dtype == kBF16 ? m->capture : nullptr;
       launch_entry(st, m->geo.dtype, table_rows(m, hs, nullptr), up, m->wsp<float>(m->lay.x), m->attn_norm[0], m->wsp<void>(m->lay.h), cap,
                    n, m->geo.hidden, m->geo.rms_eps);
-      decode_enqueue(m, st, n, (const RowMeta*)ds, key.ctx_bracket * 1024, sa_cap, nullptr, &g->sp, g->out_tokens, g->out_logprobs, nullptr);
+      decode_enqueue(m, st, n, (const RowMeta*)ds, key.ctx, sa_cap, nullptr, &g->sp, g->out_tokens, g->out_logprobs, nullptr);
       const hipError_t e_end = hipStreamEndCapture(st, &graph);  // always ends the capture
       if (e == hipSuccess) e = e_end;
     }

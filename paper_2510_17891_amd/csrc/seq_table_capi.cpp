@@ -40,6 +40,15 @@ int st_attn_alone_up_to(int n_rows, int n_kv, int group) { return rl::attn_alone
 int st_attn_rows_per_set(int group, int kv_fp8, int n_rows, int n_kv) {
   return rl::attn_rows_per_set(group, kv_fp8 != 0, n_rows, n_kv);
 }
+// segments up to which one block takes a row, segments of a block beyond
+void st_attn_split(int n_rows, int n_kv, int kv_fp8, int max_ctx, int sets, int segs_per_block, int* out) {
+  const rl::AttnSplit r = rl::attn_split(n_rows, n_kv, kv_fp8 != 0, max_ctx, sets != 0, segs_per_block);
+  out[0] = r.whole_segs;
+  out[1] = r.spb;
+}
+int st_attn_capture_ctx(int n_rows, int n_kv, int kv_fp8, int max_ctx, int sets) {
+  return rl::attn_capture_ctx(n_rows, n_kv, kv_fp8 != 0, max_ctx, sets != 0);
+}
 int st_attn_num_segments(int ctx) { return rl::attn_num_segments(ctx); }
 int st_attn_seg_begin(int sgm, int ctx) { return rl::attn_seg_begin(sgm, (ctx + 31) >> 5, rl::attn_num_segments(ctx)); }
 // plan of one decode batch: skip_out[n]; sets_out gets (rows[8], n_rows, n_segs) per set; returns the number of sets

@@ -1556,6 +1556,34 @@ def test_decode_graph_steps_equal_eager_steps(amd, kv_fp8, G, wide):
     rb.close()
 
 
+@pytest.mark.parametrize("rows,captures", [(1, 4), (2, 4), (8, 4), (9, 2)])
+def test_decode_graph_of_few_rows_keeps_one_block_up_to_the_line_of_several(amd, rows, captures):
+    """Few rows take several attention blocks and a merge beyond 384 keys (up to eight rows of eight kv heads), one block up to there: a graph
+    that crosses the line is captured again (two buffers), one of nine rows is not.  One and two rows have the norm inside gate/up as well.
+    Every step's tokens and log-probabilities are the eager ones of a second instance, bit for bit."""
+    shape = dict(ri.SHAPES["layer8b"], n_layers=2, hidden=1024, n_q=16, n_kv=8, ffn=768, vocab=8192)
+    w, _ = make_both(shape, 72, std=0.05)
+    wd = to_device(w)
+    prompts = [ri.tokens((n,), shape["vocab"], 72, 1400 + n).tolist() for n in [370, 33, 250, 5, 100, 17, 64, 320, 1][:rows]]
+    ids = list(range(rows))
+    kw = dict(max_seqs=16, max_ctx=416, max_rows=64, kv_pages=120)
+    ra, rb = amd.Rollout(shape, wd, **kw), amd.Rollout(shape, wd, **kw)
+    for r in (ra, rb):
+        r.rl_prefill(ids, prompts, 1.0, 6)
+    g = ra.decode_graph(ids, 1.0, 6)
+    torch.cuda.synchronize()
+    with torch.cuda.stream(torch.cuda.Stream()):
+        for step in range(24):
+            ta, la = g.step()
+            tb, lb = rb.rl_decode_step(ids, None, 1.0, 6)
+            torch.cuda.synchronize()
+            assert torch.equal(ta, tb) and torch.equal(la, lb), step
+    assert ra.rl_seq_len(0) == 394 and g.captures == captures, g.captures
+    g.close()
+    ra.close()
+    rb.close()
+
+
 @pytest.mark.parametrize("kind", ["tiny_f32", "small_bf16"])
 @pytest.mark.parametrize("top_k,top_p", [(0, 0.95), (50, 0.0), (300, 0.9)])
 def test_truncated_decode_graph_steps_equal_eager_steps(amd, kind, top_k, top_p):

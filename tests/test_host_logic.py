@@ -193,6 +193,30 @@ def test_attention_segments_partition_every_context(st):
         assert b[0] == 0 and b[-1] == (ctx + 31) // 32 and all(x <= y for x, y in zip(b, b[1:]))
 
 
+def test_captured_attention_launches_keep_the_split_of_their_contexts(st):
+    """A captured decode step is launched for a context that stands for those of its replays: the launch it makes is the one that each of them
+    makes by itself (segments, blocks per row), and within 1024 keys there are two of them at most."""
+    def split(*a):
+        out = (C.c_int * 2)()
+        st.st_attn_split(*a, out)
+        return tuple(out)
+
+    assert split(1, 8, 0, 384, 0, 4) == (4, 1) and split(1, 8, 0, 385, 0, 4) == (0, 1)
+    assert split(9, 8, 0, 384, 0, 4) == split(9, 8, 0, 385, 0, 4) == (4, 2)
+    assert split(64, 8, 0, 385, 0, 4) == (16, 4) and split(1, 8, 0, 385, 1, 4) == (16, 4) and split(8, 8, 1, 385, 0, 4) == (4, 1)
+    ctxs = [1, 15, 33, 383, 384, 385, 700, 1023, 1024, 1025, 2048, 2049, 4096, 4097, 9000]
+    for rows in (1, 2, 8, 9, 16, 33, 64, 128):
+        for n_kv, fp8, sets in ((8, 0, 0), (8, 1, 0), (8, 0, 1), (2, 0, 0)):
+            for ctx in ctxs:
+                cap = st.st_attn_capture_ctx(rows, n_kv, fp8, ctx, sets)
+                assert cap >= ctx and st.st_attn_num_segments(cap) == st.st_attn_num_segments(ctx)
+                for spb in (1, 2, 4, 16):
+                    assert split(rows, n_kv, fp8, cap, sets, spb) == split(rows, n_kv, fp8, ctx, sets, spb), (rows, n_kv, fp8, sets, ctx)
+                assert st.st_attn_capture_ctx(rows, n_kv, fp8, cap, sets) == cap
+            for lo in range(1, 4097, 1024):
+                assert len({st.st_attn_capture_ctx(rows, n_kv, fp8, c, sets) for c in range(lo, lo + 1024)}) <= (2 if lo == 1 else 1)
+
+
 def test_shared_attention_plan(st):
     """Sets hold rows of one sharing family at one position; the covered segments end inside the common pages;
     a left-over single row, rows at other positions and sequences that share nothing stay on their own."""
