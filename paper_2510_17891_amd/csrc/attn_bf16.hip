@@ -965,7 +965,7 @@ bool launch_attn_decode_bf16(hipStream_t s, const Geometry& g, const float* q, c
                              const int32_t* block_table, void* k_pool_layer, void* v_pool_layer, float* part,
                              int max_segs_alloc, int max_ctx_in_batch, void* o_out, int M, const int32_t* skip_segs,
                              const AttnShared* shared, int n_shared, int max_shared_segs, const AttnAppend* append,
-                             int segs_per_block, bool window_sets, bool packs, bool all_packed) {
+                             int segs_per_block, int set_segs, bool window_sets, bool packs, bool all_packed) {
   const int n_seg_max = attn_num_segments(max_ctx_in_batch);
   int page_ints = ((max_ctx_in_batch + 15) / 16 + 1 + 3) & ~3;  // keeps the partials 16-byte aligned
   if (packs) page_ints = std::max(page_ints, 4 * kPackPages);
@@ -975,12 +975,6 @@ bool launch_attn_decode_bf16(hipStream_t s, const Geometry& g, const float* q, c
   const int row_blocks = n_shared > 0 && (window_sets || all_packed) ? 0 : M;
   const AttnSplit split = attn_split(M, g.n_kv, g.kv_fp8, max_ctx_in_batch, n_shared > 0, segs_per_block);
   const int whole_segs = split.whole_segs, spb = split.spb;
-  // Set blocks take four segments, or two where those make no more than a block per compute unit (few samples, long prompts):
-  // one layer, us, four / two: 8 rows of 5000 shared keys 106.0 / 103.6, 16 of 2500 103.2 / 101.8, 24 of 1700 107.5 / 102.9,
-  // 32 of 1700 107.0 / 106.6, 32 with 1024 of 1924 shared 124.2 / 122.4.  Four / one: 16 rows with 1500 of 2500 shared 111.9 / 113.0;
-  // fp8 pages, 16 rows of 3000, four / two and less 99.6 / 102.6.
-  const bool pairs_of_segs = n_shared > 0 && !window_sets && !packs && !g.kv_fp8 && n_shared * g.n_kv * ((max_shared_segs + 1) / 2) <= kComputeUnits;
-  const int set_segs = pairs_of_segs ? 2 : 4;
   const int z = std::max(row_blocks > 0 ? attn_num_splits(n_seg_max, whole_segs, spb) : 1, (max_shared_segs + set_segs - 1) / set_segs);
   dim3 grid(g.n_kv, row_blocks + n_shared, z);
   const int segs = n_seg_max > kLdsSegs ? kLdsSegs : n_seg_max;

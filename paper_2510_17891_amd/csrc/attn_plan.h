@@ -213,6 +213,21 @@ inline void plan_packs(int n, const int32_t* pos, int n_kv, int group, int min_p
   plan->all_packed = all;
 }
 
+// Segments of a set block of a decode step: four, or two in steps of few rows with long prompts, where
+//   - those make no more than a block per compute unit: one layer, us, four / two: 8 rows of 5000 shared keys 106.0 / 103.6, 16 of 2500
+//     103.2 / 101.8, 24 of 1700 107.5 / 102.9, 32 of 1700 107.0 / 106.6, 32 with 1024 of 1924 shared 124.2 / 122.4;
+//   - and with the rows' own blocks no more than the two per unit that fit: 48 rows of 1008 keys, eight samples a prompt, 99.0 / 102.1 (576
+//     blocks), 24 rows of 16 kv heads 95.9 / 99.0 (at 512 blocks four query heads per kv head gain 1 to 4 %, two lose 2);
+//   - and no row is left to itself: such a row's blocks last as long as the launch, and with the set blocks on all units none runs beside idle ones
+//     (20 rows of 2000 keys, 16 of them in sets of four, 0.946 times as fast with two; two query groups of eight, 18 rows of 5008 keys
+//     in sets of two and alone, 0.940; all such sizes together 0.966 to 1.010).
+// Four / one: 16 rows with 1500 of 2500 shared keys 111.9 / 113.0; fp8 pages, 16 rows of 3000, four / two and less 99.6 / 102.6.
+inline int attn_set_segments(int n_rows, int n_kv, bool kv_fp8, const AttnPlan& plan) {
+  const int blocks = (int)plan.sets.size() * n_kv * ((plan.max_shared_segs + 1) / 2);
+  const bool alone = std::find(plan.skip.begin(), plan.skip.end(), 0) != plan.skip.end();
+  return kv_fp8 || plan.packs || alone || blocks > kComputeUnits || blocks + n_rows * n_kv > 2 * kComputeUnits ? 4 : 2;
+}
+
 // Rows that feed consecutive positions of one sequence (prefill, scoring).  Positions inside one aligned window of
 // 32 have the same number of 32-key steps and hence the same segments, and every row's keys are a prefix of the
 // keys of the row after it: up to rows_per_set (<= kAttnSetRows) neighbouring rows of a window form a set that computes ALL their

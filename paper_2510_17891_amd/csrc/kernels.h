@@ -143,7 +143,7 @@ bool launch_attn_decode_bf16(hipStream_t s, const Geometry& g, const float* q, c
                              float* part, int max_segs_alloc, int max_ctx_in_batch, void* o_out, int M,
                              const int32_t* skip_segs = nullptr, const AttnShared* shared = nullptr, int n_shared = 0,
                              int max_shared_segs = 0, const AttnAppend* append = nullptr, int segs_per_block = 16,
-                             bool window_sets = false, bool packs = false, bool all_packed = false);
+                             int set_segs = 4, bool window_sets = false, bool packs = false, bool all_packed = false);
 void launch_attn_merge_bf16(hipStream_t s, const Geometry& g, const RowMeta* rows, float* part, int max_segs_alloc, int max_ctx_in_batch,
                             void* o_out, int M, const int32_t* skip_segs, int n_shared);
 // fp32, even head_dim <= 128: one block per (row, q head), whole context, output fp32 row-major [M][n_q*d].  append (may

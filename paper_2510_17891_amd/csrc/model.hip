@@ -259,6 +259,7 @@ struct SharedAttn {  // device pointers into the metadata slot of the call (empt
   const int32_t* skip = nullptr;
   const AttnShared* sets = nullptr;
   int n_sets = 0, max_segs = 0;
+  int set_segs = 4;     // segments of a set block
   bool window = false;  // every row is in a set, and the sets cover all segments of their rows
   bool packs = false, all_packed = false;  // some sets are packs of single segments; no row is left to a block of its own
 };
@@ -286,7 +287,7 @@ Pending finish_layer(rl_model* m, hipStream_t st, int l, int M, const RowMeta* r
     bool merge;
     { Timer t(m, st, K_ATTN);
       merge = launch_attn_decode_bf16(st, g, q, rows, bt, m->k_pool(l), m->v_pool(l), apart, m->lay.max_segs, max_ctx_in_batch,
-                                      o, M, sa.skip, sa.sets, sa.n_sets, sa.max_segs, ap, m->attn_segs_per_block, sa.window, sa.packs, sa.all_packed); }
+                                      o, M, sa.skip, sa.sets, sa.n_sets, sa.max_segs, ap, m->attn_segs_per_block, sa.set_segs, sa.window, sa.packs, sa.all_packed); }
     if (merge) {
       Timer t(m, st, K_ATTN_MERGE);
       launch_attn_merge_bf16(st, g, rows, apart, m->lay.max_segs, max_ctx_in_batch, o, M, sa.skip, sa.n_sets);
@@ -573,6 +574,7 @@ SlotUpload build_decode_meta(rl_model* m, int32_t n, const int32_t* seq_ids, cha
   }
   SlotUpload up = slot_upload(m, hs, ds, n, true);
   place_attn_plan(m, hs, ds, n, plan, sa, &up);
+  if (sa->n_sets) sa->set_segs = attn_set_segments(n, m->geo.n_kv, m->geo.kv_fp8, plan);
   *max_ctx_out = max_ctx;
   return up;
 }
@@ -608,8 +610,8 @@ void decode_enqueue(rl_model* m, hipStream_t st, int n, const RowMeta* rows, int
 
 // A decode step of a fixed batch as a HIP graph.  What changes from step to step is data (rows and the
 // shared-attention plan: one upload from a pinned buffer that the graph's first kernel reads at every launch) except for
-// four launch shapes, which form the key of the captured graph: the context that stands for the longest one (block
-// counts and shared-memory size of the attention launch; attn_capture_ctx), the number of row sets, the blocks the sets need, and
+// five launch shapes, which form the key of the captured graph: the context that stands for the longest one (block
+// counts and shared-memory size of the attention launch; attn_capture_ctx), the number of row sets, the blocks the sets need and the segments of one, and
 // whether some or all of what the sets leave of their rows is packed.  When the key changes, the step is captured again.  A batch in
 // lock step does so every 1024 steps, once more at 384 keys if its rows leave compute units idle (attn_split), and, where it
 // holds samples of one prompt, where they begin to share (attn_alone_up_to) and with each four segments more in the
@@ -624,7 +626,7 @@ struct rl_decode_graph {
   hipEvent_t ev[2] = {nullptr, nullptr};
   bool ev_used[2] = {false, false};
   hipGraphExec_t exec[2] = {nullptr, nullptr};
-  struct Key { int ctx, n_sets, set_blocks, packs; } key[2] = {{-1, -1, -1, -1}, {-1, -1, -1, -1}};
+  struct Key { int ctx, n_sets, set_blocks, set_segs, packs; } key[2] = {{-1, -1, -1, -1, -1}, {-1, -1, -1, -1, -1}};
   int next = 0;
   int64_t captures = 0;
 };
@@ -878,9 +880,9 @@ rl_status rl_decode_graph_step(rl_decode_graph* g, void* stream, int64_t* captur
   int max_ctx = 0;
   SharedAttn sa;
   const SlotUpload up = build_decode_meta(m, n, g->ids.data(), hs, ds, &max_ctx, &sa, true);
-  const rl_decode_graph::Key key = {attn_capture_ctx(n, m->geo.n_kv, m->geo.kv_fp8, max_ctx, sa.n_sets > 0), sa.n_sets, (sa.max_segs + 3) / 4, sa.packs + sa.all_packed};
+  const rl_decode_graph::Key key = {attn_capture_ctx(n, m->geo.n_kv, m->geo.kv_fp8, max_ctx, sa.n_sets > 0), sa.n_sets, (sa.max_segs + 3) / 4, sa.set_segs, sa.packs + sa.all_packed};
   if (!g->exec[b] || key.ctx != g->key[b].ctx || key.n_sets != g->key[b].n_sets ||
-      key.set_blocks != g->key[b].set_blocks || key.packs != g->key[b].packs) {
+      key.set_blocks != g->key[b].set_blocks || key.set_segs != g->key[b].set_segs || key.packs != g->key[b].packs) {
     if (g->exec[b]) { (void)hipGraphExecDestroy(g->exec[b]); g->exec[b] = nullptr; }
     const bool prof = m->prof_on;
     m->prof_on = false;  // no event pairs inside a captured step

@@ -69,6 +69,17 @@ int st_plan_shared(void* t, int n, const int* seq_ids, const int* pos, int rows_
   return (int)plan.sets.size();
 }
 
+// segments of a set block of n rows in n_sets sets of up to max_segs segments; alone: some row is in none; packs: packed segments
+int st_attn_set_segments(int n, int n_kv, int kv_fp8, int n_sets, int max_segs, int alone, int packs) {
+  rl::AttnPlan plan;
+  plan.skip.assign(n, max_segs);
+  if (alone) plan.skip[n - 1] = 0;
+  plan.sets.resize(n_sets);
+  plan.max_shared_segs = max_segs;
+  plan.packs = packs;
+  return rl::attn_set_segments(n, n_kv, kv_fp8 != 0, plan);
+}
+
 // what is left behind the shared segments of n rows (skip[r] of them, 0: in no set): skip is updated, sets_out gets the packs
 // behind n_sets sets; returns the entries, and in *all whether no row is left
 int st_plan_packs(int n, const int* pos, int n_kv, int group, int min_pairs, int max_entries, int padded, int n_sets, int* skip,

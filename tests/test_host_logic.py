@@ -217,6 +217,17 @@ def test_captured_attention_launches_keep_the_split_of_their_contexts(st):
                 assert len({st.st_attn_capture_ctx(rows, n_kv, fp8, c, sets) for c in range(lo, lo + 1024)}) <= (2 if lo == 1 else 1)
 
 
+def test_set_blocks_of_two_segments_leave_room_and_no_row_alone(st):
+    """Two segments per set block up to 256 such blocks and 512 with the rows' own, for bf16 pages, where every row is in a set."""
+    two = lambda *a: st.st_attn_set_segments(*a) == 2                     # noqa: E731
+    assert two(8, 8, 0, 2, 19, 0, 0) and two(24, 8, 0, 6, 7, 0, 0)
+    assert two(32, 8, 0, 8, 7, 0, 0) and not two(36, 8, 0, 9, 7, 0, 0)    # 256 and 288 set blocks, 512 with the rows' own
+    assert two(40, 8, 0, 10, 3, 0, 0) and not two(48, 8, 0, 12, 3, 0, 0)  # 480, 576 blocks in all
+    assert not two(24, 16, 0, 6, 3, 0, 0)
+    assert not two(20, 8, 0, 4, 7, 1, 0) and two(20, 8, 0, 5, 7, 0, 0)    # a row alone
+    assert not two(8, 8, 1, 2, 19, 0, 0) and not two(8, 8, 0, 2, 19, 0, 1)
+
+
 def test_shared_attention_plan(st):
     """Sets hold rows of one sharing family at one position; the covered segments end inside the common pages;
     a left-over single row, rows at other positions and sequences that share nothing stay on their own."""
