@@ -1585,6 +1585,35 @@ def test_decode_graph_of_few_rows_keeps_one_block_up_to_the_line_of_several(amd,
     rb.close()
 
 
+@pytest.mark.parametrize("n_prompts,G,line", [(3, 4, 1792), (2, 5, 1792), (12, 4, 900)])
+def test_decode_graph_across_the_line_where_rows_begin_to_share(amd, n_prompts, G, line):
+    """Steps that leave every row to itself up to a line and form sets beyond it: a graph is captured again there, with set blocks of two
+    segments (96 of them, all rows in sets), or of four (a row of each prompt alone; 576 blocks if they held two).  Tokens and log-probabilities of every
+    replay are those of eager steps of a second instance that never shares, bit for bit."""
+    shape = dict(ri.SHAPES["layer8b"], n_layers=2, hidden=512, n_q=16, n_kv=8, ffn=768, vocab=8192)
+    w, _ = make_both(shape, 73, std=0.05)
+    wd = to_device(w)
+    prompts = [ri.tokens((line - 8 - 3 * (i == 1),), shape["vocab"], 73, 1500 + i).tolist() for i in range(n_prompts)]
+    ids = list(range(n_prompts * G))
+    kw = dict(max_seqs=48, max_ctx=1824, max_rows=64, kv_pages=900)
+    ra, rb = amd.Rollout(shape, wd, **kw), amd.Rollout(shape, wd, **kw)
+    rb.rl_debug_share_attention(0)
+    for r in (ra, rb):
+        r.rl_prefill_groups(ids, G, prompts, 1.0, 8)
+    g = ra.decode_graph(ids, 1.0, 8)
+    torch.cuda.synchronize()
+    with torch.cuda.stream(torch.cuda.Stream()):
+        for step in range(24):
+            ta, la = g.step()
+            tb, lb = rb.rl_decode_step(ids, None, 1.0, 8)
+            torch.cuda.synchronize()
+            assert torch.equal(ta, tb) and torch.equal(la, lb), step
+    assert ra.rl_seq_len(0) == line + 16 and g.captures == 4, g.captures  # two buffers on both sides of the line
+    g.close()
+    ra.close()
+    rb.close()
+
+
 @pytest.mark.parametrize("kind", ["tiny_f32", "small_bf16"])
 @pytest.mark.parametrize("top_k,top_p", [(0, 0.95), (50, 0.0), (300, 0.9)])
 def test_truncated_decode_graph_steps_equal_eager_steps(amd, kind, top_k, top_p):
