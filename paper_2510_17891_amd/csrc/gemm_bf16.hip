@@ -1061,24 +1061,10 @@ __global__ __launch_bounds__(NW * 64, 2) void gemm_bf16_tile_kernel(const u32x4_
   }
 }
 
-struct Plan {
-  int splits;       // K splits across blocks
-  int kb_per_wave;  // 64-wide k blocks per wave
-};
-
-Plan make_plan(int N, int K, int epi, bool allow_split) {
-  const int KB = K >> 6;
-  const int tiles = epi == kEpiSwiGLU ? (N >> 5) : (N >> 6);
-  int S = 1;
-  // Split K across blocks until about one block per CU exists; each wave keeps >= 2 k blocks.
-  while (tiles * S < 256 && (KB % (S * 2 * 4) == 0) && KB / (S * 2 * 4) >= 2 && epi == kEpiPartial && allow_split) S *= 2;
-  return Plan{S, KB / (S * 4)};
-}
-
 template <int MB, int ST>
 void launch_mb(hipStream_t s, const void* X, const void* W, void* out, int M, int N, int K, int epi, bool allow_split,
                const SampleEpilogue& se) {
-  Plan p = make_plan(N, K, epi, allow_split);
+  GemmPlan p = gemm_plan(N, K, epi, allow_split);
   const int m_tiles = (M + 32 * MB - 1) / (32 * MB);
   if (epi == kEpiSwiGLU) {
     dim3 grid(N >> 5, 1, m_tiles);
@@ -1095,7 +1081,7 @@ void launch_mb(hipStream_t s, const void* X, const void* W, void* out, int M, in
 template <int MB, int ST>
 void launch_wide(hipStream_t s, const void* X, const void* W, void* out, int M, int N, int K, int epi, bool allow_split,
                  const SampleEpilogue& se) {
-  Plan p = make_plan(N, K, epi, allow_split);  // same K split as the narrow tiling: bit-identical results
+  GemmPlan p = gemm_plan(N, K, epi, allow_split);  // same K split as the narrow tiling: bit-identical results
   const int m_tiles = (M + 32 * MB - 1) / (32 * MB);
   const int tiles = epi == kEpiSwiGLU ? (N >> 5) : (N >> 6);
   dim3 grid((tiles + 1) / 2, epi == kEpiPartial ? p.splits : 1, m_tiles);
@@ -1107,19 +1093,10 @@ void launch_wide(hipStream_t s, const void* X, const void* W, void* out, int M, 
     gemm_bf16_wide_kernel<MB, kEpiPartial, ST><<<grid, 256, 0, s>>>((const u32x4_t*)X, (const u32x4_t*)W, out, M, N, K, p.kb_per_wave, se);
 }
 
-// Tiles of two sizes (see gemm_bf16_mixed_kernel): used when the matrix has exactly three (row block, K split) units
-// per compute unit.
-bool mixed_fits(int N, int K, int epi, bool allow_split) {
-  if (epi == kEpiSample) return false;
-  const Plan p = make_plan(N, K, epi, allow_split);
-  const int row_blocks = (epi == kEpiSwiGLU ? 2 * N : N) >> 5;
-  return row_blocks % 3 == 0 && row_blocks * p.splits == 3 * kComputeUnits;
-}
-
 template <int MB, int ST>
 void launch_mixed(hipStream_t s, const void* X, const void* W, void* out, int M, int N, int K, int epi, bool allow_split,
                   const SampleEpilogue& se) {
-  const Plan p = make_plan(N, K, epi, allow_split);  // same K split as the other variants: bit-identical results
+  const GemmPlan p = gemm_plan(N, K, epi, allow_split);  // same K split as the other variants: bit-identical results
   const int row_blocks = (epi == kEpiSwiGLU ? 2 * N : N) >> 5, third = row_blocks / 3;
   const int m_tiles = (M + 32 * MB - 1) / (32 * MB);
   dim3 grid(p.splits * 2 * third, 1, m_tiles);
@@ -1131,88 +1108,11 @@ void launch_mixed(hipStream_t s, const void* X, const void* W, void* out, int M,
                                                                      p.kb_per_wave, third, third, p.splits, se);
 }
 
-// Blocks of the 128-row tiling for (N, K): it is used where they still fill the chip.
-int wide_blocks(int N, int K, int epi, bool allow_split) {
-  const Plan p = make_plan(N, K, epi, allow_split);
-  const int tiles = epi == kEpiSwiGLU ? (N >> 5) : (N >> 6);
-  return ((tiles + 1) / 2) * (epi == kEpiPartial ? p.splits : 1);
-}
-
-// Whether an M x N x K product of more than 256 rows runs over the whole K range in one block (gemm_bf16_tile_kernel with
-// running sums, no split partials): where tiles of 4 or 3 row blocks x 128 rows give every compute unit work.  Where smaller
-// ones would be needed for that (O and down projections of the 8B shape up to 512 rows), the K splits go to
-// blocks of their own.
-bool whole_k(int M, int N, int K, int epi, bool allow_split) {
-  if (M <= 256) return false;
-  const Plan p = make_plan(N, K, epi == kEpiResidual ? kEpiPartial : epi, allow_split && epi != kEpiSample);
-  if (p.kb_per_wave % 4) return false;
-  if (epi == kEpiSample) return true;
-  const int n_rb = epi == kEpiSwiGLU ? (N >> 4) : (N >> 5), m_tiles = (M + 127) / 128;
-  int best = 0, best_cost = 0;
-  for (int nb = 4; nb >= 2; --nb) {
-    const int blocks = (n_rb + nb - 1) / nb * m_tiles;
-    const int cost = (blocks + kComputeUnits - 1) / kComputeUnits * nb;
-    if (!best || cost < best_cost) { best = nb; best_cost = cost; }
-  }
-  return best > 2;
-}
-
-struct Tile {
-  int nb, nw;  // row blocks and waves of a block of gemm_bf16_tile_kernel
-};
-
-// The tile of a product of more than 64 rows (K quarters of a multiple of four k blocks).
-//   - Up to 128 rows (one batch tile, HBM bound): 128-row weight tiles where they make 192 blocks or more, 96-row ones where
-//     those make a block per compute unit and 128-row ones do not (gate/up at 128 rows 42.9 against 46.0 us, QKV 15.7 against
-//     17.9), 64-row ones for the small matrices (O 12.6 against 15.7, down 26.7 against 35.4).
-//   - Up to 256 rows: eight waves, so that the weights are read once, by the same rule; matrices with fewer tiles take two
-//     batch tiles of four waves (O at 160 / 256 rows 15.0 / 18.2 us, with eight waves 18.5 / 23.8; down 30.0 / 39.2, 39.7 / 49.8).
-//   - Beyond: the least time by rounds of blocks.  Four waves have two blocks on a unit, and a last round of one block per
-//     unit takes 0.62 of a full one; eight waves have one, and blocks of a last batch tile of up to 128 rows take 0.55 of
-//     a full one.  A full round of gate/up takes 58 us with tiles of 3 row blocks x 128 rows, 69 with 4 x 128,
-//     57 with 3 x 256 and 63 with 4 x 256 (running sums of the last do not fit the LDS).  At 301 rows this picks 3 x 256 for gate/up (87 us,
-//     3 x 128 takes 88, 4 x 128 92, 4 x 256 101), at 512 4 x 128 (112; 114, 120, 123), at 640 4 x 128 (138; 148, 149, 150), at 768
-//     3 x 256 (165; 168, 175, 177), at 1024 4 x 256 (193; 207, 214, 231); for down at 256 / 301 / 512 rows 4 x 128 / 4 x 256 / 4 x 256
-//     (39 against 50, 48 against 53, 56 against 63).
-//   - Sampling beyond 256 rows: 4 x 128 (1 050 us at 700 rows, 4 x 256 1 069: its long epilogue overlaps with the other block).
-Tile pick_tile(int M, int N, int K, int epi, bool allow_split) {
-  const Plan p = make_plan(N, K, epi == kEpiResidual ? kEpiPartial : epi, allow_split && epi != kEpiSample);
-  const bool whole = whole_k(M, N, K, epi, allow_split), sums = whole && (p.splits > 1 || epi == kEpiResidual);
-  const int n_rb = epi == kEpiSwiGLU ? (N >> 4) : (N >> 5), splits = whole ? 1 : p.splits;
-  const auto tiles = [&](int nb) { return (n_rb + nb - 1) / nb * splits; };
-  if (M <= 256) {
-    const int wide = tiles(4);
-    if (wide >= 192) {
-      const bool three = epi != kEpiSample && n_rb % 3 == 0 && wide < kComputeUnits && tiles(3) <= kComputeUnits;
-      return {three ? 3 : 4, M <= 128 ? 4 : 8};
-    }
-    return {M > 128 && wide * 2 >= 192 ? 4 : 2, 4};
-  }
-  if (epi == kEpiSample) return {4, 4};
-  const int halves = (M + 127) / 128;
-  Tile best = {4, 4};
-  float best_cost = 0.f;
-  for (const Tile t : {Tile{4, 4}, Tile{3, 4}, Tile{3, 8}, Tile{4, 8}}) {
-    if (sums && t.nb == 4 && t.nw == 8) continue;
-    float rounds;
-    if (t.nw == 4) {
-      const int blocks = tiles(t.nb) * halves, left = blocks % (2 * kComputeUnits);
-      rounds = (float)(blocks / (2 * kComputeUnits)) + (left == 0 ? 0.f : left <= kComputeUnits ? 0.62f : 1.f);
-    } else {
-      const int full = tiles(t.nb) * (halves / 2), light = tiles(t.nb) * (halves & 1);
-      rounds = full + light <= kComputeUnits ? 1.f : (float)((full + kComputeUnits - 1) / kComputeUnits) + 0.55f * light / kComputeUnits;
-    }
-    const float cost = rounds * (t.nw == 4 ? (t.nb == 4 ? 69.f : 58.f) : (t.nb == 4 ? 63.f : 57.f));
-    if (best_cost == 0.f || cost < best_cost) { best = t; best_cost = cost; }
-  }
-  return best;
-}
-
 template <int NB, int NW, bool ONE>
 void launch_tile(hipStream_t s, const void* X, const void* W, void* out, int M, int N, int K, int epi, bool allow_split,
                  const SampleEpilogue& se) {
-  const Plan p = make_plan(N, K, epi == kEpiResidual ? kEpiPartial : epi, allow_split);  // same K split as the other variants: bit-identical results
-  const bool whole = whole_k(M, N, K, epi, allow_split);
+  const GemmPlan p = gemm_plan(N, K, epi == kEpiResidual ? kEpiPartial : epi, allow_split);  // same K split as the other variants: bit-identical results
+  const bool whole = gemm_whole_k(M, N, K, epi, allow_split);
   const int n_rb = epi == kEpiSwiGLU ? (N >> 4) : (N >> 5);
   const int n_tiles = (n_rb + NB - 1) / NB, m_tiles = (M + 32 * NW - 1) / (32 * NW), splits = whole ? p.splits : 1;
   dim3 grid((n_tiles + 7) / 8 * 8 * m_tiles, whole ? 1 : p.splits);
@@ -1228,10 +1128,10 @@ void launch_tile(hipStream_t s, const void* X, const void* W, void* out, int M, 
 
 }  // namespace
 
-int gemm_bf16_partials(int M, int N, int K) { return whole_k(M, N, K, kEpiPartial, true) ? 1 : gemm_bf16_splits(N, K, kEpiPartial); }
-bool gemm_bf16_adds_residual(int M, int N, int K) { return whole_k(M, N, K, kEpiResidual, true); }
-int gemm_bf16_splits(int N, int K, int epi) { return make_plan(N, K, epi, true).splits; }
-int gemm_bf16_weight_segment(int N, int K, bool split_k) { return make_plan(N, K, kEpiPartial, split_k).kb_per_wave; }
+int gemm_bf16_partials(int M, int N, int K) { return gemm_whole_k(M, N, K, kEpiPartial, true) ? 1 : gemm_bf16_splits(N, K, kEpiPartial); }
+bool gemm_bf16_adds_residual(int M, int N, int K) { return gemm_whole_k(M, N, K, kEpiResidual, true); }
+int gemm_bf16_splits(int N, int K, int epi) { return gemm_plan(N, K, epi, true).splits; }
+int gemm_bf16_weight_segment(int N, int K, bool split_k) { return gemm_plan(N, K, kEpiPartial, split_k).kb_per_wave; }
 
 // Whole k blocks per wave and pass: hidden a multiple of 1024; the K quarters hold at least the four k blocks of the ring.
 bool norm_gate_up_takes(int M, int H, int S) { return M <= 2 && H % kRowNormPass == 0 && H <= kRowNormPass * kRowNormMaxPass && S >= 1 && S <= kRowNormMaxS; }
@@ -1240,7 +1140,7 @@ void launch_norm_gate_up(hipStream_t s, const float* x, const float* part, int S
                          int M, int F, int H) {
   const RowNorm rn = {x, part, (size_t)M * H, (const uint16_t*)gain, eps, S};
   const int tiles = F >> 4;  // row blocks of the interleaved matrix
-  const bool mixed = mixed_fits(F, H, kEpiSwiGLU, true);
+  const bool mixed = gemm_mixed_fits(F, H, kEpiSwiGLU, true);
   const int n_big = mixed ? tiles / 3 : tiles / 2, blocks = mixed ? 2 * n_big : n_big;
   if (M == 1) norm_gate_up_kernel<1, 4><<<blocks, 256, 0, s>>>(rn, (const u32x4_t*)W, out, M, F, H, n_big);
   else norm_gate_up_kernel<2, 2><<<blocks, 256, 0, s>>>(rn, (const u32x4_t*)W, out, M, F, H, n_big);
@@ -1249,7 +1149,7 @@ void launch_norm_gate_up(hipStream_t s, const float* x, const float* part, int S
 template <int MB>
 void launch_st(hipStream_t s, const void* X, const void* W, void* out, int M, int N, int K, int epi, bool allow_split,
                int stages, const SampleEpilogue& se) {
-  const int n = make_plan(N, K, epi, allow_split).kb_per_wave;
+  const int n = gemm_plan(N, K, epi, allow_split).kb_per_wave;
   if (stages > n) stages = n;  // the kernel's prologue fills all of its buffers unconditionally
   switch (stages) {
     case 1: launch_mb<MB, 1>(s, X, W, out, M, N, K, epi, allow_split, se); break;
@@ -1262,7 +1162,7 @@ void launch_st(hipStream_t s, const void* X, const void* W, void* out, int M, in
 template <int MBW, int ST>
 void launch_cols_st(hipStream_t s, const void* X, const void* W, void* out, int M, int N, int K, int epi, bool allow_split,
                     const SampleEpilogue& se) {
-  Plan p = make_plan(N, K, epi, allow_split);  // same K split as the other variants: bit-identical results
+  GemmPlan p = gemm_plan(N, K, epi, allow_split);  // same K split as the other variants: bit-identical results
   const int m_tiles = (M + 128 * MBW - 1) / (128 * MBW);
   if (epi == kEpiSwiGLU) {
     dim3 grid(N >> 5, 1, m_tiles);
@@ -1280,9 +1180,9 @@ void launch_cols_st(hipStream_t s, const void* X, const void* W, void* out, int 
 template <int MBW>
 void launch_cols(hipStream_t s, const void* X, const void* W, void* out, int M, int N, int K, int epi, bool allow_split,
                  const SampleEpilogue& se) {
-  const Plan p = make_plan(N, K, epi == kEpiResidual ? kEpiPartial : epi, allow_split);
+  const GemmPlan p = gemm_plan(N, K, epi == kEpiResidual ? kEpiPartial : epi, allow_split);
   if (p.kb_per_wave % 4 == 0) {  // weight tiles shared through LDS
-    const Tile t = pick_tile(M, N, K, epi, allow_split);
+    const GemmTile t = gemm_tile(M, N, K, epi, allow_split);
     // 193..256 rows on 96-row tiles that make exactly one K split (gate/up): 59.4 us at 256 rows and 56.9 at 200, the tile kernel takes
     // 61.4 and 57.6 (and 52.6 against 56.8 at 192).
     if (t.nb == 3 && t.nw == 8 && epi == kEpiSwiGLU && M > 192 && M <= 256) {
@@ -1316,10 +1216,10 @@ void launch_gemm_bf16(hipStream_t s, const void* X, const void* W, void* out, in
   if (epi == kEpiSample) allow_split = false;
   // 128-row tiles for the K-split projections whose halved grid still fills the chip (QKV at the 8B shape: 16 -> 15 us
   // at 32 rows, 20.5 -> 17.8 us at 64); measured a loss for gate/up and the output projection, which keep 64-row tiles.
-  const bool wide = epi == kEpiPartial && make_plan(N, K, epi, allow_split).splits > 1 &&
-                    wide_blocks(N, K, epi, allow_split) >= 192 && make_plan(N, K, epi, allow_split).kb_per_wave >= 2;
-  const bool mixed = mixed_fits(N, K, epi, allow_split);
-  const int kbw = make_plan(N, K, epi, allow_split).kb_per_wave;
+  const bool wide = epi == kEpiPartial && gemm_plan(N, K, epi, allow_split).splits > 1 &&
+                    gemm_wide_blocks(N, K, epi, allow_split) >= 192 && gemm_plan(N, K, epi, allow_split).kb_per_wave >= 2;
+  const bool mixed = gemm_mixed_fits(N, K, epi, allow_split);
+  const int kbw = gemm_plan(N, K, epi, allow_split).kb_per_wave;
   if (M <= 32 && mixed && kbw >= 4) launch_mixed<1, 4>(s, X, W, out, M, N, K, epi, allow_split, e);
   else if (M <= 64 && M > 32 && mixed && kbw >= 2) launch_mixed<2, 2>(s, X, W, out, M, N, K, epi, allow_split, e);
   else if (M <= 32 && wide) launch_wide<1, 2>(s, X, W, out, M, N, K, epi, allow_split, e);

@@ -5,6 +5,7 @@
 #include <stdint.h>
 
 #include "attn_plan.h"
+#include "gemm_plan.h"
 #include "weight_order.h"
 
 namespace rl {
@@ -153,7 +154,6 @@ void launch_attn_f32(hipStream_t s, const Geometry& g, const float* q, const Row
                      float* o_out, int M, const AttnAppend* append = nullptr);
 
 // ---- projections ---------------------------------------------------------------------------------
-enum Epilogue : int { kEpiPartial = 0, kEpiSwiGLU = 1, kEpiSample = 2, kEpiResidual = 3 };
 
 // Arguments of the sampling epilogue of the output projection (ignored by the other epilogues).
 struct SampleEpilogue {

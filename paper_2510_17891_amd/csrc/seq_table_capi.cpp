@@ -2,6 +2,7 @@
 // Built with g++ into its own small library by the CPU tests; not part of the product library.
 #include "attn_plan.h"
 #include "cut_plan.h"
+#include "gemm_plan.h"
 #include "seq_table.h"
 #include "weight_order.h"
 
@@ -97,6 +98,18 @@ int st_plan_packs(int n, const int* pos, int n_kv, int group, int min_pairs, int
   }
   *all = plan.all_packed;
   return plan.packs;
+}
+
+// the staged kernel's tile of a projection of more than 64 rows: (row blocks, waves, whether one block walks the whole K range, row blocks
+// of the matrix); returns 0 where its K quarters are not rounds of four k blocks, i.e. another kernel takes it
+int st_gemm_tile(int M, int N, int K, int epi, int* out) {
+  const bool split = epi == rl::kEpiPartial || epi == rl::kEpiResidual;
+  const rl::GemmTile t = rl::gemm_tile(M, N, K, epi, split);
+  out[0] = t.nb;
+  out[1] = t.nw;
+  out[2] = rl::gemm_whole_k(M, N, K, epi, split) ? 1 : 0;
+  out[3] = epi == rl::kEpiSwiGLU ? N >> 4 : N >> 5;
+  return rl::gemm_plan(N, K, split ? rl::kEpiPartial : epi, split).kb_per_wave % 4 == 0;
 }
 
 // slices of truncated sampling, units of 256 logits per slice, whether the units' largest logits are kept

@@ -99,3 +99,21 @@ def cut_by_units(n, vocab):
     """Whether the third pass of such a call looks at the units' largest logits."""
     u = cut_units(n, vocab)
     return u > CUT_UNITS_READ_ALL and cut_slices(n, vocab) * u <= CUT_UNITS_KEPT
+
+
+# Layers and numbers of rows at which a projection's last weight tile is partial: the shape, rows, projection, its tile (row blocks, waves)
+# and the row blocks left for the last one.  The planner is asked about them on the CPU, the kernel runs them on the GPU.
+PARTIAL_TILES = [
+    (dict(hidden=1024, n_q=8, n_kv=2, ffn=1024), 260, "gate_up", (3, 4), 1),
+    (dict(hidden=1024, n_q=8, n_kv=2, ffn=1280), 260, "gate_up", (3, 4), 2),
+    (dict(hidden=1024, n_q=8, n_kv=2, ffn=2560), 780, "gate_up", (3, 8), 1),
+    (dict(hidden=1024, n_q=8, n_kv=2, ffn=3584), 520, "gate_up", (3, 8), 2),
+    (dict(hidden=4096, n_q=24, n_kv=8, ffn=768), 385, "qkv", (3, 4), 1),
+    (dict(hidden=4096, n_q=16, n_kv=8, ffn=768), 520, "qkv", (3, 4), 2),
+    (dict(hidden=4096, n_q=24, n_kv=8, ffn=768), 780, "qkv", (3, 8), 1),
+    (dict(hidden=4096, n_q=40, n_kv=8, ffn=768), 520, "qkv", (3, 8), 2),
+    (dict(hidden=4096, n_q=32, n_kv=4, ffn=768), 520, "o", (3, 4), 2),
+    (dict(hidden=3584, n_q=8, n_kv=2, ffn=8192), 520, "down", (3, 4), 1),
+]
+# The same for the output projection of a model with hidden 1024: vocabulary, rows, tile; two of four row blocks are left.
+PARTIAL_HEAD_TILES = [(24640, 100, (4, 4)), (24640, 200, (4, 8)), (24640, 300, (4, 4)), (12352, 200, (4, 4)), (4160, 300, (4, 4))]

@@ -9,6 +9,7 @@ import pytest
 import torch
 
 import rollout_inputs as ri
+import helpers as h
 from helpers import ArgmaxCount, CUT_SHAPES, cut_groups, cut_slices, dims_of, make_both, rel_inf, to_device
 from oracle import oracle as orc
 
@@ -1812,7 +1813,7 @@ def test_bf16_layer_bits_do_not_depend_on_batch_size_class(amd):
 
 @pytest.mark.parametrize("over, sizes", [
     (dict(), (257, 512, 897)),                                       # 8B shape: whole-K tiles of 4 and 3 row blocks, residual sums
-    (dict(hidden=2048, n_q=16, n_kv=4, ffn=6400), (300, 641)),       # gate/up in 400 row blocks: ragged tiles and batch tiles
+    (dict(hidden=2048, n_q=16, n_kv=4, ffn=6400), (300, 641)),       # gate/up in 400 row blocks and ragged batch tiles
 ])
 def test_bf16_layer_bits_in_whole_k_tiles(amd, over, sizes):
     """More than 256 rows run the projections that walk the whole K range of a tile and add split sums and the residual
@@ -1831,7 +1832,7 @@ def test_bf16_layer_bits_in_whole_k_tiles(amd, over, sizes):
 @pytest.mark.parametrize("over, sizes", [
     # one batch tile, two of O and down, idle waves, three and more tiles, light last ones
     (dict(), (65, 128, 129, 161, 193, 256, 290, 385, 640, 769, 1024)),
-    (dict(hidden=2048, n_q=16, n_kv=4, ffn=6400), (130, 517)),  # row blocks that no tile divides
+    (dict(hidden=2048, n_q=16, n_kv=4, ffn=6400), (130, 517)),  # gate/up in 400 row blocks; K quarters of QKV, O and down that take no stages
 ])
 def test_bf16_layer_bits_at_the_edges_of_batch_tiles(amd, over, sizes):
     """Rows at both ends of a batch, around its tiles of 128 and 256 rows and next to waves without rows keep the bits they
@@ -1854,6 +1855,45 @@ def test_bf16_layer_bits_at_the_edges_of_batch_tiles(amd, over, sizes):
         fresh(range(big))
         few = ro.rl_decode_hidden(at, x[at].contiguous())
         assert torch.isfinite(whole).all() and torch.equal(whole[at], few), n
+    ro.close()
+
+
+@pytest.mark.parametrize("over, n, name, tile, left", h.PARTIAL_TILES)
+def test_bf16_layer_bits_in_partial_weight_tiles(amd, over, n, name, tile, left):
+    """A projection whose last weight tile holds fewer row blocks than the others: rows at the ends of the batch and of its tiles keep the bits
+    that they have in a batch of their own, in every column."""
+    ctxs = [(7 * i) % 50 for i in range(n)]
+    shape, wn, ro, ks, vs, x = _layer_case(amd, ctxs, seed=44, **over)
+    x = x.to(DEV)
+    whole = ro.rl_decode_hidden(list(range(n)), x).clone()
+    at = [0, 31, 32, 127, 128, 255, 256, n - 33, n - 1]
+    ro.rl_free_seqs(at)
+    for i in at:
+        ro.rl_seq_import_kv(i, [ks[i].to(DEV)], [vs[i].to(DEV)])
+    few = ro.rl_decode_hidden(at, x[at].contiguous())
+    assert torch.isfinite(whole).all() and torch.equal(whole[at], few)
+    ro.close()
+
+
+@pytest.mark.parametrize("V, n, tile", h.PARTIAL_HEAD_TILES)
+def test_bf16_sampled_step_bits_in_a_partial_weight_tile(amd, V, n, tile):
+    """An output projection whose last tile holds half of its row blocks: logits, tokens and log-probabilities of rows at the ends of the batch and of its
+    tiles are those of a batch of their own."""
+    shape = dict(ri.SHAPES["layer8b"], n_layers=1, hidden=1024, n_q=8, n_kv=2, ffn=1024, vocab=V)
+    w, _ = make_both(shape, 45, std=0.05)
+    ro = amd.Rollout(shape, to_device(w), max_seqs=n, max_ctx=32, max_rows=max(n, 256), kv_pages=2 * n)
+    prompts = [ri.tokens((3 + i % 5,), V, 45, 3000 + i).tolist() for i in range(n)]
+    tok = torch.tensor(ri.tokens((n,), V, 45, 2999).tolist(), dtype=torch.int32, device=DEV)
+    at = sorted({0, 31, 32, 63, 64, n - 2, n - 1} | ({127, 128} if n > 128 else set()))
+    res = []
+    for ids in (list(range(n)), at):
+        z = torch.empty(len(ids), V, device=DEV)
+        ro.rl_prefill(ids, [prompts[i] for i in ids], 1.0, 9)
+        t, lp = ro.rl_decode_step(ids, tok[ids].contiguous(), 1.0, 9, debug_logits=z)
+        res.append((t.clone(), lp.clone(), z))
+        ro.rl_free_seqs(ids)
+    for a, b in zip(*res):
+        assert torch.isfinite(b.float()).all() and torch.equal(a[at], b)
     ro.close()
 
 

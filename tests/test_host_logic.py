@@ -449,6 +449,22 @@ def test_binding_fails_loudly_without_the_library():
     assert r.returncode == 0 and "raised:" in r.stdout and "paper_2510_17891_amd.build" in r.stdout
 
 
+def test_partial_tiles_of_the_gpu_tests_are_partial(st):
+    """The sizes at which the GPU tests run the staged projection kernel with a partial last tile still make one."""
+    def tile(m, n, k, epi):
+        out = (C.c_int * 4)()
+        assert st.st_gemm_tile(m, n, k, epi, out)
+        return (out[0], out[1]), out[3] % out[0], out[2]
+
+    for s, m, name, nb_nw, left in h.PARTIAL_TILES:
+        H, Q, F = s["hidden"], s["n_q"] * 128, s["ffn"]
+        n, k, epi = {"qkv": (Q + 2 * s["n_kv"] * 128, H, 0), "o": (H, Q, 3), "gate_up": (F, H, 1), "down": (H, F, 3)}[name]
+        got = tile(m, n, k, epi)
+        assert got[:2] == (nb_nw, left) and (epi != 3 or got[2] == 1), (s, m, name, got)   # O, down: added to the residual stream
+    for V, m, nb_nw in h.PARTIAL_HEAD_TILES:
+        assert tile(m, V, 1024, 2)[:2] == (nb_nw, 2), (V, m)
+
+
 def test_truncated_sampling_keeps_the_units_of_every_row_of_up_to_2_18_logits(st):
     """However a row is sliced, the place for its units' largest logits is enough, and no slice is empty of use: vocabularies
     of 2^18 entries are real ones."""
