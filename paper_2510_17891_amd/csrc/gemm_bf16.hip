@@ -626,46 +626,35 @@ __global__ __launch_bounds__(256) void gemm_bf16_cols_kernel(const u32x4_t* __re
 
 // Gate/up of 193..256 rows: eight waves, a 96-row weight tile (three row blocks) and all batch rows, where 128-row tiles would
 // leave a quarter of the compute units without a block while 96-row tiles give every unit one.  (The same tile in
-// gemm_bf16_tile_kernel: 61.4 us at 256 rows, here 59.4.)  The first four waves stage
+// gemm_bf16_tile_kernel: 62.9 us at 256 rows and 60.1 at 224, here 59.8 and 59.3.)  The first four waves stage
 // row blocks 0 and 2, the other four row block 1; each half runs its own copy of the loop (same steps, one barrier
 // per k block in both), so that no load in the pipeline is conditional.  Same K quarters, same order: same bits.
-template <int EPI, int XS>
+// grid: x = three row blocks, all of them whole, y = K split, K quarters of a multiple of four k blocks.  (Gate/up has one split; with
+// a constant 0 in its place the compiler arranges the loop worse: 60.7 us at 256 rows.)
 __global__ __launch_bounds__(512, 1) void gemm_bf16_lds8r3_kernel(const u32x4_t* __restrict__ X, const u32x4_t* __restrict__ W,
                                                                 void* __restrict__ out, int M, int N, int K,
                                                                 int kb_per_quarter) {
-  static_assert(EPI != kEpiSample, "per-row-block epilogues only");
-  constexpr int MBW = 1, RBN = 3;
+  constexpr int RBN = 3, XS = 2;
   __shared__ u32x4_t wlds[4][RBN][256];  // four stages x three row blocks x 4 KiB
   const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
   const int KB = K >> 6;
   const int n_blocks_m = (M + 31) >> 5;
   const int t256 = tid & 255;
-  const int tile_x = blockIdx.x;
-  const int m_blk0 = blockIdx.z * 8 + wave;
-  const bool has_rows = m_blk0 < n_blocks_m;
-  const int n_rb = EPI == kEpiSwiGLU ? (N >> 4) : (N >> 5);
-  int rb[RBN];
-#pragma unroll
-  for (int b = 0; b < RBN; ++b) rb[b] = min(tile_x * RBN + b, n_rb - 1);  // past the end: shadows the last one, never stored
-  const u32x4_t* xb[MBW];
-#pragma unroll
-  for (int mb = 0; mb < MBW; ++mb) {
-    int blk = m_blk0 + mb;
-    if (blk >= n_blocks_m) blk = n_blocks_m - 1;  // idle waves shadow a valid block (never stored)
-    xb[mb] = X + (size_t)blk * KB * 256 + lane;
-  }
+  const int rb0 = blockIdx.x * RBN;
+  const bool has_rows = wave < n_blocks_m;
+  const u32x4_t* const xb = X + (size_t)min(wave, n_blocks_m - 1) * KB * 256 + lane;  // an idle wave shadows a valid block (never stored)
   const int n = 4 * kb_per_quarter;
   const int kb0 = blockIdx.y * n;
   auto kb_of = [&](int i) { return kb0 + (i < n ? i : n - 1); };  // clamped: no conditional loads in the pipeline
-  f32x16_t acc[RBN][MBW];
+  f32x16_t acc[RBN];
 
-  // NS = row blocks this half of the block stages: srb[0 .. NS-1]
+  // NS = row blocks this half of the block stages: srb0 and, if there are two, srb1
   auto run = [&](auto ns_c, int srb0, int srb1) __attribute__((always_inline)) {
     constexpr int NS = decltype(ns_c)::value;
     const int srb[2] = {srb0, srb1};
     const u32x4_t* wp[NS];
 #pragma unroll
-    for (int b = 0; b < NS; ++b) wp[b] = W + (size_t)rb[srb[b]] * KB * 256 + t256;
+    for (int b = 0; b < NS; ++b) wp[b] = W + (size_t)(rb0 + srb[b]) * KB * 256 + t256;
     // Weight k blocks are loaded strictly in order (the last one again once the range is exhausted); the slot of the
     // next one is kept as (block within its quarter, quarter) and stepped, without a division.
     int w_r = 0, w_q = 0;
@@ -675,8 +664,8 @@ __global__ __launch_bounds__(512, 1) void gemm_bf16_lds8r3_kernel(const u32x4_t*
       else if (w_q < 3) { w_r = 0; ++w_q; }
       return off;
     };
-    u32x4_t wr[4][NS];        // weight registers: slot s holds a k block with index = s (mod 4)
-    u32x4_t xr[XS][MBW][4];   // activation fragments: slot s holds a k block with index = s (mod XS)
+    u32x4_t wr[4][NS];   // weight registers: slot s holds a k block with index = s (mod 4)
+    u32x4_t xr[XS][4];   // activation fragments: slot s holds a k block with index = s (mod XS)
 #pragma unroll
     for (int s = 0; s < 4; ++s) {
       const int ow = next_wslot();
@@ -686,9 +675,7 @@ __global__ __launch_bounds__(512, 1) void gemm_bf16_lds8r3_kernel(const u32x4_t*
 #pragma unroll
     for (int s = 0; s < XS; ++s)
 #pragma unroll
-      for (int mb = 0; mb < MBW; ++mb)
-#pragma unroll
-        for (int t = 0; t < 4; ++t) xr[s][mb][t] = xb[mb][(size_t)kb_of(s) * 256 + t * 64];
+      for (int t = 0; t < 4; ++t) xr[s][t] = xb[(size_t)kb_of(s) * 256 + t * 64];
     {
       const int ow = next_wslot();
 #pragma unroll
@@ -697,7 +684,7 @@ __global__ __launch_bounds__(512, 1) void gemm_bf16_lds8r3_kernel(const u32x4_t*
         wr[0][b] = __builtin_nontemporal_load(wp[b] + ow);
       }
     }
-    auto iter = [&](f32x16_t (&a)[RBN][MBW], int i, auto jc) __attribute__((always_inline)) {
+    auto iter = [&](f32x16_t (&a)[RBN], int i, auto jc) __attribute__((always_inline)) {
       constexpr int j = decltype(jc)::value, jn = (j + 1) & 3, jx = j % XS;
       const int ow = next_wslot();  // k block i + 5
 #pragma unroll
@@ -710,26 +697,17 @@ __global__ __launch_bounds__(512, 1) void gemm_bf16_lds8r3_kernel(const u32x4_t*
       __builtin_amdgcn_s_barrier();
       __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
 #pragma unroll
-      for (int t = 0; t < 4; ++t) {
+      for (int t = 0; t < 4; ++t)
 #pragma unroll
-        for (int b = 0; b < RBN; ++b) {
-          const u32x4_t afrag = wlds[j][b][t * 64 + lane];
+        for (int b = 0; b < RBN; ++b) a[b] = mfma_f16(wlds[j][b][t * 64 + lane], xr[jx][t], a[b]);
 #pragma unroll
-          for (int mb = 0; mb < MBW; ++mb) a[b][mb] = mfma_f16(afrag, xr[jx][mb][t], a[b][mb]);
-        }
-      }
-#pragma unroll
-      for (int mb = 0; mb < MBW; ++mb)
-#pragma unroll
-        for (int t = 0; t < 4; ++t) xr[jx][mb][t] = xb[mb][(size_t)kb_of(i + XS) * 256 + t * 64];
+      for (int t = 0; t < 4; ++t) xr[jx][t] = xb[(size_t)kb_of(i + XS) * 256 + t * 64];
     };
-    auto quarter = [&](f32x16_t (&a)[RBN][MBW], int q) __attribute__((always_inline)) {
+    auto quarter = [&](f32x16_t (&a)[RBN], int q) __attribute__((always_inline)) {
 #pragma unroll
       for (int b = 0; b < RBN; ++b)
 #pragma unroll
-        for (int mb = 0; mb < MBW; ++mb)
-#pragma unroll
-          for (int r = 0; r < 16; ++r) a[b][mb][r] = 0.f;
+        for (int r = 0; r < 16; ++r) a[b][r] = 0.f;
       for (int i = q * kb_per_quarter; i < (q + 1) * kb_per_quarter; i += 4) {
         iter(a, i, std::integral_constant<int, 0>{});
         iter(a, i + 1, std::integral_constant<int, 1>{});
@@ -737,33 +715,25 @@ __global__ __launch_bounds__(512, 1) void gemm_bf16_lds8r3_kernel(const u32x4_t*
         iter(a, i + 3, std::integral_constant<int, 3>{});
       }
     };
-    f32x16_t other[RBN][MBW];
+    f32x16_t other[RBN];
     quarter(acc, 0);
     for (int q = 1; q < 4; ++q) {
       quarter(other, q);
 #pragma unroll
-      for (int b = 0; b < RBN; ++b)
-#pragma unroll
-        for (int mb = 0; mb < MBW; ++mb) acc[b][mb] += other[b][mb];
+      for (int b = 0; b < RBN; ++b) acc[b] += other[b];
     }
   };
   if (__builtin_amdgcn_readfirstlane(wave) < 4) run(std::integral_constant<int, 2>{}, 0, 2);
   else run(std::integral_constant<int, 1>{}, 1, 1);
 
-  if (!has_rows) return;
-  const int col = lane & 31, hb = lane >> 5;
+  const int col = lane & 31, hb = lane >> 5, m = wave * 32 + col;
+  if (!has_rows || m >= M) return;
 #pragma unroll
-  for (int mb = 0; mb < MBW; ++mb) {
-    const int m = (m_blk0 + mb) * 32 + col;
-    if (m >= M) continue;
+  for (int b = 0; b < RBN; ++b) {
+    float sum[16];
 #pragma unroll
-    for (int b = 0; b < RBN; ++b) {
-      if (tile_x * RBN + b >= n_rb) break;
-      float sum[16];
-#pragma unroll
-      for (int r = 0; r < 16; ++r) sum[r] = acc[b][mb][r];
-      store_rowblock<EPI>(sum, m, hb, rb[b], blockIdx.y, M, N, out);
-    }
+    for (int r = 0; r < 16; ++r) sum[r] = acc[b][r];
+    store_rowblock<kEpiSwiGLU>(sum, m, hb, rb0 + b, 0, M, N, out);
   }
 }
 
@@ -1183,10 +1153,10 @@ void launch_cols(hipStream_t s, const void* X, const void* W, void* out, int M, 
   const GemmPlan p = gemm_plan(N, K, epi == kEpiResidual ? kEpiPartial : epi, allow_split);
   if (p.kb_per_wave % 4 == 0) {  // weight tiles shared through LDS
     const GemmTile t = gemm_tile(M, N, K, epi, allow_split);
-    // 193..256 rows on 96-row tiles that make exactly one K split (gate/up): 59.4 us at 256 rows and 56.9 at 200, the tile kernel takes
-    // 61.4 and 57.6 (and 52.6 against 56.8 at 192).
+    // 193..256 rows on 96-row tiles that make exactly one K split (gate/up): 59.8 us at 256 rows and 59.3 at 224, the tile kernel takes
+    // 62.9 and 60.1 (but up to 192 rows, where two of its waves rest, 56.7 against 59.0).
     if (t.nb == 3 && t.nw == 8 && epi == kEpiSwiGLU && M > 192 && M <= 256) {
-      gemm_bf16_lds8r3_kernel<kEpiSwiGLU, 2><<<dim3((N >> 4) / 3, 1, 1), 512, 0, s>>>((const u32x4_t*)X, (const u32x4_t*)W, out, M, N, K, p.kb_per_wave);
+      gemm_bf16_lds8r3_kernel<<<dim3((N >> 4) / 3, 1), 512, 0, s>>>((const u32x4_t*)X, (const u32x4_t*)W, out, M, N, K, p.kb_per_wave);
       return;
     }
     const bool one = M <= 32 * t.nw;  // a single batch tile

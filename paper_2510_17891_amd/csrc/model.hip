@@ -389,7 +389,6 @@ void run_head(rl_model* m, hipStream_t st, int M, float* xbuf, const Pending& pe
   int32_t* last_tok = score_only ? nullptr : m->wsp<int32_t>(m->lay.last_tok);
   const Geometry& g = m->geo;
   void* h = m->wsp<void>(m->lay.h);
-  float* part = m->wsp<float>(m->lay.part);
   float* logits = m->wsp<float>(m->lay.logits);
   float* cap = m->capture ? m->capture + (size_t)g.n_layers * m->cfg.max_rows * g.hidden : nullptr;
   const bool bf = g.dtype == kBF16;
