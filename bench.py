@@ -37,7 +37,7 @@ TRAFFIC_RATIO = {
     ("wave", "attn_decode"): (1.045, "attn_bf16.hip", "8a2c7a6b92b85f6f"),
     ("layer", "attn_decode"): (1.045, "attn_bf16.hip", "8a2c7a6b92b85f6f"),
     ("full", "attn_decode"): (1.040, "attn_bf16.hip", "8a2c7a6b92b85f6f"),
-    ("full", "gemm_gate_up_swiglu"): (1.010, "gemm_bf16.hip", "06fc6efc1c536a00"),
+    ("full", "gemm_gate_up_swiglu"): (1.010, "gemm_bf16.hip", "58d94fe121b2e9c6"),
 }
 
 

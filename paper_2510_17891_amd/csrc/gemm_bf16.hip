@@ -624,13 +624,14 @@ __global__ __launch_bounds__(256) void gemm_bf16_cols_kernel(const u32x4_t* __re
   }
 }
 
-// Gate/up of 193..256 rows: eight waves, a 96-row weight tile (three row blocks) and all batch rows, where 128-row tiles would
-// leave a quarter of the compute units without a block while 96-row tiles give every unit one.  (The same tile in
-// gemm_bf16_tile_kernel: 62.9 us at 256 rows and 60.1 at 224, here 59.8 and 59.3.)  The first four waves stage
+// A full batch tile of eight waves (gate/up of 193..256 rows, QKV of 225..256): a 96-row weight tile (three row blocks) and all batch rows,
+// where 128-row tiles would leave a quarter of the compute units without a block while 96-row tiles give every unit one.  (The same tile
+// in gemm_bf16_tile_kernel: gate/up at 224 / 256 rows 60.1 / 62.9 us, here 59.3 / 59.8; QKV at 240 / 256 25.0 / 25.5, here 23.6 / 23.8.)  The first four waves stage
 // row blocks 0 and 2, the other four row block 1; each half runs its own copy of the loop (same steps, one barrier
 // per k block in both), so that no load in the pipeline is conditional.  Same K quarters, same order: same bits.
 // grid: x = three row blocks, all of them whole, y = K split, K quarters of a multiple of four k blocks.  (Gate/up has one split; with
-// a constant 0 in its place the compiler arranges the loop worse: 60.7 us at 256 rows.)
+// a constant 0 in its place the compiler arranges the loop worse: 60.7 us at 256 rows instead of 59.8.)
+template <int EPI>
 __global__ __launch_bounds__(512, 1) void gemm_bf16_lds8r3_kernel(const u32x4_t* __restrict__ X, const u32x4_t* __restrict__ W,
                                                                 void* __restrict__ out, int M, int N, int K,
                                                                 int kb_per_quarter) {
@@ -733,7 +734,7 @@ __global__ __launch_bounds__(512, 1) void gemm_bf16_lds8r3_kernel(const u32x4_t*
     float sum[16];
 #pragma unroll
     for (int r = 0; r < 16; ++r) sum[r] = acc[b][r];
-    store_rowblock<kEpiSwiGLU>(sum, m, hb, rb0 + b, 0, M, N, out);
+    store_rowblock<EPI>(sum, m, hb, rb0 + b, blockIdx.y, M, N, out);
   }
 }
 
@@ -1153,10 +1154,13 @@ void launch_cols(hipStream_t s, const void* X, const void* W, void* out, int M, 
   const GemmPlan p = gemm_plan(N, K, epi == kEpiResidual ? kEpiPartial : epi, allow_split);
   if (p.kb_per_wave % 4 == 0) {  // weight tiles shared through LDS
     const GemmTile t = gemm_tile(M, N, K, epi, allow_split);
-    // 193..256 rows on 96-row tiles that make exactly one K split (gate/up): 59.8 us at 256 rows and 59.3 at 224, the tile kernel takes
-    // 62.9 and 60.1 (but up to 192 rows, where two of its waves rest, 56.7 against 59.0).
-    if (t.nb == 3 && t.nw == 8 && epi == kEpiSwiGLU && M > 192 && M <= 256) {
-      gemm_bf16_lds8r3_kernel<<<dim3((N >> 4) / 3, 1), 512, 0, s>>>((const u32x4_t*)X, (const u32x4_t*)W, out, M, N, K, p.kb_per_wave);
+    // A full batch tile on 96-row weight tiles.  The lines: gate/up at 192 rows, where two waves of the tile kernel rest, 56.7 us there and 59.0
+    // here, at 224 60.1 and 59.3; QKV at 224 rows 23.7 and 23.4, at 256 25.5 and 23.8.  In eight splits the tile kernel stays ahead (down of 3072 x
+    // 8192 at 240 rows 25.2 and 25.9).
+    if (t.nb == 3 && t.nw == 8 && M <= 256 && (epi == kEpiSwiGLU ? M > 192 : M > 224 && p.splits <= 4)) {
+      const dim3 grid((epi == kEpiSwiGLU ? N >> 4 : N >> 5) / 3, p.splits);
+      if (epi == kEpiSwiGLU) gemm_bf16_lds8r3_kernel<kEpiSwiGLU><<<grid, 512, 0, s>>>((const u32x4_t*)X, (const u32x4_t*)W, out, M, N, K, p.kb_per_wave);
+      else gemm_bf16_lds8r3_kernel<kEpiPartial><<<grid, 512, 0, s>>>((const u32x4_t*)X, (const u32x4_t*)W, out, M, N, K, p.kb_per_wave);
       return;
     }
     const bool one = M <= 32 * t.nw;  // a single batch tile
