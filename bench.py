@@ -80,7 +80,8 @@ def parse():
     ap.add_argument("--kv-fp8", action="store_true",
                     help="wave / full workloads: cache keys and values as fp8 (opt-in performance variant, not the headline)")
     ap.add_argument("--attn-split", type=int, default=0,
-                    help="wave workload: segments per attention block beyond 4096 keys (0: the library's default)")
+                    help="wave workload: segments per attention block beyond 4096 keys at most (0: the library's default; steps of "
+                         "few rows take one or two by themselves)")
     ap.add_argument("--graph", action="store_true",
                     help="wave workload: launch every decode step as a HIP graph (rl_decode_graph_step)")
     ap.add_argument("--no-small-batch", action="store_true",
@@ -112,8 +113,8 @@ def parse():
     ap.add_argument("--no-share-attention", action="store_true",
                     help="full workload: attention over the prompt pages once per row instead of once per set of samples")
     ap.add_argument("--set-width", type=int, choices=[1, 2, 3], default=1,
-                    help="full and layer workloads: rows per set of samples; 1: the library's rule, 2: always the wide "
-                         "sets (two operands), 3: never")
+                    help="full and layer workloads: sets of samples; 1: by the library's rules, 2: in every step, wide ones (two "
+                         "operands), 3: in every step, narrow ones")
     ap.add_argument("--separate-append", action="store_true",
                     help="rotation and KV append as a kernel of their own instead of inside the decode attention kernel")
     args = ap.parse_args()

@@ -394,14 +394,13 @@ rl_status rl_debug_shuffle_free_pages(rl_model* m, uint64_t seed);
  * Test aid: switch off (on = 0) or on again (the default) the decode-step treatment of the samples of one
  * prompt (Section 2.3): sequences made by rl_prefill_groups hold the prompt's full pages in common, and rows
  * of such sequences that stand at the same position have the attention over those pages computed once per set
- * of rows instead of once per row, in steps whose size and contexts make that the faster way (on = 2, 3: in every step, in
- * sets as wide as they get, or narrow ones).  Results of every other call must not change by a single bit.
+ * of rows instead of once per row, in steps whose size and contexts make that the faster way.
+ * on = 2: in every step, in sets as large as the kernel allows (bf16 pages: two 16-column operands side by side, i.e. up to
+ * 32 / (query heads per kv head) rows), with the one to three segments that a row's sets leave packed four to a block;
+ * on = 3: in every step, with a single operand and no packs.  By default the size of the call decides all three.
+ * No bit of any result, of this or another call, depends on the choice.
  */
 rl_status rl_debug_share_attention(rl_model* m, int32_t on);
-/* on = 2: as on = 1, and the sets are as large as the kernel allows (bf16 pages: two 16-column operands side by
- * side, i.e. up to 32 / (query heads per kv head) rows) and the one to three segments that a row's sets leave are
- * packed four to a block in every call; on = 3: a single operand and no packs in any call.  By default the size of
- * the call decides both.  No bit of any result depends on the choice. */
 
 /*
  * Test aid: switch off (on = 0) or on again (the default) the fused form of a bf16 decode step in which the
@@ -412,8 +411,9 @@ rl_status rl_debug_share_attention(rl_model* m, int32_t on);
 rl_status rl_debug_attention_appends(rl_model* m, int32_t on);
 
 /*
- * Test and tuning aid: how many 256-key segments one attention block takes of a context beyond 4096 keys (1..16).
- * Smaller blocks balance better at the end of a launch, larger ones amortise their prologue.  Results of every
+ * Test and tuning aid: how many 256-key segments one attention block takes at most of a context beyond 4096 keys (1..16;
+ * 4 by default).  Smaller blocks balance better at the end of a launch, larger ones amortise their prologue.  Steps of few
+ * rows, which would leave compute units idle, take one or two whatever is set here, and cut shorter contexts as well.  Results of every
  * other call must not change by a single bit.  Not to be changed while a decode graph exists.
  */
 rl_status rl_debug_attention_split(rl_model* m, int32_t segs_per_block);

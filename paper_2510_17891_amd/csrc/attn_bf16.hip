@@ -888,11 +888,11 @@ __global__ __launch_bounds__(256, KV8 ? 3 : 2) void attn_decode_bf16_kernel(cons
   if (APPEND && appends) store_new();
 }
 
-// Merge of the rows whose partials are in the workspace, one wave per (row, head): rows of a set (short contexts:
-// the arithmetic of the in-block merge) and long-context rows (more than kLdsSegs segments, none of them empty).
-// For the latter the segment weights exp(m_c - M) are formed by the lanes in parallel (max and denominator by the wave's fixed
-// butterfly), then the O partials are accumulated in index order, eight loads in flight at a time.  Rows with
-// short contexts were finished by the first kernel.
+// Merge of the rows whose partials are in the workspace, one wave per (row, head): rows of a set and rows that took several blocks.  Up to
+// kLdsSegs segments that is the arithmetic of the in-block merge.  Of longer contexts (no segment empty)
+// the segment weights exp(m_c - M) are formed by the lanes in parallel (max and denominator by the wave's fixed
+// butterfly), then the O partials are accumulated in index order, eight loads in flight at a time.  Rows of up to
+// whole_segs segments in no set were finished by the first kernel.
 __global__ __launch_bounds__(256) void attn_merge_bf16_kernel(const float* __restrict__ part, const RowMeta* __restrict__ rows,
                                                              int max_segs, uint16_t* __restrict__ o_out, int n_q,
                                                              const int32_t* __restrict__ skip_segs, int whole_segs) {

@@ -30,8 +30,8 @@ RL_HOST_DEVICE inline int attn_seg_begin(int sgm, int n_it, int n_seg) {
 // Segments up to which a row is finished by one block, and the segments of a block beyond.
 // A compute unit draws 63 GB/s from memory whatever is in flight, so a step of four waves of a block takes 1.05 us, that of a
 // wave alone 0.7: rows that leave compute units idle take blocks of four, two or one segment, as few as still make no more
-// than a block per unit.  That costs the merge launch, 3 us, which from 1025 keys (eight segments: half the steps per wave)
-// always pays, and with four segments of bf16 pages from some 350 keys on.  One layer, us, before / with several blocks:
+// than a block per unit.  That costs the merge launch (4.7 us by itself, 3 of a layer, whose other launches overlap its start and end), which from
+// 1025 keys (eight segments: half the steps per wave) always pays, and with four segments of bf16 pages from some 350 keys on.  One layer, us, before / with several blocks:
 //   1 row:  1000 keys 93.2 / 88.3, 1500 97.6 / 89.3, 3900 102.5 / 90.3, 7000 (blocks of four / of one) 96.8 / 92.5
 //   2 rows of 2000 104.1 / 92.0;  4 rows: 1000 98.1 / 93.3, 2000 106.7 / 95.1, fp8 pages 99.7 / 94.1
 //   8 rows: 1000 99.6 / 95.8, 1500 104.0 / 97.9, 3000 118.1 / 105.3
@@ -85,7 +85,8 @@ inline int attn_rows_per_set(int group, bool kv_fp8, int n_rows, int n_kv) {
 }
 
 // The longest context up to which the rows of a decode step do better each on its own (0: sharing always pays).  Sets make a merge launch
-// necessary (4.8 us) that rows of at most 4096 keys can do without, and set blocks take two segments or more, where the blocks of few rows
+// necessary (3 us of a layer), which rows alone that one block finishes do without (attn_split: up to 4096 keys, up to 384 or 1024 where
+// few rows take several blocks); and set blocks take two segments or more, where the blocks of few rows
 // alone take as few as fill the compute units.  What sets save: bytes, as soon as the blocks of a compute unit share what it draws from memory,
 // and blocks, which few rows alone have to share a unit with beyond.  One layer, us, shared / each on its own (8 kv heads, groups of 8):
 //   2 rows: 3900 keys 94.1 / 93.3, 7000 96.9 / 95.6;  4 rows: 2000 95.2 / 94.0, 3900 97.3 / 97.4, 5000 97.7 / 99.6, 7900 105.4 / 105.0

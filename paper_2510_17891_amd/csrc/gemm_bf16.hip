@@ -275,7 +275,8 @@ __global__ __launch_bounds__(256) void gemm_bf16_mixed_kernel(const u32x4_t* __r
 // no faster than the two launches; with fences at device scope 14 us slower).  x is not changed: the split sums stay pending
 // beside those of the down projection, for the next norm to add in the same order.
 // Norm, gate/up and down over the weights of six layers, us: one row 54.0 -> 49.9, two rows 54.1 -> 51.9 (every block reads 80 KB per row
-// from L2: more rows would pay more than the launch).  Arithmetic of residual_norm_kernel and of the K-split kernels: same bits.
+// from L2: more rows would pay more than the launch).  A layer of other shapes (hidden x ffn), one / two rows: 1024 x 512 32.8 -> 30.8 / 33.2 -> 32.3,
+// 1024 x 3072 34.9 -> 32.8 / 35.0 -> 34.4, 2048 x 6144 44.7 -> 41.1 / 44.0 -> 42.3, 3072 x 8192 62.3 -> 59.6 / 60.3 -> 59.9, 4096 x 512 54.8 -> 50.7 / 54.2 -> 51.5.  Arithmetic of residual_norm_kernel and of the K-split kernels: same bits.
 // grid: x = n_big tiles of two row blocks, then n_small of one (see gemm_bf16_mixed_kernel).
 struct RowNorm {
   const float* x;
@@ -742,14 +743,15 @@ __global__ __launch_bounds__(512, 1) void gemm_bf16_lds8r3_kernel(const u32x4_t*
 // ranges of `splits` consecutive K splits.  The weight tile goes through LDS in three stages, one barrier per k block; the
 // activation fragments come straight from L2.
 //
-// What bounds it.  At 1024 rows gate/up spends 206 us with two resident blocks of four waves (128 x 128 each); without
+// What bounds it.  At 1024 rows gate/up by itself spends 206 us with two resident blocks of four waves (128 x 128 each); without
 // its activation loads 174, without its weight loads 150, without both and LDS 133, which is the matrix cores alone at
 // the clock that their power leaves (operands of zeros: 176, 116, 95 and 94, so what a compute unit draws through its L1 is
-// a bound of its own, at 70 GB/s per unit).  Both, the power and that rate, go by the bytes per product, hence:
+// a bound of its own, at 70 GB/s per unit).  Both, the power and that rate, go by the bytes per product, hence (the launch by itself,
+// without / with it):
 //   - eight waves (128 x 256) where the batch fills them: 48 KB per k block instead of 64: 206 -> 190 us;
 //   - weights that are read once (ONE: a single batch tile) pass through non-temporally: gate/up 41.0 -> 38.6 us at 72 rows;
-//   - waves without batch rows carry weights and take part in the barriers, nothing else: down at 160 rows 40 -> 30 us,
-//     gate/up at 160 rows 55 -> 50, at 301 rows 100 -> 84; with four waves every other tile holds its rows in the other two
+//   - waves without batch rows carry weights and take part in the barriers, nothing else: gate/up at 301 rows 100 -> 84 us, down at
+//     160 rows 40 -> 30; with four waves every other tile holds its rows in the other two
 //     waves, so that two blocks on a unit do not leave the same matrix cores idle.  Not with a single batch tile of four
 //     waves, where HBM is the bound and the second path only costs (128 rows: 42.9 -> 44.5).
 // And one memory instruction behind every matrix instruction (a wave issues in order: a run of LDS writes or loads leaves
@@ -761,10 +763,12 @@ __global__ __launch_bounds__(512, 1) void gemm_bf16_lds8r3_kernel(const u32x4_t*
 // in order; then, where one block takes several K splits, the splits in order, kept in LDS between them.  So at more than
 // 256 rows QKV, and at more than 512 O and down, leave no split partials: QKV writes its sum once, O and down
 // add theirs to the residual stream themselves (kEpiResidual), in the order in which the norm kernel would.
-// Measured over the weights of twelve layers, against the staged kernels before (us): 128 rows QKV 17.0 -> 15.7, O 13.5 -> 12.6; 160 rows
-// gate/up 58 -> 49, QKV 23 -> 19, O 19.4 -> 15.0, down 42.6 -> 30.0; 256 rows O 20.1 -> 18.2, down 42.4 -> 39.2; 301 rows
-// gate/up 94 -> 87, O 31 -> 24, down 57 -> 48; 512 rows O 33 -> 29, down 61 -> 56; 768 rows gate/up 175 -> 165, QKV 61 ->
-// 59; 1024 rows gate/up 209 -> 193, QKV 67 -> 63.
+// Kernel times in a step of the 8B shape (us), the staged kernels that it replaced -> now:
+//   rows           72            128           160           192           301           512            640            768            1024
+//   QKV       17.6 -> 15.7  18.8 -> 17.9  21.2 -> 20.5  21.6 -> 21.5  33.7 -> 33.5  38.4 -> 38.6   44.9 -> 45.3   59.8 -> 57.5   64.1 -> 61.2
+//   O         14.6 -> 14.2  15.0 -> 15.4  18.4 -> 15.1  18.5 -> 15.7  25.0 -> 21.8  26.0 -> 25.5   36.8 -> 36.8   44.2 -> 43.9   47.0 -> 46.4
+//   gate/up   41.8 -> 39.7  44.5 -> 44.9  56.5 -> 52.2  57.0 -> 55.3  86.9 -> 79.4 106.7 -> 107.3 141.8 -> 134.1 168.3 -> 157.5 202.7 -> 188.7
+//   down      27.2 -> 26.8  29.1 -> 29.0  39.2 -> 32.0  39.1 -> 33.8  52.7 -> 44.0  55.7 -> 54.2   93.0 -> 93.1  112.1 -> 111.4 115.6 -> 115.7
 __device__ __forceinline__ __amdgpu_buffer_rsrc_t buffer_of(const void* base, uint32_t bytes) {
   return __builtin_amdgcn_make_buffer_rsrc((void*)base, 0, bytes, 0x00020000);
 }

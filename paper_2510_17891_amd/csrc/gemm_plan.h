@@ -60,7 +60,8 @@ struct GemmTile {
   int nb, nw;  // row blocks and waves of a block of gemm_bf16_tile_kernel
 };
 
-// The tile of a product of more than 64 rows (K quarters of a multiple of four k blocks).
+// The tile of a product of more than 64 rows (K quarters of a multiple of four k blocks).  Figures: the launch by itself, over the weights
+// of twelve layers.
 //   - Up to 128 rows (one batch tile, HBM bound): 128-row weight tiles where they make 192 blocks or more, 96-row ones where
 //     those make a block per compute unit and 128-row ones do not (gate/up at 128 rows 42.9 against 46.0 us, QKV 15.7 against
 //     17.9), 64-row ones for the small matrices (O 12.6 against 15.7, down 26.7 against 35.4).
